@@ -88,7 +88,7 @@ int flux_destroy(flux_ctx* ctx);
 const char* flux_strerror(int code);
 
 /* Bytes of workspace flux_attn_decode needs for this shape (pure host arithmetic;
- * prefill, router and append need less than 64 KiB).  0 on invalid arguments. */
+ * prefill, router and append need less than 64 KiB; flux_xa_select uses what there is).  0 on invalid arguments. */
 size_t flux_workspace_needed(const flux_attn_cfg* cfg, int batch, int max_kv_len);
 
 /* Returns the sticky device status bits (>= 0) and clears them.  Synchronous: copies the word back and
@@ -176,8 +176,9 @@ int flux_attn_prefill_blocksparse(flux_ctx* ctx, const flux_attn_cfg* cfg, const
  * block_mask: dev uint8 [batch, n_q_heads, n_qblocks, n_kblocks], every byte written (0 or 1);
  * n_kblocks * 64 >= max_kv_len, n_qblocks * 64 >= max_q_len, n_kblocks <= 4096 (262144 positions), else FLUX_EINVAL.
  * max_q_len bounds the prompt lengths (host); a prompt found longer on the device is scored up to the bound, rounded
- * up to whole blocks, and FLUX_DEV_BAD_LENGTH is raised.  Prompts of up to 65536 positions (by that bound) are
- * scored in one walk over the keys, longer ones in two.
+ * up to whole blocks, and FLUX_DEV_BAD_LENGTH is raised.  The scores of as many heads at a time as fit go through the
+ * workspace (with r = ceil(max_q_len / 2048), one head takes 32 KB * r * (r + 1), and 64 KB * r are used at least; a smaller
+ * workspace is valid and slower).
  * The masses are computed in fp32 from exact bf16 products: near a tie between the threshold and a partial sum
  * of masses the selection can differ from one made in higher precision. */
 int flux_xa_select(flux_ctx* ctx, const flux_attn_cfg* cfg, const void* q, const int32_t* cu_q, int max_q_len,

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "../../include/flux.h"
 
 // The host-only build that checks the C ABI under sanitizers compiles flux_api.hip as plain C++ (no device pass):
@@ -173,6 +175,15 @@ __device__ __forceinline__ float sum_across_halves(float x) {
   auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
   return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
 }
+
+// One wave-wide direct global -> LDS transfer: every lane fetches its own 16 bytes, the 64 pieces land
+// at lds_base + 16 * lane.  Issued as inline assembly so that the compiler does not serialise later LDS
+// reads of the OTHER stage behind it; completion is awaited explicitly with vmcnt(0) before the barrier.
+// M0 (the LDS base of the transfer) is written here and declared as clobbered.
+__device__ __forceinline__ void lds_copy16(const char* base /*uniform*/, int lane_off, uint32_t lds_base /*uniform*/) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(lane_off), "s"(base), "s"(lds_base) : "memory", "m0");
+}
+
 #endif  // __HIP__
 
 }  // namespace flux

@@ -56,14 +56,6 @@ struct PrefillArgs {
 
 constexpr float kWeightGuard = 1073741824.0f;   // 2^30: a block whose weights sum past this moves the softmax reference
 
-// One wave-wide direct global -> LDS transfer: every lane fetches its own 16 bytes, the 64 pieces land
-// at lds_base + 16 * lane.  Issued as inline assembly so that the compiler does not serialise later LDS
-// reads of the OTHER stage behind it; completion is awaited explicitly with vmcnt(0) before the barrier.
-// M0 (the LDS base of the transfer) is written here and declared as clobbered.
-__device__ __forceinline__ void dma16(const char* base /*uniform*/, int lane_off, uint32_t lds_base /*uniform*/) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(lane_off), "s"(base), "s"(lds_base) : "memory", "m0");
-}
-
 // All transfers of one wave for one whole tile in a single statement (four for K and four for V, or two and two):
 // the LDS destination of transfer t is the uniform base plus a compile-time offset, so M0 is produced by one
 // scalar add, and nothing is scheduled between the transfers.  A transfer keeps the issuing wave for about 64
@@ -274,10 +266,10 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
     const uint32_t lk = lds_w + stage * STAGE;
 #pragma unroll
     for (int t = 0; t < KPW; ++t)
-      dma16(kt, k_slot(t, rmax), lk + 1024 * NW * t);
+      lds_copy16(kt, k_slot(t, rmax), lk + 1024 * NW * t);
 #pragma unroll
     for (int t = 0; t < VPW; ++t)
-      dma16(vt, v_slot(t, rmax), lk + KTILE + 1024 * NW * t);
+      lds_copy16(vt, v_slot(t, rmax), lk + KTILE + 1024 * NW * t);
   };
 
   // ---- per-lane LDS read offsets (bytes, relative to stage 0; the stage is added as an immediate)

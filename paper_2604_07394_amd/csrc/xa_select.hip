@@ -13,7 +13,8 @@
 //      in descending order, first reach the threshold; and always its own block.
 //
 // Step 1 is a matrix product over 16 * D numbers per square: the 16 query rows of square row a laid end to end
-// against the 16 key rows of square column b laid end to end in inverse order.  One workgroup owns 32 square
+// against the 16 key rows of square column b laid end to end in inverse order.  Short prompts (and contexts with a tiny
+// workspace) take the walk described here, all others the tiled form further down.  One workgroup owns 32 square
 // rows (512 queries, 8 query blocks) of one head and walks the square columns 16 at a time (256 keys):
 //   - the contraction is split over the four waves by the row offset r (wave w takes r = 4w .. 4w+3), so each
 //     wave keeps its share of the query operand in registers for the whole kernel and loads only its share of
@@ -306,6 +307,414 @@ __global__ __launch_bounds__(256, 2) void xa_select_kernel(XaArgs a) {
   }
 }
 
+// ---- the same selection as a tiled matrix product followed by a small row kernel
+//
+// xa_scores_kernel computes the antidiagonal sums as the matrix product they are: a workgroup owns a tile of 128 square
+// rows x 128 square columns of one head (four waves of 64 x 64, MFMA 16x16x32 bf16 on S^T = K Q^T) and walks the 16 * D
+// numbers of a square in stages of 64, both operands coming through LDS by direct transfers (double buffered, one
+// barrier per stage, two workgroups per CU).  Only tiles on or below the diagonal are launched.  The means e[a][b] go to
+// the workspace in pieces of [128 square rows][16 square columns]; xa_keep_kernel (one wave per query block) reads its
+// 4 rows piece by piece, does what the reduction phase of the walk does and writes the row of the keep matrix.  The
+// sums are taken in the order of the walk (four chains of 4 row offsets, added in pairs), and so is everything after
+// them: the two forms keep the same blocks.
+// What bounds it: the rate at which the L2s deliver operand rows to the CUs.  The walk above fetches every key row once
+// per 32 square rows, this form every operand row once per 128 of the other operand: 16384 positions x 32 heads 1.2 GB
+// instead of 2.1 GB (walk 340 us; here 144 us, 700 TFLOP/s at its core, a quarter of it for the 75 MB of means, plus 46 us
+// for the row kernel, which is bound by its vector instructions).
+constexpr int kXaTile = 128;                 // square rows / columns of a tile
+constexpr int kXaPiece = kXaTile * 16;       // floats of a piece: 128 square rows x 16 square columns
+
+struct XaScoreArgs {
+  const __bf16* q;
+  const int32_t* cu_q;
+  const __bf16* k;
+  int64_t stride_b, stride_h, stride_t;
+  const int32_t* kv_len;
+  int capacity;
+  int hq, group;
+  int bh0, n_bh;          // heads (of the whole batch, numbered b * hq + h) this launch works on
+  int rt0, rt1;           // their row tiles
+  int share;              // 0: plain order; else XCDs per (sequence, KV head) pair (see the kernel)
+  int tab_cols;
+  float scale, threshold;
+  float* e;               // [n_bh][row tile rt0 <= rt < rt1][8 (rt + 1) pieces]
+  uint8_t* mask;
+  int n_qblocks, n_kblocks;
+  int qb0, qb1;           // query blocks of this launch
+  uint32_t* status;
+};
+
+// Length of the prompt that is scored; what is inconsistent is reported when `report` is set.
+__device__ __forceinline__ int xa_prompt_len(int n_q, int kv_len, int capacity, int tab_cols, bool report, uint32_t* status) {
+  bool bad = kv_len < 0 || kv_len > capacity || n_q != kv_len;
+  const int len = kv_len < 0 ? 0 : (kv_len > capacity ? capacity : kv_len);
+  int n = n_q < len ? (n_q < 0 ? 0 : n_q) : len;
+  if (n > 64 * tab_cols) {
+    bad = true;
+    n = 64 * tab_cols;
+  }
+  if (report && bad) atomicOr(status, (uint32_t)FLUX_DEV_BAD_LENGTH);
+  return n;
+}
+
+// Tiles of the row tiles below rt; a tile is 8 pieces.
+__device__ __host__ __forceinline__ int64_t xa_tiles_below(int rt) { return (int64_t)rt * (rt + 1) / 2; }
+constexpr int64_t kXaTileFloats = 8 * kXaPiece;
+
+template <int D>
+__global__ __launch_bounds__(256, 2) void xa_scores_kernel(XaScoreArgs a) {
+  constexpr int HPR = D / 64;              // stages per row offset r
+  constexpr int SEG = 4 * HPR;             // stages per chain of 4 row offsets
+  constexpr int NST = 4 * SEG;             // stages of 64 numbers
+  constexpr int OPB = kXaTile * 128;       // bytes of one operand tile of a stage: 128 rows of 128 bytes
+  __shared__ __attribute__((aligned(1024))) char smem[2 * 2 * OPB];
+
+  const int tid = threadIdx.x;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+  const int g = l >> 4, nn = l & 15;
+  const int64_t tiles0 = xa_tiles_below(a.rt0);
+  const int n_tiles = (int)(xa_tiles_below(a.rt1) - tiles0);
+  // which head and tile.  Workgroups go to the 8 XCDs by id mod 8: where the pairs of the launch are a multiple of 8 or
+  // divide 8, all tiles of a pair get ids of `share` residues (1: one XCD, one L2), the heads of its group side by side
+  int bh, tile;
+  {
+    const int i = blockIdx.x;
+    if (a.share > 0) {
+      const int x = i & 7, per = a.group * n_tiles, px = 8 / a.share;   // px: pairs worked on at a time
+      const int item = (i >> 3) * a.share + x / px;                     // items of the pair sequence of this residue
+      const int pair = x % px + px * (item / per);
+      tile = (item % per) / a.group;
+      bh = pair * a.group + item % a.group;
+      if (bh >= a.n_bh) return;                            // padding of the last round
+    } else {
+      bh = i / n_tiles;
+      tile = i % n_tiles;
+    }
+  }
+  const int64_t t_abs = tiles0 + tile;
+  int rt = (int)((__builtin_sqrtf(8.f * (float)t_abs + 1.f) - 1.f) * 0.5f);
+  while (xa_tiles_below(rt) > t_abs) --rt;
+  while (xa_tiles_below(rt + 1) <= t_abs) ++rt;
+  rt = __builtin_amdgcn_readfirstlane(rt);                 // (it came through the vector unit)
+  const int ct = (int)(t_abs - xa_tiles_below(rt));
+  const int b = (a.bh0 + bh) / a.hq, h = (a.bh0 + bh) % a.hq, kvh = h / a.group;
+  const int q_begin = a.cu_q[b];
+  const int n = xa_prompt_len(a.cu_q[b + 1] - q_begin, a.kv_len[b], a.capacity, a.tab_cols, false, a.status);
+  const int n_sq = (n + kXaStride - 1) / kXaStride;
+  const int a0 = rt * kXaTile, b0 = ct * kXaTile;
+  if (a0 >= n_sq) return;                                  // uniform: past the prompt
+
+  // ---- direct transfers: every stage brings 128 bytes of each of the 128 rows of both operands, 8 rows per transfer.
+  // Transfer t, lane l: row 8t + l/8, 16-byte piece l%8; the piece a lane fetches is swizzled by the row (as the K tile of
+  // the prefill kernel with rows of 128 bytes: no bank conflicts on the fragment reads below).
+  const int pitch_q = a.hq * D * 2, pitch_k = (int)a.stride_t * 2;      // bytes between positions
+  const char* qbase = (const char*)(a.q + ((int64_t)(q_begin + kXaStride * a0) * a.hq + h) * D);
+  const char* kbase = (const char*)(a.k + (int64_t)b * a.stride_b + (int64_t)kvh * a.stride_h + (int64_t)kXaStride * b0 * a.stride_t);
+  const int piece = ((l & 7) ^ ((4 * (w & 1) + (l >> 4)) & 7)) * 16;
+  const int q_lim = n - 1 - kXaStride * a0, k_lim = n - 1 - kXaStride * b0;   // last position of the prompt, from the tile's first
+  int pos[4], off_q[4], off_k[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    pos[t] = kXaStride * (8 * (w + 4 * t) + (l >> 3));
+    off_q[t] = pos[t] * pitch_q + piece;
+    off_k[t] = pos[t] * pitch_k + piece;
+  }
+  const bool rag_q = kXaStride * kXaTile - 1 > q_lim, rag_k = kXaStride * kXaTile - 1 > k_lim;
+  const uint32_t lds_w = (uint32_t)(uintptr_t)(FLUX_LDS char*)smem + 1024 * w;
+  auto issue = [&](int s, int buf) __attribute__((always_inline)) {
+    const int r = s / HPR, half = s % HPR;
+    const uint32_t lk = lds_w + buf * 2 * OPB, lq = lk + OPB;
+    // positions past the prompt are fetched from its last one; what they would contribute is left out below
+    if (!rag_k) {
+      const char* p = kbase + (int64_t)(kXaStride - 1 - r) * pitch_k + half * 128;      // keys in inverse order
+#pragma unroll
+      for (int t = 0; t < 4; ++t) lds_copy16(p, off_k[t], lk + 4096 * t);
+    } else {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) lds_copy16(kbase + half * 128, min(pos[t] + kXaStride - 1 - r, k_lim) * pitch_k + piece, lk + 4096 * t);
+    }
+    if (!rag_q) {
+      const char* p = qbase + (int64_t)r * pitch_q + half * 128;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) lds_copy16(p, off_q[t], lq + 4096 * t);
+    } else {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) lds_copy16(qbase + half * 128, min(pos[t] + r, q_lim) * pitch_q + piece, lq + 4096 * t);
+    }
+  };
+
+  const int wa = w & 1, wb = w >> 1;                       // this wave's 64 square rows and 64 square columns of the tile
+  const int aw = a0 + 64 * wa, bw = b0 + 64 * wb;
+  const bool idle = bw > aw + 63 || aw >= n_sq;            // above the diagonal or past the prompt: transfers only
+  const int last = n_sq - 1;                               // the prompt's last square holds last_cnt positions
+  const int last_cnt = n - kXaStride * last;
+  const bool part = last_cnt < kXaStride && aw <= last && last < aw + 64;   // this wave's rows hold a partial square
+  const bool diag = bw == aw;                              // this wave's tile lies on the diagonal
+  // acc[i][j][t]: square (aw + 16j + nn, bw + 16i + 4g + t), the chain of row offsets in progress
+  f32x4 acc[4][4];
+  int rd[2];                                               // LDS offsets of this lane's fragments (row nn of a 16-row block)
+#pragma unroll
+  for (int kc = 0; kc < 2; ++kc) rd[kc] = nn * 128 + (((4 * kc + g) ^ ((nn >> 1) & 7)) * 16);
+
+  auto stage = [&](int s, int buf) __attribute__((always_inline)) {
+    __builtin_amdgcn_s_waitcnt(0x0F70);                    // vmcnt(0): this wave's transfers have landed
+    __syncthreads();                                       // ... and everyone's; the other buffer is free
+    if (s + 1 < NST) issue(s + 1, buf ^ 1);
+    if (idle) return;
+    const int r = s / HPR;
+    // the column of the prompt's last square holds the samples from 16 - last_cnt on: what the chain has of that square
+    // on the diagonal (the only place where it matters) is cleared before the first of them
+    if (diag && part && s % HPR == 0 && r == kXaStride - last_cnt) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          if (4 * g + t == nn && bw + 16 * i + nn == last) acc[i][i][t] = 0.f;
+    }
+    FLUX_LDS char* st = (FLUX_LDS char*)smem + buf * 2 * OPB;
+#pragma unroll
+    for (int kc = 0; kc < 2; ++kc) {
+      bf16x8 kf[4], qf[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) kf[i] = *(FLUX_LDS bf16x8*)(st + (64 * wb + 16 * i) * 128 + rd[kc]);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) qf[j] = *(FLUX_LDS bf16x8*)(st + OPB + (64 * wa + 16 * j) * 128 + rd[kc]);
+      if (part && r >= last_cnt) {                         // the last square row has no such sample
+        const u32x4 zero = {0, 0, 0, 0};
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (aw + 16 * j + nn == last) qf[j] = __builtin_bit_cast(bf16x8, zero);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[i], qf[j], acc[i][j], 0, 0, 0);
+    }
+  };
+  // The sums of the chains 0 and 1 wait in this lane's own places of the workspace: with them, chain 2 and the chain in
+  // progress in registers the kernel spills (192 accumulators; 256 registers at two waves per SIMD).
+  f32x4 hi[4][4];                                          // sums of chain 0, later of chain 2
+  float* out = a.e + ((int64_t)bh * n_tiles + (xa_tiles_below(rt) - tiles0)) * kXaTileFloats + (int64_t)(8 * ct + 4 * wb) * kXaPiece +
+               (64 * wa + nn) * 16 + 4 * g;
+  auto chain = [&](int c) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int s = SEG * c; s < SEG * (c + 1); s += 2) {
+      stage(s, 0);
+      stage(s + 1, 1);
+    }
+  };
+  issue(0, 0);
+  chain(0);
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) hi[i][j] = acc[i][j];
+  chain(1);
+  if (!idle) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) *(f32x4*)(out + i * kXaPiece + j * 256) = hi[i][j] + acc[i][j];
+  }
+  chain(2);
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) hi[i][j] = acc[i][j];
+  chain(3);
+  if (idle) return;
+
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int a_abs = aw + 16 * j + nn;
+      const f32x4 lo = *(const f32x4*)(out + i * kXaPiece + j * 256);
+      f32x4 v;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int b_abs = bw + 16 * i + 4 * g + t;
+        const int r_min = max(max(b_abs == a_abs ? 8 : 0, kXaStride * b_abs + kXaStride - n), 0);
+        const int cnt = min(kXaStride - 1, n - 1 - kXaStride * a_abs) - r_min + 1;
+        // on the diagonal the samples r < 8 are not causal
+        const float l01 = b_abs == a_abs ? 0.f : lo[t];
+        const float l2 = r_min >= 12 ? 0.f : hi[i][j][t];
+        const float sum = l01 + (l2 + acc[i][j][t]);
+        v[t] = (a_abs > last || b_abs > a_abs || cnt <= 0) ? -INFINITY : a.scale * sum / (float)cnt;
+      }
+      *(f32x4*)(out + i * kXaPiece + j * 256) = v;
+    }
+}
+
+// Values of other lanes by data-parallel-primitive moves (CTRL: quad_perm 0x00-0xff, row_ror:n 0x120+n,
+// row_mirror 0x140, row_half_mirror 0x141).
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
+// Lane l ends up with the sum over the wave, added in the order of xor exchanges over 32, 16, 8, 4, 2, 1 (once the lanes
+// whose numbers agree mod 2k hold the same value, the lane k further round the row holds that of lane l ^ k).
+__device__ __forceinline__ float wave_sum_xor(float x) {
+  x = sum_across_halves(x);
+  const uint32_t u = __builtin_bit_cast(uint32_t, x);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  x = __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
+  x += dpp<0x128>(x);
+  x += dpp<0x124>(x);
+  x += dpp<0x4e>(x);      // quad_perm [2, 3, 0, 1]
+  x += dpp<0xb1>(x);      // quad_perm [1, 0, 3, 2]
+  return x;
+}
+
+// One wave per query block; NR: masses a lane holds (one per 64 key blocks).  The row part is the reduction phase of the
+// walk on the same 4 x 16 lanes: lane l reads square row l / 16 of the block, column l % 16 of every piece.  The logarithm
+// of the summed exponentials of a key block's 4 squares is kept in LDS ([4 rows][tab] per wave).
+template <int NR, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void xa_keep_kernel(XaScoreArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char xa_smem[];
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), l = threadIdx.x & 63;
+  const int n_qb = a.qb1 - a.qb0;
+  const int64_t id = (int64_t)blockIdx.x * WAVES + w;
+  if (id >= (int64_t)a.n_bh * n_qb) return;                // uniform for the wave; there is no workgroup barrier below
+  const int bh = (int)(id / n_qb), qb = a.qb1 - 1 - (int)(id % n_qb);
+  const int b = (a.bh0 + bh) / a.hq, h = (a.bh0 + bh) % a.hq;
+  const int n_q = a.cu_q[b + 1] - a.cu_q[b];
+  const int n = xa_prompt_len(n_q, a.kv_len[b], a.capacity, a.tab_cols, qb == 0 && h == 0 && l == 0, a.status);
+  uint8_t* mrow = a.mask + (((int64_t)b * a.hq + h) * a.n_qblocks + qb) * (int64_t)a.n_kblocks;
+  const int n_blk = (n + 63) / 64;
+  if (qb >= n_blk) {                                       // a row of the matrix beyond the prompt
+    for (int j = l; j < a.n_kblocks; j += 64) mrow[j] = 0;
+    return;
+  }
+  const int tab = 64 * NR;
+  float* table = (float*)xa_smem + w * 4 * tab;
+  const int rr = l >> 4, rb = l & 15;
+  const int n_ct = qb / 4 + 1;                             // pieces up to the diagonal
+  const int rt = qb / 32, rows = min(4, (n + kXaStride - 1) / kXaStride - 4 * qb);
+  const int64_t tiles0 = xa_tiles_below(a.rt0);
+  const float* src = a.e + ((int64_t)bh * (xa_tiles_below(a.rt1) - tiles0) + (xa_tiles_below(rt) - tiles0)) * kXaTileFloats +
+                     (4 * (qb % 32) + rr) * 16 + rb;
+  // m_use is m_row, or 0 while the row has no finite value (the exponentials of -inf are 0 then as well).
+  float m_row = -INFINITY, m_use = 0.f, l_row = 0.f;
+  float e_next[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) e_next[u] = src[(int64_t)min(u, n_ct - 1) * kXaPiece];
+  for (int c0 = 0; c0 < n_ct; c0 += 4) {
+    float e4[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) e4[u] = rr < rows && c0 + u < n_ct ? e_next[u] : -INFINITY;   // (rows past the prompt are not written)
+    if (c0 + 4 < n_ct) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) e_next[u] = src[(int64_t)min(c0 + 4 + u, n_ct - 1) * kXaPiece];
+    }
+    float pe_mine = 0.f, m_mine = 0.f;                     // of the piece c0 + rb % 4: its key block rb / 4
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      float mt = e4[u];
+      mt = fmaxf(mt, dpp<0xb1>(mt));
+      mt = fmaxf(mt, dpp<0x4e>(mt));
+      mt = fmaxf(mt, dpp<0x141>(mt));
+      mt = fmaxf(mt, dpp<0x140>(mt));
+      if (__builtin_amdgcn_ballot_w64(mt > m_row) != 0) {  // a row's reference moves (in the others the factor is 1)
+        const float m_new = fmaxf(m_row, mt);
+        l_row *= m_row == -INFINITY ? 0.f : __expf(m_row - m_new);
+        m_row = m_new;
+        m_use = m_new == -INFINITY ? 0.f : m_new;
+      }
+      float pe = __expf(e4[u] - m_use);
+      pe += dpp<0xb1>(pe);
+      pe += dpp<0x4e>(pe);
+      pe_mine = (rb & 3) == u ? pe : pe_mine;
+      m_mine = (rb & 3) == u ? m_use : m_mine;
+      pe += dpp<0x141>(pe);
+      pe += dpp<0x140>(pe);
+      l_row += pe;
+    }
+    table[rr * tab + 4 * (c0 + (rb & 3)) + (rb >> 2)] = pe_mine > 0.f ? m_mine + __logf(pe_mine) : -INFINITY;
+  }
+  const float lse = m_row + __logf(l_row);
+  float lse_r[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) lse_r[r] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lse), 16 * r));
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the table is this wave's own
+  __builtin_amdgcn_wave_barrier();
+  // masses of key blocks l, l + 64, ...
+  float mass[NR];
+  float tot = 0.f, top = 0.f;
+#pragma unroll
+  for (int i = 0; i < NR; ++i) {
+    mass[i] = 0.f;
+    const int j = 64 * i + l;
+    if (j <= qb) {
+      float acc = 0.f;
+      for (int r = 0; r < rows; ++r) acc += __expf(table[r * tab + j] - lse_r[r]);
+      mass[i] = acc / (float)rows;
+      tot += mass[i];
+      top = fmaxf(top, mass[i]);
+    }
+  }
+  tot = wave_sum_xor(tot);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) top = fmaxf(top, __shfl_xor(top, off));
+  // ---- the cut: largest t (as a bit pattern; positive floats order like their bits) with sum(mass >= t) >= need
+  const float need = a.threshold * tot;
+  // (found as soon as at most one mass lies between the bounds: the blocks kept are the same for any t above the mass before)
+  uint32_t lo = 0, hi = __builtin_bit_cast(uint32_t, top) + 1;
+  int above_lo = 64 * NR, above_hi = 0;                    // masses at or above the bounds
+  while (hi - lo > 1 && above_lo - above_hi > 1) {
+    const uint32_t mid = lo + (hi - lo) / 2;
+    const float t = __builtin_bit_cast(float, mid);
+    float sm = 0.f;
+    int above = 0;
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+      const bool in = mass[i] >= t;
+      sm += in ? mass[i] : 0.f;
+      above += __builtin_popcountll(__builtin_amdgcn_ballot_w64(in));
+    }
+    sm = wave_sum_xor(sm);
+    if (sm >= need) {
+      lo = mid;
+      above_lo = above;
+    } else {
+      hi = mid;
+      above_hi = above;
+    }
+  }
+  const float cut = __builtin_bit_cast(float, lo);
+#pragma unroll
+  for (int i = 0; i < NR; ++i) {
+    const int j = 64 * i + l;
+    if (j < a.n_kblocks) mrow[j] = (j <= qb && (mass[i] >= cut || j == qb)) ? 1 : 0;
+  }
+  for (int j = 64 * NR + l; j < a.n_kblocks; j += 64) mrow[j] = 0;
+}
+
+// Launch both kernels for the heads and row tiles of x; `whole`: the query blocks past the last row tile are cleared too.
+template <int D>
+static hipError_t launch_xa_tiles(XaScoreArgs& x, int n_rt, hipStream_t s) {
+  const long long n_tiles = xa_tiles_below(x.rt1) - xa_tiles_below(x.rt0);
+  x.qb0 = 32 * x.rt0;
+  x.qb1 = x.rt1 == n_rt ? x.n_qblocks : (32 * x.rt1 < x.n_qblocks ? 32 * x.rt1 : x.n_qblocks);
+  long long n_wg = n_tiles * x.n_bh;
+  x.share = 0;
+  if (x.bh0 % x.group == 0 && x.n_bh % x.group == 0) {
+    const int pairs = x.n_bh / x.group;
+    x.share = pairs % 8 == 0 ? 1 : (8 % pairs == 0 ? 8 / pairs : 0);
+    if (x.share > 1) n_wg = (n_tiles * x.group + x.share - 1) / x.share * 8;
+  }
+  hipLaunchKernelGGL(xa_scores_kernel<D>, dim3((unsigned)n_wg), dim3(256), 0, s, x);
+  const long long waves = (long long)x.n_bh * (x.qb1 - x.qb0);
+  // four waves per workgroup while their tables leave room for two workgroups in the LDS of a CU
+  if (x.tab_cols <= 256) hipLaunchKernelGGL((xa_keep_kernel<4, 4>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 4 * 4 * 256 * 4, s, x);
+  else if (x.tab_cols <= 1024) hipLaunchKernelGGL((xa_keep_kernel<16, 2>), dim3((unsigned)((waves + 1) / 2)), dim3(128), 2 * 4 * 1024 * 4, s, x);
+  else hipLaunchKernelGGL((xa_keep_kernel<64, 1>), dim3((unsigned)waves), dim3(64), 4 * 4096 * 4, s, x);
+  return hipGetLastError();
+}
+
 hipError_t launch_xa_select(const Ctx& c, const flux_attn_cfg& cfg, const void* q, const int32_t* cu_q, int max_q_len,
                             const flux_kv_cache& cache, float threshold, uint8_t* mask, int n_qblocks, int n_kblocks,
                             hipStream_t s) {
@@ -330,6 +739,62 @@ hipError_t launch_xa_select(const Ctx& c, const flux_attn_cfg& cfg, const void* 
   a.tab_cols = need < n_kblocks ? (need > 0 ? need : 1) : n_kblocks;
   a.single_walk = a.tab_cols <= kXaSingleWalkMaxKBlocks;
   a.status = c.status;
+  // Tiled form.  Its scratch is one float per square at or below the diagonal (rounded up to tiles); heads, or row tiles of
+  // one head, are worked off in as many rounds as the context's workspace makes necessary (it must hold one row tile).
+  // 32-bit byte offsets inside a tile bound the strides.
+  // Prompts bounded by less than 1024 positions (head dimension 64: 320) stay with the walk above: one launch instead of
+  // two, and a tile of 128 square rows would be mostly empty.  One prompt, walk / tiles in us, 32/8 heads of 128: 300
+  // positions 29 / 32, 1000 positions 34.8 / 34.2, 4096 positions 65 / 42, 8192 positions 129 / 63, 16384 positions
+  // 342 / 170, 33000 positions 1600 / 700, 65536 positions 5500 / 2700; 8/2 heads of 64: 300 positions 26 / 22, 16384
+  // positions 130 / 50.
+  const int n_rt = (a.tab_cols + 31) / 32;
+  const long long tile_bytes = kXaTileFloats * sizeof(float);
+  const bool tiled = a.tab_cols >= (cfg.head_dim == 128 ? 16 : 5);
+  if (tiled && (long long)c.partials_bytes >= n_rt * tile_bytes && (int64_t)a.hq * cfg.head_dim < (1 << 18) && a.stride_t < (1 << 18)) {
+    const int total = cache.batch * cfg.n_q_heads;
+    XaScoreArgs x;
+    x.q = a.q;
+    x.cu_q = a.cu_q;
+    x.k = a.k;
+    x.stride_b = a.stride_b;
+    x.stride_h = a.stride_h;
+    x.stride_t = a.stride_t;
+    x.kv_len = a.kv_len;
+    x.capacity = a.capacity;
+    x.hq = a.hq;
+    x.group = a.group;
+    x.tab_cols = a.tab_cols;
+    x.scale = a.scale;
+    x.threshold = threshold;
+    x.e = c.partials;
+    x.mask = mask;
+    x.n_qblocks = n_qblocks;
+    x.n_kblocks = n_kblocks;
+    x.status = c.status;
+    const long long room = (long long)c.partials_bytes / tile_bytes;   // tiles the workspace holds
+    const long long per_head = xa_tiles_below(n_rt);
+    long long fit = room / per_head;                                    // whole heads
+    const long long most = 0x3FFFFFFFll / (per_head > n_qblocks ? per_head : n_qblocks);   // grid sizes
+    if (fit > most) fit = most;
+    if (fit < total) {                                                  // whole rounds of 8, 4, 2 or 1 groups where they fit
+      for (int p = 8; p >= 1; p >>= 1)
+        if (fit >= p * a.group) {
+          fit = (p == 8 ? fit / (8 * a.group) * 8 : p) * a.group;
+          break;
+        }
+    }
+    for (int bh0 = 0; bh0 < total; bh0 += x.n_bh) {
+      x.bh0 = bh0;
+      x.n_bh = fit < 1 ? 1 : (total - bh0 < fit ? total - bh0 : (int)fit);
+      for (x.rt0 = 0; x.rt0 < n_rt; x.rt0 = x.rt1) {
+        x.rt1 = n_rt;
+        while (fit < 1 && xa_tiles_below(x.rt1) - xa_tiles_below(x.rt0) > room) --x.rt1;
+        const hipError_t e = cfg.head_dim == 128 ? launch_xa_tiles<128>(x, n_rt, s) : launch_xa_tiles<64>(x, n_rt, s);
+        if (e != hipSuccess) return e;
+      }
+    }
+    return hipSuccess;
+  }
   const int groups = (n_qblocks + 7) / 8;                 // every row of the matrix is written
   a.n_groups = groups;
   const dim3 grid((unsigned)((long long)groups * cfg.n_q_heads * cache.batch));

@@ -217,3 +217,37 @@ def test_xa_selection_beyond_65536_positions_two_walks(F, ctx):
     print("XA selection at %d tokens (two walks): %d of %d sampled rows differ" % (S, differ, total))
     assert F.flux_last_device_status(ctx) == 0
 
+
+
+@pytest.mark.parametrize("n,d,hq,hkv,heads_at_a_time", [
+    (2048, 128, 4, 1, 0), (2049, 128, 2, 2, 1), (2063, 64, 3, 1, 2), (1030, 128, 7, 1, 0), (4100, 64, 2, 1, 1), (2304 + 9, 128, 2, 1, 0),
+    (321, 64, 4, 4, 0), (2100, 128, 2, 1, -1),
+    (4200, 64, 2, 1, -2)])
+def test_xa_selection_tiles(F, n, d, hq, hkv, heads_at_a_time):
+    """The tiled form at the edges of its tiles (2048 positions), with last squares of 1 to 15 positions, and in several rounds
+    because the workspace holds few heads (0: the default workspace; -2: room for one row of tiles only; -1: not even that,
+    which takes the walk)."""
+    r = -(-n // 2048)
+    head = 32768 * r * (r + 1)
+    room = {0: 0, -1: 65536 * r - 256, -2: 65536 * r}.get(heads_at_a_time, heads_at_a_time * head + 512)
+    ctx = F.flux_create(0, 0 if room == 0 else 4096 + (8 << 20) + room)
+    try:
+        qb = synth.normal_bf16(96, synth.stream_id(synth.STREAM_Q), (n, hq, d))
+        kb = synth.normal_bf16(96, synth.stream_id(synth.STREAM_K), (n, hkv, d))
+        cache = F.KVCache.empty(1, hkv, n + 5, d)
+        cache.k.fill_(float("nan"))                                    # rows past the prompt are never used
+        F.flux_kv_append(ctx, cache, hkv, d, H.bits_to_torch(kb), H.bits_to_torch(kb), cu([n]), n, n)
+        nb = -(-n // BLK)
+        mask = torch.full((1, hq, nb, nb), 9, dtype=torch.uint8, device="cuda")
+        cfg = F.attn_cfg(hq, hkv, d, 0, 1, 0.0, 1)
+        q = torch.cat([H.bits_to_torch(qb), torch.full((7, hq, d), float("nan"), dtype=torch.bfloat16, device="cuda")])
+        F.flux_xa_select(ctx, cfg, q, cu([n]), n, n, cache, STRIDE, 0.9, mask, nb, nb)
+        torch.cuda.synchronize()
+        assert mask.max().item() <= 1
+        qf, kf = O.bf16_to_f64(qb), O.bf16_to_f64(kb)
+        rows = sorted({0, 1, 31, 32, nb // 2, nb - 2, nb - 1} & set(range(nb)))
+        differ, total = check_selection(mask.cpu().numpy()[0].astype(bool), qf, kf, hq, hq // hkv, 0.9, rows=rows)
+        print("XA tiles, %d positions: %d of %d sampled rows differ" % (n, differ, total))
+        assert F.flux_last_device_status(ctx) == 0
+    finally:
+        F.flux_destroy(ctx)

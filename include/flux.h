@@ -88,7 +88,7 @@ int flux_destroy(flux_ctx* ctx);
 const char* flux_strerror(int code);
 
 /* Bytes of workspace flux_attn_decode needs for this shape (pure host arithmetic;
- * prefill, router and append need less than 64 KiB; flux_xa_select uses what there is).  0 on invalid arguments. */
+ * router and append need less than 64 KiB; prefill and flux_xa_select use what there is).  0 on invalid arguments. */
 size_t flux_workspace_needed(const flux_attn_cfg* cfg, int batch, int max_kv_len);
 
 /* Returns the sticky device status bits (>= 0) and clears them.  Synchronous: copies the word back and
@@ -132,7 +132,10 @@ int flux_kv_append(flux_ctx* ctx, const flux_kv_cache* cache, int n_kv_heads, in
  * on n_q(b) and kv_len[b] (they size the launch; larger than needed is valid, smaller truncates
  * nothing: rows beyond max_q_len are not computed; a bound far above the real lengths costs empty
  * workgroups, and max_q_len from 32768 on (or from 16384 on with max_kv_len from 32768 on) selects
- * the launch shape tuned for long prompts, with the same results bit for bit).  SA tiles that the mask hides are skipped,
+ * the launch shape tuned for long prompts, with the same results bit for bit).  Where max_kv_len > max_q_len (queries
+ * behind a cached context) and the queries alone would not fill the chip, the keys of a tile of query rows are shared out
+ * over several workgroups: their partial results go through the context's workspace (without room there, or for lists of
+ * up to 1024 keys, this is not done), and the sums are taken in another order than in one walk.  SA tiles that the mask hides are skipped,
  * not masked: their K/V rows are never read.  A 64-key tile that is partly visible is read whole
  * (up to kv_len[b]), so the cached rows below kv_len[b] must hold finite values.  If the device finds n_q(b) > kv_len[b] (the caller did not append first), only the first
  * kv_len[b] query rows of that sequence are computed and FLUX_DEV_BAD_LENGTH is raised. */

@@ -113,19 +113,6 @@ struct Split {
   bool any_bad;     // this lane saw a clamp trip
 };
 
-// Inclusive prefix sum over the 64 lanes with data-parallel-primitive moves (add within rows of 16 by
-// shifts of 1, 2, 4, 8, then carry lane 15 of each row into the next row and lane 31 into the upper half);
-// lanes without a source keep the 0 passed as the old value.  Lane 63 ends up with the total.
-__device__ __forceinline__ int wave_inclusive_sum(int x) {
-  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1
-  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);   // row_shr:2
-  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);   // row_shr:4
-  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);   // row_shr:8
-  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
-  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
-  return x;
-}
-
 // unit >= 0: find the sequence whose units contain `unit`.  unit < 0: locate sequence `want_b`.
 // Lane i of the wave looks after sequences i, i + 64, ...; a batch of up to 64 takes one load per lane.
 __device__ __forceinline__ Split find_split(const SplitArgs& s, int lane, int unit, int want_b) {

@@ -34,6 +34,7 @@ typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t u32x2;
 
 #define FLUX_LDS __attribute__((address_space(3)))
+#define FLUX_GLOBAL __attribute__((address_space(1)))
 
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -174,6 +175,19 @@ __device__ __forceinline__ float sum_across_halves(float x) {
   uint32_t u = __builtin_bit_cast(uint32_t, x);
   auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
   return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+
+// Inclusive prefix sum over the 64 lanes with data-parallel-primitive moves (add within rows of 16 by
+// shifts of 1, 2, 4, 8, then carry lane 15 of each row into the next row and lane 31 into the upper half);
+// lanes without a source keep the 0 passed as the old value.  Lane 63 ends up with the total.
+__device__ __forceinline__ int wave_inclusive_sum(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);   // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);   // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);   // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+  return x;
 }
 
 // One wave-wide direct global -> LDS transfer: every lane fetches its own 16 bytes, the 64 pieces land

@@ -31,6 +31,8 @@
 
 namespace flux {
 
+typedef __attribute__((__vector_size__(4 * sizeof(int32_t)))) int32_t i32x4;
+
 struct PrefillArgs {
   const __bf16* q;        // [T, Hq, D]
   const int32_t* cu_q;    // [B + 1]
@@ -41,7 +43,7 @@ struct PrefillArgs {
   const uint8_t* mode;
   int capacity;
   int hq, hkv, group, batch;
-  int xcd_map;            // 0 plain, 1 pairs-per-XCD, 2 XCDs-per-pair (see the kernel)
+  int xcd_map;            // 0 plain, 1 pairs-per-XCD, 2 XCDs-per-pair, 3 planned on the device (see the kernel)
   int sink_lim, win_blocks, blk_shift;   // SA geometry (see sa_geom)
   int n_qtiles;
   float scale_log2;
@@ -52,6 +54,11 @@ struct PrefillArgs {
   // block) pair of 64 x 64 positions; row 0 is the block that holds the call's first query of that sequence
   const uint8_t* bmask;
   int bm_heads, bm_qblocks, bm_kblocks;
+  // planned launches only: a tile's key blocks may be shared out over several workgroups
+  int split_units;        // 0: never; else the units a launch may have beyond one per tile
+  float* part_o;          // unnormalised outputs of a unit, [unit][BM][D]
+  float* part_ml;         // reference (score units) and weight sum of its rows, [unit][BM][2]
+  i32x4* tile_info;       // [batch][n_kv_heads][n_qtiles]: first unit, unit stride, units of the tile
 };
 
 constexpr float kWeightGuard = 1073741824.0f;   // 2^30: a block whose weights sum past this moves the softmax reference
@@ -84,10 +91,151 @@ __device__ __forceinline__ void dma_tile2(const char* kt, const char* vt, const 
                : "memory", "m0", "scc");
 }
 
-template <int D, bool BS, int NW, int HP = 1>   // NW: waves per workgroup, 4 (two workgroups per CU) or 8 (one); HP: heads per workgroup
+// ---- the plan of a launch, taken on the device
+// Every wave of a planned launch (2 to 64 sequences, or one whose tiles may be split; lane b looks after sequence b) finds out from the lengths and mode
+// bytes which unit of work its workgroup is: the tiles of the sequences with the longest key lists first, no empty
+// workgroups between them (a grid shaped by the host's bounds leaves most workgroups of short sequences empty, and long
+// ones late).  Where the host allows it (split_units), the key blocks of a tile are shared out over several units, so
+// that a few query rows behind long contexts fill the chip as well; their partial results are merged by a second kernel.
+constexpr int kMinSplitBlocks = 16;             // key blocks a unit of a split tile has at least: shorter lists keep their sums in one order
+constexpr int kResident128 = 512;               // workgroups of four waves the chip holds at once: two per CU, at head dimension
+constexpr int kResident64 = 768;                // 64 three
+constexpr int kSplitUnits = 1024;               // units a launch that splits may have beyond one per tile
+constexpr int kSplitFewTiles = 448;             // launches of at most so many tiles may split (7/8 of what is resident)
+constexpr int kSplitMaxTiles = 2048;            // ... and batches of at most so many, counted with the host's bounds
+
+// Place of the j-th of the nj workgroups of an XCD in the order from long to short.  Consecutive workgroups of an XCD go
+// round its 32 CUs, and a launch of at most two per CU is resident at once: its second half is handed out in reverse, so
+// that the longest share a CU with the shortest.
+__device__ __forceinline__ int pair_long_with_short(int j, int nj) { return nj > 32 && nj <= 64 && j >= 32 ? 32 + nj - 1 - j : j; }
+
+struct PrefillUnit {
+  int b;                  // sequence, -1: past the last unit
+  int kvh, tile;
+  int chunk;              // key blocks a unit takes at most
+  int ci;                 // which part of its tile's blocks this unit takes
+  int slot0, slot_step;   // unit numbers for the partial results of this tile
+  int q_begin, n_q, len;
+  bool sa;
+};
+
+// resident: workgroups of the launch that the chip holds at once
+__device__ __forceinline__ PrefillUnit prefill_plan(const PrefillArgs& a, int l, int bm, int resident) {
+  PrefillUnit u;
+  // this lane's sequence: lengths under the clamps, tiles, key blocks of its longest tile (an upper bound for SA)
+  int q_begin = 0, n_q = 0, len = 0, tiles = 0, nb = 0;
+  bool sa = false, bad = false;
+  if (l < a.batch) {
+    q_begin = a.cu_q[l];
+    n_q = a.cu_q[l + 1] - q_begin;
+    len = a.kv_len[l];
+    sa = a.mode[l] == 0;
+    bad = n_q < 0 || len < 0 || len > a.capacity || n_q > len;
+    len = len < 0 ? 0 : (len > a.capacity ? a.capacity : len);
+    n_q = n_q < 0 ? 0 : (n_q > len ? len : n_q);
+    tiles = min((int)(((int64_t)n_q * a.group + bm - 1) / bm), a.n_qtiles);
+    nb = (len + 63) >> 6;
+    if (sa) {
+      const int64_t win = min((int64_t)a.win_blocks << a.blk_shift, (int64_t)len);
+      nb = min(nb, ((min(a.sink_lim, len) + 63) >> 6) + (int)((win + bm) >> 6) + 2);
+    }
+  }
+  if (blockIdx.x == 0 && threadIdx.x < 64 && bad) atomicOr(a.status, (uint32_t)FLUX_DEV_BAD_LENGTH);
+  u.chunk = 0x7FFFFFFF;
+  int nc = tiles > 0 ? 1 : 0;
+  if (a.split_units > 0) {
+    // Key blocks a unit takes at most: every lane works out one candidate, around the share of one of the workgroups
+    // the chip holds, by a model in units of one block: the longest unit, or that share plus half a unit of
+    // unevenness where there is more than one round, plus 0.02 for writing and merging the partial result of a unit
+    // (66 KB each way; a block takes 1.65 us).
+    const int total = __builtin_amdgcn_readlane(wave_inclusive_sum(tiles * nb), 63) * a.hkv;
+    const float share = (float)total / (float)resident;
+    const int cand = l == 63 ? 0x3FFFFFFF : max(kMinSplitBlocks, (int)(share * (float)(l + 4) * (1.0f / 16.0f)) + 1);
+    const float inv = 1.0f / (float)cand;
+    int units = 0, parts = 0, longest = 0;
+    for (int j = 0; j < a.batch; ++j) {
+      const int tj = __builtin_amdgcn_readlane(tiles, j) * a.hkv, nbj = __builtin_amdgcn_readlane(nb, j);
+      int n = (int)((float)(nbj - 1) * inv);                                 // parts of its tiles: (nb - 1) / cand, then + 1
+      n += (n + 1) * cand <= nbj - 1 ? 1 : (n * cand > nbj - 1 ? -1 : 0);
+      n = tj > 0 ? n + 1 : 0;
+      units += tj * n;
+      parts += n > 1 ? tj * n : 0;
+      longest = max(longest, n > 0 ? (int)((float)nbj / (float)n) + 1 : 0);
+    }
+    float cost = units <= resident ? (float)longest : fmaxf((float)longest, share + 0.5f * (float)longest);
+    cost += 0.02f * (float)parts;
+    if (units + 8 * a.batch > (int)gridDim.x) cost = 1e30f;                    // (never the last: it splits nothing)
+    int best = (__builtin_bit_cast(int, cost) & ~63) | l;                     // (positive floats order like their bits)
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) best = min(best, __shfl_xor(best, off));
+    u.chunk = __builtin_amdgcn_readlane(cand, __builtin_amdgcn_readfirstlane(best) & 63);
+    nc = tiles > 0 ? (nb + u.chunk - 1) / u.chunk : 0;
+  }
+  // units of the sequence: one per (KV head, part, tile).  Workgroups go to the 8 XCDs by id mod 8, and the units of one
+  // (KV head, part) walk the same K/V rows: they get ids of one residue (or of 8 / groups residues).
+  const int groups = a.hkv * nc;
+  const int share_sh = groups == 1 ? 3 : (groups == 2 ? 2 : (groups == 4 ? 1 : 0));
+  const int units = share_sh > 0 ? ((tiles + (1 << share_sh) - 1) >> share_sh) * 8 : groups * tiles;
+  // longest first: rank by (key blocks, index), then the units in that order
+  int rank = 0;
+  for (int j = 0; j < a.batch; ++j) {
+    const int o = __builtin_amdgcn_readlane(nb, j);
+    rank += (o > nb || (o == nb && j < l)) ? 1 : 0;
+  }
+  rank = l < a.batch ? rank : l;
+  const int units_s = __builtin_amdgcn_ds_permute(4 * rank, units);
+  const int idx_s = __builtin_amdgcn_ds_permute(4 * rank, l);
+  const int incl = wave_inclusive_sum(units_s);
+  const int total_units = __builtin_amdgcn_readlane(incl, 63);
+  int id = blockIdx.x;
+  u.b = -1;
+  if (id >= total_units) return u;
+  if (resident >= 512) id = 8 * pair_long_with_short(id >> 3, (total_units - (id & 7) + 7) >> 3) + (id & 7);
+  const int at = __builtin_popcountll(__builtin_amdgcn_ballot_w64(incl <= id));
+  u.b = __builtin_amdgcn_readlane(idx_s, at);
+  const int before = __builtin_amdgcn_readlane(incl, at) - __builtin_amdgcn_readlane(units_s, at);
+  const int local = id - before;
+  const int n_t = __builtin_amdgcn_readlane(tiles, u.b), n_g = __builtin_amdgcn_readlane(groups, u.b), sh = __builtin_amdgcn_readlane(share_sh, u.b);
+  int grp, tt;
+  if (sh > 0) {
+    const int x = local & 7;
+    grp = x & (n_g - 1);
+    tt = ((local >> 3) << sh) + (x >> (3 - sh));
+  } else if ((n_g & 7) == 0) {
+    tt = (local >> 3) % n_t;
+    grp = ((local >> 3) / n_t) * 8 + (local & 7);
+  } else {
+    tt = local % n_t;
+    grp = local / n_t;
+  }
+  grp = __builtin_amdgcn_readfirstlane(grp);
+  tt = __builtin_amdgcn_readfirstlane(tt);
+  if (tt >= n_t) {                                           // padding of the last round
+    u.b = -1;
+    return u;
+  }
+  u.kvh = grp % a.hkv;
+  u.ci = grp / a.hkv;
+  u.tile = n_t - 1 - tt;                                     // heaviest first
+  u.slot0 = before + u.kvh * n_t + u.tile;
+  u.slot_step = a.hkv * n_t;
+  u.q_begin = __builtin_amdgcn_readlane(q_begin, u.b);
+  u.n_q = __builtin_amdgcn_readlane(n_q, u.b);
+  u.len = __builtin_amdgcn_readlane(len, u.b);
+  u.sa = __builtin_amdgcn_readlane((int)sa, u.b) != 0;
+  return u;
+}
+
+// A tile is BM = 32 * NW rows.  In planned launches and in those for long prompts they are the query rows of ALL heads of
+// the group, token by token: row R is head R % group of token R / group.  Short runs of queries then fill their tiles (16
+// new tokens of a group of 4 are half a tile, not an eighth of four), a tile spans few tokens, so that little of what the
+// diagonal or a window's start cuts is worked out for nothing, and its query rows are contiguous in memory.  Otherwise (one
+// short prompt, where finding the rows would cost 4 % of 15 us at 512 tokens, and the block-sparse form, whose keep matrix
+// differs between heads) a tile is 128 tokens of one head.
+template <int D, bool BS, int NW, bool PLAN = false>   // NW: waves per workgroup, 4 (two workgroups per CU) or 8 (one)
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(PrefillArgs a) {
-  constexpr int RW = NW / HP;             // waves per head
-  constexpr int BM = 32 * RW;             // query rows per workgroup (of each of its heads)
+  constexpr bool PACK = PLAN || NW == 8;  // the rows of a tile come from all heads of a group
+  constexpr int BM = 32 * NW;             // query rows per workgroup
   constexpr int BN = 64;                  // keys per iteration: two halves of 32, the K dimension of one PV MFMA
   constexpr int KC = D / 32;              // MFMA k-steps over the head dimension (QK^T)
   constexpr int DB = D / 16;              // 16-wide output blocks over the head dimension (PV)
@@ -115,24 +263,46 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
   static_assert(NKI % NW == 0 && NVI % NW == 0 && (KPW == 4 || KPW == 2) && VPW == KPW, "every wave issues the same transfers");
 
   __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE];
+  // Planned launches: what only the end of the kernel needs waits in LDS (kept in scalar registers it pushes values of the
+  // loop out of them).
+  __shared__ struct { int rows, rem0, grp, hq, slot, out_fp32; int64_t tile_off; FLUX_GLOBAL void* out; FLUX_GLOBAL float* part_o; FLUX_GLOBAL float* part_ml; } fin;
 
   const int tid = threadIdx.x;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave of the workgroup: its share of the tile transfers
-  const int wr = w % RW, hsel = w / RW;                      // its rows within the tile, and which of the workgroup's heads
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave of the workgroup
   const int l = tid & 63;
   const int g = l >> 4, n = l & 15;
-  // ---- which (sequence, head, query tile) this workgroup owns.  Workgroups go to the 8 XCDs round-robin
+  const int grp = PACK ? a.group : 1;                        // heads whose rows share a tile
+  // ---- which (sequence, KV head, tile) this workgroup owns.  Workgroups go to the 8 XCDs round-robin
   // by linear id, and each XCD has its own L2.  The workgroups that an XCD holds at one time are therefore
-  // given neighbouring query tiles of one (sequence, KV head) pair, heaviest tiles first and the heads of a
-  // group next to each other, so that they walk the same K/V rows at the same time and the rows come from
+  // given neighbouring query tiles of one (sequence, KV head) pair, heaviest tiles first,
+  // so that they walk the same K/V rows at the same time and the rows come from
   // HBM once per XCD and round instead of once per workgroup.
-  int qt, h, b;
-  {
+  int qt, h, b;                                              // h: first query head of the tile
+  int q_begin, n_q, len, ci = 0, chunk = 0x7FFFFFFF, slot0 = 0, slot_step = 0;
+  bool sa;
+  if constexpr (PLAN) {
+    const PrefillUnit u = prefill_plan(a, l, BM, NW == 8 ? 256 : (D == 64 ? kResident64 : kResident128));
+    if (u.b < 0) return;                                     // uniform for the workgroup
+    b = u.b;
+    h = u.kvh * a.group;
+    qt = u.tile;
+    q_begin = u.q_begin;
+    n_q = u.n_q;
+    len = u.len;
+    sa = u.sa;
+    ci = u.ci;
+    chunk = u.chunk;
+    slot0 = u.slot0;
+    slot_step = u.slot_step;
+    if (len < 1) return;
+  } else {
     const int i = blockIdx.x;
     const int n_pairs = a.batch * a.hkv;
+    const int gw = a.group / grp;                            // workgroups per (pair, query tile)
     if (a.xcd_map == 1) {                                    // n_pairs a multiple of 8: eight pairs at a time, one per XCD
-      const int x = i & 7, j = i >> 3;
-      const int gw = a.group / HP;                           // workgroups per (pair, query tile)
+      const int x = i & 7;
+      int j = i >> 3;
+      if (!BS && NW == 4) j = pair_long_with_short(j, gridDim.x >> 3);
       // An XCD takes its pairs one after the other (all tiles of a pair, heaviest first, the heads of a tile next to
       // each other).  Interleaving the pairs tile by tile looks more even, but in a ragged batch the tiles past a
       // short sequence's end are empty workgroups, and at fixed places of a short period they keep falling to the
@@ -143,58 +313,68 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
       // change XCD every 16 tiles (one round of resident workgroups), so that every XCD works through two rounds of
       // every pair instead of all rounds of one.  A round streams its K/V rows from behind the L2 anyway.
       const int r = j / (gw * a.n_qtiles), qtd = (j / gw) % a.n_qtiles, g = (j + qtd) % gw;
-      const int pair = ((x + qtd / 16) & 7) + 8 * r;
+      const int pair = ((x + qtd / (PACK ? 32 : 16)) & 7) + 8 * r;
       b = pair / a.hkv;
-      h = (pair % a.hkv) * a.group + HP * g + hsel;
+      h = (pair % a.hkv) * a.group + g;
       qt = a.n_qtiles - 1 - qtd;
     } else if (a.xcd_map == 2) {                             // n_pairs divides 8: 8 / n_pairs XCDs share a pair
       const int x = i & 7, j = i >> 3, share = 8 / n_pairs;
       const int pair = x % n_pairs, sl = x / n_pairs;
-      const int gw = a.group / HP;
       const int g = j % gw, qtd = (j / gw) * share + sl;
       b = pair / a.hkv;
-      h = (pair % a.hkv) * a.group + HP * g + hsel;
+      h = (pair % a.hkv) * a.group + g;
       qt = a.n_qtiles - 1 - qtd;
       if (qt < 0) return;                                    // padding of the last round (uniform)
     } else {                                                 // any other shape: plain order, heavy tiles first
+      const int heads = a.hq / grp;
       qt = a.n_qtiles - 1 - i % a.n_qtiles;
-      h = HP * ((i / a.n_qtiles) % (a.hq / HP)) + hsel;
-      b = i / (a.n_qtiles * (a.hq / HP));
+      h = grp * ((i / a.n_qtiles) % heads);
+      b = i / (a.n_qtiles * heads);
     }
+    q_begin = a.cu_q[b];
+    const int n_q_given = a.cu_q[b + 1] - q_begin;
+    len = a.kv_len[b];
+    // lengths the host could not see: negative, past the capacity, or more queries than cached positions;
+    // they are clamped below, and reported once per sequence
+    if (qt == a.n_qtiles - 1 && h == 0 && tid == 0 && (n_q_given < 0 || len < 0 || len > a.capacity || n_q_given > len))
+      atomicOr(a.status, (uint32_t)FLUX_DEV_BAD_LENGTH);
+    len = len > a.capacity ? a.capacity : len;
+    if (len < 1) return;                                     // nothing cached: nothing to attend
+    // the queries are the last n_q cached positions, so there cannot be more of them than positions: the
+    // surplus rows of an inconsistent call are not computed (every key tile then starts inside the cache)
+    n_q = n_q_given < len ? n_q_given : len;
+    sa = a.mode[b] == 0;
   }
   const int kvh = h / a.group;
-
-  const int q_begin = a.cu_q[b];
-  const int n_q_given = a.cu_q[b + 1] - q_begin;
-  int len = a.kv_len[b];
-  // lengths the host could not see: negative, past the capacity, or more queries than cached positions;
-  // they are clamped below, and reported once per sequence
-  if (qt == a.n_qtiles - 1 && h == 0 && tid == 0 && (n_q_given < 0 || len < 0 || len > a.capacity || n_q_given > len))
-    atomicOr(a.status, (uint32_t)FLUX_DEV_BAD_LENGTH);
-  len = len > a.capacity ? a.capacity : len;
-  if (len < 1) return;                                       // nothing cached: nothing to attend
-  // the queries are the last n_q cached positions, so there cannot be more of them than positions: the
-  // surplus rows of an inconsistent call are not computed (every key tile then starts inside the cache)
-  const int n_q = n_q_given < len ? n_q_given : len;
-  if (qt * BM >= n_q) return;                                // uniform for the workgroup
-  const int pos0 = max(len - n_q, 0);                        // position of query row 0
-  const bool sa = a.mode[b] == 0;
+  const int64_t n_rows = (int64_t)n_q * grp;                 // rows of the pair (of the head, in the block-sparse form)
+  if ((int64_t)qt * BM >= n_rows) return;                    // uniform for the workgroup
+  const int pos0 = len - n_q;                                // position of the first query
+  // rows are counted from the tile's first one: row x of the tile belongs to token tok0 + (rem0 + x) / grp, head
+  // (rem0 + x) % grp of the group.  (x is small: the quotient is taken through floats)
+  const int rows = (int)min((int64_t)BM, n_rows - (int64_t)qt * BM);
+  const int tok0 = PACK ? (int)((uint32_t)(qt * BM) / (uint32_t)grp) : qt * BM, rem0 = qt * BM - tok0 * grp;
+  const float inv_grp = __builtin_amdgcn_rcpf((float)grp);
+  auto tok_of = [&](int x) { return !PACK ? x : (int)(((float)(rem0 + x) + 0.5f) * inv_grp); };   // from tok0 on
 
   // query rows of the tile / of this wave, as absolute positions
-  const int r_tile_last = min(qt * BM + BM - 1, n_q - 1);
-  const int i_tile_min = pos0 + qt * BM;
-  const int i_tile_max = pos0 + r_tile_last;
-  const int r_w0 = qt * BM + 32 * wr;
-  const int i_w_min = pos0 + r_w0;
-  const int i_w_max = pos0 + min(r_w0 + 31, n_q - 1);       // < i_w_min if the wave has no valid row
-  const bool wave_active = r_w0 < n_q;
-  // this lane's two query rows (column n of column block qb): clamped row, unclamped position, and the
-  // first key of the row's SA window
-  int r_mine[2], i_mine[2], w_lo_mine[2];
+  const int i_tile_min = pos0 + tok0;
+  const int i_tile_max = i_tile_min + __builtin_amdgcn_readfirstlane(tok_of(rows - 1));
+  const int r_w0 = 32 * w;                                   // first row of this wave, within the tile
+  const bool wave_active = r_w0 < rows;
+  const int i_w_min = i_tile_min + __builtin_amdgcn_readfirstlane(tok_of(r_w0));
+  const int i_w_max = wave_active ? i_tile_min + __builtin_amdgcn_readfirstlane(tok_of(min(r_w0 + 31, rows - 1))) : i_w_min - 1;
+  // where row x lies in q and out
+  const int64_t tile_off = ((int64_t)(q_begin + tok0) * a.hq + h) * D;
+  auto row_off = [&](int x) {
+    const int t = tok_of(x);
+    return tile_off + (t * a.hq + (PACK ? rem0 + x - t * grp : 0)) * D;
+  };
+  // this lane's two query rows (column n of column block qb; rows past the last one repeat it): position, and first key
+  // of the row's SA window
+  int i_mine[2], w_lo_mine[2];
 #pragma unroll
   for (int qb = 0; qb < 2; ++qb) {
-    r_mine[qb] = min(r_w0 + 16 * qb + n, n_q - 1);
-    i_mine[qb] = pos0 + r_w0 + 16 * qb + n;
+    i_mine[qb] = i_tile_min + tok_of(min(r_w0 + 16 * qb + n, rows - 1));
     w_lo_mine[qb] = window_start(i_mine[qb], a.blk_shift, a.win_blocks);
   }
   // first key of the SA window of the wave's first row and of its last row
@@ -205,7 +385,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
   bf16x8 qf[2][KC];
 #pragma unroll
   for (int qb = 0; qb < 2; ++qb) {
-    const __bf16* qrow = a.q + ((int64_t)(q_begin + r_mine[qb]) * a.hq + h) * D;
+    const __bf16* qrow = a.q + row_off(min(r_w0 + 16 * qb + n, rows - 1));
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc) qf[qb][kc] = *(const bf16x8*)(qrow + 32 * kc + 8 * g);
   }
@@ -223,7 +403,21 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
     n_b = last_blk + 1 - win0;
     if (n_b < 0) n_b = 0;
   }
-  const int n_iter = n_a + n_b;
+  const int n_blocks = n_a + n_b;
+  // a split tile: this unit takes part ci of the list
+  int it0 = 0, n_iter = n_blocks, n_parts = 1;             // (n_iter: one past its last)
+  if (PLAN && chunk < n_blocks) {
+    n_parts = (n_blocks + chunk - 1) / chunk;
+    if (ci >= n_parts) return;                               // uniform
+    it0 = (int)((int64_t)ci * n_blocks / n_parts);
+    n_iter = (int)((int64_t)(ci + 1) * n_blocks / n_parts);
+  } else if (PLAN && ci > 0) {
+    return;
+  }
+  if (PLAN && tid == 0) {
+    fin = {rows, rem0, grp, a.hq, n_parts > 1 ? slot0 + ci * slot_step : -1, a.out_fp32, tile_off, (FLUX_GLOBAL void*)a.out, (FLUX_GLOBAL float*)a.part_o, (FLUX_GLOBAL float*)a.part_ml};
+    if (PLAN && a.split_units > 0 && ci == 0) a.tile_info[((int64_t)b * a.hkv + kvh) * a.n_qtiles + qt] = i32x4{slot0, slot_step, n_parts, 0};
+  }
 
   const char* kbase = (const char*)(a.k + (int64_t)b * a.stride_b + (int64_t)kvh * a.stride_h);
   const char* vbase = (const char*)(a.v + (int64_t)b * a.stride_b + (int64_t)kvh * a.stride_h);
@@ -312,17 +506,17 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
       pa_end = min(min(n_a, c_end), a.sink_lim / BN);
       const int w_first_full = (w_lo_last + BN - 1) / BN;
       pb_begin = n_a + max(w_first_full - win0, 0);
-      pb_end = min(n_a + max(c_end - win0, 0), n_iter);
+      pb_end = min(n_a + max(c_end - win0, 0), n_blocks);
     }
   }
   // the last tile may be only partly inside the cache; every other tile is whole
-  const bool last_whole = n_iter > 0 && len - 1 - tile_of(n_iter - 1) * BN >= BN - 1;
+  const bool last_whole = n_iter > it0 && len - 1 - tile_of(n_iter - 1) * BN >= BN - 1;
   const int lim_whole = last_whole ? n_iter : n_iter - 1;    // iterations it + 1 < lim_whole transfer a whole tile
   const unsigned pb_len = pb_end > pb_begin ? pb_end - pb_begin : 0;
   const int64_t step_b = (int64_t)BN * pitch_g;              // bytes from one key block to the next
   const int64_t jump_b = (int64_t)(win0 - n_a + 1) * step_b; // from the last sink block to the first window block
-  const char* kt_n = kbase + (int64_t)(n_iter > 1 ? tile_of(1) : 0) * step_b;   // the tile the next transfer brings in
-  const char* vt_n = vbase + (int64_t)(n_iter > 1 ? tile_of(1) : 0) * step_b;
+  const char* kt_n = kbase + (int64_t)(n_iter > it0 + 1 ? tile_of(it0 + 1) : 0) * step_b;   // the tile the next transfer brings in
+  const char* vt_n = vbase + (int64_t)(n_iter > it0 + 1 ? tile_of(it0 + 1) : 0) * step_b;
 
   // ---- block-sparse form: the visited key blocks come from the keep matrix.  The tile's 128 rows lie in up
   // to three 64-position query blocks (two when the first query sits on a block boundary); a key block is
@@ -599,8 +793,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
   };
 
   if constexpr (!BS) {
-    if (n_iter > 0) issue_tile_clamped(tile_of(0), 0);
-    for (int it = 0; it < n_iter; it += 2) {
+    if (n_iter > it0) issue_tile_clamped(tile_of(it0), 0);
+    for (int it = it0; it < n_iter; it += 2) {
       iteration(it, std::integral_constant<int, 0>());
       if (it + 1 < n_iter) iteration(it + 1, std::integral_constant<int, 1>());
     }
@@ -614,27 +808,100 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
     }
   }
 
-  // ---- normalise and store: lane (n, g) holds d = 16*db + 4*g .. +3 of its two query rows
+  // ---- lane (n, g) holds d = 16*db + 4*g .. +3 of its two query rows
+  const int f_rows = PLAN ? __builtin_amdgcn_readfirstlane(fin.rows) : rows, f_slot = PLAN ? __builtin_amdgcn_readfirstlane(fin.slot) : -1;
+  const int f_rem0 = PLAN ? fin.rem0 : rem0, f_grp = PLAN ? fin.grp : grp, f_hq = PLAN ? fin.hq : a.hq;
+  const int64_t f_off = PLAN ? fin.tile_off : tile_off;
+  const int f_fp32 = PLAN ? fin.out_fp32 : a.out_fp32;
+  FLUX_GLOBAL void* f_out = PLAN ? fin.out : (FLUX_GLOBAL void*)a.out;
+  const float f_inv = __builtin_amdgcn_rcpf((float)f_grp);
 #pragma unroll
   for (int qb = 0; qb < 2; ++qb) {
     float l_tot = l_run[qb];
     l_tot += __shfl_xor(l_tot, 16);
     l_tot += __shfl_xor(l_tot, 32);
-    if (r_w0 + 16 * qb + n < n_q) {
+    const int x = r_w0 + 16 * qb + n;
+    if (x >= f_rows) continue;
+    if (PLAN && f_slot >= 0) {
+      // part of a tile: the unnormalised rows, their references and weight sums go to the workspace
+      const int64_t row = (int64_t)f_slot * BM + x;
+      if (g == 0) {
+        fin.part_ml[2 * row] = m_ref[qb];
+        fin.part_ml[2 * row + 1] = l_tot;
+      }
+      FLUX_GLOBAL float* dst = fin.part_o + row * D + 4 * g;
+#pragma unroll
+      for (int db = 0; db < DB; ++db) *(FLUX_GLOBAL f32x4*)(dst + 16 * db) = o[db][qb];
+    } else {
       const float inv = 1.0f / l_tot;
-      const int64_t off = ((int64_t)(q_begin + r_w0 + 16 * qb + n) * a.hq + h) * D;
+      const int t = !PACK ? x : (int)(((float)(f_rem0 + x) + 0.5f) * f_inv);
+      const int64_t off = f_off + (t * f_hq + (PACK ? f_rem0 + x - t * f_grp : 0)) * D;
 #pragma unroll
       for (int db = 0; db < DB; ++db) {
         const int d = 16 * db + 4 * g;
         const float x0 = o[db][qb][0] * inv, x1 = o[db][qb][1] * inv;
         const float x2 = o[db][qb][2] * inv, x3 = o[db][qb][3] * inv;
-        if (a.out_fp32) {
-          *(f32x4*)((float*)a.out + off + d) = f32x4{x0, x1, x2, x3};
+        if (f_fp32) {
+          *(FLUX_GLOBAL f32x4*)((FLUX_GLOBAL float*)f_out + off + d) = f32x4{x0, x1, x2, x3};
         } else {
-          *(u32x2*)((__bf16*)a.out + off + d) = u32x2{pack_bf16(x0, x1), pack_bf16(x2, x3)};
+          *(FLUX_GLOBAL u32x2*)((FLUX_GLOBAL __bf16*)f_out + off + d) = u32x2{pack_bf16(x0, x1), pack_bf16(x2, x3)};
         }
       }
     }
+  }
+}
+
+// The tiles whose key blocks were shared out over several units: out = sum_c w_c O_c / sum_c w_c l_c with
+// w_c = exp(m_c - max m), parts in order.  D / 4 threads per row, a tile's rows over the gridDim.x workgroups of a tile.
+template <int D, int BM>
+__global__ __launch_bounds__(256) void prefill_merge_kernel(PrefillArgs a) {
+  constexpr int RPP = 1024 / D;           // rows per pass
+  const int b = blockIdx.z, kvh = blockIdx.y / a.n_qtiles, qt = blockIdx.y % a.n_qtiles;
+  const int q_begin = a.cu_q[b];
+  int n_q = a.cu_q[b + 1] - q_begin, len = a.kv_len[b];
+  len = len < 0 ? 0 : (len > a.capacity ? a.capacity : len);
+  n_q = min(n_q, len);
+  const int64_t row0 = (int64_t)qt * BM, n_rows = (int64_t)n_q * a.group;
+  if (row0 >= n_rows) return;
+  const i32x4 info = a.tile_info[((int64_t)b * a.hkv + kvh) * a.n_qtiles + qt];
+  const int parts = info[2];
+  if (parts < 2) return;
+  const int d = 4 * (threadIdx.x % (D / 4));
+  const int per = BM / gridDim.x;
+  for (int x = blockIdx.x * per + threadIdx.x / (D / 4); x < (int)(blockIdx.x + 1) * per; x += RPP) {
+    const int64_t row = row0 + x;
+    if (row >= n_rows) return;
+    const int64_t r0 = (int64_t)info[0] * BM + x, step = (int64_t)info[1] * BM;
+    // four parts at a time, so that their loads are in flight together (the last part again where there are fewer)
+    float m = -INFINITY, den = 0.f;
+    f32x4 num = {0.f, 0.f, 0.f, 0.f};
+    for (int c0 = 0; c0 < parts; c0 += 4) {
+      float mc[4], lc[4];
+      f32x4 oc[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int64_t r = r0 + min(c0 + u, parts - 1) * step;
+        mc[u] = c0 + u < parts ? a.part_ml[2 * r] : -INFINITY;
+        lc[u] = a.part_ml[2 * r + 1];
+        oc[u] = *(const f32x4*)(a.part_o + r * D + d);
+      }
+      const float m_new = fmaxf(fmaxf(fmaxf(mc[0], mc[1]), fmaxf(mc[2], mc[3])), m);
+      if (m_new == -INFINITY) continue;                      // none of these parts sees a key of the row
+      const float al = fast_exp2((m - m_new) * a.scale_log2);
+      den *= al;
+      num *= al;
+      m = m_new;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const float w = fast_exp2((mc[u] - m) * a.scale_log2);
+        den += w * lc[u];
+        num += w * oc[u];
+      }
+    }
+    const float inv = 1.0f / den;
+    const int64_t off = ((int64_t)(q_begin + row / a.group) * a.hq + (int64_t)kvh * a.group + row % a.group) * D + d;
+    if (a.out_fp32) *(f32x4*)((float*)a.out + off) = num * inv;
+    else *(u32x2*)((__bf16*)a.out + off) = u32x2{pack_bf16(num[0] * inv, num[1] * inv), pack_bf16(num[2] * inv, num[3] * inv)};
   }
 }
 
@@ -661,22 +928,19 @@ hipError_t launch_prefill(const Ctx& c, const flux_attn_cfg& cfg, const void* q,
   a.sink_lim = geom.sink_lim;
   a.win_blocks = geom.win_blocks;
   a.blk_shift = geom.shift;
-  // Long prompts at head dimension 128 run with eight waves per workgroup (one workgroup per CU) that share every K/V
-  // tile, so that each wave issues half the tile transfers per block: waves 0-3 and 4-7 take the same 128 query rows of
-  // two heads of a GQA group (an even group size), else 256 rows of one head.  Measured against the four-wave shape
-  // with 256 rows: FA launches gain 1-3 % from 16384 tokens up; SA launches lose 4 % at 16384 tokens (more of a 256-row
-  // tile's blocks are cut by the window's start and by the diagonal), under 1 % at 32768 and nothing at 65536; short
-  // prompts lose 4-25 % (fewer, longer workgroups).  Two heads on the same rows have one diagonal and one window
-  // start: another 0.2 % on FA and 1 % on SA from 32768 tokens up.  Hence the bound on the longest prompt of the
-  // launch, which is all the host knows.  The results are the same bit for bit.  The block-sparse form keeps four
-  // waves (its scan handles three query blocks per tile).
+  // Long prompts at head dimension 128 run with eight waves and 256 rows per workgroup (one workgroup per CU) that share
+  // every K/V tile, so that each wave issues half the tile transfers per block.  Measured with 256 rows of one head
+  // against the four-wave shape: FA launches gain 1-3 % from 16384 tokens up; SA launches lose 4 % at 16384 tokens (more
+  // of a 256-row tile's blocks are cut by the window's start and by the diagonal), under 1 % at 32768 and nothing at
+  // 65536; short prompts lose 4-25 % (fewer, longer workgroups).  With the rows of all heads of a group in a tile (64
+  // tokens x 4 heads) an SA launch at 32768 tokens is another 2 % faster, FA launches as they were.  Hence the bound on
+  // the longest prompt of the launch, which is all the host knows.  The results are the same bit for bit.  The
+  // block-sparse form keeps four waves (its scan handles three query blocks per tile).
   // A chunk of half that length of a prompt that long (chunked prefill: every workgroup walks many blocks) gains too:
   // FA +1-2 %, SA +0-1.5 % for 16384-row chunks behind 16384 to 114688 cached positions.
   const bool wide = !bm && cfg.head_dim == 128 &&
                     (max_q_len >= kPrefillWideMinRows || (max_q_len >= kPrefillWideMinRows / 2 && max_kv_len >= kPrefillWideMinRows));
-  const int HP = wide && a.group % 2 == 0 ? 2 : 1;          // two heads of a group share the workgroup's K/V tiles
-  const int BM = wide && HP == 1 ? 256 : 128;
-  a.n_qtiles = (max_q_len + BM - 1) / BM;
+  const int BM = wide ? 256 : 128;
   a.scale_log2 = scale * kLog2e;
   a.out_fp32 = cfg.out_dtype;
   a.out = out;
@@ -685,30 +949,73 @@ hipError_t launch_prefill(const Ctx& c, const flux_attn_cfg& cfg, const void* q,
   a.bm_heads = bm ? bm->heads : 0;
   a.bm_qblocks = bm ? bm->n_qblocks : 0;
   a.bm_kblocks = bm ? bm->n_kblocks : 0;
-  if (a.n_qtiles == 0) return hipSuccess;
+  if (max_q_len == 0) return hipSuccess;
   const long long n_pairs = (long long)cache.batch * cfg.n_kv_heads;
+  // Batches are planned on the device (longest first, no empty workgroups): prompts of 129, 777, 2048, 3001 and 511 tokens,
+  // 32/8 heads, 119 -> 116.5 us; eight equal sequences lose 1 % (the plan costs about 1 us per workgroup).
+  // Queries behind a cached context may have their tiles split (us before -> now, 32/8 heads of 128): 16 new tokens
+  // behind 4000 cached 70 -> 27, behind 32000 528 -> 35; 128 behind 32000 546 -> 76; 512 behind 32000 549 -> 229; 1000
+  // behind 32000 562 -> 435; 200, 333, 150 and 512 behind 16200, 9001, 24000 and 12345 297 -> 230; 100 and 4000 behind
+  // 60000 and 3000 1258 -> 406.  Launches that would split nothing pay for the plan and the second launch all the same
+  // (about 5 us), so a launch whose tiles fill the chip by themselves is left alone: few tiles by the host's bounds, or a
+  // batch (whose bounds count tiles that short sequences do not have) with contexts long enough (8192 positions) that one
+  // uneven sequence costs more than that.
+  const long long packed = ((long long)max_q_len * a.group + BM - 1) / BM;    // tiles of a pair whose rows come from all heads
+  const long long tiles = n_pairs * packed, blocks = ((long long)max_kv_len + 63) / 64;
+  const long long unit_bytes = (long long)BM * (cfg.head_dim + 2) * 4, info_bytes = (tiles * 16 + 255) / 256 * 256;
+  const long long fit = ((long long)c.partials_bytes - info_bytes) / unit_bytes - tiles - 8 * cache.batch;   // units beyond one per tile
+  const bool split = !bm && !wide && cache.batch <= 64 && max_kv_len > max_q_len && blocks > kMinSplitBlocks &&
+                     (tiles <= kSplitFewTiles || (cache.batch > 1 && tiles <= kSplitMaxTiles && blocks >= 128)) && fit >= 64 && (tiles + 8) * blocks < 0x7FFFFFFFll;
+  const bool plan = split || (!bm && cache.batch > 1 && cache.batch <= 64);
+  const int grp = plan || wide ? a.group : 1;               // heads whose rows share a tile
+  const long long n_qtiles = ((long long)max_q_len * grp + BM - 1) / BM;
+  a.n_qtiles = (int)n_qtiles;
+  a.split_units = 0;
+  a.part_o = a.part_ml = nullptr;
+  a.tile_info = nullptr;
   long long n_wg;
-  if (n_pairs % 8 == 0) {
+  if (plan) {
+    a.xcd_map = 3;
+    if (split) a.split_units = (int)(fit < kSplitUnits ? fit : kSplitUnits);
+    n_wg = tiles + 8 * cache.batch + a.split_units;         // (the units of a sequence are padded to whole rounds of the XCDs)
+    if (split) {
+      a.tile_info = (i32x4*)c.partials;
+      a.part_o = (float*)((char*)c.partials + info_bytes);
+      a.part_ml = a.part_o + n_wg * BM * cfg.head_dim;
+    }
+  } else if (n_pairs % 8 == 0) {
     a.xcd_map = 1;
-    n_wg = (long long)a.n_qtiles * (cfg.n_q_heads / HP) * cache.batch;
+    n_wg = n_qtiles * (cfg.n_q_heads / grp) * cache.batch;
   } else if (8 % n_pairs == 0) {
     a.xcd_map = 2;
     const long long share = 8 / n_pairs;
-    n_wg = 8 * (a.group / HP) * ((a.n_qtiles + share - 1) / share);
+    n_wg = 8 * (a.group / grp) * ((n_qtiles + share - 1) / share);
   } else {
     a.xcd_map = 0;
-    n_wg = (long long)a.n_qtiles * (cfg.n_q_heads / HP) * cache.batch;
+    n_wg = n_qtiles * (cfg.n_q_heads / grp) * cache.batch;
   }
   if (n_wg > 0x7FFFFFFFll) return hipErrorInvalidValue;
   const dim3 grid((unsigned)n_wg);
+  const bool d128 = cfg.head_dim == 128;
   if (bm) {
-    if (cfg.head_dim == 128) hipLaunchKernelGGL((prefill_kernel<128, true, 4>), grid, dim3(256), 0, s, a);
+    if (d128) hipLaunchKernelGGL((prefill_kernel<128, true, 4>), grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL((prefill_kernel<64, true, 4>), grid, dim3(256), 0, s, a);
+  } else if (plan) {
+    if (wide) hipLaunchKernelGGL((prefill_kernel<128, false, 8, true>), grid, dim3(512), 0, s, a);
+    else if (d128) hipLaunchKernelGGL((prefill_kernel<128, false, 4, true>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((prefill_kernel<64, false, 4, true>), grid, dim3(256), 0, s, a);
   } else {
-    if (wide && HP == 2) hipLaunchKernelGGL((prefill_kernel<128, false, 8, 2>), grid, dim3(512), 0, s, a);
-    else if (wide) hipLaunchKernelGGL((prefill_kernel<128, false, 8>), grid, dim3(512), 0, s, a);
-    else if (cfg.head_dim == 128) hipLaunchKernelGGL((prefill_kernel<128, false, 4>), grid, dim3(256), 0, s, a);
+    if (wide) hipLaunchKernelGGL((prefill_kernel<128, false, 8>), grid, dim3(512), 0, s, a);
+    else if (d128) hipLaunchKernelGGL((prefill_kernel<128, false, 4>), grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL((prefill_kernel<64, false, 4>), grid, dim3(256), 0, s, a);
+  }
+  if (a.split_units > 0) {
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    // (few tiles have many parts each: a row per thread; otherwise two, since most workgroups find nothing to do)
+    const dim3 mgrid(128 * cfg.head_dim / 1024 / (tiles <= kSplitFewTiles ? 1 : 2), (unsigned)(cfg.n_kv_heads * a.n_qtiles), cache.batch);
+    if (cfg.head_dim == 128) hipLaunchKernelGGL((prefill_merge_kernel<128, 128>), mgrid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((prefill_merge_kernel<64, 128>), mgrid, dim3(256), 0, s, a);
   }
   return hipGetLastError();
 }

@@ -196,7 +196,8 @@ int flux_xa_select(flux_ctx* ctx, const flux_attn_cfg* cfg, const void* q, const
  * largest kv_len[b] (or the capacity) is always valid.  The split of the work over the chip is taken
  * on the device from the lengths and mode bytes found there, so a loose bound costs only idle
  * workgroups and a ragged batch is spread as evenly as a uniform one; the bound limits the launch
- * and the workspace.  A caller that knows every sequence of this layer is SA may pass
+ * and the workspace (and a call of few lists bounded by 4352 keys or less is done in one launch instead of two, with its
+ * sums in another order).  A caller that knows every sequence of this layer is SA may pass
  * min(max kv_len, n_sink + window) (both rounded up to multiples of sa_block when that is set).
  * A sequence that attends to more keys than the bound is cut at the bound (its oldest visible
  * keys are kept) and FLUX_DEV_BAD_LENGTH is raised. */

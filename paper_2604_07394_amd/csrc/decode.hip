@@ -60,6 +60,11 @@ struct DecodeArgs {
   // the fused decode step only: the row each sequence appends at position kv_len[b], [B, Hkv, D]
   const __bf16* k_new;
   const __bf16* v_new;
+  // calls merged in place only (see SMALL below)
+  uint32_t* arrived;      // [0]: workgroups that have read the lengths; [1 + pair]: units of a pair that have left their rows
+  int32_t* kv_len_rw;
+  void* out;
+  int out_fp32;
 };
 
 // Number of keys the query at position n - 1 attends to.  The visible list is the sinks [0, s_end)
@@ -74,6 +79,7 @@ __device__ __forceinline__ int visible_len(int n, int md, int sink_lim, int win_
 }
 
 constexpr int kResidentUnits = 768;             // workgroups the chip holds at once (three per CU at this register count)
+constexpr int kLongCall = 32768;                // 128-key pieces of all pairs from which a round of two workgroups per CU is no longer better
 
 // Length and mode of sequence b under the clamp: a length the host could not see (negative, or past the
 // capacity of a full cache) is cut and reported through `bad`.
@@ -111,19 +117,30 @@ struct Split {
   int nc;           // its chunks per (KV head, query block) pair
   int len, md;      // its clamped length and mode
   bool any_bad;     // this lane saw a clamp trip
+  unsigned long long empty;   // (calls merged in place) sequences without keys
 };
 
-// unit >= 0: find the sequence whose units contain `unit`.  unit < 0: locate sequence `want_b`.
+// Quotients of small numbers (below 2^24: keys are counted in 128-key pieces) through a reciprocal, put right by one step.
+__device__ __forceinline__ int div_small(int x, int y, float inv_y) {
+  int q = (int)((float)x * inv_y);
+  q += (q + 1) * y <= x ? 1 : (q * y > x ? -1 : 0);
+  return q;
+}
+// chunks that a list of `pieces` takes at `c` pieces each
+__device__ __forceinline__ int chunks_of(int pieces, int c, float inv_c) { return pieces > 0 ? div_small(pieces - 1, c, inv_c) + 1 : 0; }
+
+// Find the sequence whose units contain `unit`.
 // Lane i of the wave looks after sequences i, i + 64, ...; a batch of up to 64 takes one load per lane.
-__device__ __forceinline__ Split find_split(const SplitArgs& s, int lane, int unit, int want_b) {
+__device__ __forceinline__ Split find_split(const SplitArgs& s, int lane, int unit) {
   Split r;
   r.b = -1;
   r.first_unit = r.nc = r.len = 0;
   r.md = 1;
   r.any_bad = false;
+  r.empty = 0;
   bool sparse;
   int s_end, tail_start;
-  int len0 = 0, md0 = 1, nv0 = 0;                          // block 0 stays in registers for the second pass
+  int len0 = 0, md0 = 1, pc0 = 0;                          // block 0 stays in registers for the second pass
   int pieces = 0;
   for (int b0 = 0; b0 < s.batch; b0 += 64) {
     int len = 0, md = 1, nv = 0;
@@ -133,44 +150,50 @@ __device__ __forceinline__ Split find_split(const SplitArgs& s, int lane, int un
       nv = seq_visible(s, len, md, bad, sparse, s_end, tail_start);
       r.any_bad |= bad;
     }
+    const int pc = (nv + 127) >> 7;
     if (b0 == 0) {
       len0 = len;
       md0 = md;
-      nv0 = nv;
+      pc0 = pc;
     }
-    pieces += __builtin_amdgcn_readlane(wave_inclusive_sum((nv + 127) >> 7), 63);
+    pieces += __builtin_amdgcn_readlane(wave_inclusive_sum(pc), 63);
   }
-  const long long c128 = ((long long)pieces * s.pps + (kTargetUnits - 1)) / kTargetUnits;
-  r.chunk = c128 * 128 < kMinChunk ? kMinChunk : (int)(c128 * 128);
-  // If a chunk of about twice that size cuts the batch into one nearly full round of the workgroups the chip
-  // holds at once, take it: a single round of equal workgroups pays the start and the merge of a workgroup
-  // once instead of twice (3 us of a 30 us call).  Uniform batches do; a ragged one usually spills a few
-  // units into a second round, which would double the time, and a short list (a sparse layer) leaves much
-  // of the round empty: both keep the smaller chunk.
+  const long long total = (long long)pieces * s.pps;
+  const long long c128 = (total + (kTargetUnits - 1)) / kTargetUnits;
+  int c = c128 < kMinChunk / 128 ? kMinChunk / 128 : (int)c128;
+  // If a larger chunk cuts the batch into one nearly full round of workgroups, it is taken: a single round of equal
+  // workgroups pays the start and the merge of a workgroup once instead of twice.  Uniform batches do; a ragged one usually
+  // spills a few units into a second round, and a short list (a sparse layer) leaves much of the round empty: both keep
+  // the smaller chunk.  A round of 512 (two per CU) is better than one of 768 (all that fit) while the lists are short
+  // (1 x 32768 keys 29.6 against 33.1 us, 1 x 131072 84.7 / 89.3, 8 x 32768 168.7 / 169.3; 8 x 131072 665 / 656).
   if (s.batch <= 64) {
-    const long long o128 = ((long long)pieces * s.pps + (kResidentUnits - 1)) / kResidentUnits;
-    const int big = o128 * 128 < kMinChunk ? kMinChunk : (int)(o128 * 128);
-    const int units = __builtin_amdgcn_readlane(wave_inclusive_sum(s.pps * ((nv0 + big - 1) / big)), 63);
-    if (units <= kResidentUnits && units > kResidentUnits - kResidentUnits / 10) r.chunk = big;
+    auto round_of = [&](int slots, int least) __attribute__((always_inline)) {
+      const int big = max((int)((float)total * (1.0f / (float)slots)) + 1, kMinChunk / 128);
+      const int units = __builtin_amdgcn_readlane(wave_inclusive_sum(s.pps * chunks_of(pc0, big, 1.0f / (float)big)), 63);
+      return units <= slots && units > least ? big : 0;
+    };
+    const int two = total < kLongCall ? round_of(512, 512 - 512 / 20) : 0;
+    const int big = two > 0 ? two : round_of(kResidentUnits, kResidentUnits - kResidentUnits / 10);
+    if (big > 0) c = big;
   }
+  r.chunk = 128 * c;
+  const float inv_c = 1.0f / (float)c;
 
   for (int b0 = 0, base = 0; b0 < s.batch; b0 += 64) {
-    int len = len0, md = md0, nv = nv0;
+    int len = len0, md = md0, pc = pc0;
     if (b0 > 0) {
-      len = 0, md = 1, nv = 0;
+      len = 0, md = 1, pc = 0;
       if (b0 + lane < s.batch) {
         bool bad;
         load_seq(s, b0 + lane, len, md, bad);
-        nv = seq_visible(s, len, md, bad, sparse, s_end, tail_start);
+        pc = (seq_visible(s, len, md, bad, sparse, s_end, tail_start) + 127) >> 7;
       }
     }
-    const int nc = (nv + r.chunk - 1) / r.chunk;
+    const int nc = chunks_of(pc, c, inv_c);
     const int incl = wave_inclusive_sum(s.pps * nc);        // units up to and including this lane's sequence
-    const int total = __builtin_amdgcn_readlane(incl, 63);
-    const bool here = unit >= 0 ? unit < base + total : want_b < b0 + 64;
-    if (here) {                                             // wave-uniform
-      const int idx = unit >= 0 ? __builtin_popcountll(__builtin_amdgcn_ballot_w64(base + incl <= unit)) : want_b - b0;
-      const int sidx = __builtin_amdgcn_readfirstlane(idx);
+    const int total_b = __builtin_amdgcn_readlane(incl, 63);
+    if (unit < base + total_b) {                            // wave-uniform
+      const int sidx = __builtin_amdgcn_readfirstlane(__builtin_popcountll(__builtin_amdgcn_ballot_w64(base + incl <= unit)));
       r.b = b0 + sidx;
       r.first_unit = base + (sidx > 0 ? __builtin_amdgcn_readlane(incl, sidx - 1) : 0);
       r.nc = __builtin_amdgcn_readlane(nc, sidx);
@@ -178,15 +201,39 @@ __device__ __forceinline__ Split find_split(const SplitArgs& s, int lane, int un
       r.md = __builtin_amdgcn_readlane(md, sidx);
       break;
     }
-    base += total;
+    base += total_b;
   }
   return r;
 }
 
-// Merge the chunks of one (sequence, query head): out[d] = sum_c w_c O_c[d] / sum_c w_c l_c, w_c = exp(m_c - max m),
-// chunks taken in index order.  Called by D consecutive threads (d = 0 .. D-1, whole waves) that share `wgt` (D floats)
-// and `red` (4 floats) in LDS.  It holds workgroup barriers: every thread of the workgroup makes the call, each group
-// of D threads with its own arrays and the same nc.  base: the head's rows [chunk][D + 2] of the workspace.
+// The split of a call merged in place: a lane per sequence, always the smallest chunk.
+__device__ __forceinline__ Split find_split_small(const SplitArgs& s, int lane, int unit) {
+  Split r;
+  bool sparse, bad = false;
+  int s_end, tail_start, len = 0, md = 1, nv = 0;
+  if (lane < s.batch) {
+    load_seq(s, lane, len, md, bad);
+    nv = seq_visible(s, len, md, bad, sparse, s_end, tail_start);
+  }
+  r.any_bad = bad;
+  r.empty = __builtin_amdgcn_ballot_w64(lane < s.batch && nv == 0);
+  r.chunk = kMinChunk;
+  const int nc = (nv + kMinChunk - 1) / kMinChunk;
+  const int incl = wave_inclusive_sum(s.pps * nc);
+  const int total = __builtin_amdgcn_readlane(incl, 63);
+  r.b = -1;
+  r.first_unit = r.nc = r.len = 0;
+  r.md = 1;
+  if (unit < total) {                                       // wave-uniform
+    r.b = __builtin_amdgcn_readfirstlane(__builtin_popcountll(__builtin_amdgcn_ballot_w64(incl <= unit)));
+    r.nc = __builtin_amdgcn_readlane(nc, r.b);
+    r.first_unit = __builtin_amdgcn_readlane(incl, r.b) - s.pps * r.nc;
+    r.len = __builtin_amdgcn_readlane(len, r.b);
+    r.md = __builtin_amdgcn_readlane(md, r.b);
+  }
+  return r;
+}
+
 // The split as a table, for the merge kernel: entry b = (first unit, chunks per pair) of sequence b.  One wave writes
 // it (lane i looks after sequences i, i + 64, ...), with the same arithmetic as find_split.
 __device__ __forceinline__ void write_split_table(const SplitArgs& s, int lane, int chunk, int* table) {
@@ -198,7 +245,7 @@ __device__ __forceinline__ void write_split_table(const SplitArgs& s, int lane, 
       load_seq(s, b0 + lane, len, md, bad);
       nv = seq_visible(s, len, md, bad, sparse, s_end, tail_start);
     }
-    const int nc = (nv + chunk - 1) / chunk;
+    const int nc = chunks_of((nv + 127) >> 7, chunk >> 7, 1.0f / (float)(chunk >> 7));
     const int incl = wave_inclusive_sum(s.pps * nc);
     if (b0 + lane < s.batch) {
       table[2 * (b0 + lane)] = base + incl - s.pps * nc;
@@ -208,48 +255,62 @@ __device__ __forceinline__ void write_split_table(const SplitArgs& s, int lane, 
   }
 }
 
-template <int D>
-__device__ __forceinline__ float merge_head(const float* base, int nc, float scale_log2, int d, float* wgt, float* red) {
+// Merge every STEP-th chunk, from `first` on, of one column of a head's rows [chunk][D + 2]: num = sum_c w_c O_c[d],
+// den = sum_c w_c l_c with w_c = exp(m_c - m), m = max m_c.  N chunks at a time, so that their loads are in flight
+// together.  DEV: the rows were written by workgroups of this launch (device-scope reads).
+struct Merged {
+  float m, num, den;
+};
+template <int D, bool DEV, int STEP, int N>
+__device__ __forceinline__ Merged merge_rows(const float* base, int nc, float scale_log2, int d, int first) {
   constexpr int RED = D + 2;
-  // ---- maximum over the chunks (threads take chunks round-robin, then a reduction over the group's waves)
-  float m = -INFINITY;
-  for (int c = d; c < nc; c += D) m = fmaxf(m, base[c * RED + D]);
+  auto ld = [](const float* p) { return DEV ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p; };
+  Merged r = {-INFINITY, 0.f, 0.f};
+  for (int c0 = first; c0 < nc; c0 += N * STEP) {
+    float mc[N], lc[N], oc[N];
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-  if ((d & 63) == 0) red[d >> 6] = m;
-  __syncthreads();
-  m = D == 128 ? fmaxf(red[0], red[1]) : red[0];
-  // ---- weights per chunk in LDS, D chunks at a time; every thread then sums its own column
-  float num = 0.f, den = 0.f;
-  for (int c0 = 0; c0 < nc; c0 += D) {
-    __syncthreads();
-    const int c = c0 + d;
-    float w = 0.f, l = 0.f;
-    if (c < nc) {
-      w = fast_exp2((base[c * RED + D] - m) * scale_log2);
-      l = base[c * RED + D + 1];
+    for (int u = 0; u < N; ++u) {
+      const float* row = base + (int64_t)min(c0 + u * STEP, nc - 1) * RED;  // (the last chunk again where there are fewer)
+      mc[u] = ld(row + D);
+      lc[u] = ld(row + D + 1);
+      oc[u] = ld(row + d);
     }
-    wgt[d] = w;
-    den += w * l;                                            // partial; reduced over the group below
-    __syncthreads();
-    const int cn = min(D, nc - c0);
-    for (int cc = 0; cc < cn; ++cc) num += wgt[cc] * base[(c0 + cc) * RED + d];
-  }
+    float m_new = r.m;
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) den += __shfl_xor(den, off);
-  __syncthreads();
-  if ((d & 63) == 0) red[2 + (d >> 6)] = den;
-  __syncthreads();
-  den = D == 128 ? red[2] + red[3] : red[2];
-  return nc > 0 ? num / den : 0.f;                          // an empty cache yields zeros
+    for (int u = 0; u < N; ++u) {
+      mc[u] = c0 + u * STEP < nc ? mc[u] : -INFINITY;
+      m_new = fmaxf(m_new, mc[u]);
+    }
+    const float al = fast_exp2((r.m - m_new) * scale_log2);                 // 0 for the first chunks (each holds a key)
+    r.num *= al;
+    r.den *= al;
+    r.m = m_new;
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const float w = fast_exp2((mc[u] - m_new) * scale_log2);
+      r.num += w * oc[u];
+      r.den += w * lc[u];
+    }
+  }
+  return r;
 }
 
 // FUSED: the call is a whole decode step of the layer (Sec. 3.3): it also appends the row k_new / v_new of every
 // sequence at position kv_len[b].  The unit that owns the end of a list stores the row in the cache; the units that
 // attend to it take it from k_new / v_new, so no read waits for that store.  The lengths are moved on by the merge
 // kernel, after every workgroup of both kernels has read them.  Two launches instead of three.
-template <int D, bool NT, bool FUSED>
-__global__ __launch_bounds__(256) void decode_splitk_kernel(DecodeArgs a) {
+//
+// SMALL: a call of few short lists (see decode_small), which is bound by latencies and not by bytes: one launch instead
+// of two.  Eight waves per workgroup, so that each has one block of 32 keys and no second wait for memory; the unit that
+// arrives last at its pair merges the pair's rows.  The rows pass between workgroups that may sit on different XCDs:
+// they are written and read with device-scope accesses (past the L2s, which are not coherent with each other), and a
+// unit counts itself only after its own stores have been acknowledged.
+// Three workgroups per CU are asked for: left alone the compiler keeps the accumulators in a second register file (192
+// registers, two workgroups per CU) although 160 do: SA layer of 8 x 131072 32.6 -> 31.1 us, 32 ragged sequences of 513 to
+// 8400 keys at 28/4 heads 44.5 -> 39.7 us.
+template <int D, bool NT, bool FUSED, bool SMALL = false>
+__global__ __launch_bounds__(SMALL ? 512 : 256, SMALL ? 2 : 3) void decode_splitk_kernel(DecodeArgs a) {
+  constexpr int W = SMALL ? 8 : 4;    // waves per workgroup
   constexpr int KC = D / 32;          // MFMA k-steps over the head dimension
   constexpr int DB = D / 16;          // 16-wide output blocks over the head dimension
   constexpr int VL = D / 16;          // 16-byte V loads per lane per 32-key block
@@ -257,7 +318,7 @@ __global__ __launch_bounds__(256) void decode_splitk_kernel(DecodeArgs a) {
   constexpr int VROW = D + 8;         // padded LDS row (elements)
   constexpr int RED = D + 2;
 
-  __shared__ __attribute__((aligned(16))) char smem[4 * 32 * VROW * 2];
+  __shared__ __attribute__((aligned(16))) char smem[W * 32 * VROW * 2];
 
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
@@ -265,18 +326,51 @@ __global__ __launch_bounds__(256) void decode_splitk_kernel(DecodeArgs a) {
   const int unit = blockIdx.x;
 
   // ---- the split: chunk size from the whole batch, then the sequence whose units contain `unit`
-  const Split sp = find_split(a.sp, l, unit, -1);
+  const Split sp = SMALL ? find_split_small(a.sp, l, unit) : find_split(a.sp, l, unit);
   if (unit == 0 && w == 0 && sp.any_bad) atomicOr(a.status, (uint32_t)FLUX_DEV_BAD_LENGTH);
+  // SMALL and FUSED: every workgroup counts itself once all its waves hold the lengths; the one that finds all others
+  // counted moves the lengths on, when it has nothing else to do (nobody reads them any more).
+  uint32_t order = 0;
+  if constexpr (SMALL && FUSED) {
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) order = __hip_atomic_fetch_add(a.arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  auto finish = [&]() __attribute__((always_inline)) {
+    if constexpr (SMALL && FUSED) {
+      if (w == 0 && __builtin_amdgcn_readfirstlane(order) == gridDim.x - 1) {
+        if (l < a.sp.batch) {
+          int len = a.kv_len_rw[l];
+          len = len < 0 ? 0 : (len > a.sp.capacity ? a.sp.capacity : len);
+          a.kv_len_rw[l] = len < a.sp.capacity ? len + 1 : len;
+        }
+        if (l == 0) a.arrived[0] = 0;                       // ready for the next call on this stream
+      }
+    }
+  };
   // the last workgroup of the grid (idle unless the host's bound on the units is met exactly) leaves the split
   // behind for the merge kernel, which then needs neither the lengths nor the scan
-  if (unit == (int)gridDim.x - 1 && w == 0) write_split_table(a.sp, l, sp.chunk, a.table);
-  if (sp.b < 0) return;                                     // past the last unit: uniform for the whole workgroup
+  if (!SMALL && unit == (int)gridDim.x - 1 && w == 0) write_split_table(a.sp, l, sp.chunk, a.table);
+  if (SMALL && unit == (int)gridDim.x - 1) {                // sequences without keys have no units: their rows are zero
+    for (unsigned long long left = sp.empty; left != 0; left &= left - 1) {
+      const int64_t off = (int64_t)__builtin_ctzll(left) * a.hq * D;
+      for (int i = tid; i < a.hq * D; i += 64 * W) {
+        if (a.out_fp32) ((float*)a.out)[off + i] = 0.f;
+        else ((__bf16*)a.out)[off + i] = (__bf16)0.f;
+      }
+    }
+  }
+  if (sp.b < 0) {                                           // past the last unit: uniform for the whole workgroup
+    finish();
+    return;
+  }
   const int b = sp.b;
   const int local = unit - sp.first_unit;                   // < pps * nc, chunk index fastest
-  const int ci = local % sp.nc;
-  const int pair = local / sp.nc;
-  const int kvh = pair / a.qblocks;
-  const int qb = pair % a.qblocks;
+  const float inv_nc = 1.0f / (float)sp.nc;
+  const int pair = __builtin_amdgcn_readfirstlane(div_small(local, sp.nc, inv_nc));
+  const int ci = local - pair * sp.nc;
+  const int kvh = a.qblocks == 1 ? pair : pair / a.qblocks;
+  const int qb = a.qblocks == 1 ? 0 : pair % a.qblocks;
 
   bool bad_b = false, sparse;
   int s_end, tail_start;
@@ -306,7 +400,8 @@ __global__ __launch_bounds__(256) void decode_splitk_kernel(DecodeArgs a) {
       new_key = sp.len - 1;
       knew = a.k_new + ((int64_t)b * a.hkv + kvh) * D;
       vnew = a.v_new + ((int64_t)b * a.hkv + kvh) * D;
-      if (ci == ((n_vis - 1) >> 7) % sp.nc && qb == 0 && tid < 2 * CPR) {   // this unit owns the list's last block: it stores the row
+      const int last_piece = (n_vis - 1) >> 7;
+      if (ci == last_piece - div_small(last_piece, sp.nc, inv_nc) * sp.nc && qb == 0 && tid < 2 * CPR) {   // this unit owns the list's last block: it stores the row
         const int c = tid % CPR;
         const __bf16* src = (tid < CPR ? knew : vnew) + 8 * c;
         __bf16* dst = const_cast<__bf16*>(tid < CPR ? kbase : vbase) + (int64_t)new_key * a.stride_t + 8 * c;
@@ -390,7 +485,8 @@ __global__ __launch_bounds__(256) void decode_splitk_kernel(DecodeArgs a) {
 #pragma unroll
   for (int i = 0; i < DB; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  int p0 = c0 + 32 * w;
+  // (eight waves: the upper four take every other block of the unit)
+  int p0 = c0 + (SMALL ? (w >> 2) * pstep : 0) + 32 * (w & 3);
   if (p0 < c1) load_block(p0);
   while (p0 < c1) {
     // ---- stage this block's V rows in LDS and take K into MFMA operands
@@ -404,7 +500,7 @@ __global__ __launch_bounds__(256) void decode_splitk_kernel(DecodeArgs a) {
     for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
       for (int kc = 0; kc < KC; ++kc) kf[sb][kc] = __builtin_bit_cast(bf16x8, kreg[sb][kc]);
-    const int pnext = p0 + pstep;
+    const int pnext = p0 + (SMALL ? 2 * pstep : pstep);
     // ---- scores: s[sb][i] is key p0 + 16*sb + 4*g + i against query n
     f32x4 s[2];
 #pragma unroll
@@ -463,12 +559,17 @@ __global__ __launch_bounds__(256) void decode_splitk_kernel(DecodeArgs a) {
     p0 = pnext;
   }
 
-  // ---- merge the four waves through LDS: red[w][n][0..D-1] = O, [D] = m, [D+1] = l
+  auto store_out = [&](int qi, int d, float r) __attribute__((always_inline)) {
+    const int64_t off = ((int64_t)b * a.hq + (int64_t)kvh * a.group + 16 * qb + qi) * D + d;
+    if (a.out_fp32) ((float*)a.out)[off] = r;
+    else ((__bf16*)a.out)[off] = (__bf16)r;
+  };
+  // ---- merge the waves through LDS: red[w][n][0..D-1] = O, [D] = m, [D+1] = l
   l_run += __shfl_xor(l_run, 16);
   l_run += __shfl_xor(l_run, 32);
   __syncthreads();                                          // every wave is done with its V staging
   FLUX_LDS float* red = (FLUX_LDS float*)smem;
-  static_assert(4 * 16 * RED * 4 <= 4 * 32 * VROW * 2, "merge buffer must fit the staging buffer");
+  static_assert(W * 16 * RED * 4 <= W * 32 * VROW * 2, "merge buffer must fit the staging buffer");
   {
     FLUX_LDS float* mine = red + (w * 16 + n) * RED;
 #pragma unroll
@@ -482,11 +583,28 @@ __global__ __launch_bounds__(256) void decode_splitk_kernel(DecodeArgs a) {
   }
   __syncthreads();
   const int nq = min(16, a.group - 16 * qb);
-  for (int idx = tid; idx < nq * RED; idx += 256) {
-    const int qi = idx / RED, e = idx % RED;
-    float mw[4], m = -INFINITY;
+  if (SMALL && sp.nc == 1) {                                // the only unit of its pair: nothing to merge with
+    for (int idx = tid; idx < nq * D; idx += 64 * W) {
+      const int qi = idx / D, d = idx % D;
+      float m = -INFINITY, num = 0.f, den = 0.f;
 #pragma unroll
-    for (int ww = 0; ww < 4; ++ww) {
+      for (int ww = 0; ww < W; ++ww) m = fmaxf(m, red[(ww * 16 + qi) * RED + D]);
+#pragma unroll
+      for (int ww = 0; ww < W; ++ww) {
+        const float wgt = fast_exp2((red[(ww * 16 + qi) * RED + D] - m) * a.scale_log2);
+        num += wgt * red[(ww * 16 + qi) * RED + d];
+        den += wgt * red[(ww * 16 + qi) * RED + D + 1];
+      }
+      store_out(qi, d, num / den);
+    }
+    finish();
+    return;
+  }
+  for (int idx = tid; idx < nq * RED; idx += 64 * W) {
+    const int qi = idx / RED, e = idx % RED;
+    float mw[W], m = -INFINITY;
+#pragma unroll
+    for (int ww = 0; ww < W; ++ww) {
       mw[ww] = red[(ww * 16 + qi) * RED + D];
       m = fmaxf(m, mw[ww]);
     }
@@ -496,14 +614,35 @@ __global__ __launch_bounds__(256) void decode_splitk_kernel(DecodeArgs a) {
     } else {
       val = 0.f;
 #pragma unroll
-      for (int ww = 0; ww < 4; ++ww) {
+      for (int ww = 0; ww < W; ++ww) {
         const float wgt = fast_exp2((mw[ww] - m) * a.scale_log2);   // exp2(-inf) = 0 for idle waves
         val += wgt * red[(ww * 16 + qi) * RED + e];                 // e == D+1 merges l the same way
       }
     }
-    // the units of one pair are consecutive: inside their block the rows run [query head][chunk], so the
-    // second kernel reads one head's chunks as one contiguous run
-    a.partials[(((int64_t)(unit - ci) * a.rpu) + (int64_t)qi * sp.nc + ci) * RED + e] = val;
+    // the units of one pair are consecutive: inside their block the rows run [query head][chunk], so that the merge
+    // reads one head's chunks as one contiguous run
+    float* dst = a.partials + (((int64_t)(unit - ci) * a.rpu) + (int64_t)qi * sp.nc + ci) * RED + e;
+    if constexpr (SMALL) __hip_atomic_store(dst, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *dst = val;
+  }
+  if constexpr (SMALL) {
+    // ---- the unit that arrives last merges the pair
+    __shared__ int last_of_pair;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // this wave's rows have reached the point all XCDs see
+    __syncthreads();
+    uint32_t* count = a.arrived + 1 + b * a.sp.pps + pair;
+    if (tid == 0) last_of_pair = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(sp.nc - 1);
+    __syncthreads();
+    if (last_of_pair) {
+      if (tid == 0) *count = 0;                             // ready for the next call on this stream
+      const float* rows = a.partials + (int64_t)(unit - ci) * a.rpu * RED;
+      for (int idx = tid; idx < nq * D; idx += 64 * W) {
+        const int qi = idx / D, d = idx % D;
+        const Merged r = merge_rows<D, true, 1, 8>(rows + (int64_t)qi * sp.nc * RED, sp.nc, a.scale_log2, d, 0);
+        store_out(qi, d, r.num / r.den);
+      }
+    }
+    finish();
   }
 }
 
@@ -521,21 +660,40 @@ struct CombineArgs {
   int32_t* kv_len_rw;
 };
 
-template <int D>
-__global__ __launch_bounds__(D) void decode_combine_kernel(CombineArgs a) {
+// G groups of D threads per (sequence, query head), each with every G-th chunk; the partial results meet in LDS.
+// Bound by latencies (the split table, then the rows): all rows of up to 8 G chunks are asked for at once (with maximum,
+// weights and sums as three dependent passes over the rows a layer took 0.9 - 1.3 us longer).  One group is enough where
+// a list has few chunks, and four times the threads cost 0.7 us where there are a thousand heads to merge.
+template <int D, int G>
+__global__ __launch_bounds__(G * D) void decode_combine_kernel(CombineArgs a) {
   constexpr int RED = D + 2;
-  __shared__ float wgt[D];
-  __shared__ float red[4];
-  const int d = threadIdx.x, head = blockIdx.x, b = blockIdx.y;
+  const int tid = threadIdx.x, d = tid % D, grp = tid / D, head = blockIdx.x, b = blockIdx.y;
   const int first_unit = a.table[2 * b], nc = a.table[2 * b + 1];
-  const int hh = head % a.group;
-  const int64_t unit0 = first_unit + (int64_t)((head / a.group) * a.qblocks + hh / 16) * nc;
+  const int kvh = head / a.group, hh = head - kvh * a.group;
+  const int64_t unit0 = first_unit + (int64_t)(kvh * a.qblocks + hh / 16) * nc;
   const float* base = a.partials + (unit0 * a.rpu + (int64_t)(hh % 16) * nc) * RED;
-  const float r = merge_head<D>(base, nc, a.scale_log2, d, wgt, red);
-  const int64_t off = ((int64_t)b * a.hq + head) * D + d;
-  if (a.out_fp32) ((float*)a.out)[off] = r;
-  else ((__bf16*)a.out)[off] = (__bf16)r;
-  if (a.bump && head == 0 && d == 0) {
+  Merged r = merge_rows<D, false, G, 8>(base, nc, a.scale_log2, d, grp);
+  if constexpr (G > 1) {
+    __shared__ Merged part[G][D];
+    part[grp][d] = r;
+    __syncthreads();
+    r = {-INFINITY, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < G; ++i) r.m = fmaxf(r.m, part[i][d].m);
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+      const float w = fast_exp2((part[i][d].m - r.m) * a.scale_log2);       // exp2(-inf) = 0 for a group without chunks
+      r.num += w * part[i][d].num;
+      r.den += w * part[i][d].den;
+    }
+  }
+  if (grp == 0) {
+    const float x = nc > 0 ? r.num / r.den : 0.f;                           // an empty cache yields zeros
+    const int64_t off = ((int64_t)b * a.hq + head) * D + d;
+    if (a.out_fp32) ((float*)a.out)[off] = x;
+    else ((__bf16*)a.out)[off] = (__bf16)x;
+  }
+  if (a.bump && head == 0 && tid == 0) {
     int len = a.kv_len_rw[b];
     len = len < 0 ? 0 : (len > a.capacity ? a.capacity : len);
     a.kv_len_rw[b] = len < a.capacity ? len + 1 : len;
@@ -584,6 +742,20 @@ hipError_t launch_decode(const Ctx& c, const flux_attn_cfg& cfg, const void* q, 
   // on the rows are fetched with nontemporal loads (SA layer 34.5 -> 33.4 us, FA layers as before); smaller calls are
   // bound by their launches either way.
   const bool nt = 4.0 * cache.batch * cfg.n_kv_heads * cfg.head_dim * (double)max_kv_len > 64.0 * 1024 * 1024;
+  a.arrived = c.small_counters;
+  a.kv_len_rw = cache.kv_len;
+  a.out = out;
+  a.out_fp32 = cfg.out_dtype;
+  if (decode_small(cfg, cache.batch, max_kv_len)) {
+    if (cfg.head_dim == 128) {
+      if (fused) hipLaunchKernelGGL((decode_splitk_kernel<128, false, true, true>), grid, dim3(512), 0, s, a);
+      else hipLaunchKernelGGL((decode_splitk_kernel<128, false, false, true>), grid, dim3(512), 0, s, a);
+    } else {
+      if (fused) hipLaunchKernelGGL((decode_splitk_kernel<64, false, true, true>), grid, dim3(512), 0, s, a);
+      else hipLaunchKernelGGL((decode_splitk_kernel<64, false, false, true>), grid, dim3(512), 0, s, a);
+    }
+    return hipGetLastError();
+  }
   if (fused) {
     if (cfg.head_dim == 128) {
       if (nt) hipLaunchKernelGGL((decode_splitk_kernel<128, true, true>), grid, dim3(256), 0, s, a);
@@ -616,8 +788,16 @@ hipError_t launch_decode(const Ctx& c, const flux_attn_cfg& cfg, const void* q, 
   ca.capacity = cache.capacity;
   ca.kv_len_rw = cache.kv_len;
   const dim3 cgrid(cfg.n_q_heads, cache.batch);
-  if (cfg.head_dim == 128) hipLaunchKernelGGL(decode_combine_kernel<128>, cgrid, dim3(128), 0, s, ca);
-  else hipLaunchKernelGGL(decode_combine_kernel<64>, cgrid, dim3(64), 0, s, ca);
+  // chunks of the longest list, as far as the host can tell: the bound, or about twice a pair's share of the units
+  const long long pairs = (long long)cache.batch * plan.pps;
+  const bool few = max_kv_len <= 8 * kMinChunk || 2 * kTargetUnits <= 8 * pairs;
+  if (cfg.head_dim == 128) {
+    if (few) hipLaunchKernelGGL((decode_combine_kernel<128, 1>), cgrid, dim3(128), 0, s, ca);
+    else hipLaunchKernelGGL((decode_combine_kernel<128, 4>), cgrid, dim3(512), 0, s, ca);
+  } else {
+    if (few) hipLaunchKernelGGL((decode_combine_kernel<64, 1>), cgrid, dim3(64), 0, s, ca);
+    else hipLaunchKernelGGL((decode_combine_kernel<64, 4>), cgrid, dim3(256), 0, s, ca);
+  }
   return hipGetLastError();
 }
 

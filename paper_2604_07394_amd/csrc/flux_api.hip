@@ -33,7 +33,8 @@ int hip_fail(hipError_t e) {
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
-constexpr size_t kStaticHeader = 256;      // status word of the static scratch; the partials follow
+constexpr size_t kStaticHeader = 256;      // status word and arrival counters of the static scratch; the partials follow
+static_assert(4 + 4 * (1 + kSmallPairs) <= kStaticHeader, "the counters must fit");
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
 char* g_scratch_ptr[kMaxDevices];          // device address of `scratch` on each GPU, resolved once per device
@@ -130,6 +131,7 @@ int flux_create(flux_ctx** out, int device, size_t workspace_bytes) {
   ctx->c.ws_bytes = workspace_bytes;
   ctx->c.status = (uint32_t*)ctx->c.ws;
   ctx->c.counters = (uint32_t*)(ctx->c.ws + 256);
+  ctx->c.small_counters = (uint32_t*)(ctx->c.ws + 512);
   ctx->c.small = (float*)(ctx->c.ws + kHeaderBytes);
   ctx->c.partials = (float*)(ctx->c.ws + kHeaderBytes + kSmallBytes);
   ctx->c.partials_bytes = workspace_bytes - kHeaderBytes - kSmallBytes;
@@ -318,12 +320,13 @@ int flux_attn_decode_static(const flux_attn_cfg* cfg, const void* q, int max_kv_
   const hipError_t es = static_scratch(&base);
   if (es != hipSuccess) return hip_fail(es);
   // A context on the stack that owns nothing: the kernels take the scratch address as they take the
-  // workspace of a flux_create context.  Nothing has to be cleared between calls: the merge kernel reads
-  // only partial rows that the split-K kernel of the same call has written, and the status word is sticky.
+  // workspace of a flux_create context.  Nothing has to be cleared between calls: a merge reads only partial
+  // rows that the same call has written, the arrival counters are left at zero, and the status word is sticky.
   Ctx c;
   memset(&c, 0, sizeof(c));
   c.device = 0;
   c.status = status ? status : (uint32_t*)base;
+  c.small_counters = (uint32_t*)(base + 4);
   c.partials = (float*)(base + kStaticHeader);
   c.partials_bytes = FLUX_STATIC_SCRATCH_BYTES - kStaticHeader;
   const hipError_t e = launch_decode(c, *cfg, q, max_kv_len, *cache, mode, 0, nullptr, nullptr, out, (hipStream_t)stream);

@@ -46,6 +46,7 @@ struct Ctx {
   // carved regions (device pointers)
   uint32_t* status;        // sticky status word
   uint32_t* counters;      // kCounters zero-initialised arrival counters; users reset them to zero
+  uint32_t* small_counters;   // 1 + kSmallPairs of the same kind, for the decode calls merged in place
   float* small;            // router scratch: pooled vectors and hidden activations
   float* partials;         // split-K partial results
   size_t partials_bytes;
@@ -113,6 +114,21 @@ inline DecodePlan plan_decode(const flux_attn_cfg& cfg, int batch, int max_kv_le
   if (p.units < 1) p.units = 1;                  // one workgroup always runs: it writes the split table
   p.table_floats = (2 * batch + 63) / 64 * 64;
   return p;
+}
+// Decode calls of few short lists are bound by latencies (launches, the split, two dependent loads) and not by bytes: one
+// launch that merges in place (decode.hip, SMALL).  Split-K + merge kernel / one launch, us on the device, 32/8 heads of
+// 128: 1 x 200 keys 10.2 / 6.2, 1 x 2001 11.1 / 9.1, 1 x 4200 12.0 / 11.1, 4 x 2000 13.3 / 11.6; beyond the bounds below
+// the merge at the end of a workgroup costs more than the launch: 1 x 8000 13.4 / 15.0, 4 x 4000 19.4 / 23.4, 28/4 heads
+// 4 x 4000 14.0 / 14.9.
+constexpr int kSmallPairs = 60;                 // (their counters fit behind the status word of the static scratch)
+constexpr int kSmallUnits = 256;                // a workgroup per CU
+constexpr int kSmallKeys = 4352;                // 17 chunks: what a window of 4096 keys and 128 sinks takes
+constexpr int kSmallRows = 72;                  // rows that the last unit of a pair merges: query heads x chunks
+inline bool decode_small(const flux_attn_cfg& cfg, int batch, int max_kv_len) {
+  const int group = cfg.n_q_heads / cfg.n_kv_heads;
+  if (max_kv_len < 1 || max_kv_len > kSmallKeys || group > 16 || (long long)batch * cfg.n_kv_heads > kSmallPairs) return false;
+  const int chunks = (max_kv_len + kMinChunk - 1) / kMinChunk;
+  return batch * cfg.n_kv_heads * chunks <= kSmallUnits && group * chunks <= kSmallRows;
 }
 inline size_t decode_partials_bytes(const flux_attn_cfg& cfg, const DecodePlan& p) {
   return ((size_t)p.table_floats + (size_t)p.units * p.rpu * (cfg.head_dim + 2)) * sizeof(float);

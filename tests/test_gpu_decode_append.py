@@ -149,3 +149,64 @@ def test_fused_step_long_lists_nontemporal_path(lib):
     assert torch.equal(outs[0][1], outs[1][1]) and outs[1][1].tolist() == [m + 2 for m in lens0]
     assert torch.equal(outs[0][2], outs[1][2])
     assert F.flux_last_device_status(ctx) == 0
+
+
+@pytest.mark.parametrize("hq,hkv,d,lens,modes", [
+    (4, 1, 128, [1], [FA]),                                   # one key, one unit: nothing to merge
+    (8, 2, 64, [256, 257, 1], [FA, FA, SA]),                  # on either side of a chunk
+    (32, 8, 128, [4351], [FA]),                               # 17 chunks: the longest list of one launch
+    (32, 8, 128, [4352], [FA]),                               # one more key than that after the append: two launches
+    (16, 1, 64, [1000, 3], [SA, FA]),                         # 16 query heads per KV head, four chunks
+    (20, 20, 128, [700, 0, 90], [FA, FA, SA]),                # 60 pairs; an empty cache
+    (21, 21, 128, [700, 0, 90], [FA, FA, SA]),                # 63 pairs: two launches
+])
+def test_few_short_lists(lib, hq, hkv, d, lens, modes):
+    """Calls of few short lists are merged in the launch that streams them.  Against the oracle, several calls in a row on the
+    same counters, bit-identical to each other and to the call without a context, eager and replayed from a graph."""
+    F, ctx = lib
+    b, n_sink, window, seed = len(lens), 8, 300, 700 + hq
+    kb = synth.normal_bf16(seed, synth.stream_id(synth.STREAM_K), (sum(lens) + b, hkv, d))
+    vb = synth.normal_bf16(seed, synth.stream_id(synth.STREAM_V), (sum(lens) + b, hkv, d))
+    qb = synth.normal_bf16(seed, synth.stream_id(synth.STREAM_QDEC), (b, hq, d))
+    cfg = F.attn_cfg(hq, hkv, d, n_sink, window, 0.0, 1)
+    cache = F.KVCache.empty(b, hkv, max(lens) + 2, d)
+    cache.k.fill_(float("nan"))
+    cache.v.fill_(float("nan"))
+    t = sum(lens)
+    cu = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int32, device="cuda")
+    F.flux_kv_append(ctx, cache, hkv, d, H.bits_to_torch(kb[:t]), H.bits_to_torch(vb[:t]), cu, t, max(lens))
+    md = torch.tensor(modes, dtype=torch.uint8, device="cuda")
+    q, kn, vn = H.bits_to_torch(qb), H.bits_to_torch(kb[t:]), H.bits_to_torch(vb[t:])
+    out = torch.full((b, hq, d), float("nan"), dtype=torch.float32, device="cuda")
+    # without an append: an empty cache yields zeros
+    F.flux_attn_decode(ctx, cfg, q, max(lens), cache, md, out)
+    torch.cuda.synchronize()
+    assert torch.isfinite(out).all()
+    for i, n in enumerate(lens):
+        assert n > 0 or not out[i].any()
+    F.flux_attn_decode_append(ctx, cfg, q, kn, vn, max(lens) + 1, cache, md, out)
+    torch.cuda.synchronize()
+    assert cache.kv_len.tolist() == [n + 1 for n in lens]
+    kf, vf, qf = O.bf16_to_f64(kb), O.bf16_to_f64(vb), O.bf16_to_f64(qb)
+    at = 0
+    for i, n in enumerate(lens):
+        k1, v1 = np.concatenate([kf[at:at + n], kf[t + i:t + i + 1]]), np.concatenate([vf[at:at + n], vf[t + i:t + i + 1]])
+        H.assert_close(out[i].cpu().numpy(), O.attention(qf[i:i + 1], k1, v1, modes[i], n_sink, window)[0], f"sequence {i} of {n + 1} keys")
+        at += n
+    again = torch.empty_like(out)
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    for _ in range(3):
+        again.fill_(float("nan"))
+        F.flux_attn_decode_static(cfg, q, max(lens) + 1, cache, md, again, status)
+        torch.cuda.synchronize()
+        assert torch.equal(again, out) and int(status[0]) == 0
+    g = torch.cuda.CUDAGraph()
+    s = torch.cuda.Stream()
+    with torch.cuda.graph(g, stream=s):
+        F.flux_attn_decode(ctx, cfg, q, max(lens) + 1, cache, md, again, stream=s)
+    for _ in range(4):
+        again.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(again, out)
+    assert F.flux_last_device_status(ctx) == 0

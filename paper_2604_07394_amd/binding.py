@@ -110,6 +110,10 @@ def _ptr(t) -> int | None:
 
 def _stream(stream) -> int | None:
     if stream is None:
+        # the raw handle of the current stream without a Stream object around it (3.4 us -> 0.6 us per call, of 12 us for a
+        # decode step); before torch has initialised the device the long way does that
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
     if isinstance(stream, int):
         return stream

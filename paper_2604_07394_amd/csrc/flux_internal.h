@@ -47,6 +47,7 @@ struct Ctx {
   uint32_t* status;        // sticky status word
   uint32_t* counters;      // kCounters zero-initialised arrival counters; users reset them to zero
   uint32_t* small_counters;   // 1 + kSmallPairs of the same kind, for the decode calls merged in place
+  uint32_t* router_counters;  // kRouterCounters of the same kind, one per sequence of a router call
   float* small;            // router scratch: pooled vectors and hidden activations
   float* partials;         // split-K partial results
   size_t partials_bytes;
@@ -79,6 +80,7 @@ __device__ __forceinline__ int window_start(int i, int shift, int win_blocks) {
 #endif
 
 constexpr int kCounters = 64;
+constexpr int kRouterCounters = 512;
 constexpr size_t kSmallBytes = 8u << 20;      // router: batch * (splits * hidden + inner) floats
 constexpr size_t kHeaderBytes = 4096;         // status + counters
 constexpr int kPrefillWideMinRows = 32768;    // prefill launches whose longest prompt has at least this many rows use 256-row workgroups

@@ -18,61 +18,100 @@ struct AppendArgs {
   u32x4* vc;
   int64_t stride_b, stride_h, stride_t;   // in 16-byte chunks
   int32_t* kv_len;
-  int batch, capacity, hkv, chunks_per_row;
+  int batch, capacity, hkv, cpr_shift;     // 1 << cpr_shift chunks per row
   int total_new;
   int ring, n_sink, window;                // ring != 0: sink + ring rows, lengths are logical
   uint32_t* counter;
   uint32_t* status;
 };
 
+constexpr int kAppendTokens = 4;            // token rows a thread has in flight in a launch of more than kAppendFew workgroups
+constexpr int kAppendFew = 256;
+constexpr int kAppendTable = 256;           // sequences whose lengths fit the table in LDS
+constexpr int kAppendBlocks = 512;          // workgroups at most
+
+// What bounds it: the copy where there is much to copy; else latencies and the arrival counter.  Every workgroup counts
+// itself on one word (some 10 ns each, one after the other), so there are few of them, each with four token rows per
+// thread in flight; and the lengths are read once into LDS, where a row's sequence is then looked up (looked up in global
+// memory for every row, that is a chain of 4 to 6 loads).  8 KV heads of 128: 1195 tokens of 4 sequences 10.4 -> 7.2 us,
+// 6466 tokens of 5 32 -> 18.3, 16384 tokens 44.5 -> 32, 32768 tokens 66.7 -> 56 (4.8 TB/s); 256 and 1024 workgroups: 21.7
+// and 22.6 for the 6466 tokens.
+template <int U>   // token rows a thread has in flight; with one, lengths are looked up in global memory
 __global__ __launch_bounds__(256) void kv_append_kernel(AppendArgs a) {
   __shared__ int is_last;
-  const int cpt = a.hkv * a.chunks_per_row;                  // 16-byte chunks per token
+  __shared__ int s_cu[kAppendTable + 1], s_len[kAppendTable];
+  const int cpt = a.hkv << a.cpr_shift;                      // 16-byte chunks per token
   const int lanes = cpt < 256 ? cpt : 256;                   // threads that share one token
-  const int tpi = 256 / lanes;                               // tokens per workgroup iteration
+  const int tpi = 256 / lanes;                               // tokens per workgroup iteration and row in flight
   const int tid = threadIdx.x;
-  const int c0 = tid % lanes, trow = tid / lanes;
+  const int trow = tid / lanes, c0 = tid - trow * lanes;
+  const bool table = U > 1 && a.batch <= kAppendTable;
+  if (table) {
+    for (int i = tid; i <= a.batch; i += 256) {
+      s_cu[i] = a.cu_new[i];
+      if (i < a.batch) s_len[i] = a.kv_len[i];
+    }
+    __syncthreads();
+  }
+  auto cu = [&](int i) { return table ? s_cu[i] : a.cu_new[i]; };
   bool overflow = false;
   if (trow < tpi) {
-    for (int t = blockIdx.x * tpi + trow; t < a.total_new; t += gridDim.x * tpi) {
-      // sequence of token row t: largest b with cu_new[b] <= t
-      int lo = 0, hi = a.batch;
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (a.cu_new[mid] <= t) lo = mid; else hi = mid;
-      }
-      const int len0 = a.kv_len[lo];
-      const int pos = len0 + (t - a.cu_new[lo]);
-      int row = pos;
-      bool keep = pos >= 0 && pos < a.capacity;
-      if (a.ring) {
-        // only rows that are still resident after the whole call are written: the sinks and the last
-        // `window` positions (an earlier row of this call may share a ring row with a later one)
-        const int len1 = len0 + (a.cu_new[lo + 1] - a.cu_new[lo]);
-        keep = pos >= 0 && (pos < a.n_sink || pos >= len1 - a.window);
-        row = pos < a.n_sink ? pos : a.n_sink + (pos - a.n_sink) % a.window;
-      }
-      if (keep) {
-        const int64_t dst0 = (int64_t)lo * a.stride_b + (int64_t)row * a.stride_t;
-        const int64_t src0 = (int64_t)t * cpt;
-        for (int c = c0; c < cpt; c += lanes) {
-          const int h = c / a.chunks_per_row, cc = c - h * a.chunks_per_row;
-          const int64_t off = dst0 + (int64_t)h * a.stride_h + cc;
-          // ordinary loads and stores: the appended rows are read again at once by the attention call
-          // that follows (nontemporal accesses measured 10 % slower here)
-          a.kc[off] = a.k_new[src0 + c];
-          a.vc[off] = a.v_new[src0 + c];
+    for (int64_t t0 = (int64_t)blockIdx.x * tpi * U + trow; t0 < a.total_new; t0 += (int64_t)gridDim.x * tpi * U) {
+      int64_t dst0[U];                                       // where the row goes, -1: nowhere
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t tt = t0 + u * tpi;
+        dst0[u] = -1;
+        if (tt >= a.total_new) continue;
+        const int t = (int)tt;
+        // sequence of token row t: largest b with cu_new[b] <= t
+        int lo = 0, hi = a.batch;
+        while (hi - lo > 1) {
+          const int mid = (lo + hi) >> 1;
+          if (cu(mid) <= t) lo = mid; else hi = mid;
         }
-      } else if (!a.ring) {
-        overflow = true;
+        const int len0 = table ? s_len[lo] : a.kv_len[lo];
+        const int pos = len0 + (t - cu(lo));
+        int row = pos;
+        bool keep = pos >= 0 && pos < a.capacity;
+        if (a.ring) {
+          // only rows that are still resident after the whole call are written: the sinks and the last
+          // `window` positions (an earlier row of this call may share a ring row with a later one)
+          const int len1 = len0 + (cu(lo + 1) - cu(lo));
+          keep = pos >= 0 && (pos < a.n_sink || pos >= len1 - a.window);
+          row = pos < a.n_sink ? pos : a.n_sink + (pos - a.n_sink) % a.window;
+        }
+        if (keep) dst0[u] = (int64_t)lo * a.stride_b + (int64_t)row * a.stride_t;
+        else if (!a.ring) overflow = true;
+      }
+      for (int c = c0; c < cpt; c += lanes) {
+        const int h = c >> a.cpr_shift, cc = c - (h << a.cpr_shift);
+        const int64_t off = (int64_t)h * a.stride_h + cc;
+        // ordinary loads and stores: the appended rows are read again at once by the attention call
+        // that follows (nontemporal accesses measured 10 % slower here)
+        u32x4 k[U], v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (dst0[u] >= 0) {
+            const int64_t src = (t0 + u * tpi) * cpt + c;
+            k[u] = a.k_new[src];
+            v[u] = a.v_new[src];
+          }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (dst0[u] >= 0) {
+            a.kc[dst0[u] + off] = k[u];
+            a.vc[dst0[u] + off] = v[u];
+          }
       }
     }
   }
   if (overflow) atomicOr(a.status, (uint32_t)FLUX_DEV_KV_OVERFLOW);
 
   // The last workgroup to arrive bumps the lengths.  The others only READ kv_len, and a thread's loads
-  // have returned (its stores depend on them) before the barrier lets thread 0 count the arrival, so no
+  // have returned (waited for here) before the barrier lets thread 0 count the arrival, so no
   // fence is needed for this read-before-write order.
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (tid == 0) is_last = (atomicAdd(a.counter, 1u) == gridDim.x - 1);
   __syncthreads();
@@ -103,7 +142,7 @@ hipError_t launch_kv_append(const Ctx& c, const flux_kv_cache& cache, int hkv, i
   a.batch = cache.batch;
   a.capacity = cache.capacity;
   a.hkv = hkv;
-  a.chunks_per_row = d / 8;
+  a.cpr_shift = d == 128 ? 4 : 3;
   a.total_new = total_new;
   a.ring = ring;
   a.n_sink = n_sink;
@@ -112,10 +151,15 @@ hipError_t launch_kv_append(const Ctx& c, const flux_kv_cache& cache, int hkv, i
   a.status = c.status;
   const int cpt = hkv * (d / 8);
   const int tpi = 256 / (cpt < 256 ? cpt : 256);
-  long long blocks = ((long long)total_new + tpi - 1) / tpi;
-  if (blocks < 1) blocks = 1;
-  if (blocks > 2048) blocks = 2048;
-  hipLaunchKernelGGL(kv_append_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a);
+  // A launch of few workgroups with one token row per thread is as short as it gets (4 rows per thread and the table: 100
+  // tokens 4.3 against 3.0 us, one token 2.8 / 2.4); from there on the counter shows.
+  const long long single = ((long long)total_new + tpi - 1) / tpi;
+  if (single <= kAppendFew) {
+    hipLaunchKernelGGL(kv_append_kernel<1>, dim3((unsigned)(single < 1 ? 1 : single)), dim3(256), 0, s, a);
+  } else {
+    const long long blocks = (single + kAppendTokens - 1) / kAppendTokens;
+    hipLaunchKernelGGL(kv_append_kernel<kAppendTokens>, dim3((unsigned)(blocks < kAppendBlocks ? blocks : kAppendBlocks)), dim3(256), 0, s, a);
+  }
   return hipGetLastError();
 }
 

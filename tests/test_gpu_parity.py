@@ -669,3 +669,67 @@ def test_workspace_sizing_for_decode(F):
     torch.cuda.synchronize()
     assert torch.isnan(out).all()                                     # nothing was launched
     F.flux_destroy(small)
+
+
+@pytest.mark.parametrize("batch,hidden,inner", [(3, 4096 + 8, 24), (600, 64, 8), (512, 72, 16), (2, 16384, 8)])
+def test_router_rounds_and_counters(F, ctx, batch, hidden, inner):
+    """Hidden sizes on either side of a round of 4096 columns; more sequences than arrival counters (512), where the head
+    is a launch of its own.  Two calls in a row, equal bit for bit, and the oracle at 1e-6."""
+    rng = np.random.default_rng(batch + hidden)
+    lens = [int(x) for x in rng.integers(1, 9, size=batch)]
+    xb = synth.f32_to_bf16_bits(rng.standard_normal((sum(lens), hidden)).astype(np.float32))
+    w1b = synth.f32_to_bf16_bits((rng.standard_normal((inner, hidden)) * 0.02).astype(np.float32))
+    w2b = synth.f32_to_bf16_bits((rng.standard_normal((2, inner)) * 0.02).astype(np.float32))
+    outs = []
+    for _ in range(2):
+        mode = torch.full((batch,), 9, dtype=torch.uint8, device="cuda")
+        logits = torch.full((batch, 2), float("nan"), dtype=torch.float32, device="cuda")
+        F.flux_router(ctx, H.bits_to_torch(xb), cu(lens), batch, hidden, 3, H.bits_to_torch(w1b), None, H.bits_to_torch(w2b), None, inner, mode, logits)
+        torch.cuda.synchronize()
+        outs.append((mode.cpu().numpy(), logits.cpu().numpy()))
+    assert np.array_equal(outs[0][0], outs[1][0]) and np.array_equal(outs[0][1], outs[1][1])
+    off = 0
+    for b, n in enumerate(lens):
+        if b < 5 or b > batch - 5:
+            ref, dec = O.router(O.bf16_to_f64(xb[off:off + n]), 3, O.bf16_to_f64(w1b), None, O.bf16_to_f64(w2b), None)
+            assert np.abs(outs[0][1][b] - ref).max() < 1e-6
+            assert abs(ref[0] - ref[1]) < 1e-6 or int(outs[0][0][b]) == dec
+        off += n
+
+
+@pytest.mark.parametrize("hkv,d,lens", [
+    (8, 128, [513]),                                          # one more token than one row per thread takes (256 workgroups of 2)
+    (3, 64, [2700, 0, 2801]),                                 # 24 chunks per token: 10 tokens and 16 idle threads per workgroup
+    (40, 128, [300]),                                         # a token of more chunks than a workgroup has threads
+    (8, 128, [3] * 255 + [9]), (8, 128, [2] * 257),           # on either side of the table of lengths
+])
+def test_append_rows_in_flight(F, ctx, hkv, d, lens):
+    """Copies of more than 256 workgroups with one row per thread: several rows per thread, lengths looked up in LDS."""
+    b, t = len(lens), sum(lens)
+    cache = F.KVCache.empty(b, hkv, max(lens) + 20, d)
+    cache.k.zero_(), cache.v.zero_()
+    first = [i % 3 for i in range(b)]
+    cache.kv_len.copy_(i32(first))
+    kn = torch.randn(t, hkv, d, device="cuda").to(torch.bfloat16)
+    vn = torch.randn(t, hkv, d, device="cuda").to(torch.bfloat16)
+    F.flux_kv_append(ctx, cache, hkv, d, kn, vn, cu(lens), t, max(lens))
+    torch.cuda.synchronize()
+    assert cache.kv_len.tolist() == [f + n for f, n in zip(first, lens)]
+    off = 0
+    for i, (f, n) in enumerate(zip(first, lens)):
+        for c, x in ((cache.k, kn), (cache.v, vn)):
+            assert torch.equal(c[i, :, f:f + n], x[off:off + n].transpose(0, 1))
+            assert not c[i, :, :f].any() and not c[i, :, f + n:].any()
+        off += n
+    ring = F.KVCache.empty(b, hkv, 5 + 40, d)
+    ring.kv_len.copy_(i32(first))
+    F.flux_kv_append_ring(ctx, ring, hkv, d, 5, 40, kn, vn, cu(lens), t, max(lens))
+    torch.cuda.synchronize()
+    off = 0
+    for i, (f, n) in enumerate(zip(first, lens)):
+        for p in {f, f + n - 1, max(f, f + n - 40), min(4, f + n - 1)} if n else ():
+            if p >= f:
+                row = p if p < 5 else 5 + (p - 5) % 40
+                assert torch.equal(ring.k[i, :, row], kn[off + p - f]) and torch.equal(ring.v[i, :, row], vn[off + p - f])
+        off += n
+    assert F.flux_last_device_status(ctx) == 0

@@ -1,9 +1,8 @@
 // flux_attn_prefill: tiled causal GQA attention on bf16 MFMA, Full (Eq. 1) or Sparse (Eq. 2 with the
 // sink + window subset of Sec. 4.1 / App. C.3), chosen per sequence by the cached mode byte.
 //
-// Shape of the computation (one workgroup = 128 query rows of one head, 4 waves x 32 rows = 2 column blocks
-// of 16 queries; launches for long prompts use 8 waves per workgroup: the same 128 rows of two heads of a GQA
-// group, or 256 rows of one head, see launch_prefill):
+// Shape of the computation (one workgroup = 128 query rows, 4 waves x 32 rows = 2 column blocks of 16 queries;
+// launches for long prompts use 8 waves per workgroup, 256 rows; which rows these are, see the kernel):
 //   for each VISITED 64-key block (FA: all blocks up to the diagonal; SA: the sink blocks and the
 //   blocks that intersect the tile's window, nothing else: hidden blocks are skipped, not masked)
 //     S^T[key][q]  = K[key][:] . Q[q][:]     MFMA 16x16x32 bf16, A = K rows from LDS, B = Q in registers

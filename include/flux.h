@@ -224,7 +224,8 @@ int flux_attn_decode_append(flux_ctx* ctx, const flux_attn_cfg* cfg, const void*
  * call inside.  The split-K partial results go to a static device array of FLUX_STATIC_SCRATCH_BYTES that
  * every GPU the library runs on holds until the process ends; the call works on the CURRENT device, whose
  * copy of the array is looked up once (at flux_create on that device, else at the first call).
- * Same arguments, kernels and results (bit for bit) as flux_attn_decode, plus
+ * Same arguments and results (bit for bit) as flux_attn_decode (a call of few short lists, which flux_attn_decode
+ * merges in one launch on arrival counters of its context, takes two here: the array holds no state between calls), plus
  *   status: dev uint32 (4-byte aligned), caller-owned, or NULL.  The FLUX_DEV_* bits of this call are OR-ed
  *           into it (sticky; the caller reads and clears it); with NULL they go to a word nobody reads.
  * A shape whose partials exceed the array gives FLUX_EWORKSPACE: the partials take

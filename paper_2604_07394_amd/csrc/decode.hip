@@ -304,15 +304,18 @@ __device__ __forceinline__ Merged merge_rows(const float* base, int nc, float sc
 // of two.  Eight waves per workgroup, so that each has one block of 32 keys and no second wait for memory; the unit that
 // arrives last at its pair merges the pair's rows.  The rows pass between workgroups that may sit on different XCDs:
 // they are written and read with device-scope accesses (past the L2s, which are not coherent with each other), and a
-// unit counts itself only after its own stores have been acknowledged.
+// unit counts itself only after its own stores have been acknowledged.  ROWS: the same eight waves and chunks, but the rows
+// are left for the merge kernel, as in the two-launch form: for callers without arrival counters (the static scratch).
+// The merge takes the same sums in the same order, so the results are those of the one-launch form bit for bit.
 // Three workgroups per CU are asked for: left alone the compiler keeps the accumulators in a second register file (192
 // registers, two workgroups per CU) although 160 do: SA layer of 8 x 131072 32.6 -> 31.1 us, 32 ragged sequences of 513 to
 // 8400 keys at 28/4 heads 44.5 -> 39.7 us.  Very long calls stream at the rate of the memory with two as well, and start
 // fewer workgroups at a time (19 sequences of 6 to 120 thousand keys, 16/8 heads, 413.7 -> 411.8 us; 8, 32, 64 and 128
 // thousand keys, 32/8 heads, 150.6 -> 148.9; 8 x 131072 at head dimension 64 324.4 -> 321.4): LONG.
-template <int D, bool NT, bool FUSED, bool SMALL = false, bool LONG = false>
+template <int D, bool NT, bool FUSED, bool SMALL = false, bool LONG = false, bool ROWS = false>
 __global__ __launch_bounds__(SMALL ? 512 : 256, SMALL ? 2 : (LONG ? 1 : 3)) void decode_splitk_kernel(DecodeArgs a) {
   constexpr int W = SMALL ? 8 : 4;    // waves per workgroup
+  constexpr bool IN_PLACE = SMALL && !ROWS;   // the unit that arrives last merges its pair
   constexpr int KC = D / 32;          // MFMA k-steps over the head dimension
   constexpr int DB = D / 16;          // 16-wide output blocks over the head dimension
   constexpr int VL = D / 16;          // 16-byte V loads per lane per 32-key block
@@ -352,8 +355,8 @@ __global__ __launch_bounds__(SMALL ? 512 : 256, SMALL ? 2 : (LONG ? 1 : 3)) void
   };
   // the last workgroup of the grid (idle unless the host's bound on the units is met exactly) leaves the split
   // behind for the merge kernel, which then needs neither the lengths nor the scan
-  if (!SMALL && unit == (int)gridDim.x - 1 && w == 0) write_split_table(a.sp, l, sp.chunk, a.table);
-  if (SMALL && unit == (int)gridDim.x - 1) {                // sequences without keys have no units: their rows are zero
+  if (!IN_PLACE && unit == (int)gridDim.x - 1 && w == 0) write_split_table(a.sp, l, sp.chunk, a.table);
+  if (IN_PLACE && unit == (int)gridDim.x - 1) {             // sequences without keys have no units: their rows are zero
     for (unsigned long long left = sp.empty; left != 0; left &= left - 1) {
       const int64_t off = (int64_t)__builtin_ctzll(left) * a.hq * D;
       for (int i = tid; i < a.hq * D; i += 64 * W) {
@@ -585,7 +588,7 @@ __global__ __launch_bounds__(SMALL ? 512 : 256, SMALL ? 2 : (LONG ? 1 : 3)) void
   }
   __syncthreads();
   const int nq = min(16, a.group - 16 * qb);
-  if (SMALL && sp.nc == 1) {                                // the only unit of its pair: nothing to merge with
+  if (IN_PLACE && sp.nc == 1) {                             // the only unit of its pair: nothing to merge with
     for (int idx = tid; idx < nq * D; idx += 64 * W) {
       const int qi = idx / D, d = idx % D;
       float m = -INFINITY, num = 0.f, den = 0.f;
@@ -624,10 +627,10 @@ __global__ __launch_bounds__(SMALL ? 512 : 256, SMALL ? 2 : (LONG ? 1 : 3)) void
     // the units of one pair are consecutive: inside their block the rows run [query head][chunk], so that the merge
     // reads one head's chunks as one contiguous run
     float* dst = a.partials + (((int64_t)(unit - ci) * a.rpu) + (int64_t)qi * sp.nc + ci) * RED + e;
-    if constexpr (SMALL) __hip_atomic_store(dst, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if constexpr (IN_PLACE) __hip_atomic_store(dst, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     else *dst = val;
   }
-  if constexpr (SMALL) {
+  if constexpr (IN_PLACE) {
     // ---- the unit that arrives last merges the pair
     __shared__ int last_of_pair;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // this wave's rows have reached the point all XCDs see
@@ -702,6 +705,7 @@ __global__ __launch_bounds__(G * D) void decode_combine_kernel(CombineArgs a) {
   }
 }
 
+// c.small_counters may be null: a call of few short lists then takes two launches.
 hipError_t launch_decode(const Ctx& c, const flux_attn_cfg& cfg, const void* q, int max_kv_len,
                          const flux_kv_cache& cache, const uint8_t* mode, int ring, const void* k_new,
                          const void* v_new, void* out, hipStream_t s) {
@@ -748,7 +752,8 @@ hipError_t launch_decode(const Ctx& c, const flux_attn_cfg& cfg, const void* q, 
   a.kv_len_rw = cache.kv_len;
   a.out = out;
   a.out_fp32 = cfg.out_dtype;
-  if (decode_small(cfg, cache.batch, max_kv_len)) {
+  const bool small = decode_small(cfg, cache.batch, max_kv_len) && (c.small_counters || !fused);
+  if (small && c.small_counters) {
     if (cfg.head_dim == 128) {
       if (fused) hipLaunchKernelGGL((decode_splitk_kernel<128, false, true, true>), grid, dim3(512), 0, s, a);
       else hipLaunchKernelGGL((decode_splitk_kernel<128, false, false, true>), grid, dim3(512), 0, s, a);
@@ -763,7 +768,9 @@ hipError_t launch_decode(const Ctx& c, const flux_attn_cfg& cfg, const void* q, 
   auto launch = [&](auto d, auto f) {
     constexpr int D = decltype(d)::value;
     constexpr bool FU = decltype(f)::value;
-    if (lng) hipLaunchKernelGGL((decode_splitk_kernel<D, true, FU, false, true>), grid, dim3(256), 0, s, a);
+    if (small) {
+      if constexpr (!FU) hipLaunchKernelGGL((decode_splitk_kernel<D, false, false, true, false, true>), grid, dim3(512), 0, s, a);
+    } else if (lng) hipLaunchKernelGGL((decode_splitk_kernel<D, true, FU, false, true>), grid, dim3(256), 0, s, a);
     else if (nt) hipLaunchKernelGGL((decode_splitk_kernel<D, true, FU>), grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL((decode_splitk_kernel<D, false, FU>), grid, dim3(256), 0, s, a);
   };
@@ -793,7 +800,7 @@ hipError_t launch_decode(const Ctx& c, const flux_attn_cfg& cfg, const void* q, 
   const dim3 cgrid(cfg.n_q_heads, cache.batch);
   // chunks of the longest list, as far as the host can tell: the bound, or about twice a pair's share of the units
   const long long pairs = (long long)cache.batch * plan.pps;
-  const bool few = max_kv_len <= 8 * kMinChunk || 2 * kTargetUnits <= 8 * pairs;
+  const bool few = small || max_kv_len <= 8 * kMinChunk || 2 * kTargetUnits <= 8 * pairs;
   if (cfg.head_dim == 128) {
     if (few) hipLaunchKernelGGL((decode_combine_kernel<128, 1>), cgrid, dim3(128), 0, s, ca);
     else hipLaunchKernelGGL((decode_combine_kernel<128, 4>), cgrid, dim3(512), 0, s, ca);

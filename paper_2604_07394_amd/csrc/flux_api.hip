@@ -33,8 +33,7 @@ int hip_fail(hipError_t e) {
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
-constexpr size_t kStaticHeader = 256;      // status word and arrival counters of the static scratch; the partials follow
-static_assert(4 + 4 * (1 + kSmallPairs) <= kStaticHeader, "the counters must fit");
+constexpr size_t kStaticHeader = 256;      // status word of the static scratch; the partials follow
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
 char* g_scratch_ptr[kMaxDevices];          // device address of `scratch` on each GPU, resolved once per device
@@ -322,13 +321,14 @@ int flux_attn_decode_static(const flux_attn_cfg* cfg, const void* q, int max_kv_
   const hipError_t es = static_scratch(&base);
   if (es != hipSuccess) return hip_fail(es);
   // A context on the stack that owns nothing: the kernels take the scratch address as they take the
-  // workspace of a flux_create context.  Nothing has to be cleared between calls: a merge reads only partial
-  // rows that the same call has written, the arrival counters are left at zero, and the status word is sticky.
+  // workspace of a flux_create context.  Nothing has to be cleared between calls: the merge kernel reads only partial
+  // rows that the split-K kernel of the same call has written, and the status word is sticky.  It has no arrival
+  // counters: the array lives until the process ends, so a counter that overlapping calls left non-zero would spoil
+  // every later call on the GPU, where without them each call spoils at most itself.
   Ctx c;
   memset(&c, 0, sizeof(c));
   c.device = 0;
   c.status = status ? status : (uint32_t*)base;
-  c.small_counters = (uint32_t*)(base + 4);
   c.partials = (float*)(base + kStaticHeader);
   c.partials_bytes = FLUX_STATIC_SCRATCH_BYTES - kStaticHeader;
   const hipError_t e = launch_decode(c, *cfg, q, max_kv_len, *cache, mode, 0, nullptr, nullptr, out, (hipStream_t)stream);

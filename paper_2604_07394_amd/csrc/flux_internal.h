@@ -46,7 +46,7 @@ struct Ctx {
   // carved regions (device pointers)
   uint32_t* status;        // sticky status word
   uint32_t* counters;      // kCounters zero-initialised arrival counters; users reset them to zero
-  uint32_t* small_counters;   // 1 + kSmallPairs of the same kind, for the decode calls merged in place
+  uint32_t* small_counters;   // 1 + kSmallPairs of the same kind, for the decode calls merged in place; null: such calls take two launches
   uint32_t* router_counters;  // kRouterCounters of the same kind, one per sequence of a router call
   float* small;            // router scratch: pooled vectors and hidden activations
   float* partials;         // split-K partial results
@@ -122,7 +122,7 @@ inline DecodePlan plan_decode(const flux_attn_cfg& cfg, int batch, int max_kv_le
 // 128: 1 x 200 keys 10.2 / 6.2, 1 x 2001 11.1 / 9.1, 1 x 4200 12.0 / 11.1, 4 x 2000 13.3 / 11.6; beyond the bounds below
 // the merge at the end of a workgroup costs more than the launch: 1 x 8000 13.4 / 15.0, 4 x 4000 19.4 / 23.4, 28/4 heads
 // 4 x 4000 14.0 / 14.9.
-constexpr int kSmallPairs = 60;                 // (their counters fit behind the status word of the static scratch)
+constexpr int kSmallPairs = 60;                 // (more pairs have not been timed in this form)
 constexpr int kSmallUnits = 256;                // a workgroup per CU
 constexpr int kSmallKeys = 4352;                // 17 chunks: what a window of 4096 keys and 128 sinks takes
 constexpr int kSmallRows = 72;                  // rows that the last unit of a pair merges: query heads x chunks

@@ -9,6 +9,8 @@
 
 #include "../../include/flux.h"
 
+extern "C" const void *hostcheck_status, *hostcheck_partials, *hostcheck_counters;   // what the last decode launcher was given
+
 static int failures = 0;
 #define EXPECT(expr, want)                                                                   \
   do {                                                                                       \
@@ -78,6 +80,16 @@ int main() {
   bigc.batch = 256; bigc.capacity = 1 << 20; bigc.stride_h = (int64_t)1 << 27; bigc.stride_b = (int64_t)1 << 31;
   EXPECT(flux_attn_decode_static(&g16, p, 1 << 20, &bigc, pb, p, nullptr, nullptr), FLUX_EWORKSPACE);
   EXPECT(flux_attn_decode_static(&cfg, p, 32, &kc, pb, p, (uint32_t*)(buf + 2), nullptr), FLUX_EINVAL);
+  // the static scratch outlives every caller: its calls leave nothing there that a later one goes by but the status word,
+  // so a short call (which a context merges in one launch, on arrival counters) is given no counters
+  uint32_t word = 0;
+  EXPECT(flux_attn_decode_static(&cfg, p, 32, &kc, pb, p, &word, nullptr), FLUX_EHIP);
+  EXPECT(hostcheck_partials != nullptr, 1);
+  EXPECT(hostcheck_counters == nullptr, 1);
+  EXPECT(hostcheck_status == &word, 1);
+  EXPECT(flux_attn_decode_static(&cfg, p, 32, &kc, pb, p, nullptr, nullptr), FLUX_EHIP);
+  EXPECT(hostcheck_counters == nullptr, 1);
+  EXPECT((const char*)hostcheck_partials - (const char*)hostcheck_status, 256);
   // ---- append, ring, router
   EXPECT(flux_kv_append(ctx, &kc, 2, 128, p, p, pi, 10, 10, nullptr), FLUX_EHIP);
   EXPECT(flux_kv_append(ctx, &kc, 2, 128, p, p, pi, INT_MAX, INT_MAX, nullptr), FLUX_ECAPACITY);

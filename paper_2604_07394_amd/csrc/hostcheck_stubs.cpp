@@ -1,14 +1,28 @@
 // Launchers of the host-only build that checks the C ABI under sanitizers: nothing can be launched there, so each
-// reports that there is no device.  (The real ones live next to their kernels.)
+// reports that there is no device.  (The real ones live next to their kernels.)  The two calls of the runtime with which the
+// static scratch is looked up are answered here, so that flux_attn_decode_static gets as far as its launcher, which notes
+// what it was given.
 #include "flux_internal.h"
+
+extern "C" {
+hipError_t hipGetDevice(int* device) { *device = 0; return hipSuccess; }
+hipError_t hipGetSymbolAddress(void** p, const void* symbol) { *p = const_cast<void*>(symbol); return hipSuccess; }
+// of the last launch_decode
+const void *hostcheck_status, *hostcheck_partials, *hostcheck_counters;
+}
 
 namespace flux {
 
 hipError_t launch_kv_append(const Ctx&, const flux_kv_cache&, int, int, const void*, const void*, const int32_t*, int, int, int,
                             int, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_kv_compact_ring(const flux_kv_cache&, const flux_kv_cache&, int, int, int, int, hipStream_t) { return hipErrorNoDevice; }
-hipError_t launch_decode(const Ctx&, const flux_attn_cfg&, const void*, int, const flux_kv_cache&, const uint8_t*, int, const void*,
-                         const void*, void*, hipStream_t) { return hipErrorNoDevice; }
+hipError_t launch_decode(const Ctx& c, const flux_attn_cfg&, const void*, int, const flux_kv_cache&, const uint8_t*, int, const void*,
+                         const void*, void*, hipStream_t) {
+  hostcheck_status = c.status;
+  hostcheck_partials = c.partials;
+  hostcheck_counters = c.counters ? c.counters : c.small_counters ? c.small_counters : c.router_counters;
+  return hipErrorNoDevice;
+}
 hipError_t launch_prefill(const Ctx&, const flux_attn_cfg&, const void*, const int32_t*, int, int, const flux_kv_cache&,
                           const uint8_t*, const BlockMask*, void*, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_router(const Ctx&, const void*, const int32_t*, int, int, int, const void*, const void*, const void*,

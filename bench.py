@@ -540,7 +540,7 @@ def main():
             "fa_layer_ms": fa_avg, "sa_layer_ms": sa_avg,
             "fa_layer_ms_median": float(np.median(fa_ms)) if fa_ms else None,
             "sa_layer_ms_median": float(np.median(sa_ms)) if sa_ms else None,
-            "roofline": {"kernel": "decode_splitk_kernel<128, true, true, false, true> + decode_combine_kernel<128, 4> (FA layers)",
+            "roofline": {"kernel": "decode_splitk_kernel<128, true, true> + decode_combine_kernel<128, 4> (FA layers)",
                          "bound": "hbm", "achieved": ach, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                          "frac": ach / PEAK_HBM_GBS,
                          "traffic": None, "traffic_note": "not the profiled workload",

@@ -309,11 +309,11 @@ __device__ __forceinline__ Merged merge_rows(const float* base, int nc, float sc
 // The merge takes the same sums in the same order, so the results are those of the one-launch form bit for bit.
 // Three workgroups per CU are asked for: left alone the compiler keeps the accumulators in a second register file (192
 // registers, two workgroups per CU) although 160 do: SA layer of 8 x 131072 32.6 -> 31.1 us, 32 ragged sequences of 513 to
-// 8400 keys at 28/4 heads 44.5 -> 39.7 us.  Very long calls stream at the rate of the memory with two as well, and start
-// fewer workgroups at a time (19 sequences of 6 to 120 thousand keys, 16/8 heads, 413.7 -> 411.8 us; 8, 32, 64 and 128
-// thousand keys, 32/8 heads, 150.6 -> 148.9; 8 x 131072 at head dimension 64 324.4 -> 321.4): LONG.
-template <int D, bool NT, bool FUSED, bool SMALL = false, bool LONG = false, bool ROWS = false>
-__global__ __launch_bounds__(SMALL ? 512 : 256, SMALL ? 2 : (LONG ? 1 : 3)) void decode_splitk_kernel(DecodeArgs a) {
+// 8400 keys at 28/4 heads 44.5 -> 39.7 us.  (Very long calls stream at the rate of the memory with two as well, up to 1 %
+// faster, but the host cannot tell them from short lists under a large bound, which lose 10 %: with a bound of 65536 the
+// 32 ragged sequences take 38.0 us, 41.9 with two; 8 x 131072 651.7 and 650.5.)
+template <int D, bool NT, bool FUSED, bool SMALL = false, bool ROWS = false>
+__global__ __launch_bounds__(SMALL ? 512 : 256, SMALL ? 2 : 3) void decode_splitk_kernel(DecodeArgs a) {
   constexpr int W = SMALL ? 8 : 4;    // waves per workgroup
   constexpr bool IN_PLACE = SMALL && !ROWS;   // the unit that arrives last merges its pair
   constexpr int KC = D / 32;          // MFMA k-steps over the head dimension
@@ -763,15 +763,12 @@ hipError_t launch_decode(const Ctx& c, const flux_attn_cfg& cfg, const void* q, 
     }
     return hipGetLastError();
   }
-  // (by the host's bound, which a ragged batch stays well below: hence a large one)
-  const bool lng = 4.0 * cache.batch * cfg.n_kv_heads * cfg.head_dim * (double)max_kv_len > 3.5e9;
   auto launch = [&](auto d, auto f) {
     constexpr int D = decltype(d)::value;
     constexpr bool FU = decltype(f)::value;
     if (small) {
-      if constexpr (!FU) hipLaunchKernelGGL((decode_splitk_kernel<D, false, false, true, false, true>), grid, dim3(512), 0, s, a);
-    } else if (lng) hipLaunchKernelGGL((decode_splitk_kernel<D, true, FU, false, true>), grid, dim3(256), 0, s, a);
-    else if (nt) hipLaunchKernelGGL((decode_splitk_kernel<D, true, FU>), grid, dim3(256), 0, s, a);
+      if constexpr (!FU) hipLaunchKernelGGL((decode_splitk_kernel<D, false, false, true, true>), grid, dim3(512), 0, s, a);
+    } else if (nt) hipLaunchKernelGGL((decode_splitk_kernel<D, true, FU>), grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL((decode_splitk_kernel<D, false, FU>), grid, dim3(256), 0, s, a);
   };
   if (cfg.head_dim == 128) {

@@ -1,0 +1,59 @@
+"""What the host and the device code assume about the compiled kernels, read from the metadata of the code objects in the
+built library (registers and LDS per workgroup; no GPU needed)."""
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIB = os.path.join(ROOT, "paper_2604_07394_amd", "lib", "libflux.so")
+READELF = "/opt/rocm/lib/llvm/bin/llvm-readelf"
+MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """{mangled name: metadata} of every gfx950 kernel of the library."""
+    if not os.path.exists(LIB):
+        from paper_2604_07394_amd import build
+        build.build_all()
+    blob = open(LIB, "rb").read()
+    found = {}
+    at = blob.find(MAGIC)
+    while at >= 0:
+        pos = at + len(MAGIC) + 8
+        for _ in range(struct.unpack_from("<Q", blob, at + len(MAGIC))[0]):
+            offset, size, n = struct.unpack_from("<QQQ", blob, pos)
+            triple = blob[pos + 24:pos + 24 + n]
+            pos += 24 + n
+            if b"gfx950" not in triple or size == 0:
+                continue
+            obj = tmp_path_factory.mktemp("obj") / "code.o"
+            obj.write_bytes(blob[at + offset:at + offset + size])
+            notes = subprocess.run([READELF, "--notes", str(obj)], capture_output=True, text=True, check=True).stdout
+            for part in re.split(r"\n  - \.", notes)[1:]:
+                get = lambda key: re.search(r"\.?" + key + r":\s*(\S+)", part)
+                if get("name") and get("vgpr_count"):
+                    found[get("symbol").group(1)] = {k: int(get(k).group(1)) for k in ("vgpr_count", "max_flat_workgroup_size", "group_segment_fixed_size", "vgpr_spill_count")}
+        at = blob.find(MAGIC, at + 1)
+    return found
+
+
+def workgroups_per_cu(k):
+    """512 registers per SIMD lane, handed out to a wave in steps of 8; four SIMDs and 160 KB of LDS per CU."""
+    waves = 4 * (512 // (-(-k["vgpr_count"] // 8) * 8))
+    return min(waves // (k["max_flat_workgroup_size"] // 64), 163840 // max(1, k["group_segment_fixed_size"]))
+
+
+def test_every_two_launch_decode_kernel_holds_the_round_its_split_is_made_for(kernels):
+    """The split of a decode call aims at one round of the workgroups that the chip holds at once (kResidentUnits, three per
+    CU on 256 CUs), and two-launch calls must not lose that to the choice of an instance."""
+    src = open(os.path.join(ROOT, "paper_2604_07394_amd", "csrc", "decode.hip")).read()
+    resident = int(re.search(r"constexpr int kResidentUnits = (\d+);", src).group(1))
+    names = [n for n, k in kernels.items() if "decode_splitk_kernel" in n and k["max_flat_workgroup_size"] == 256]
+    assert len(names) >= 8
+    for n in names:
+        assert 256 * workgroups_per_cu(kernels[n]) >= resident, (n, kernels[n])
+        assert kernels[n]["vgpr_spill_count"] == 0, n

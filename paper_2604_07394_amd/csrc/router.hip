@@ -2,14 +2,14 @@
 // and last `pool` token rows (App. C.1) -> Context Encoder Linear+SiLU -> Router Head Linear ->
 // argmax (tie to FA).  Everything after the bf16 loads is fp32; nothing is rounded in between.
 //
-// Two launches, tiny and latency-bound:
+// Two launches (three where there are many sequences), tiny and latency-bound:
 //  1. router_pool: partial column sums of the pooled rows.  grid (column blocks, row splits, batch);
 //     a lane owns 8 adjacent columns (one 16-byte load per row), the 4 waves of a workgroup take
 //     different rows and are merged in LDS.  Row splits keep whole-sequence pooling (pool = 0) spread
 //     over the chip; with pool > 0 the cost is independent of the sequence length.
 //  2. router_mlp: grid (inner/8, batch); each wave produces two hidden units (dot of a bf16 W1 row
 //     with the pooled fp32 vector held in LDS) and applies SiLU; the workgroup that finishes a sequence's
-//     hidden vector turns it into the two logits and the decision.
+//     hidden vector turns it into the two logits and the decision (in launches of many workgroups a third kernel does).
 // Batch 4, hidden 4096, inner 256, pool 100: 17.4 us per call with the head as a
 // third launch and the loads of a column block waiting for those of the one before, 12.8 now.
 #include "flux_internal.h"
@@ -121,10 +121,12 @@ __device__ __forceinline__ void router_head(const float* h, const __bf16* w2, co
 }
 
 // Bound by latencies: what a workgroup reads (8 weight rows, the partial sums of one sequence) is asked for in two rounds
-// per 4096 columns, the weights first, since they wait for nothing; then everything is summed in a fixed order.
-__global__ __launch_bounds__(256, 2) void router_mlp_kernel(MlpArgs a) {
+// per BLK columns, the weights first, since they wait for nothing; then everything is summed in a fixed order (the same
+// for every BLK).
+template <int BLK>                                           // columns per round
+__global__ __launch_bounds__(256, BLK > 2048 ? 2 : (BLK > 1024 ? 3 : 5)) void router_mlp_kernel(MlpArgs a) {
   extern __shared__ float pvec[];                           // hidden floats
-  constexpr int BLK = 4096;                                  // columns per round
+  constexpr int NW = BLK / 512, NQ = BLK / 1024;             // 16-byte loads of a weight row and of a split's sums per lane
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
   const int b = blockIdx.y;
   // two hidden units per wave, their weight rows streamed together
@@ -138,26 +140,26 @@ __global__ __launch_bounds__(256, 2) void router_mlp_kernel(MlpArgs a) {
   const float inv = n_pooled > 0 ? 1.0f / (float)n_pooled : 0.f;
   float acc0 = 0.f, acc1 = 0.f;
   for (int c0 = 0; c0 < a.hidden; c0 += BLK) {
-    u32x4 v0[BLK / 512], v1[BLK / 512];
+    u32x4 v0[NW], v1[NW];
 #pragma unroll
-    for (int k = 0; k < BLK / 512; ++k) {
+    for (int k = 0; k < NW; ++k) {
       const int c = c0 + 512 * k + l * 8;
       const int cc = c < a.hidden ? c : 0;                   // (columns past the end are not used)
       v0[k] = *(const u32x4*)(wrow0 + cc);
       v1[k] = *(const u32x4*)(wrow1 + cc);
     }
-    // pooled mean: the row-split partial sums are added in split order (fixed, so the result is reproducible); 16
-    // columns per thread, eight splits' loads in flight together
-    f32x4 s[4];
+    // pooled mean: the row-split partial sums are added in split order (fixed, so the result is reproducible); 4
+    // columns per thread and 1024, eight splits' loads in flight together
+    f32x4 s[NQ];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) s[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int q = 0; q < NQ; ++q) s[q] = f32x4{0.f, 0.f, 0.f, 0.f};
     const float* p = a.psum + (int64_t)b * a.splits * a.hidden;
     for (int sp = 0; sp < a.splits; sp += 8) {
-      f32x4 v[8][4];
+      f32x4 v[8][NQ];
 #pragma unroll
       for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
+        for (int q = 0; q < NQ; ++q) {
           const int c = c0 + 1024 * q + 4 * tid;
           v[i][q] = *(const f32x4*)(p + (int64_t)min(sp + i, a.splits - 1) * a.hidden + (c < a.hidden ? c : 0));
         }
@@ -165,17 +167,17 @@ __global__ __launch_bounds__(256, 2) void router_mlp_kernel(MlpArgs a) {
       for (int i = 0; i < 8; ++i)
         if (sp + i < a.splits) {
 #pragma unroll
-          for (int q = 0; q < 4; ++q) s[q] += v[i][q];
+          for (int q = 0; q < NQ; ++q) s[q] += v[i][q];
         }
     }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < NQ; ++q) {
       const int c = c0 + 1024 * q + 4 * tid;
       if (c < a.hidden) *(f32x4*)(pvec + c) = s[q] * inv;
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < BLK / 512; ++k) {
+    for (int k = 0; k < NW; ++k) {
       const int c = c0 + 512 * k + l * 8;
       if (c < a.hidden) {
 #pragma unroll
@@ -214,11 +216,20 @@ __global__ __launch_bounds__(256, 2) void router_mlp_kernel(MlpArgs a) {
   }
 }
 
-// The head as a launch of its own (batches with more sequences than there are counters).
+// The head as a launch of its own (launches of many workgroups).
 __global__ __launch_bounds__(64) void router_head_kernel(MlpArgs a) {
   const int b = blockIdx.x;
   router_head<false>(a.hbuf + (int64_t)b * a.inner, a.w2, a.b2, a.inner, threadIdx.x, a.mode_out + b, a.logits_out ? a.logits_out + 2 * b : nullptr);
 }
+
+// Columns per round: wide rounds wait for memory fewer times, but take the registers of most of a CU's waves and load what
+// lies past the last column for nothing, so they are for wide layers and launches that leave the chip room.  us per call,
+// hidden 4096, inner 256, rounds of 4096 / 1024: batch 1 10.8 / 11.7, 8 14.8 / 15.7, 16 22.4 / 22.5, 24 32.2 / 27.1, 64
+// 61.9 / 51; hidden 2048, batch 16, rounds of 4096 / 2048 13.9 / 13.4; hidden 256, 512 sequences, 4096 / 1024 35.9 / 21.7;
+// hidden 64 6.4 / 5.6.  From there on the head is a launch of its own as well: what every workgroup pays for counting
+// itself is more than a launch (hidden 4096, batch 24 27.1 / 24.2, 32 32.5 / 28.8, 64 50.7 / 47.1).
+constexpr int kMlpFew = 512;   // workgroups of a launch up to which rounds are as wide as the layer, and the last one runs the head
+static_assert(kMlpFew <= kRouterCounters, "a counter per sequence");
 
 hipError_t launch_router(const Ctx& c, const void* x, const int32_t* cu_seqlens, int batch, int hidden, int pool,
                          const void* w1, const void* b1, const void* w2, const void* b2, int inner,
@@ -252,10 +263,15 @@ hipError_t launch_router(const Ctx& c, const void* x, const int32_t* cu_seqlens,
   ma.inner = inner;
   ma.pool = pool;
   ma.splits = splits;
-  ma.arrived = batch <= kRouterCounters ? c.router_counters : nullptr;
+  const dim3 grid((inner + 7) / 8, batch);
+  const bool few = (long long)grid.x * batch <= kMlpFew;
+  ma.arrived = few ? c.router_counters : nullptr;
   ma.mode_out = mode_out;
   ma.logits_out = logits_out;
-  hipLaunchKernelGGL(router_mlp_kernel, dim3((inner + 7) / 8, batch), dim3(256), hidden * sizeof(float), s, ma);
+  const size_t lds = hidden * sizeof(float);
+  if (few && hidden > 2048) hipLaunchKernelGGL(router_mlp_kernel<4096>, grid, dim3(256), lds, s, ma);
+  else if (few && hidden > 1024) hipLaunchKernelGGL(router_mlp_kernel<2048>, grid, dim3(256), lds, s, ma);
+  else hipLaunchKernelGGL(router_mlp_kernel<1024>, grid, dim3(256), lds, s, ma);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
 

@@ -697,6 +697,28 @@ def test_router_rounds_and_counters(F, ctx, batch, hidden, inner):
         off += n
 
 
+@pytest.mark.parametrize("hidden,inner,few,many", [(4096 + 8, 256, 16, 17), (1032, 512, 8, 9), (2048, 256, 16, 17), (1024, 256, 16, 17)])
+def test_router_rounds_are_the_same_sums(F, ctx, hidden, inner, few, many):
+    """On either side of 512 workgroups (and of 1024 and 2048 columns) the hidden layer is worked off in rounds of another
+    width: a sequence's logits are the same bits in both."""
+    n = 60
+    g = torch.Generator(device="cuda").manual_seed(hidden)
+    x = torch.empty(many * n, hidden, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    w1 = torch.empty(inner, hidden, dtype=torch.bfloat16, device="cuda").normal_(generator=g) * 0.02
+    w2 = torch.empty(2, inner, dtype=torch.bfloat16, device="cuda").normal_(generator=g) * 0.02
+    logits = []
+    for batch in (few, many):
+        mode = torch.full((batch,), 9, dtype=torch.uint8, device="cuda")
+        out = torch.full((batch, 2), float("nan"), dtype=torch.float32, device="cuda")
+        F.flux_router(ctx, x, cu([n] * batch), batch, hidden, 25, w1, None, w2, None, inner, mode, out)
+        torch.cuda.synchronize()
+        assert torch.isfinite(out).all() and torch.equal(mode.bool(), out[:, 0] >= out[:, 1])
+        logits.append(out)
+    assert torch.equal(logits[0], logits[1][:few])
+    ref, _ = O.router(H.torch_to_f64(x[:n]), 25, H.torch_to_f64(w1), None, H.torch_to_f64(w2), None)
+    assert np.abs(logits[0][0].cpu().numpy() - ref).max() < 1e-6
+
+
 @pytest.mark.parametrize("hkv,d,lens", [
     (8, 128, [513]),                                          # one more token than one row per thread takes (256 workgroups of 2)
     (3, 64, [2700, 0, 2801]),                                 # 24 chunks per token: 10 tokens and 16 idle threads per workgroup

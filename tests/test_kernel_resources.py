@@ -57,3 +57,10 @@ def test_every_two_launch_decode_kernel_holds_the_round_its_split_is_made_for(ke
     for n in names:
         assert 256 * workgroups_per_cu(kernels[n]) >= resident, (n, kernels[n])
         assert kernels[n]["vgpr_spill_count"] == 0, n
+
+
+def test_router_launches_of_many_workgroups_run_an_instance_that_shares_the_cus(kernels):
+    """An MLP workgroup that keeps rounds of 4096 columns in registers leaves room for two per CU.  The instance for many
+    workgroups and for narrow layers holds five."""
+    k = [v for n, v in kernels.items() if "router_mlp_kernelILi1024E" in n]
+    assert len(k) == 1 and workgroups_per_cu(k[0]) >= 5 and k[0]["vgpr_spill_count"] == 0, k

@@ -175,20 +175,25 @@ __device__ __forceinline__ PrefillUnit prefill_plan(const PrefillArgs& a, int l,
   const int groups = a.hkv * nc;
   const int share_sh = groups == 1 ? 3 : (groups == 2 ? 2 : (groups == 4 ? 1 : 0));
   const int units = share_sh > 0 ? ((tiles + (1 << share_sh) - 1) >> share_sh) * 8 : groups * tiles;
-  // longest first: rank by (key blocks, index), then the units in that order
-  int rank = 0;
-  for (int j = 0; j < a.batch; ++j) {
-    const int o = __builtin_amdgcn_readlane(nb, j);
-    rank += (o > nb || (o == nb && j < l)) ? 1 : 0;
-  }
-  rank = l < a.batch ? rank : l;
-  const int units_s = __builtin_amdgcn_ds_permute(4 * rank, units);
-  const int idx_s = __builtin_amdgcn_ds_permute(4 * rank, l);
-  const int incl = wave_inclusive_sum(units_s);
+  int units_s = units, idx_s = l;
+  int incl = wave_inclusive_sum(units);
   const int total_units = __builtin_amdgcn_readlane(incl, 63);
   int id = blockIdx.x;
   u.b = -1;
-  if (id >= total_units) return u;
+  if (id >= total_units) return u;                           // (most workgroups, where the host's bounds are far above the lengths)
+  // longest first, if they are not all alike: rank by (key blocks, index), then the units in that order
+  if (__builtin_amdgcn_ballot_w64(l < a.batch && nb != __builtin_amdgcn_readlane(nb, 0)) != 0) {
+    const int key = (nb << 6) | (63 - l);                    // no two alike; lanes without a sequence hold the lowest
+    int rank = 0;
+    for (int j = 0; j < a.batch; j += 8) {
+#pragma unroll
+      for (int v = 0; v < 8; ++v) rank += __builtin_amdgcn_readlane(key, j + v) > key ? 1 : 0;
+    }
+    rank = l < a.batch ? rank : l;
+    units_s = __builtin_amdgcn_ds_permute(4 * rank, units);
+    idx_s = __builtin_amdgcn_ds_permute(4 * rank, l);
+    incl = wave_inclusive_sum(units_s);
+  }
   if (resident >= 512) id = 8 * pair_long_with_short(id >> 3, (total_units - (id & 7) + 7) >> 3) + (id & 7);
   const int at = __builtin_popcountll(__builtin_amdgcn_ballot_w64(incl <= id));
   u.b = __builtin_amdgcn_readlane(idx_s, at);

@@ -1,7 +1,7 @@
 """Prefill launches that are planned on the device: tiles whose rows come from all heads of a group, ragged batches worked
 off longest first, and (queries behind a cached context) tiles whose keys are shared out over several workgroups and
 merged.  Against the oracle at the attention tolerance, and against the same call on a context whose workspace has no
-room for partial results (nothing is split there).  Both sides round every weight to bf16 (relative 2^-9), each against
+room for partial results (nothing is split there; results differ in bits exactly where something was).  Both sides round every weight to bf16 (relative 2^-9), each against
 softmax references of its own, so two correct results differ by at most 2 * 2^-9 * max|v - o| (3.5e-2 for values of up to 9)
 in the worst case; the bound asserted is the attention tolerance of 1e-2."""
 import numpy as np
@@ -63,6 +63,32 @@ def test_planned_prefill(F, ctxs, past, new, modes, hq, hkv, d, n_sink, window, 
     lay.ctx = ctxs[1]
     whole, _ = lay.prefill(qb, new, modes, want_ref=False)
     assert np.abs(whole - got).max() <= H.MAX_ABS
+    assert not np.array_equal(whole, got)                    # (every case splits: its sums are taken in another order)
+    for c in ctxs:
+        assert F.flux_last_device_status(c) == 0
+
+
+@pytest.mark.parametrize("past,new,modes,hq,hkv,d,n_sink,window", [
+    ([3000], [40], [SA], 8, 2, 128, 16, 128),               # may split by its bounds, but the window's list is short
+    ([3000, 2900, 3001], [40, 1, 90], [SA, SA, SA], 4, 4, 64, 16, 300),
+    ([0] * 9, [70] * 9, [FA, SA] * 4 + [FA], 8, 2, 64, 3, 40),   # sequences all alike
+    ([0] * 5, [300, 1, 777, 0, 64], [FA, SA, FA, FA, SA], 14, 7, 128, 3, 40),
+])
+def test_calls_that_split_nothing(F, ctxs, past, new, modes, hq, hkv, d, n_sink, window):
+    """Bit-identical to the call that has no room to split, also after a call on the same context that did."""
+    batch = len(new)
+    lay = Layer(F, ctxs[0], 3200 + hq + d, batch, hq, hkv, d, max(p + n for p, n in zip(past, new)), n_sink, window, scales=True)
+    if sum(past):
+        _, kb, vb = lay.new_tokens(past)
+        lay.append(kb, vb, past)
+    qb, kb, vb = lay.new_tokens(new)
+    lay.append(kb, vb, new)
+    lay.prefill(qb, new, [FA] * batch, want_ref=False)
+    got, ref = lay.prefill(qb, new, modes)
+    H.assert_close(got, ref, "nothing split")
+    lay.ctx = ctxs[1]
+    whole, _ = lay.prefill(qb, new, modes, want_ref=False)
+    assert np.array_equal(whole, got)
     for c in ctxs:
         assert F.flux_last_device_status(c) == 0
 

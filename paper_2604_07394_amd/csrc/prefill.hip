@@ -57,7 +57,7 @@ struct PrefillArgs {
   int split_units;        // 0: never; else the units a launch may have beyond one per tile
   float* part_o;          // unnormalised outputs of a unit, [unit][BM][D]
   float* part_ml;         // reference (score units) and weight sum of its rows, [unit][BM][2]
-  i32x4* tile_info;       // [batch][n_kv_heads][n_qtiles]: first unit, unit stride, units of the tile
+  i32x4* tile_info;       // [batch][n_kv_heads][n_qtiles]: first unit, unit stride, units of the tile; behind them, whether any tile was split
 };
 
 constexpr float kWeightGuard = 1073741824.0f;   // 2^30: a block whose weights sum past this moves the softmax reference
@@ -142,7 +142,8 @@ __device__ __forceinline__ PrefillUnit prefill_plan(const PrefillArgs& a, int l,
   if (blockIdx.x == 0 && threadIdx.x < 64 && bad) atomicOr(a.status, (uint32_t)FLUX_DEV_BAD_LENGTH);
   u.chunk = 0x7FFFFFFF;
   int nc = tiles > 0 ? 1 : 0;
-  if (a.split_units > 0) {
+  // (no list long enough: nothing to search for)
+  if (a.split_units > 0 && __builtin_amdgcn_ballot_w64(tiles > 0 && nb > kMinSplitBlocks) != 0) {
     // Key blocks a unit takes at most: every lane works out one candidate, around the share of one of the workgroups
     // the chip holds, by a model in units of one block: the longest unit, or that share plus half a unit of
     // unevenness where there is more than one round, plus 0.02 for writing and merging the partial result of a unit
@@ -175,6 +176,10 @@ __device__ __forceinline__ PrefillUnit prefill_plan(const PrefillArgs& a, int l,
   const int groups = a.hkv * nc;
   const int share_sh = groups == 1 ? 3 : (groups == 2 ? 2 : (groups == 4 ? 1 : 0));
   const int units = share_sh > 0 ? ((tiles + (1 << share_sh) - 1) >> share_sh) * 8 : groups * tiles;
+  if (a.split_units > 0 && blockIdx.x == 0) {
+    const bool any = __builtin_amdgcn_ballot_w64(nc > 1) != 0;
+    if (threadIdx.x == 0) a.tile_info[a.batch * a.hkv * a.n_qtiles] = i32x4{any, 0, 0, 0};
+  }
   int units_s = units, idx_s = l;
   int incl = wave_inclusive_sum(units);
   const int total_units = __builtin_amdgcn_readlane(incl, 63);
@@ -860,6 +865,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
 template <int D, int BM>
 __global__ __launch_bounds__(256) void prefill_merge_kernel(PrefillArgs a) {
   constexpr int RPP = 1024 / D;           // rows per pass
+  if (a.tile_info[a.batch * a.hkv * a.n_qtiles][0] == 0) return;   // nothing was split
   const int b = blockIdx.z, kvh = blockIdx.y / a.n_qtiles, qt = blockIdx.y % a.n_qtiles;
   const int q_begin = a.cu_q[b];
   int n_q = a.cu_q[b + 1] - q_begin, len = a.kv_len[b];
@@ -966,7 +972,7 @@ hipError_t launch_prefill(const Ctx& c, const flux_attn_cfg& cfg, const void* q,
   // uneven sequence costs more than that.
   const long long packed = ((long long)max_q_len * a.group + BM - 1) / BM;    // tiles of a pair whose rows come from all heads
   const long long tiles = n_pairs * packed, blocks = ((long long)max_kv_len + 63) / 64;
-  const long long unit_bytes = (long long)BM * (cfg.head_dim + 2) * 4, info_bytes = (tiles * 16 + 255) / 256 * 256;
+  const long long unit_bytes = (long long)BM * (cfg.head_dim + 2) * 4, info_bytes = ((tiles + 1) * 16 + 255) / 256 * 256;
   const long long fit = ((long long)c.partials_bytes - info_bytes) / unit_bytes - tiles - 8 * cache.batch;   // units beyond one per tile
   const bool split = !bm && !wide && cache.batch <= 64 && max_kv_len > max_q_len && blocks > kMinSplitBlocks &&
                      (tiles <= kSplitFewTiles || (cache.batch > 1 && tiles <= kSplitMaxTiles && blocks >= 128)) && fit >= 64 && (tiles + 8) * blocks < 0x7FFFFFFFll;

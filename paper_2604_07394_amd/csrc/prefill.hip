@@ -664,8 +664,10 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
           o[db][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[ks][db], pf[qb][ks], o[db][qb], 0, 0, 0);
     };
     // Only when a row has no reference yet, or some weight of the block left the guarded range (or
-    // overflowed), does the wave take the block's maximum, move the reference there (rescaling l and O) and
-    // redo the weights.  In the steady state the maximum, its cross-lane steps and the rescale are not executed.
+    // overflowed), does the wave take the block's maximum, move the reference of THAT row there (rescaling l and O) and
+    // redo the weights.  In the steady state the maximum, its cross-lane steps and the rescale are not executed.  Rows
+    // that need no move keep their reference, so that a row's result does not depend on the rows that share its wave
+    // (launch shapes group rows differently, and give the same bits).
     auto weights_guarded = [&]() {
       weights();
       // (one ballot per comparison: each is then the comparison's own lane mask, with no vector instruction between)
@@ -679,8 +681,11 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
             for (int i = 0; i < 4; ++i) mloc = fmaxf(mloc, s[kb][qb][i]);
           mloc = fmaxf(mloc, __shfl_xor(mloc, 16));                              // over the 4 lanes of the row
           mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
+          // the row's own reason: no reference yet, or a weight of 2^31 and more (which trips the guard by itself, so that
+          // the row moves whatever the others do)
+          const bool move = m_ref[qb] == -INFINITY || __builtin_fmaf(mloc, a.scale_log2, mneg[qb]) >= 31.f;
           const float m_new = fmaxf(m_ref[qb], mloc);
-          if (m_new > m_ref[qb]) {                                               // false while both are -inf
+          if (move && m_new > m_ref[qb]) {                                       // false while both are -inf
             const float al = fast_exp2((m_ref[qb] - m_new) * a.scale_log2);      // 0 for a row's first reference
             l_run[qb] *= al;
 #pragma unroll

@@ -8,6 +8,8 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import flux_oracle as O
+from paper_2604_07394_amd import synth
 from tests import helpers as H
 from tests.test_gpu_parity import Layer, FA, SA, cu, u8
 
@@ -91,6 +93,28 @@ def test_calls_that_split_nothing(F, ctxs, past, new, modes, hq, hkv, d, n_sink,
     assert np.array_equal(whole, got)
     for c in ctxs:
         assert F.flux_last_device_status(c) == 0
+
+
+@pytest.mark.parametrize("n,hq,hkv,n_sink,window,peak", [
+    (620, 6, 2, 0, 7, 1.0),                                 # rows of a wave whose windows begin in different key blocks
+    (400, 8, 1, 0, 7, 1.0),
+    (500, 4, 2, 300, 64, 40.0),                             # some rows' weights leave the guarded range, others' do not
+])
+def test_a_row_does_not_depend_on_the_rows_of_its_wave(F, ctxs, n, hq, hkv, n_sink, window, peak):
+    """The launch shape of long prompts (rows of all heads of a group share a wave) against the ordinary one (rows of one
+    head): the same bits, also where some rows of a wave move their softmax reference and others do not."""
+    lay = Layer(F, ctxs[0], 3300 + n, 1, hq, hkv, 128, 32768, n_sink, window, scales=True)
+    qb, kb, vb = lay.new_tokens([n])
+    if peak != 1.0:
+        q = O.bf16_to_f64(qb).astype(np.float32)
+        q[::7] *= peak
+        qb = synth.f32_to_bf16_bits(q)
+    lay.append(kb, vb, [n])
+    for mode in (FA, SA):
+        got, ref = lay.prefill(qb, [n], [mode])
+        H.assert_close(got, ref, "ordinary launch shape")
+        wide, _ = lay.prefill(qb, [n], [mode], max_q_len=32768, want_ref=False)
+        assert np.array_equal(wide, got)
 
 
 def test_batches_past_the_planned_size_and_bad_lengths(F, ctxs):

@@ -120,12 +120,6 @@ struct Split {
   unsigned long long empty;   // (calls merged in place) sequences without keys
 };
 
-// Quotients of small numbers (below 2^24: keys are counted in 128-key pieces) through a reciprocal, put right by one step.
-__device__ __forceinline__ int div_small(int x, int y, float inv_y) {
-  int q = (int)((float)x * inv_y);
-  q += (q + 1) * y <= x ? 1 : (q * y > x ? -1 : 0);
-  return q;
-}
 // chunks that a list of `pieces` takes at `c` pieces each
 __device__ __forceinline__ int chunks_of(int pieces, int c, float inv_c) { return pieces > 0 ? div_small(pieces - 1, c, inv_c) + 1 : 0; }
 

@@ -208,6 +208,13 @@ __device__ __forceinline__ int wave_inclusive_sum(int x) {
   return x;
 }
 
+// Quotients of small numbers (below 2^24) through a reciprocal, put right by one step.
+__device__ __forceinline__ int div_small(int x, int y, float inv_y) {
+  int q = (int)((float)x * inv_y);
+  q += (q + 1) * y <= x ? 1 : (q * y > x ? -1 : 0);
+  return q;
+}
+
 // One wave-wide direct global -> LDS transfer: every lane fetches its own 16 bytes, the 64 pieces land
 // at lds_base + 16 * lane.  Issued as inline assembly so that the compiler does not serialise later LDS
 // reads of the OTHER stage behind it; completion is awaited explicitly with vmcnt(0) before the barrier.

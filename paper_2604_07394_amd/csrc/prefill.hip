@@ -91,14 +91,20 @@ __device__ __forceinline__ void dma_tile2(const char* kt, const char* vt, const 
 }
 
 // ---- the plan of a launch, taken on the device
-// Every wave of a planned launch (2 to 64 sequences, or one whose tiles may be split; lane b looks after sequence b) finds out from the lengths and mode
-// bytes which unit of work its workgroup is: the tiles of the sequences with the longest key lists first, no empty
-// workgroups between them (a grid shaped by the host's bounds leaves most workgroups of short sequences empty, and long
-// ones late).  Where the host allows it (split_units), the key blocks of a tile are shared out over several units, so
-// that a few query rows behind long contexts fill the chip as well; their partial results are merged by a second kernel.
-constexpr int kMinSplitBlocks = 16;             // key blocks a unit of a split tile has at least: shorter lists keep their sums in one order
+// Every wave of a planned launch (2 to 64 sequences, or one whose tiles may be split; lane b looks after sequence b) finds
+// out from the lengths and mode bytes which unit of work its workgroup is: the tiles of the sequences with the longest key
+// lists first, no empty workgroups between them (a grid shaped by the host's bounds leaves most workgroups of short
+// sequences empty, and long ones late).  Where the host allows it (split_units), the key blocks of a tile are shared out
+// over several units, so that a few query rows behind long contexts fill the chip as well; their partial results are
+// merged by a second kernel.  The plan is latency at the start of every workgroup: those past the last unit leave as soon
+// as the units are summed (8192 + 63 x 100 tokens, 32/8 heads: 1324 us with all workgroups ranking first, 605 now, 616
+// without a plan), and sequences that are all alike need no ranking.
+constexpr int kMinSplitBlocks = 16;             // lists of at most so many key blocks are never split (a unit has about half of it at least)
 constexpr int kResident128 = 512;               // workgroups of four waves the chip holds at once: two per CU, at head dimension
 constexpr int kResident64 = 768;                // 64 three
+constexpr int kPlanTiles = 512;                 // batches of at least so many tiles by the host's bounds are planned: a smaller
+                                                // one is resident at once, and the plan only delays it (us without / with
+                                                // it: 8 x 100 tokens 7.65 / 9.1, 4 x 64 at 8/2 heads of 64 4.7 / 5.0)
 constexpr int kSplitUnits = 1024;               // units a launch that splits may have beyond one per tile
 constexpr int kSplitFewTiles = 448;             // launches of at most so many tiles may split (7/8 of what is resident)
 constexpr int kSplitMaxTiles = 2048;            // ... and batches of at most so many, counted with the host's bounds
@@ -119,6 +125,7 @@ struct PrefillUnit {
 };
 
 // resident: workgroups of the launch that the chip holds at once
+template <bool PACK>
 __device__ __forceinline__ PrefillUnit prefill_plan(const PrefillArgs& a, int l, int bm, int resident) {
   PrefillUnit u;
   // this lane's sequence: lengths under the clamps, tiles, key blocks of its longest tile (an upper bound for SA)
@@ -132,7 +139,7 @@ __device__ __forceinline__ PrefillUnit prefill_plan(const PrefillArgs& a, int l,
     bad = n_q < 0 || len < 0 || len > a.capacity || n_q > len;
     len = len < 0 ? 0 : (len > a.capacity ? a.capacity : len);
     n_q = n_q < 0 ? 0 : (n_q > len ? len : n_q);
-    tiles = min((int)(((int64_t)n_q * a.group + bm - 1) / bm), a.n_qtiles);
+    tiles = PACK ? min((int)(((int64_t)n_q * a.group + bm - 1) / bm), a.n_qtiles) : min((n_q + bm - 1) / bm, a.n_qtiles) * a.group;
     nb = (len + 63) >> 6;
     if (sa) {
       const int64_t win = min((int64_t)a.win_blocks << a.blk_shift, (int64_t)len);
@@ -143,7 +150,7 @@ __device__ __forceinline__ PrefillUnit prefill_plan(const PrefillArgs& a, int l,
   u.chunk = 0x7FFFFFFF;
   int nc = tiles > 0 ? 1 : 0;
   // (no list long enough: nothing to search for)
-  if (a.split_units > 0 && __builtin_amdgcn_ballot_w64(tiles > 0 && nb > kMinSplitBlocks) != 0) {
+  if (PACK && a.split_units > 0 && __builtin_amdgcn_ballot_w64(tiles > 0 && nb > kMinSplitBlocks) != 0) {
     // Key blocks a unit takes at most: every lane works out one candidate, around the share of one of the workgroups
     // the chip holds, by a model in units of one block: the longest unit, or that share plus half a unit of
     // unevenness where there is more than one round, plus 0.02 for writing and merging the partial result of a unit
@@ -171,23 +178,70 @@ __device__ __forceinline__ PrefillUnit prefill_plan(const PrefillArgs& a, int l,
     u.chunk = __builtin_amdgcn_readlane(cand, __builtin_amdgcn_readfirstlane(best) & 63);
     nc = tiles > 0 ? (nb + u.chunk - 1) / u.chunk : 0;
   }
+  const bool parts = __builtin_amdgcn_ballot_w64(nc > 1) != 0;
+  if (PACK && a.split_units > 0 && blockIdx.x == 0 && threadIdx.x == 0) a.tile_info[a.batch * a.hkv * a.n_qtiles] = i32x4{parts, 0, 0, 0};
+  u.b = -1;
+  const int t0 = __builtin_amdgcn_readlane(tiles, 0);
+  const bool alike = __builtin_amdgcn_ballot_w64(l < a.batch && (tiles != t0 || nb != __builtin_amdgcn_readlane(nb, 0))) == 0;
+  if (!parts && alike) {
+    // Nothing is split and the sequences are as long as each other: a unit per (KV head, tile), found without a ranking.
+    // Workgroups go to the 8 XCDs by id mod 8, and the units of one KV head walk the same K/V rows: they get ids of one
+    // residue, or of 8 / hkv residues.  q: the unit's place among those of its head
+    const int total = t0 * a.batch;
+    int q, nj = total;                                       // nj: units of this XCD
+    const int x = blockIdx.x & 7;
+    int j = blockIdx.x >> 3;
+    if ((a.hkv & 7) == 0) {
+      nj = total * (a.hkv >> 3);
+      if (j >= nj) return u;
+      if (resident >= 512) j = pair_long_with_short(j, nj);
+      const int o = a.hkv == 8 ? 0 : j / total;
+      u.kvh = 8 * o + x;
+      q = j - o * total;
+    } else if (a.hkv < 8 && (a.hkv & (a.hkv - 1)) == 0) {
+      const int sh = a.hkv == 1 ? 3 : (a.hkv == 2 ? 2 : 1);
+      nj = (total + (1 << sh) - 1) >> sh;
+      if (j >= nj) return u;
+      if (resident >= 512) j = pair_long_with_short(j, nj);
+      u.kvh = x & (a.hkv - 1);
+      q = (j << sh) + (x >> (3 - sh));
+      if (q >= total) return u;                              // padding of the last round
+    } else {
+      if ((int)blockIdx.x >= total * a.hkv) return u;
+      u.kvh = blockIdx.x / total;
+      q = blockIdx.x - u.kvh * total;
+    }
+    // Few rounds: the sequences take turns, heaviest tiles first (28/4 heads, 4 x 1000 tokens 41 us, one sequence after
+    // the other 49).  Many rounds, or a sequence that fills a round by itself: one after the other, for the L2 (4 x 8192
+    // 1806, in turn 1816; 16 x 700 99, in turn 102)
+    int tt;
+    if (t0 < 64 && nj < resident / 2) {
+      tt = __builtin_amdgcn_readfirstlane(div_small(q, a.batch, 1.0f / (float)a.batch));
+      u.b = q - tt * a.batch;
+    } else {
+      u.b = __builtin_amdgcn_readfirstlane(div_small(q, t0, 1.0f / (float)t0));
+      tt = q - u.b * t0;
+    }
+    u.tile = t0 - 1 - tt;
+    u.ci = u.slot0 = u.slot_step = 0;
+    u.q_begin = __builtin_amdgcn_readlane(q_begin, u.b);
+    u.n_q = __builtin_amdgcn_readlane(n_q, u.b);
+    u.len = __builtin_amdgcn_readlane(len, u.b);
+    u.sa = __builtin_amdgcn_readlane((int)sa, u.b) != 0;
+    return u;
+  }
   // units of the sequence: one per (KV head, part, tile).  Workgroups go to the 8 XCDs by id mod 8, and the units of one
   // (KV head, part) walk the same K/V rows: they get ids of one residue (or of 8 / groups residues).
   const int groups = a.hkv * nc;
   const int share_sh = groups == 1 ? 3 : (groups == 2 ? 2 : (groups == 4 ? 1 : 0));
   const int units = share_sh > 0 ? ((tiles + (1 << share_sh) - 1) >> share_sh) * 8 : groups * tiles;
-  if (a.split_units > 0 && blockIdx.x == 0) {
-    const bool any = __builtin_amdgcn_ballot_w64(nc > 1) != 0;
-    if (threadIdx.x == 0) a.tile_info[a.batch * a.hkv * a.n_qtiles] = i32x4{any, 0, 0, 0};
-  }
   int units_s = units, idx_s = l;
   int incl = wave_inclusive_sum(units);
   const int total_units = __builtin_amdgcn_readlane(incl, 63);
   int id = blockIdx.x;
-  u.b = -1;
   if (id >= total_units) return u;                           // (most workgroups, where the host's bounds are far above the lengths)
   // longest first, if they are not all alike: rank by (key blocks, index), then the units in that order
-  if (__builtin_amdgcn_ballot_w64(l < a.batch && nb != __builtin_amdgcn_readlane(nb, 0)) != 0) {
+  if (a.batch > 1) {
     const int key = (nb << 6) | (63 - l);                    // no two alike; lanes without a sequence hold the lowest
     int rank = 0;
     for (int j = 0; j < a.batch; j += 8) {
@@ -235,15 +289,16 @@ __device__ __forceinline__ PrefillUnit prefill_plan(const PrefillArgs& a, int l,
   return u;
 }
 
-// A tile is BM = 32 * NW rows.  In planned launches and in those for long prompts they are the query rows of ALL heads of
-// the group, token by token: row R is head R % group of token R / group.  Short runs of queries then fill their tiles (16
-// new tokens of a group of 4 are half a tile, not an eighth of four), a tile spans few tokens, so that little of what the
-// diagonal or a window's start cuts is worked out for nothing, and its query rows are contiguous in memory.  Otherwise (one
-// short prompt, where finding the rows would cost 4 % of 15 us at 512 tokens, and the block-sparse form, whose keep matrix
-// differs between heads) a tile is 128 tokens of one head.
-template <int D, bool BS, int NW, bool PLAN = false>   // NW: waves per workgroup, 4 (two workgroups per CU) or 8 (one)
+// A tile is BM = 32 * NW rows.  PACK: they are the query rows of ALL heads of the group, token by token: row R is head
+// R % group of token R / group.  Short runs of queries then fill their tiles (16 new tokens of a group of 4 are half a
+// tile, not an eighth of four), a tile spans few tokens, so that little of what the diagonal or a window's start cuts is
+// worked out for nothing, and its query rows are contiguous in memory.  Otherwise a tile is 128 tokens of one head:
+// finding the rows costs a workgroup about a microsecond, more than that saves where tiles are full (8 x 2048 tokens
+// packed 3 % slower), and in the block-sparse form the keep matrix differs between heads.
+// NW: waves per workgroup, 4 (two workgroups per CU) or 8 (one)
+template <int D, bool BS, int NW, bool PLAN = false, bool PACK = NW == 8>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(PrefillArgs a) {
-  constexpr bool PACK = PLAN || NW == 8;  // the rows of a tile come from all heads of a group
+  constexpr bool SPLIT = PLAN && PACK;    // tiles may be split
   constexpr int BM = 32 * NW;             // query rows per workgroup
   constexpr int BN = 64;                  // keys per iteration: two halves of 32, the K dimension of one PV MFMA
   constexpr int KC = D / 32;              // MFMA k-steps over the head dimension (QK^T)
@@ -290,11 +345,15 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
   int q_begin, n_q, len, ci = 0, chunk = 0x7FFFFFFF, slot0 = 0, slot_step = 0;
   bool sa;
   if constexpr (PLAN) {
-    const PrefillUnit u = prefill_plan(a, l, BM, NW == 8 ? 256 : (D == 64 ? kResident64 : kResident128));
+    const PrefillUnit u = prefill_plan<PACK>(a, l, BM, NW == 8 ? 256 : (D == 64 ? kResident64 : kResident128));
     if (u.b < 0) return;                                     // uniform for the workgroup
     b = u.b;
     h = u.kvh * a.group;
     qt = u.tile;
+    if constexpr (!PACK) {                                   // tiles of one head: the heads of a group next to each other
+      qt = u.tile / a.group;
+      h += u.tile - qt * a.group;
+    }
     q_begin = u.q_begin;
     n_q = u.n_q;
     len = u.len;
@@ -415,17 +474,17 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
   const int n_blocks = n_a + n_b;
   // a split tile: this unit takes part ci of the list
   int it0 = 0, n_iter = n_blocks, n_parts = 1;             // (n_iter: one past its last)
-  if (PLAN && chunk < n_blocks) {
+  if (SPLIT && chunk < n_blocks) {
     n_parts = (n_blocks + chunk - 1) / chunk;
     if (ci >= n_parts) return;                               // uniform
     it0 = (int)((int64_t)ci * n_blocks / n_parts);
     n_iter = (int)((int64_t)(ci + 1) * n_blocks / n_parts);
-  } else if (PLAN && ci > 0) {
+  } else if (SPLIT && ci > 0) {
     return;
   }
-  if (PLAN && tid == 0) {
+  if (SPLIT && tid == 0) {
     fin = {rows, rem0, grp, a.hq, n_parts > 1 ? slot0 + ci * slot_step : -1, a.out_fp32, tile_off, (FLUX_GLOBAL void*)a.out, (FLUX_GLOBAL float*)a.part_o, (FLUX_GLOBAL float*)a.part_ml};
-    if (PLAN && a.split_units > 0 && ci == 0) a.tile_info[((int64_t)b * a.hkv + kvh) * a.n_qtiles + qt] = i32x4{slot0, slot_step, n_parts, 0};
+    if (a.split_units > 0 && ci == 0) a.tile_info[((int64_t)b * a.hkv + kvh) * a.n_qtiles + qt] = i32x4{slot0, slot_step, n_parts, 0};
   }
 
   const char* kbase = (const char*)(a.k + (int64_t)b * a.stride_b + (int64_t)kvh * a.stride_h);
@@ -823,11 +882,11 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
   }
 
   // ---- lane (n, g) holds d = 16*db + 4*g .. +3 of its two query rows
-  const int f_rows = PLAN ? __builtin_amdgcn_readfirstlane(fin.rows) : rows, f_slot = PLAN ? __builtin_amdgcn_readfirstlane(fin.slot) : -1;
-  const int f_rem0 = PLAN ? fin.rem0 : rem0, f_grp = PLAN ? fin.grp : grp, f_hq = PLAN ? fin.hq : a.hq;
-  const int64_t f_off = PLAN ? fin.tile_off : tile_off;
-  const int f_fp32 = PLAN ? fin.out_fp32 : a.out_fp32;
-  FLUX_GLOBAL void* f_out = PLAN ? fin.out : (FLUX_GLOBAL void*)a.out;
+  const int f_rows = SPLIT ? __builtin_amdgcn_readfirstlane(fin.rows) : rows, f_slot = SPLIT ? __builtin_amdgcn_readfirstlane(fin.slot) : -1;
+  const int f_rem0 = SPLIT ? fin.rem0 : rem0, f_grp = SPLIT ? fin.grp : grp, f_hq = SPLIT ? fin.hq : a.hq;
+  const int64_t f_off = SPLIT ? fin.tile_off : tile_off;
+  const int f_fp32 = SPLIT ? fin.out_fp32 : a.out_fp32;
+  FLUX_GLOBAL void* f_out = SPLIT ? fin.out : (FLUX_GLOBAL void*)a.out;
   const float f_inv = __builtin_amdgcn_rcpf((float)f_grp);
 #pragma unroll
   for (int qb = 0; qb < 2; ++qb) {
@@ -836,7 +895,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
     l_tot += __shfl_xor(l_tot, 32);
     const int x = r_w0 + 16 * qb + n;
     if (x >= f_rows) continue;
-    if (PLAN && f_slot >= 0) {
+    if (SPLIT && f_slot >= 0) {
       // part of a tile: the unnormalised rows, their references and weight sums go to the workspace
       const int64_t row = (int64_t)f_slot * BM + x;
       if (g == 0) {
@@ -966,8 +1025,11 @@ hipError_t launch_prefill(const Ctx& c, const flux_attn_cfg& cfg, const void* q,
   a.bm_kblocks = bm ? bm->n_kblocks : 0;
   if (max_q_len == 0) return hipSuccess;
   const long long n_pairs = (long long)cache.batch * cfg.n_kv_heads;
-  // Batches are planned on the device (longest first, no empty workgroups): prompts of 129, 777, 2048, 3001 and 511 tokens,
-  // 32/8 heads, 119 -> 116.5 us; eight equal sequences lose 1 % (the plan costs about 1 us per workgroup).
+  // Batches are planned on the device (longest first, no empty workgroups).  us without a plan -> with it: 45 to 4876
+  // tokens in 6 sequences, 28/4 heads, 317 -> 182; 17 and 2856 tokens 115 -> 66; 32/8 heads, 2782, 35, 64 and 802 tokens 78
+  // -> 74; 300 and 400 tokens under a bound of 8192 18.6 -> 12.7; 8 x 2048 equal ones 278 -> 280.  Their tiles are packed
+  // where that leaves a quarter fewer (64 prompts of 16 tokens 18.5 -> 9.1), or behind a cached context any fewer (64 x 16
+  // tokens behind 900 81 -> 41).
   // Queries behind a cached context may have their tiles split (us before -> now, 32/8 heads of 128): 16 new tokens
   // behind 4000 cached 70 -> 27, behind 32000 528 -> 35; 128 behind 32000 546 -> 76; 512 behind 32000 549 -> 229; 1000
   // behind 32000 562 -> 435; 200, 333, 150 and 512 behind 16200, 9001, 24000 and 12345 297 -> 230; 100 and 4000 behind
@@ -981,8 +1043,11 @@ hipError_t launch_prefill(const Ctx& c, const flux_attn_cfg& cfg, const void* q,
   const long long fit = ((long long)c.partials_bytes - info_bytes) / unit_bytes - tiles - 8 * cache.batch;   // units beyond one per tile
   const bool split = !bm && !wide && cache.batch <= 64 && max_kv_len > max_q_len && blocks > kMinSplitBlocks &&
                      (tiles <= kSplitFewTiles || (cache.batch > 1 && tiles <= kSplitMaxTiles && blocks >= 128)) && fit >= 64 && (tiles + 8) * blocks < 0x7FFFFFFFll;
-  const bool plan = split || (!bm && cache.batch > 1 && cache.batch <= 64);
-  const int grp = plan || wide ? a.group : 1;               // heads whose rows share a tile
+  const long long whole = n_pairs * a.group * ((max_q_len + 127ll) / 128);    // tiles of one head each
+  const bool plan = split || (!bm && cache.batch > 1 && cache.batch <= 64 && (wide || whole >= kPlanTiles));
+  const long long unpacked = whole / n_pairs;
+  const bool pack = split || wide || (plan && (max_kv_len > max_q_len ? packed < unpacked : 4 * packed <= 3 * unpacked));
+  const int grp = pack ? a.group : 1;                       // heads whose rows share a tile
   const long long n_qtiles = ((long long)max_q_len * grp + BM - 1) / BM;
   a.n_qtiles = (int)n_qtiles;
   a.split_units = 0;
@@ -992,7 +1057,7 @@ hipError_t launch_prefill(const Ctx& c, const flux_attn_cfg& cfg, const void* q,
   if (plan) {
     a.xcd_map = 3;
     if (split) a.split_units = (int)(fit < kSplitUnits ? fit : kSplitUnits);
-    n_wg = tiles + 8 * cache.batch + a.split_units;         // (the units of a sequence are padded to whole rounds of the XCDs)
+    n_wg = (pack ? tiles : whole) + 8 * cache.batch + a.split_units;         // (the units of a sequence are padded to whole rounds of the XCDs)
     if (split) {
       a.tile_info = (i32x4*)c.partials;
       a.part_o = (float*)((char*)c.partials + info_bytes);
@@ -1017,6 +1082,8 @@ hipError_t launch_prefill(const Ctx& c, const flux_attn_cfg& cfg, const void* q,
     else hipLaunchKernelGGL((prefill_kernel<64, true, 4>), grid, dim3(256), 0, s, a);
   } else if (plan) {
     if (wide) hipLaunchKernelGGL((prefill_kernel<128, false, 8, true>), grid, dim3(512), 0, s, a);
+    else if (pack && d128) hipLaunchKernelGGL((prefill_kernel<128, false, 4, true, true>), grid, dim3(256), 0, s, a);
+    else if (pack) hipLaunchKernelGGL((prefill_kernel<64, false, 4, true, true>), grid, dim3(256), 0, s, a);
     else if (d128) hipLaunchKernelGGL((prefill_kernel<128, false, 4, true>), grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL((prefill_kernel<64, false, 4, true>), grid, dim3(256), 0, s, a);
   } else {

@@ -75,6 +75,12 @@ def test_planned_prefill(F, ctxs, past, new, modes, hq, hkv, d, n_sink, window, 
     ([3000, 2900, 3001], [40, 1, 90], [SA, SA, SA], 4, 4, 64, 16, 300),
     ([0] * 9, [70] * 9, [FA, SA] * 4 + [FA], 8, 2, 64, 3, 40),   # sequences all alike
     ([0] * 5, [300, 1, 777, 0, 64], [FA, SA, FA, FA, SA], 14, 7, 128, 3, 40),
+    ([0] * 4, [513, 400, 3, 1026], [FA, SA, FA, FA], 28, 4, 128, 3, 40),   # 1008 tiles of one head each
+    ([0] * 24, [100, 128, 97, 100] * 6, [FA] * 24, 14, 2, 64, 3, 40),      # 672, every sequence one per head
+    ([0] * 6, [385, 400, 512, 386, 420, 500], [FA] * 6, 12, 3, 128, 3, 40),   # as many tiles each, other lists: ranked
+    ([0] * 8, [900] * 8, [FA] * 8, 16, 16, 64, 3, 40),       # all alike, 16 KV heads, several rounds
+    ([0] * 40, [17] * 40, [SA, FA] * 20, 32, 2, 128, 3, 8),  # short: packed, group of 16
+    ([90] * 33, [5] * 33, [FA] * 33, 20, 5, 64, 3, 40),      # behind a context: packed, KV heads that do not divide 8
 ])
 def test_calls_that_split_nothing(F, ctxs, past, new, modes, hq, hkv, d, n_sink, window):
     """Bit-identical to the call that has no room to split, also after a call on the same context that did."""

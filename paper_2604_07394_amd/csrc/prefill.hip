@@ -106,8 +106,19 @@ constexpr int kPlanTiles = 512;                 // batches of at least so many t
                                                 // one is resident at once, and the plan only delays it (us without / with
                                                 // it: 8 x 100 tokens 7.65 / 9.1, 4 x 64 at 8/2 heads of 64 4.7 / 5.0)
 constexpr int kSplitUnits = 1024;               // units a launch that splits may have beyond one per tile
-constexpr int kSplitFewTiles = 448;             // launches of at most so many tiles may split (7/8 of what is resident)
-constexpr int kSplitMaxTiles = 2048;            // ... and batches of at most so many, counted with the host's bounds
+constexpr int kSplitFewTiles = 448;             // merges of at most so many tiles give a row to every thread
+constexpr int kSplitMaxTiles = 2048;            // batches of at most so many tiles, counted with the host's bounds, may split
+
+// Whether it pays to share out the keys of so many tiles, the longest of which walks so many key blocks: what the idle
+// part of the chip can take of the walk has to be worth the plan, the partial results and the second launch.  us whole /
+// split, one sequence of 32/8 heads of 128 (a tile is 32 tokens of a KV head): 128 tiles, 18, 24 and 32 blocks 24.8 /
+// 30.7, 31.2 / 33.0, 39.7 / 37.1; 250 tiles, 32, 47 and 64 blocks 31.5 / 37.7, 56.1 / 57.1, 74.8 / 70.9; 320 tiles, 64 and
+// 96 blocks 86 / 91, 128 / 125; 376 tiles, 256 blocks 365 / 389; 8 tiles, 18 blocks 22.7 / 18.8.  8/2 heads of 64: 2
+// tiles, 18 blocks 16.2 / 14.6; 32 tiles, 18 and 32 blocks 17.5 / 20.2, 27.7 / 20.8.
+__host__ __device__ __forceinline__ bool split_pays(int tiles, int blocks, int resident) {
+  const float t = (float)tiles;
+  return 3 * tiles <= 2 * resident && (float)blocks * (1.0f - t / (float)resident) >= (resident <= kResident128 ? 15.0f + t / 18.0f : 16.0f + t / 8.0f);
+}
 
 // Place of the j-th of the nj workgroups of an XCD in the order from long to short.  Consecutive workgroups of an XCD go
 // round its 32 CUs, and a launch of at most two per CU is resident at once: its second half is handed out in reverse, so
@@ -149,14 +160,19 @@ __device__ __forceinline__ PrefillUnit prefill_plan(const PrefillArgs& a, int l,
   if (blockIdx.x == 0 && threadIdx.x < 64 && bad) atomicOr(a.status, (uint32_t)FLUX_DEV_BAD_LENGTH);
   u.chunk = 0x7FFFFFFF;
   int nc = tiles > 0 ? 1 : 0;
-  // (no list long enough: nothing to search for)
-  if (PACK && a.split_units > 0 && __builtin_amdgcn_ballot_w64(tiles > 0 && nb > kMinSplitBlocks) != 0) {
+  float share = 0.f;
+  bool worth = false;                                        // this lane's lists are a reason to split
+  if (PACK && a.split_units > 0) {
+    const int t = __builtin_amdgcn_readlane(wave_inclusive_sum(tiles), 63) * a.hkv;
+    share = (float)(__builtin_amdgcn_readlane(wave_inclusive_sum(tiles * nb), 63) * a.hkv) / (float)resident;
+    // few tiles; or enough of them, but a list that takes twice as long as its share of the chip
+    worth = tiles > 0 && nb > kMinSplitBlocks && (3 * t <= 2 * resident ? split_pays(t, nb, resident) : nb >= 64 && (float)nb > 2.0f * share);
+  }
+  if (PACK && __builtin_amdgcn_ballot_w64(worth) != 0) {
     // Key blocks a unit takes at most: every lane works out one candidate, around the share of one of the workgroups
     // the chip holds, by a model in units of one block: the longest unit, or that share plus half a unit of
     // unevenness where there is more than one round, plus 0.02 for writing and merging the partial result of a unit
     // (66 KB each way; a block takes 1.65 us).
-    const int total = __builtin_amdgcn_readlane(wave_inclusive_sum(tiles * nb), 63) * a.hkv;
-    const float share = (float)total / (float)resident;
     const int cand = l == 63 ? 0x3FFFFFFF : max(kMinSplitBlocks, (int)(share * (float)(l + 4) * (1.0f / 16.0f)) + 1);
     const float inv = 1.0f / (float)cand;
     int units = 0, parts = 0, longest = 0;
@@ -1033,16 +1049,19 @@ hipError_t launch_prefill(const Ctx& c, const flux_attn_cfg& cfg, const void* q,
   // Queries behind a cached context may have their tiles split (us before -> now, 32/8 heads of 128): 16 new tokens
   // behind 4000 cached 70 -> 27, behind 32000 528 -> 35; 128 behind 32000 546 -> 76; 512 behind 32000 549 -> 229; 1000
   // behind 32000 562 -> 435; 200, 333, 150 and 512 behind 16200, 9001, 24000 and 12345 297 -> 230; 100 and 4000 behind
-  // 60000 and 3000 1258 -> 406.  Launches that would split nothing pay for the plan and the second launch all the same
-  // (about 5 us), so a launch whose tiles fill the chip by themselves is left alone: few tiles by the host's bounds, or a
-  // batch (whose bounds count tiles that short sequences do not have) with contexts long enough (8192 positions) that one
-  // uneven sequence costs more than that.
+  // 60000 and 3000 1258 -> 406.  Whether they are is decided on the device (split_pays); a launch that may split but does
+  // not (a layer with a short sparse window, say) pays for the plan and the second launch all the same, 0.5 to 3 us.  So
+  // the host lets only those that its bounds say may gain: few tiles for the length of the lists, or a batch (whose bounds
+  // count tiles that short sequences do not have) with contexts long enough (8192 positions) that one uneven sequence
+  // costs more than that.
   const long long packed = ((long long)max_q_len * a.group + BM - 1) / BM;    // tiles of a pair whose rows come from all heads
   const long long tiles = n_pairs * packed, blocks = ((long long)max_kv_len + 63) / 64;
   const long long unit_bytes = (long long)BM * (cfg.head_dim + 2) * 4, info_bytes = ((tiles + 1) * 16 + 255) / 256 * 256;
   const long long fit = ((long long)c.partials_bytes - info_bytes) / unit_bytes - tiles - 8 * cache.batch;   // units beyond one per tile
   const bool split = !bm && !wide && cache.batch <= 64 && max_kv_len > max_q_len && blocks > kMinSplitBlocks &&
-                     (tiles <= kSplitFewTiles || (cache.batch > 1 && tiles <= kSplitMaxTiles && blocks >= 128)) && fit >= 64 && (tiles + 8) * blocks < 0x7FFFFFFFll;
+                     ((tiles <= 768 && split_pays((int)tiles, (int)blocks, cfg.head_dim == 64 ? kResident64 : kResident128)) ||
+                      (cache.batch > 1 && tiles <= kSplitMaxTiles && blocks >= 128)) &&
+                     fit >= 64 && (tiles + 8) * blocks < 0x7FFFFFFFll;
   const long long whole = n_pairs * a.group * ((max_q_len + 127ll) / 128);    // tiles of one head each
   const bool plan = split || (!bm && cache.batch > 1 && cache.batch <= 64 && (wide || whole >= kPlanTiles));
   const long long unpacked = whole / n_pairs;

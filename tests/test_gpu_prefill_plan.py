@@ -73,6 +73,7 @@ def test_planned_prefill(F, ctxs, past, new, modes, hq, hkv, d, n_sink, window, 
 @pytest.mark.parametrize("past,new,modes,hq,hkv,d,n_sink,window", [
     ([3000], [40], [SA], 8, 2, 128, 16, 128),               # may split by its bounds, but the window's list is short
     ([3000, 2900, 3001], [40, 1, 90], [SA, SA, SA], 4, 4, 64, 16, 300),
+    ([640], [512], [FA], 32, 8, 128, 16, 128),              # 128 tiles of 18 blocks: not worth it
     ([0] * 9, [70] * 9, [FA, SA] * 4 + [FA], 8, 2, 64, 3, 40),   # sequences all alike
     ([0] * 5, [300, 1, 777, 0, 64], [FA, SA, FA, FA, SA], 14, 7, 128, 3, 40),
     ([0] * 4, [513, 400, 3, 1026], [FA, SA, FA, FA], 28, 4, 128, 3, 40),   # 1008 tiles of one head each

@@ -27,7 +27,7 @@ struct AppendArgs {
 
 constexpr int kAppendTokens = 4;            // token rows a thread has in flight in a launch of more than kAppendFew workgroups
 constexpr int kAppendFew = 256;
-constexpr int kAppendTable = 256;           // sequences whose lengths fit the table in LDS
+constexpr int kAppendTable = 1024;          // sequences whose lengths fit the table in LDS
 constexpr int kAppendBlocks = 512;          // workgroups at most
 
 // What bounds it: the copy where there is much to copy; else latencies and the arrival counter.  Every workgroup counts
@@ -152,9 +152,11 @@ hipError_t launch_kv_append(const Ctx& c, const flux_kv_cache& cache, int hkv, i
   const int cpt = hkv * (d / 8);
   const int tpi = 256 / (cpt < 256 ? cpt : 256);
   // A launch of few workgroups with one token row per thread is as short as it gets (4 rows per thread and the table: 100
-  // tokens 4.3 against 3.0 us, one token 2.8 / 2.4); from there on the counter shows.
+  // tokens 4.3 against 3.0 us, one token 2.8 / 2.4); from there on the counter shows.  Many sequences take longer to look
+  // up, which more workgroups share: 600 sequences of one token 11.0 / 9.2, 200 of three 8.9 / 8.5, 1500 of one at 4 KV heads
+  // 12.9 / 10.8.
   const long long single = ((long long)total_new + tpi - 1) / tpi;
-  if (single <= kAppendFew) {
+  if (single <= (cache.batch <= 128 ? kAppendFew : 2 * kAppendFew)) {
     hipLaunchKernelGGL(kv_append_kernel<1>, dim3((unsigned)(single < 1 ? 1 : single)), dim3(256), 0, s, a);
   } else {
     const long long blocks = (single + kAppendTokens - 1) / kAppendTokens;

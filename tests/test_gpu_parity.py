@@ -723,7 +723,8 @@ def test_router_rounds_are_the_same_sums(F, ctx, hidden, inner, few, many):
     (8, 128, [513]),                                          # one more token than one row per thread takes (256 workgroups of 2)
     (3, 64, [2700, 0, 2801]),                                 # 24 chunks per token: 10 tokens and 16 idle threads per workgroup
     (40, 128, [300]),                                         # a token of more chunks than a workgroup has threads
-    (8, 128, [3] * 255 + [9]), (8, 128, [2] * 257),           # on either side of the table of lengths
+    (8, 128, [3] * 255 + [9]), (8, 128, [2] * 257),           # many sequences: on either side of 512 workgroups ...
+    (8, 128, [2] * 1024), (2, 64, [9] * 1025),                # ... and of the table of lengths
 ])
 def test_append_rows_in_flight(F, ctx, hkv, d, lens):
     """Copies of more than 256 workgroups with one row per thread: several rows per thread, lengths looked up in LDS."""

@@ -316,7 +316,8 @@ __global__ __launch_bounds__(256, 2) void xa_select_kernel(XaArgs a) {
 // the workspace in pieces of [128 square rows][16 square columns]; xa_keep_kernel (one wave per query block) reads its
 // 4 rows piece by piece, does what the reduction phase of the walk does and writes the row of the keep matrix.  The
 // sums are taken in the order of the walk (four chains of 4 row offsets, added in pairs), and so is everything after
-// them: the two forms keep the same blocks.
+// them: the two forms keep the same blocks, up to the 65536 positions of the single walk.  (Two walks take the quotient of
+// exponentials where the others take the difference of logarithms: there a mass next to the cut may fall on either side.)
 // What bounds it: the rate at which the L2s deliver operand rows to the CUs.  The walk above fetches every key row once
 // per 32 square rows, this form every operand row once per 128 of the other operand: 16384 positions x 32 heads 1.2 GB
 // instead of 2.1 GB (walk 340 us; here 144 us, 700 TFLOP/s at its core, a quarter of it for the 75 MB of means, plus 46 us

@@ -27,9 +27,11 @@ def F():
     return binding
 
 
-@pytest.fixture(scope="module")
-def ctx(F):
-    c = F.flux_create(0, 0)
+@pytest.fixture(scope="module", params=["tiles", "walk"])
+def ctx(F, request):
+    """The two forms of the selection: with the default workspace prompts from 1024 positions on (head dimension 64: 320)
+    are scored in tiles; the smallest workspace holds no row of tiles, so that every prompt is walked."""
+    c = F.flux_create(0, 0 if request.param == "tiles" else 1)
     yield c
     F.flux_destroy(c)
 
@@ -188,8 +190,9 @@ def test_xa_selection_long_prompt_sampled_rows(F, ctx):
 
 
 def test_xa_selection_beyond_65536_positions_two_walks(F, ctx):
-    """A prompt of 66100 positions: the (square row, key block) table of a workgroup no longer fits LDS, so the kernel
-    walks the keys twice (maximum and sum first, probabilities second).  Sampled rows against the oracle."""
+    """A prompt of 66100 positions.  Walked: the (square row, key block) table of a workgroup no longer fits LDS, so the
+    kernel walks the keys twice (maximum and sum first, probabilities second).  In tiles: the widest row kernel.  Sampled
+    rows against the oracle."""
     S, HQ, HKV, D = 66100, 2, 1, 64
     from paper_2604_07394_amd import synth_gpu as G
     q = torch.empty(1, S, HQ, D, dtype=torch.bfloat16, device="cuda")
@@ -214,7 +217,7 @@ def test_xa_selection_beyond_65536_positions_two_walks(F, ctx):
         dd, tt = check_selection(got[h:h + 1], qf[:, None, :], kf[:, None, :], 1, 1, 0.9, rows=rows)
         differ += dd
         total += tt
-    print("XA selection at %d tokens (two walks): %d of %d sampled rows differ" % (S, differ, total))
+    print("XA selection at %d tokens: %d of %d sampled rows differ" % (S, differ, total))
     assert F.flux_last_device_status(ctx) == 0
 
 
@@ -251,3 +254,46 @@ def test_xa_selection_tiles(F, n, d, hq, hkv, heads_at_a_time):
         assert F.flux_last_device_status(ctx) == 0
     finally:
         F.flux_destroy(ctx)
+
+
+@pytest.mark.parametrize("lens,d,hq,hkv,heads_at_a_time", [
+    ([15, 64, 250], 64, 4, 2, 0), ([319, 1, 100], 64, 2, 2, 0),          # walked on the default workspace
+    ([15, 517, 900], 128, 4, 1, 0), ([950, 0, 33], 128, 2, 2, 0),
+    ([4500, 2049, 15], 128, 2, 1, 0),                                    # ragged over several rows of tiles
+    ([4500, 2049, 15, 2048], 64, 3, 1, 4),                               # 12 heads, 4 at a time: rounds that end inside sequences
+    ([2100, 700], 128, 4, 2, 3),
+])
+def test_xa_ragged_batches(F, lens, d, hq, hkv, heads_at_a_time):
+    """Against the oracle, and the same matrices from the walk (the smallest workspace) bit for bit."""
+    t, B, nb = sum(lens), len(lens), -(-max(lens) // BLK)
+    r = -(-max(lens) // 2048)
+    room = 0 if heads_at_a_time == 0 else 4096 + (8 << 20) + heads_at_a_time * 32768 * r * (r + 1) + 512
+    qb = synth.normal_bf16(97, synth.stream_id(synth.STREAM_Q), (t, hq, d))
+    kb = synth.normal_bf16(97, synth.stream_id(synth.STREAM_K), (t, hkv, d))
+    cfg = F.attn_cfg(hq, hkv, d, 0, 1, 0.0, 1)
+    masks = []
+    for workspace in (room, 1):
+        ctx = F.flux_create(0, workspace)
+        try:
+            cache = F.KVCache.empty(B, hkv, max(lens), d)
+            cache.k.fill_(float("nan"))
+            F.flux_kv_append(ctx, cache, hkv, d, H.bits_to_torch(kb), H.bits_to_torch(kb), cu(lens), t, max(lens))
+            mask = torch.full((B, hq, nb, nb), 9, dtype=torch.uint8, device="cuda")
+            F.flux_xa_select(ctx, cfg, H.bits_to_torch(qb), cu(lens), max(lens), max(lens), cache, STRIDE, 0.9, mask, nb, nb)
+            torch.cuda.synchronize()
+            assert F.flux_last_device_status(ctx) == 0
+            masks.append(mask.cpu().numpy())
+        finally:
+            F.flux_destroy(ctx)
+    assert masks[0].max() <= 1 and np.array_equal(masks[0], masks[1])
+    qf, kf = O.bf16_to_f64(qb), O.bf16_to_f64(kb)
+    off = 0
+    for b, n in enumerate(lens):
+        nbb = -(-n // BLK)
+        assert not masks[0][b, :, nbb:].any() and not masks[0][b, :, :, nbb:].any()
+        if 0 < n < 9:                                        # no causal sample at all: the own block alone
+            assert masks[0][b, :, 0, 0].all()
+        elif n:
+            rows = sorted({0, 1, nbb // 2, nbb - 2, nbb - 1} & set(range(nbb)))
+            check_selection(masks[0][b].astype(bool)[:, :nbb, :nbb], qf[off:off + n], kf[off:off + n], hq, hq // hkv, 0.9, rows=rows)
+        off += n

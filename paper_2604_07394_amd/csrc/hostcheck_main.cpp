@@ -10,6 +10,7 @@
 #include "../../include/flux.h"
 
 extern "C" const void *hostcheck_status, *hostcheck_partials, *hostcheck_counters;   // what the last decode launcher was given
+extern "C" int hostcheck_decode_small(const flux_attn_cfg* cfg, int batch, int max_kv_len);
 
 static int failures = 0;
 #define EXPECT(expr, want)                                                                   \
@@ -90,6 +91,23 @@ int main() {
   EXPECT(flux_attn_decode_static(&cfg, p, 32, &kc, pb, p, nullptr, nullptr), FLUX_EHIP);
   EXPECT(hostcheck_counters == nullptr, 1);
   EXPECT((const char*)hostcheck_partials - (const char*)hostcheck_status, 256);
+  // ---- which decode calls are merged in the launch that streams them: on either side of every bound
+  auto small = [](int hq, int hkv, int d, int batch, int keys) {
+    const flux_attn_cfg c = {hq, hkv, d, 4, 16, 0.f, 0, 0};
+    return hostcheck_decode_small(&c, batch, keys);
+  };
+  EXPECT(small(4, 1, 128, 1, 0), 0);
+  EXPECT(small(4, 1, 128, 1, 1), 1);
+  EXPECT(small(32, 8, 128, 1, 4352), 1);                    // 17 chunks of 256 keys
+  EXPECT(small(32, 8, 128, 1, 4353), 0);
+  EXPECT(small(8, 8, 64, 4, 2048), 1);                      // 256 units
+  EXPECT(small(8, 8, 64, 4, 2049), 0);
+  EXPECT(small(20, 20, 128, 3, 701), 1);                    // 60 pairs
+  EXPECT(small(21, 21, 128, 3, 701), 0);
+  EXPECT(small(16, 1, 64, 2, 1024), 1);                     // 16 query heads x 4 chunks to merge
+  EXPECT(small(16, 1, 64, 2, 1281), 0);                     // ... x 6
+  EXPECT(small(17, 1, 64, 1, 100), 0);                      // more query heads than rows of a unit
+  EXPECT(small(8, 8, 64, INT_MAX, 100), 0);
   // ---- append, ring, router
   EXPECT(flux_kv_append(ctx, &kc, 2, 128, p, p, pi, 10, 10, nullptr), FLUX_EHIP);
   EXPECT(flux_kv_append(ctx, &kc, 2, 128, p, p, pi, INT_MAX, INT_MAX, nullptr), FLUX_ECAPACITY);

@@ -9,6 +9,8 @@ hipError_t hipGetDevice(int* device) { *device = 0; return hipSuccess; }
 hipError_t hipGetSymbolAddress(void** p, const void* symbol) { *p = const_cast<void*>(symbol); return hipSuccess; }
 // of the last launch_decode
 const void *hostcheck_status, *hostcheck_partials, *hostcheck_counters;
+// whether a decode call with counters is merged in the launch that streams it
+int hostcheck_decode_small(const flux_attn_cfg* cfg, int batch, int max_kv_len) { return flux::decode_small(*cfg, batch, max_kv_len); }
 }
 
 namespace flux {

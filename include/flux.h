@@ -20,8 +20,12 @@
  *  - mode bytes: 1 = FA, 0 = SA (the paper's r_hard; "r_hard = 0 executes SA", Sec. 3.1).
  *  - bf16 tensors are 16-bit brain floats; their base addresses and all strides must be
  *    multiples of 8 elements (16 bytes).  head_dim must be 64 or 128.
- *  - Results are deterministic: same inputs and same shapes give bit-identical outputs.
- *  - Calls that share one flux_ctx must be ordered on one stream (they share its workspace).
+ *  - Results are deterministic: the same call (inputs, host bounds, workspace size) gives bit-identical outputs.  In
+ *    decode, and in prefill where keys are shared out over workgroups (see there), the order of a sequence's sums also
+ *    depends on the other sequences of the call.
+ *  - Calls that share one flux_ctx must be ordered on one stream: they share its workspace and the arrival counters in
+ *    it.  Calls that overlap on one context all the same can spoil each other's results and leave a counter non-zero,
+ *    which spoils later calls too: such a context is to be destroyed.
  */
 #ifndef FLUX_H_
 #define FLUX_H_
@@ -132,12 +136,15 @@ int flux_kv_append(flux_ctx* ctx, const flux_kv_cache* cache, int n_kv_heads, in
  * on n_q(b) and kv_len[b] (they size the launch; larger than needed is valid, smaller truncates
  * nothing: rows beyond max_q_len are not computed; a bound far above the real lengths costs empty
  * workgroups, and max_q_len from 32768 on (or from 16384 on with max_kv_len from 32768 on) selects
- * the launch shape tuned for long prompts, with the same results bit for bit).  Where max_kv_len > max_q_len (queries
- * behind a cached context) and the queries alone would not fill the chip, the keys of a tile of query rows are shared out
- * over several workgroups: their partial results go through the context's workspace (without room there, or for lists of
- * up to 1024 keys, this is not done), and the sums are taken in another order than in one walk.  SA tiles that the mask hides are skipped,
+ * the launch shape tuned for long prompts).  All launch shapes give the same results bit for bit, with one exception:
+ * where max_kv_len > max_q_len (queries behind a cached context), the batch has at most 64 sequences, the launch is not of
+ * the long shape, and the queries alone would not fill the chip, the keys of a tile of query rows may be shared out over
+ * several workgroups.  Whether and how depends on both bounds, on the lengths and modes of the whole batch and on the room
+ * for partial results in the workspace (lists of up to 1024 keys never are); the sums are then taken in another order
+ * than in one walk.  SA tiles that the mask hides are skipped,
  * not masked: their K/V rows are never read.  A 64-key tile that is partly visible is read whole
- * (up to kv_len[b]), so the cached rows below kv_len[b] must hold finite values.  If the device finds n_q(b) > kv_len[b] (the caller did not append first), only the first
+ * (up to kv_len[b]), so the cached rows below kv_len[b] must hold finite values.  If the device finds n_q(b) > kv_len[b]
+ * (the caller did not append first), only the first
  * kv_len[b] query rows of that sequence are computed and FLUX_DEV_BAD_LENGTH is raised. */
 int flux_attn_prefill(flux_ctx* ctx, const flux_attn_cfg* cfg, const void* q, const int32_t* cu_q,
                       int max_q_len, int max_kv_len, const flux_kv_cache* cache,
@@ -181,7 +188,7 @@ int flux_attn_prefill_blocksparse(flux_ctx* ctx, const flux_attn_cfg* cfg, const
  * max_q_len bounds the prompt lengths (host); a prompt found longer on the device is scored up to the bound, rounded
  * up to whole blocks, and FLUX_DEV_BAD_LENGTH is raised.  The scores of as many heads at a time as fit go through the
  * workspace (with r = ceil(max_q_len / 2048), one head takes 32 KB * r * (r + 1), and 64 KB * r are used at least; a smaller
- * workspace is valid and slower).
+ * workspace is valid and slower; so is a bound far above the lengths, which counts here as if the prompts were as long).
  * The masses are computed in fp32 from exact bf16 products: near a tie between the threshold and a partial sum
  * of masses the selection can differ from one made in higher precision. */
 int flux_xa_select(flux_ctx* ctx, const flux_attn_cfg* cfg, const void* q, const int32_t* cu_q, int max_q_len,
@@ -194,7 +201,7 @@ int flux_xa_select(flux_ctx* ctx, const flux_attn_cfg* cfg, const void* q, const
  * [kv_len[b]-window, kv_len[b]) and never touches the rest (App. B.3).
  * max_kv_len: host upper bound on the number of keys any sequence of this call ATTENDS TO; the
  * largest kv_len[b] (or the capacity) is always valid.  The split of the work over the chip is taken
- * on the device from the lengths and mode bytes found there, so a loose bound costs only idle
+ * on the device from the lengths and mode bytes found there, so a loose bound costs idle
  * workgroups and a ragged batch is spread as evenly as a uniform one; the bound limits the launch
  * and the workspace (and a call of few lists bounded by 4352 keys or less is done in one launch instead of two, with its
  * sums in another order).  A caller that knows every sequence of this layer is SA may pass
@@ -205,9 +212,8 @@ int flux_attn_decode(flux_ctx* ctx, const flux_attn_cfg* cfg, const void* q, int
                      const flux_kv_cache* cache, const uint8_t* mode, void* out, void* stream);
 
 /* One whole decode step of a layer (Sec. 3.3, the decode path; App. B.3): the same result and the same cache
- * contents as flux_kv_append of one row per sequence followed by flux_attn_decode, bit for bit, in two launches
- * instead of three (for a sparse layer, whose kernels run for some tens of microseconds, the append launch is a
- * tenth of the step).
+ * contents as flux_kv_append of one row per sequence followed by flux_attn_decode, bit for bit, in one launch fewer
+ * (for a sparse layer, whose kernels run for some tens of microseconds, the append launch is a tenth of the step).
  *   k_new, v_new: dev bf16 [batch, n_kv_heads, head_dim], 16-byte aligned: the row sequence b appends at position
  *                 kv_len[b] (before the call).  A sequence whose cache is full drops its row, raises
  *                 FLUX_DEV_KV_OVERFLOW and attends to what is cached, as the pair of calls would.
@@ -215,7 +221,8 @@ int flux_attn_decode(flux_ctx* ctx, const flux_attn_cfg* cfg, const void* q, int
  *   cache:        a full cache (not a ring); kv_len[b] is read by every workgroup and moved on at the end of the
  *                 call (kv_len[b] += 1, cut at the capacity).
  * Other arguments as flux_attn_decode.  The workgroup that owns the end of a sequence's key list stores the new row;
- * workgroups that attend to it read it from k_new / v_new; the merge kernel moves the lengths on. */
+ * workgroups that attend to it read it from k_new / v_new; the merge kernel moves the lengths on (in calls of one launch
+ * the last workgroup that has read them). */
 int flux_attn_decode_append(flux_ctx* ctx, const flux_attn_cfg* cfg, const void* q, const void* k_new, const void* v_new,
                             int max_kv_len, const flux_kv_cache* cache, const uint8_t* mode, void* out, void* stream);
 
@@ -232,7 +239,8 @@ int flux_attn_decode_append(flux_ctx* ctx, const flux_attn_cfg* cfg, const void*
  * min(1024 + pairs, pairs * ceil(max_kv_len / 256)) * min(group, 16) * (head_dim + 2) * 4 bytes with
  * pairs = batch * n_kv_heads * ceil(group / 16), group = n_q_heads / n_kv_heads (2.3 MB for batch 8, 32/8
  * heads of 128 at any length).  All calls on one GPU share that GPU's array: calls that overlap on one GPU
- * (two streams, two threads) race and must be ordered by the caller.  Nothing needs clearing between calls. */
+ * (two streams, two threads) race and must be ordered by the caller (they spoil each other's results, not those of later
+ * calls).  Nothing needs clearing between calls. */
 #define FLUX_STATIC_SCRATCH_BYTES ((size_t)16 * 1024 * 1024 + 256)
 int flux_attn_decode_static(const flux_attn_cfg* cfg, const void* q, int max_kv_len, const flux_kv_cache* cache,
                             const uint8_t* mode, void* out, uint32_t* status, void* stream);

@@ -1024,7 +1024,7 @@ hipError_t launch_prefill(const Ctx& c, const flux_attn_cfg& cfg, const void* q,
   // of a 256-row tile's blocks are cut by the window's start and by the diagonal), under 1 % at 32768 and nothing at
   // 65536; short prompts lose 4-25 % (fewer, longer workgroups).  With the rows of all heads of a group in a tile (64
   // tokens x 4 heads) an SA launch at 32768 tokens is another 2 % faster, FA launches as they were.  Hence the bound on
-  // the longest prompt of the launch, which is all the host knows.  The results are the same bit for bit.  The
+  // the longest prompt of the launch, which is all the host knows.  The results are those of the unsplit four-wave shape bit for bit.  The
   // block-sparse form keeps four waves (its scan handles three query blocks per tile).
   // A chunk of half that length of a prompt that long (chunked prefill: every workgroup walks many blocks) gains too:
   // FA +1-2 %, SA +0-1.5 % for 16384-row chunks behind 16384 to 114688 cached positions.

@@ -78,7 +78,7 @@ __device__ __forceinline__ int visible_len(int n, int md, int sink_lim, int win_
   return sparse ? s_end + (n - tail_start) : n;
 }
 
-constexpr int kResidentUnits = 768;             // workgroups the chip holds at once (three per CU at this register count)
+constexpr int kResidentUnits = 768;             // workgroups the chip holds at once: three per CU (at head dimension 64 four would fit; the round is the same)
 constexpr int kLongCall = 32768;                // 128-key pieces of all pairs from which a round of two workgroups per CU is no longer better
 
 // Length and mode of sequence b under the clamp: a length the host could not see (negative, or past the

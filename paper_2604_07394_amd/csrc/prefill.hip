@@ -1022,10 +1022,11 @@ hipError_t launch_prefill(const Ctx& c, const flux_attn_cfg& cfg, const void* q,
   // every K/V tile, so that each wave issues half the tile transfers per block.  Measured with 256 rows of one head
   // against the four-wave shape: FA launches gain 1-3 % from 16384 tokens up; SA launches lose 4 % at 16384 tokens (more
   // of a 256-row tile's blocks are cut by the window's start and by the diagonal), under 1 % at 32768 and nothing at
-  // 65536; short prompts lose 4-25 % (fewer, longer workgroups).  With the rows of all heads of a group in a tile (64
-  // tokens x 4 heads) an SA launch at 32768 tokens is another 2 % faster, FA launches as they were.  Hence the bound on
-  // the longest prompt of the launch, which is all the host knows.  The results are those of the unsplit four-wave shape bit for bit.  The
-  // block-sparse form keeps four waves (its scan handles three query blocks per tile).
+  // 65536; short prompts lose 4-25 % (fewer, longer workgroups).  The rows of two heads of a
+  // group in a tile gain 1 % on SA launches, those of all heads (64 tokens x 4 heads) no more than the runs differ beyond
+  // that.  Hence the bound on the longest prompt of the launch, which is all the host knows.  The results are those of the
+  // unsplit four-wave shape bit for bit.  The block-sparse form keeps four waves (its scan handles three query blocks per
+  // tile).
   // A chunk of half that length of a prompt that long (chunked prefill: every workgroup walks many blocks) gains too:
   // FA +1-2 %, SA +0-1.5 % for 16384-row chunks behind 16384 to 114688 cached positions.
   const bool wide = !bm && cfg.head_dim == 128 &&

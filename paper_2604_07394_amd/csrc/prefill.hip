@@ -106,8 +106,9 @@ constexpr int kPlanTiles = 512;                 // batches of at least so many t
                                                 // one is resident at once, and the plan only delays it (us without / with
                                                 // it: 8 x 100 tokens 7.65 / 9.1, 4 x 64 at 8/2 heads of 64 4.7 / 5.0)
 constexpr int kSplitUnits = 1024;               // units a launch that splits may have beyond one per tile
-constexpr int kSplitFewTiles = 448;             // merges of at most so many tiles give a row to every thread
-constexpr int kSplitMaxTiles = 2048;            // batches of at most so many tiles, counted with the host's bounds, may split
+constexpr int kSplitFewTiles = 448;             // merges of at most so many tiles give a row to every thread; batches of at most so
+                                                // many by the host's bounds may split from 40 key blocks on
+constexpr int kSplitMaxTiles = 2048;            // ... and of at most so many from 128 on
 
 // Whether it pays to share out the keys of so many tiles, the longest of which walks so many key blocks: what the idle
 // part of the chip can take of the walk has to be worth the plan, the partial results and the second launch.  us whole /
@@ -1053,15 +1054,15 @@ hipError_t launch_prefill(const Ctx& c, const flux_attn_cfg& cfg, const void* q,
   // 60000 and 3000 1258 -> 406.  Whether they are is decided on the device (split_pays); a launch that may split but does
   // not (a layer with a short sparse window, say) pays for the plan and the second launch all the same, 0.5 to 3 us.  So
   // the host lets only those that its bounds say may gain: few tiles for the length of the lists, or a batch (whose bounds
-  // count tiles that short sequences do not have) with contexts long enough (8192 positions) that one uneven sequence
-  // costs more than that.
+  // count tiles that short sequences do not have) with contexts long enough that one uneven sequence costs more than that:
+  // 512, 40 and 30 tokens behind 5000 to 5800 123 -> 66, 4 x 256 equal ones behind 2300 50 -> 53.
   const long long packed = ((long long)max_q_len * a.group + BM - 1) / BM;    // tiles of a pair whose rows come from all heads
   const long long tiles = n_pairs * packed, blocks = ((long long)max_kv_len + 63) / 64;
   const long long unit_bytes = (long long)BM * (cfg.head_dim + 2) * 4, info_bytes = ((tiles + 1) * 16 + 255) / 256 * 256;
   const long long fit = ((long long)c.partials_bytes - info_bytes) / unit_bytes - tiles - 8 * cache.batch;   // units beyond one per tile
   const bool split = !bm && !wide && cache.batch <= 64 && max_kv_len > max_q_len && blocks > kMinSplitBlocks &&
                      ((tiles <= 768 && split_pays((int)tiles, (int)blocks, cfg.head_dim == 64 ? kResident64 : kResident128)) ||
-                      (cache.batch > 1 && tiles <= kSplitMaxTiles && blocks >= 128)) &&
+                      (cache.batch > 1 && ((tiles <= kSplitFewTiles && blocks >= 40) || (tiles <= kSplitMaxTiles && blocks >= 128)))) &&
                      fit >= 64 && (tiles + 8) * blocks < 0x7FFFFFFFll;
   const long long whole = n_pairs * a.group * ((max_q_len + 127ll) / 128);    // tiles of one head each
   const bool plan = split || (!bm && cache.batch > 1 && cache.batch <= 64 && (wide || whole >= kPlanTiles));

@@ -35,6 +35,7 @@ def ctxs(F):
     ([2113], [33], [FA], 7, 1, 128, 16, 500, 1),            # 231 rows: a tile and a ragged one, a group that divides neither
     ([1024, 1025], [31, 32], [FA, FA], 1, 1, 64, 16, 500, 1),   # 17 blocks: the shortest list that splits; group of one
     ([1500, 40, 5000, 0], [130, 40, 64, 1], [FA, FA, SA, FA], 8, 2, 64, 70, 2100, 1),   # ragged, split and whole tiles mixed
+    ([3000, 3500, 2800], [512, 40, 30], [FA, FA, FA], 32, 8, 128, 16, 500, 1),   # 384 tiles by the bounds, 152 in fact
     ([4000, 2500], [17, 200], [SA, FA], 20, 1, 128, 64, 2048, 64),   # more rows of a token than columns of an MFMA, block rule
     ([1800, 1700, 1600], [5, 0, 300], [SA, SA, FA], 6, 3, 128, 0, 1200, 1),   # no new tokens in one; KV heads that do not divide 8
     ([2000] * 3 + [0] * 20, [3] * 3 + [50] * 20, [FA, SA] * 11 + [FA], 4, 2, 64, 5, 1300, 16),

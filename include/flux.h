@@ -203,8 +203,7 @@ int flux_xa_select(flux_ctx* ctx, const flux_attn_cfg* cfg, const void* q, const
  * largest kv_len[b] (or the capacity) is always valid.  The split of the work over the chip is taken
  * on the device from the lengths and mode bytes found there, so a loose bound costs idle
  * workgroups and a ragged batch is spread as evenly as a uniform one; the bound limits the launch
- * and the workspace (and a call of few lists bounded by 4352 keys or less is done in one launch instead of two, with its
- * sums in another order).  A caller that knows every sequence of this layer is SA may pass
+ * and the workspace.  One launch.  A caller that knows every sequence of this layer is SA may pass
  * min(max kv_len, n_sink + window) (both rounded up to multiples of sa_block when that is set).
  * A sequence that attends to more keys than the bound is cut at the bound (its oldest visible
  * keys are kept) and FLUX_DEV_BAD_LENGTH is raised. */
@@ -212,7 +211,7 @@ int flux_attn_decode(flux_ctx* ctx, const flux_attn_cfg* cfg, const void* q, int
                      const flux_kv_cache* cache, const uint8_t* mode, void* out, void* stream);
 
 /* One whole decode step of a layer (Sec. 3.3, the decode path; App. B.3): the same result and the same cache
- * contents as flux_kv_append of one row per sequence followed by flux_attn_decode, bit for bit, in one launch fewer
+ * contents as flux_kv_append of one row per sequence followed by flux_attn_decode, bit for bit, in one launch instead of two
  * (for a sparse layer, whose kernels run for some tens of microseconds, the append launch is a tenth of the step).
  *   k_new, v_new: dev bf16 [batch, n_kv_heads, head_dim], 16-byte aligned: the row sequence b appends at position
  *                 kv_len[b] (before the call).  A sequence whose cache is full drops its row, raises
@@ -220,9 +219,8 @@ int flux_attn_decode(flux_ctx* ctx, const flux_attn_cfg* cfg, const void* q, int
  *   max_kv_len:   >= 1; bound on the keys any sequence attends to AFTER the append (see flux_attn_decode).
  *   cache:        a full cache (not a ring); kv_len[b] is read by every workgroup and moved on at the end of the
  *                 call (kv_len[b] += 1, cut at the capacity).
- * Other arguments as flux_attn_decode.  The workgroup that owns the end of a sequence's key list stores the new row;
- * workgroups that attend to it read it from k_new / v_new; the merge kernel moves the lengths on (in calls of one launch
- * the last workgroup that has read them). */
+ * Other arguments as flux_attn_decode.  The workgroup with the beginning of a sequence's key list stores the new row;
+ * workgroups that attend to it read it from k_new / v_new; the last workgroup to have read the lengths moves them on. */
 int flux_attn_decode_append(flux_ctx* ctx, const flux_attn_cfg* cfg, const void* q, const void* k_new, const void* v_new,
                             int max_kv_len, const flux_kv_cache* cache, const uint8_t* mode, void* out, void* stream);
 
@@ -231,8 +229,8 @@ int flux_attn_decode_append(flux_ctx* ctx, const flux_attn_cfg* cfg, const void*
  * call inside.  The split-K partial results go to a static device array of FLUX_STATIC_SCRATCH_BYTES that
  * every GPU the library runs on holds until the process ends; the call works on the CURRENT device, whose
  * copy of the array is looked up once (at flux_create on that device, else at the first call).
- * Same arguments and results (bit for bit) as flux_attn_decode (a call of few short lists, which flux_attn_decode
- * merges in one launch on arrival counters of its context, takes two here: the array holds no state between calls), plus
+ * Same arguments and results (bit for bit) as flux_attn_decode (which merges in the launch that streams the keys, on arrival
+ * counters of its context; here that takes a second launch: the array holds no state between calls), plus
  *   status: dev uint32 (4-byte aligned), caller-owned, or NULL.  The FLUX_DEV_* bits of this call are OR-ed
  *           into it (sticky; the caller reads and clears it); with NULL they go to a word nobody reads.
  * A shape whose partials exceed the array gives FLUX_EWORKSPACE: the partials take

@@ -3,17 +3,15 @@
 //
 // Decode is bound by reading the K and V rows of the cache once from HBM.  The work of one
 // (sequence, KV head) pair is the VISIBLE key list (FA: all positions; SA: the sinks followed by the
-// window tail, so the hidden middle of the cache is never addressed), taken in blocks of 128 keys that
-// go round the pair's units.  One 256-thread workgroup is one unit and serves all query heads of the GQA
+// window tail, so the hidden middle of the cache is never addressed) in blocks of 32 keys.  The lists of all pairs
+// are laid end to end, and every workgroup takes the same number of blocks of that one long list, wherever it begins
+// and ends: a run of blocks of one pair is a PART, and a workgroup whose range crosses from one pair into the next works
+// off its parts one after the other.  One 256-thread workgroup serves all query heads of the GQA
 // group at once, so every K/V row is fetched exactly once per step.
 //
-// The split is taken ON THE DEVICE from the lengths and mode bytes the call finds there: the chunk
-// size (the keys one unit takes) is the one that cuts the visible keys of the whole batch into about
-// kTargetUnits workgroups, a pair of nv visible keys gets ceil(nv / chunk) units, and workgroup u finds
-// its (sequence, KV head, unit of the pair) by a prefix sum over the batch.  Every
-// workgroup with work therefore sits at the front of the grid whatever the mix of lengths and
-// modes in the batch, and a ragged batch fills the chip like a uniform one (a grid shaped by the
-// longest sequence leaves most workgroups of the short ones empty and the rest badly spread).
+// The range is found ON THE DEVICE from the lengths and mode bytes the call finds there (a prefix sum over the batch), so
+// neither the mix of lengths and modes in the batch nor the host's bounds show in how evenly the chip is loaded (see
+// kDecodeWgs for why it is cut into equal ranges).
 //
 // Per wave, 32 keys at a time:
 //   S^T[key][q]  = K[key][:] . Q[q][:]       4 (D=128) MFMA 16x16x32 bf16 per 16 keys; the A operand
@@ -25,14 +23,18 @@
 //                                            V operand needs keys along the lane's registers, so V
 //                                            rows are staged in wave-private LDS and read back with
 //                                            the transposing LDS read
-// The four waves keep private (m, l, O) and are merged through LDS at the end; the unit's
-// unnormalised result goes to the workspace and a second small kernel merges the units of a pair in a fixed
-// order (deterministic, no float atomics).
+// The four waves keep private (m, l, O) and are merged through LDS at the end of a part.  A pair that lies in one workgroup's
+// range is done then; otherwise the part's unnormalised rows go to the workspace, and the part that arrives last at its
+// pair (an arrival counter) merges the pair's parts in a fixed order (deterministic, no float atomics).  Without arrival
+// counters (the static scratch) a second small kernel does, with the same sums in the same order.
+#include <type_traits>
+#include <utility>
+
 #include "flux_internal.h"
 
 namespace flux {
 
-// What both kernels read to agree on the split.
+// What the cut is taken from.
 struct SplitArgs {
   const int32_t* kv_len;
   const uint8_t* mode;
@@ -42,6 +44,8 @@ struct SplitArgs {
   int max_keys;           // the host's bound on the keys any sequence attends to
   int pps;                // (KV head, query block) pairs per sequence = hkv * qblocks
   int bump;               // 1: the call also appends one row per sequence, so every list is one key longer than kv_len says
+  int block_shift;        // lists are cut into blocks of 2^block_shift keys
+  int aligned_shift;      // few blocks: one workgroup per 4 or 8 of a list while that takes at most 2^aligned_shift (see Cut)
 };
 
 struct DecodeArgs {
@@ -52,16 +56,16 @@ struct DecodeArgs {
   SplitArgs sp;
   int hq, hkv, group;     // group = hq / hkv
   int qblocks;            // ceil(group / 16)
-  int rpu;                // partial rows per unit = min(group, 16)
+  int rpu;                // rows per part = min(group, 16)
   float scale_log2;       // softmax scale * log2(e)
-  float* partials;        // per pair [rpu, chunks of the pair, D + 2], pairs in unit order
-  int* table;             // [batch][2]: first unit and chunks per pair of every sequence, for the merge kernel
+  float* part_o;          // unnormalised rows of the parts of unfinished pairs, [place][rpu][D] (see part_place)
+  float* part_ml;         // their reference (score units) and weight sum, [place][rpu][2]
+  int* table;             // two launches: [batch][2]: first block and blocks per pair of every sequence, for the merge kernel
   uint32_t* status;       // sticky device status word
   // the fused decode step only: the row each sequence appends at position kv_len[b], [B, Hkv, D]
   const __bf16* k_new;
   const __bf16* v_new;
-  // calls merged in place only (see SMALL below)
-  uint32_t* arrived;      // [0]: workgroups that have read the lengths; [1 + pair]: units of a pair that have left their rows
+  uint32_t* arrived;      // calls merged in place: the counters (see kDecodeCounters); all zero between calls
   int32_t* kv_len_rw;
   void* out;
   int out_fp32;
@@ -77,9 +81,6 @@ __device__ __forceinline__ int visible_len(int n, int md, int sink_lim, int win_
   sparse = ((md & 1) == 0) && (tail_start > s_end);          // bit 0 of md: 1 = FA
   return sparse ? s_end + (n - tail_start) : n;
 }
-
-constexpr int kResidentUnits = 768;             // workgroups the chip holds at once: three per CU (at head dimension 64 four would fit; the round is the same)
-constexpr int kLongCall = 32768;                // 128-key pieces of all pairs from which a round of two workgroups per CU is no longer better
 
 // Length and mode of sequence b under the clamp: a length the host could not see (negative, or past the
 // capacity of a full cache) is cut and reported through `bad`.
@@ -108,331 +109,378 @@ __device__ __forceinline__ int seq_visible(const SplitArgs& s, int len, int md, 
   return nv;
 }
 
-// The split of one call, as every wave of both kernels computes it from the lengths and mode bytes.
-struct Split {
-  int chunk;        // keys per unit: the visible keys of all pairs, counted in 128-key pieces, divided over
-                    // kTargetUnits (at least kMinChunk); the units then number at most kTargetUnits + batch * pps
-  int b;            // the sequence found (-1: the unit lies past the last one)
-  int first_unit;   // first unit of that sequence
-  int nc;           // its chunks per (KV head, query block) pair
-  int len, md;      // its clamped length and mode
-  bool any_bad;     // this lane saw a clamp trip
-  unsigned long long empty;   // (calls merged in place) sequences without keys
+constexpr int kResidentUnits = 256;             // workgroups that share long lists out: one per CU
+static_assert(kResidentUnits == 1 << kDecodeWgsShift, "every CU takes the same");
+
+// ---- the cut.  Blocks of all pairs, sequence by sequence and pair by pair, numbered from 0.  While they are few (one per
+// wave of two workgroups per CU) every list is rounded up to a multiple of 4 and a workgroup takes 4, so that none
+// crosses from one pair into the next; 8 where every list has no more than that (nothing to merge) or more than 64 (half
+// the rows to merge); otherwise the lists lie end to end as they are, and workgroup u takes
+// [range_begin(u), range_begin(u + 1)).
+struct Cut {
+  int total;        // blocks
+  int align;        // log2 of the blocks that a workgroup takes of a list; 0: an equal share of all lists
 };
+__device__ __forceinline__ int cut_wgs(const SplitArgs& s, Cut c) { return c.align > 0 ? c.total >> c.align : 1 << kDecodeWgsShift; }
+__device__ __forceinline__ int range_begin(const SplitArgs& s, Cut c, int u) {
+  return c.align > 0 ? u << c.align : (int)(((unsigned long long)(unsigned)u * (unsigned)c.total) >> kDecodeWgsShift);
+}
+// the workgroup whose range holds block x
+__device__ __forceinline__ int range_of(const SplitArgs& s, Cut c, int x) {
+  if (c.align > 0) return x >> c.align;
+  int u = min((int)((float)x * ((float)(1 << kDecodeWgsShift) / (float)c.total)), (1 << kDecodeWgsShift) - 1);
+  while (range_begin(s, c, u) > x) --u;
+  while (range_begin(s, c, u + 1) <= x) ++u;
+  return u;
+}
+// Where the rows of part `i` of a pair go whose first part lies in the range of workgroup `first`: a range holds at most one
+// part that its pair goes on behind and one that its pair began before.
+__device__ __forceinline__ int part_place(int first, int i) { return i == 0 ? 2 * first + 1 : 2 * (first + i); }
 
-// chunks that a list of `pieces` takes at `c` pieces each
-__device__ __forceinline__ int chunks_of(int pieces, int c, float inv_c) { return pieces > 0 ? div_small(pieces - 1, c, inv_c) + 1 : 0; }
+__device__ __forceinline__ int blocks_of(const SplitArgs& s, int nv) { return (nv >> s.block_shift) + ((nv & ((1 << s.block_shift) - 1)) != 0 ? 1 : 0); }
 
-// Find the sequence whose units contain `unit`.
 // Lane i of the wave looks after sequences i, i + 64, ...; a batch of up to 64 takes one load per lane.
-__device__ __forceinline__ Split find_split(const SplitArgs& s, int lane, int unit) {
-  Split r;
-  r.b = -1;
-  r.first_unit = r.nc = r.len = 0;
-  r.md = 1;
-  r.any_bad = false;
-  r.empty = 0;
-  bool sparse;
-  int s_end, tail_start;
-  int len0 = 0, md0 = 1, pc0 = 0;                          // block 0 stays in registers for the second pass
-  int pieces = 0;
-  for (int b0 = 0; b0 < s.batch; b0 += 64) {
-    int len = 0, md = 1, nv = 0;
-    if (b0 + lane < s.batch) {
-      bool bad;
-      load_seq(s, b0 + lane, len, md, bad);
-      nv = seq_visible(s, len, md, bad, sparse, s_end, tail_start);
-      r.any_bad |= bad;
-    }
-    const int pc = (nv + 127) >> 7;
-    if (b0 == 0) {
-      len0 = len;
-      md0 = md;
-      pc0 = pc;
-    }
-    pieces += __builtin_amdgcn_readlane(wave_inclusive_sum(pc), 63);
-  }
-  const long long total = (long long)pieces * s.pps;
-  const long long c128 = (total + (kTargetUnits - 1)) / kTargetUnits;
-  int c = c128 < kMinChunk / 128 ? kMinChunk / 128 : (int)c128;
-  // If a larger chunk cuts the batch into one nearly full round of workgroups, it is taken: a single round of equal
-  // workgroups pays the start and the merge of a workgroup once instead of twice.  Uniform batches do; a ragged one usually
-  // spills a few units into a second round, and a short list (a sparse layer) leaves much of the round empty: both keep
-  // the smaller chunk.  A round of 512 (two per CU) is better than one of 768 (all that fit) while the lists are short
-  // (1 x 32768 keys 29.6 against 33.1 us, 1 x 131072 84.7 / 89.3, 8 x 32768 168.7 / 169.3; 8 x 131072 665 / 656).
-  if (s.batch <= 64) {
-    auto round_of = [&](int slots, int least) __attribute__((always_inline)) {
-      const int big = max((int)((float)total * (1.0f / (float)slots)) + 1, kMinChunk / 128);
-      const int units = __builtin_amdgcn_readlane(wave_inclusive_sum(s.pps * chunks_of(pc0, big, 1.0f / (float)big)), 63);
-      return units <= slots && units > least ? big : 0;
-    };
-    const int two = total < kLongCall ? round_of(512, 512 - 512 / 20) : 0;
-    const int big = two > 0 ? two : round_of(kResidentUnits, kResidentUnits - kResidentUnits / 10);
-    if (big > 0) c = big;
-  }
-  r.chunk = 128 * c;
-  const float inv_c = 1.0f / (float)c;
+struct Lanes {
+  int len, md, nb;  // of this lane's sequence among the first 64
+  int incl;         // blocks up to and including it
+  bool bad;         // this lane saw a clamp trip
+};
+__device__ __forceinline__ int padded(Cut c, int nb) { return ((nb + (1 << c.align) - 1) >> c.align) << c.align; }
 
-  for (int b0 = 0, base = 0; b0 < s.batch; b0 += 64) {
-    int len = len0, md = md0, pc = pc0;
-    if (b0 > 0) {
-      len = 0, md = 1, pc = 0;
-      if (b0 + lane < s.batch) {
-        bool bad;
+__device__ __forceinline__ Cut find_cut(const SplitArgs& s, int lane, Lanes& r) {
+  r.bad = false;
+  Cut c = {0, 2};
+  for (;;) {                                                // (once with the lists rounded up, and again without if that is too many)
+    int total = 0;
+    for (int b0 = 0; b0 < s.batch; b0 += 64) {
+      int len = 0, md = 1, nb = 0;
+      if (b0 == 0 && c.align == 0) {
+        len = r.len, md = r.md, nb = r.nb;
+      } else if (b0 + lane < s.batch) {
+        bool bad, sparse;
+        int s_end, tail_start;
         load_seq(s, b0 + lane, len, md, bad);
-        pc = (seq_visible(s, len, md, bad, sparse, s_end, tail_start) + 127) >> 7;
+        nb = blocks_of(s, seq_visible(s, len, md, bad, sparse, s_end, tail_start));
+        r.bad |= bad;
       }
+      if (b0 == 0 && c.align > 0) c.align = s.batch <= 64 && __builtin_amdgcn_ballot_w64(nb > 8 && nb <= 64) == 0 ? 3 : 2;
+      const int incl = wave_inclusive_sum(s.pps * padded(c, nb));
+      if (b0 == 0) {
+        r.len = len;
+        r.md = md;
+        r.nb = nb;
+        r.incl = incl;
+      }
+      total += __builtin_amdgcn_readlane(incl, 63);
     }
-    const int nc = chunks_of(pc, c, inv_c);
-    const int incl = wave_inclusive_sum(s.pps * nc);        // units up to and including this lane's sequence
-    const int total_b = __builtin_amdgcn_readlane(incl, 63);
-    if (unit < base + total_b) {                            // wave-uniform
-      const int sidx = __builtin_amdgcn_readfirstlane(__builtin_popcountll(__builtin_amdgcn_ballot_w64(base + incl <= unit)));
-      r.b = b0 + sidx;
-      r.first_unit = base + (sidx > 0 ? __builtin_amdgcn_readlane(incl, sidx - 1) : 0);
-      r.nc = __builtin_amdgcn_readlane(nc, sidx);
-      r.len = __builtin_amdgcn_readlane(len, sidx);
-      r.md = __builtin_amdgcn_readlane(md, sidx);
+    c.total = total;
+    if (c.align == 0 || total <= 1 << (s.aligned_shift + c.align)) return c;
+    c.align = 0;
+  }
+}
+
+// The sequence whose lists hold block x (x < total).
+struct Place {
+  int b, len, md;
+  int begin;        // first block of its first pair
+  int nb;           // blocks of a pair, as numbered
+};
+__device__ __forceinline__ Place find_place(const SplitArgs& s, Cut c, const Lanes& r, int lane, int x) {
+  Place p = {0, 0, 1, 0, 1};
+  int base = 0;
+  for (int b0 = 0; b0 < s.batch; b0 += 64) {
+    int len = r.len, md = r.md, nb = padded(c, r.nb), incl = r.incl;
+    if (b0 > 0) {
+      len = 0, md = 1, nb = 0;
+      if (b0 + lane < s.batch) {
+        bool bad, sparse;
+        int s_end, tail_start;
+        load_seq(s, b0 + lane, len, md, bad);
+        nb = padded(c, blocks_of(s, seq_visible(s, len, md, bad, sparse, s_end, tail_start)));
+      }
+      incl = wave_inclusive_sum(s.pps * nb);
+    }
+    const int end = base + __builtin_amdgcn_readlane(incl, 63);
+    if (x < end) {                                          // wave-uniform
+      const int i = __builtin_amdgcn_readfirstlane(__builtin_popcountll(__builtin_amdgcn_ballot_w64(base + incl <= x)));
+      p.b = b0 + i;
+      p.len = __builtin_amdgcn_readlane(len, i);
+      p.md = __builtin_amdgcn_readlane(md, i);
+      p.nb = __builtin_amdgcn_readlane(nb, i);
+      p.begin = base + __builtin_amdgcn_readlane(incl, i) - s.pps * p.nb;
       break;
     }
-    base += total_b;
+    base = end;
   }
-  return r;
+  return p;
+}
+// The next sequence behind p that has keys (there is one).
+__device__ __forceinline__ Place next_place(const SplitArgs& s, Cut c, const Lanes& r, int lane, Place p) {
+  const int begin = p.begin + s.pps * p.nb;
+  if (s.batch <= 64) return find_place(s, c, r, lane, begin);
+  for (int b = p.b + 1; b < s.batch; ++b) {
+    bool bad, sparse;
+    int len, md, s_end, tail_start;
+    load_seq(s, b, len, md, bad);
+    const int nb = __builtin_amdgcn_readfirstlane(padded(c, blocks_of(s, seq_visible(s, len, md, bad, sparse, s_end, tail_start))));
+    if (nb > 0) return Place{b, __builtin_amdgcn_readfirstlane(len), __builtin_amdgcn_readfirstlane(md), begin, nb};
+  }
+  return p;
 }
 
-// The split of a call merged in place: a lane per sequence, always the smallest chunk.
-__device__ __forceinline__ Split find_split_small(const SplitArgs& s, int lane, int unit) {
-  Split r;
-  bool sparse, bad = false;
-  int s_end, tail_start, len = 0, md = 1, nv = 0;
-  if (lane < s.batch) {
-    load_seq(s, lane, len, md, bad);
-    nv = seq_visible(s, len, md, bad, sparse, s_end, tail_start);
-  }
-  r.any_bad = bad;
-  r.empty = __builtin_amdgcn_ballot_w64(lane < s.batch && nv == 0);
-  r.chunk = kMinChunk;
-  const int nc = (nv + kMinChunk - 1) / kMinChunk;
-  const int incl = wave_inclusive_sum(s.pps * nc);
-  const int total = __builtin_amdgcn_readlane(incl, 63);
-  r.b = -1;
-  r.first_unit = r.nc = r.len = 0;
-  r.md = 1;
-  if (unit < total) {                                       // wave-uniform
-    r.b = __builtin_amdgcn_readfirstlane(__builtin_popcountll(__builtin_amdgcn_ballot_w64(incl <= unit)));
-    r.nc = __builtin_amdgcn_readlane(nc, r.b);
-    r.first_unit = __builtin_amdgcn_readlane(incl, r.b) - s.pps * r.nc;
-    r.len = __builtin_amdgcn_readlane(len, r.b);
-    r.md = __builtin_amdgcn_readlane(md, r.b);
-  }
-  return r;
-}
-
-// The split as a table, for the merge kernel: entry b = (first unit, chunks per pair) of sequence b.  One wave writes
-// it (lane i looks after sequences i, i + 64, ...), with the same arithmetic as find_split.
-__device__ __forceinline__ void write_split_table(const SplitArgs& s, int lane, int chunk, int* table) {
-  bool sparse, bad;
-  int s_end, tail_start;
+// The cut as a table, for the merge kernel: entry b = (first block, blocks per pair) of sequence b; behind them, align.
+__device__ __forceinline__ void write_cut_table(const SplitArgs& s, Cut c, int lane, int* table) {
   for (int b0 = 0, base = 0; b0 < s.batch; b0 += 64) {
-    int len = 0, md = 1, nv = 0;
+    int nb = 0;
     if (b0 + lane < s.batch) {
+      bool bad, sparse;
+      int len, md, s_end, tail_start;
       load_seq(s, b0 + lane, len, md, bad);
-      nv = seq_visible(s, len, md, bad, sparse, s_end, tail_start);
+      nb = padded(c, blocks_of(s, seq_visible(s, len, md, bad, sparse, s_end, tail_start)));
     }
-    const int nc = chunks_of((nv + 127) >> 7, chunk >> 7, 1.0f / (float)(chunk >> 7));
-    const int incl = wave_inclusive_sum(s.pps * nc);
+    const int incl = wave_inclusive_sum(s.pps * nb);
     if (b0 + lane < s.batch) {
-      table[2 * (b0 + lane)] = base + incl - s.pps * nc;
-      table[2 * (b0 + lane) + 1] = nc;
+      table[2 * (b0 + lane)] = base + incl - s.pps * nb;
+      table[2 * (b0 + lane) + 1] = nb;
     }
     base += __builtin_amdgcn_readlane(incl, 63);
   }
+  if (lane == 0) table[2 * s.batch] = c.align;
 }
 
-// Merge every STEP-th chunk, from `first` on, of one column of a head's rows [chunk][D + 2]: num = sum_c w_c O_c[d],
-// den = sum_c w_c l_c with w_c = exp(m_c - m), m = max m_c.  N chunks at a time, so that their loads are in flight
-// together.  DEV: the rows were written by workgroups of this launch (device-scope reads).
+// ---- rows that pass between workgroups of one launch, which may sit on different XCDs: written and read at device
+// scope (past the L2s, which are not coherent with each other).  `base` is wave-uniform, `at` a byte offset.
+__device__ __forceinline__ void store16_dev(float* base, int at, f32x4 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), __builtin_amdgcn_make_buffer_rsrc(base, 0, -1, 0x00027000), at, 0, 16 /*sc1*/);
+}
+__device__ __forceinline__ f32x4 load16_dev(const float* base, int at) {
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, -1, 0x00027000), at, 0, 16));
+}
+template <bool DEV>
+__device__ __forceinline__ f32x2 load_ml(const float* p) {
+  if (!DEV) return *(const f32x2*)p;
+  return __builtin_bit_cast(f32x2, __hip_atomic_load((const unsigned long long*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
+// ---- the merge of a pair's parts: out = sum_c w_c O_c / sum_c w_c l_c, w_c = exp(m_c - max m).  A wave takes 64 / (D / 4)
+// heads at a time, D / 4 lanes each with four columns, and the parts in runs of 16: lane i of every 16 works out the weight
+// of part i, which the sum over the parts then takes from it.  The rows of a run are all asked for at once.
+template <int CTRL>
+__device__ __forceinline__ float row16(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float sum16(float x) {           // over the 16 lanes of a row, the same in all of them
+  x += row16<0x128>(x);                                     // row_ror:8, 4, 2, 1
+  x += row16<0x124>(x);
+  x += row16<0x122>(x);
+  return x + row16<0x121>(x);
+}
+__device__ __forceinline__ float max16(float x) {
+  x = fmaxf(x, row16<0x128>(x));
+  x = fmaxf(x, row16<0x124>(x));
+  x = fmaxf(x, row16<0x122>(x));
+  return fmaxf(x, row16<0x121>(x));
+}
+template <int... I>
+__device__ __forceinline__ void add_weighted(f32x4& num, float w, const f32x4 (&o)[16], std::integer_sequence<int, I...>) {
+  ((num += row16<0x150 + I>(w) * o[I]), ...);               // row_newbcast:I, the weight of part I
+}
 struct Merged {
-  float m, num, den;
+  float m, den;
+  f32x4 num;
 };
-template <int D, bool DEV, int STEP, int N>
-__device__ __forceinline__ Merged merge_rows(const float* base, int nc, float scale_log2, int d, int first) {
-  constexpr int RED = D + 2;
-  auto ld = [](const float* p) { return DEV ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p; };
-  Merged r = {-INFINITY, 0.f, 0.f};
-  for (int c0 = first; c0 < nc; c0 += N * STEP) {
-    float mc[N], lc[N], oc[N];
+// Lane l's columns of head `head0` + l / (D / 4), over the runs first_run, first_run + step, ...
+template <int D, bool DEV>
+__device__ __forceinline__ Merged merge_runs(const float* part_o, const float* part_ml, int rpu, int first, int parts, int nq, float scale_log2, int head0, int first_run, int step, int l) {
+  constexpr int TPR = D / 4;
+  const int row = min(head0 + l / TPR, nq - 1), d = 4 * (l % TPR), j = l & 15;
+  Merged r = {-INFINITY, 0.f, f32x4{0.f, 0.f, 0.f, 0.f}};
+  for (int c0 = 16 * first_run; c0 < parts; c0 += 16 * step) {
+    const f32x2 ml = load_ml<DEV>(part_ml + 2 * (part_place(first, min(c0 + j, parts - 1)) * rpu + row));
+    f32x4 o[16];
 #pragma unroll
-    for (int u = 0; u < N; ++u) {
-      const float* row = base + (int64_t)min(c0 + u * STEP, nc - 1) * RED;  // (the last chunk again where there are fewer)
-      mc[u] = ld(row + D);
-      lc[u] = ld(row + D + 1);
-      oc[u] = ld(row + d);
+    for (int i = 0; i < 16; ++i) {
+      const int at = (part_place(first, min(c0 + i, parts - 1)) * rpu + row) * D + d;   // (the last part again where there are fewer)
+      if (DEV) o[i] = load16_dev(part_o, at * 4);
+      else o[i] = *(const f32x4*)(part_o + at);
     }
-    float m_new = r.m;
-#pragma unroll
-    for (int u = 0; u < N; ++u) {
-      mc[u] = c0 + u * STEP < nc ? mc[u] : -INFINITY;
-      m_new = fmaxf(m_new, mc[u]);
-    }
-    const float al = fast_exp2((r.m - m_new) * scale_log2);                 // 0 for the first chunks (each holds a key)
+    const float mj = c0 + j < parts ? ml[0] : -INFINITY;
+    const float m_new = fmaxf(r.m, max16(mj));
+    const float al = fast_exp2((r.m - m_new) * scale_log2); // 0 for the first run (every part holds a key)
+    const float w = fast_exp2((mj - m_new) * scale_log2);
     r.num *= al;
-    r.den *= al;
+    r.den = r.den * al + sum16(w * ml[1]);
     r.m = m_new;
-#pragma unroll
-    for (int u = 0; u < N; ++u) {
-      const float w = fast_exp2((mc[u] - m_new) * scale_log2);
-      r.num += w * oc[u];
-      r.den += w * lc[u];
-    }
+    add_weighted(r.num, w, o, std::make_integer_sequence<int, 16>());
   }
   return r;
 }
+// All heads of one pair by a workgroup of four waves; `store` is given (head, column, four values).  Where the heads take one
+// or two waves and there are several runs, the other waves take every other run and all meet in LDS (Merged[4][64]).
+template <int D, bool DEV, class Store>
+__device__ __forceinline__ void merge_pair(const float* part_o, const float* part_ml, int rpu, int first, int parts, int nq, float scale_log2, char* lds, int w, int l, Store store) {
+  constexpr int TPR = D / 4, HPW = 64 / TPR;
+  auto finish = [&](int head0, const Merged& r) __attribute__((always_inline)) {
+    const int qi = head0 + l / TPR;
+    if (qi < nq) store(qi, 4 * (l % TPR), f32x4{r.num[0] / r.den, r.num[1] / r.den, r.num[2] / r.den, r.num[3] / r.den});
+  };
+  const int groups = (nq + HPW - 1) / HPW;                  // of heads that a wave takes at a time
+  const int split = groups > 2 || parts <= 16 ? 1 : 4 / groups;
+  for (int i = w; i < groups * split; i += 4) {
+    const int head0 = (split == 1 ? i : i % groups) * HPW;
+    const Merged r = merge_runs<D, DEV>(part_o, part_ml, rpu, first, parts, nq, scale_log2, head0, split == 1 ? 0 : i / groups, split, l);
+    if (split == 1) finish(head0, r);
+    else ((Merged*)lds)[64 * i + l] = r;
+  }
+  if (split == 1) return;                                   // uniform for the workgroup
+  __syncthreads();
+  if (w >= groups) return;
+  float m = -INFINITY;
+  for (int i = 0; i < split; ++i) m = fmaxf(m, ((Merged*)lds)[64 * (w + i * groups) + l].m);
+  Merged t = {m, 0.f, f32x4{0.f, 0.f, 0.f, 0.f}};
+  for (int i = 0; i < split; ++i) {
+    const Merged r = ((Merged*)lds)[64 * (w + i * groups) + l];
+    const float wgt = fast_exp2((r.m - m) * scale_log2);    // exp2(-inf) = 0 for a wave without runs
+    t.num += wgt * r.num;
+    t.den += wgt * r.den;
+  }
+  finish(w * HPW, t);
+}
 
 // FUSED: the call is a whole decode step of the layer (Sec. 3.3): it also appends the row k_new / v_new of every
-// sequence at position kv_len[b].  The unit that owns the end of a list stores the row in the cache; the units that
-// attend to it take it from k_new / v_new, so no read waits for that store.  The lengths are moved on by the merge
-// kernel, after every workgroup of both kernels has read them.  Two launches instead of three.
+// sequence at position kv_len[b].  The workgroup with the first block of a list stores the row in the cache; the
+// workgroups that attend to it take it from k_new / v_new, so no read waits for that store.  The lengths are moved on by the
+// last workgroup to have read them.
 //
-// SMALL: a call of few short lists (see decode_small), which is bound by latencies and not by bytes: one launch instead
-// of two.  Eight waves per workgroup, so that each has one block of 32 keys and no second wait for memory; the unit that
-// arrives last at its pair merges the pair's rows.  The rows pass between workgroups that may sit on different XCDs:
-// they are written and read with device-scope accesses (past the L2s, which are not coherent with each other), and a
-// unit counts itself only after its own stores have been acknowledged.  ROWS: the same eight waves and chunks, but the rows
-// are left for the merge kernel, as in the two-launch form: for callers without arrival counters (the static scratch).
-// The merge takes the same sums in the same order, so the results are those of the one-launch form bit for bit.
-// Three workgroups per CU are asked for: left alone the compiler keeps the accumulators in a second register file (192
-// registers, two workgroups per CU) although 160 do: SA layer of 8 x 131072 32.6 -> 31.1 us, 32 ragged sequences of 513 to
-// 8400 keys at 28/4 heads 44.5 -> 39.7 us.  (Very long calls stream at the rate of the memory with two as well, up to 1 %
-// faster, but the host cannot tell them from short lists under a large bound, which lose 10 %: with a bound of 65536 the
-// 32 ragged sequences take 38.0 us, 41.9 with two; 8 x 131072 651.7 and 650.5.)
-template <int D, bool NT, bool FUSED, bool SMALL = false, bool ROWS = false>
-__global__ __launch_bounds__(SMALL ? 512 : 256, SMALL ? 2 : 3) void decode_splitk_kernel(DecodeArgs a) {
-  constexpr int W = SMALL ? 8 : 4;    // waves per workgroup
-  constexpr bool IN_PLACE = SMALL && !ROWS;   // the unit that arrives last merges its pair
+// IN_PLACE: the part that arrives last at its pair merges the pair.  Its rows pass between workgroups that may sit on
+// different XCDs: they are written and read with device-scope accesses, and a part counts itself only after its own
+// stores have been acknowledged.
+template <int D, bool NT, bool FUSED, bool IN_PLACE>
+__global__ __launch_bounds__(256, 2) void decode_splitk_kernel(DecodeArgs a) {
+  constexpr int W = 4;                // waves per workgroup
   constexpr int KC = D / 32;          // MFMA k-steps over the head dimension
   constexpr int DB = D / 16;          // 16-wide output blocks over the head dimension
   constexpr int VL = D / 16;          // 16-byte V loads per lane per 32-key block
   constexpr int CPR = D / 8;          // 16-byte chunks per row
   constexpr int VROW = D + 8;         // padded LDS row (elements)
-  constexpr int RED = D + 2;
+  constexpr int RED = D + 4;          // floats from one row of the merge buffer to the next
 
-  __shared__ __attribute__((aligned(16))) char smem[W * 32 * VROW * 2];
+  // V staging of the waves; at the end of a part the merge of the waves ([W][16][RED] floats and [W][16][2])
+  constexpr int STAGING = W * 32 * VROW * 2, RED_BYTES = W * 16 * (RED + 2) * 4;
+  __shared__ __attribute__((aligned(16))) char smem[STAGING > RED_BYTES ? STAGING : RED_BYTES];
+  __shared__ int last_of_pair;
 
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
   const int g = l >> 4, n = l & 15;
-  const int unit = blockIdx.x;
+  const int wg = blockIdx.x;
 
-  // ---- the split: chunk size from the whole batch, then the sequence whose units contain `unit`
-  const Split sp = SMALL ? find_split_small(a.sp, l, unit) : find_split(a.sp, l, unit);
-  if (unit == 0 && w == 0 && sp.any_bad) atomicOr(a.status, (uint32_t)FLUX_DEV_BAD_LENGTH);
-  // SMALL and FUSED: every workgroup counts itself once all its waves hold the lengths; the one that finds all others
-  // counted moves the lengths on, when it has nothing else to do (nobody reads them any more).
-  uint32_t order = 0;
-  if constexpr (SMALL && FUSED) {
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (tid == 0) order = __hip_atomic_fetch_add(a.arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  auto finish = [&]() __attribute__((always_inline)) {
-    if constexpr (SMALL && FUSED) {
-      if (w == 0 && __builtin_amdgcn_readfirstlane(order) == gridDim.x - 1) {
-        if (l < a.sp.batch) {
-          int len = a.kv_len_rw[l];
-          len = len < 0 ? 0 : (len > a.sp.capacity ? a.sp.capacity : len);
-          a.kv_len_rw[l] = len < a.sp.capacity ? len + 1 : len;
-        }
-        if (l == 0) a.arrived[0] = 0;                       // ready for the next call on this stream
-      }
-    }
+  // ---- the range of this workgroup
+  Lanes lanes;
+  const Cut cut = find_cut(a.sp, l, lanes);
+  if (wg == 0 && w == 0 && lanes.bad) atomicOr(a.status, (uint32_t)FLUX_DEV_BAD_LENGTH);
+  // FUSED: the workgroups count themselves, first on one of kDecodeGather words (a word takes some 10 ns per count), when
+  // all their waves hold the lengths; the one that completes the count moves the lengths on.  Called by one wave, in two
+  // steps: the answer to the first count is not waited for until there is nothing else to do.
+  uint32_t counted = 0;
+  auto count_in = [&]() __attribute__((always_inline)) {
+    if (l == 0) counted = __hip_atomic_fetch_add(a.arrived + kCounterStride * (1 + (wg & (kDecodeGather - 1))), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
-  // the last workgroup of the grid (idle unless the host's bound on the units is met exactly) leaves the split
-  // behind for the merge kernel, which then needs neither the lengths nor the scan
-  if (!IN_PLACE && unit == (int)gridDim.x - 1 && w == 0) write_split_table(a.sp, l, sp.chunk, a.table);
-  if (IN_PLACE && unit == (int)gridDim.x - 1) {             // sequences without keys have no units: their rows are zero
-    for (unsigned long long left = sp.empty; left != 0; left &= left - 1) {
-      const int64_t off = (int64_t)__builtin_ctzll(left) * a.hq * D;
-      for (int i = tid; i < a.hq * D; i += 64 * W) {
-        if (a.out_fp32) ((float*)a.out)[off + i] = 0.f;
-        else ((__bf16*)a.out)[off + i] = (__bf16)0.f;
+  auto count_out = [&]() __attribute__((always_inline)) {
+    const int x = wg & (kDecodeGather - 1), expected = ((int)gridDim.x - 1 - x) / kDecodeGather + 1;
+    const int words = min((int)gridDim.x, kDecodeGather);
+    if (__builtin_amdgcn_readfirstlane(counted) + 1 != (uint32_t)expected) return;
+    if (l == 0) {
+      a.arrived[kCounterStride * (1 + x)] = 0;              // ready for the next call on this stream
+      counted = __hip_atomic_fetch_add(a.arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (__builtin_amdgcn_readfirstlane(counted) + 1 != (uint32_t)words) return;
+    for (int i = l; i < a.sp.batch; i += 64) {
+      int len = a.kv_len_rw[i];
+      len = len < 0 ? 0 : (len > a.sp.capacity ? a.sp.capacity : len);
+      a.kv_len_rw[i] = len < a.sp.capacity ? len + 1 : len;
+    }
+    if (l == 0) a.arrived[0] = 0;
+  };
+  if (wg == (int)gridDim.x - 1) {
+    if constexpr (!IN_PLACE) {
+      // leaves the cut behind for the merge kernel, which then needs neither the lengths nor the scan
+      if (w == 0) write_cut_table(a.sp, cut, l, a.table);
+    } else if (a.sp.batch > 64 || __builtin_amdgcn_ballot_w64(l < a.sp.batch && lanes.nb == 0) != 0) {
+      // sequences without keys have no blocks: their rows are zero
+      for (int b0 = 0; b0 < a.sp.batch; b0 += 64) {
+        int len = 1, md;
+        bool bad;
+        if (b0 + l < a.sp.batch) load_seq(a.sp, b0 + l, len, md, bad);
+        for (unsigned long long left = __builtin_amdgcn_ballot_w64(b0 + l < a.sp.batch && (len == 0 || a.sp.max_keys == 0)); left != 0; left &= left - 1) {
+          const int64_t off = (int64_t)(b0 + __builtin_ctzll(left)) * a.hq * D;
+          for (int i = tid; i < a.hq * D; i += 64 * W) {
+            if (a.out_fp32) ((float*)a.out)[off + i] = 0.f;
+            else ((__bf16*)a.out)[off + i] = (__bf16)0.f;
+          }
+        }
       }
     }
   }
-  if (sp.b < 0) {                                           // past the last unit: uniform for the whole workgroup
-    finish();
+  if (wg >= cut_wgs(a.sp, cut) || cut.total == 0) {         // nothing to do: uniform for the whole workgroup
+    if constexpr (FUSED) {
+      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+      __syncthreads();                                      // every wave holds the lengths
+      if (w == 0) {
+        count_in();
+        count_out();
+      }
+    }
     return;
   }
-  const int b = sp.b;
-  const int local = unit - sp.first_unit;                   // < pps * nc, chunk index fastest
-  const float inv_nc = 1.0f / (float)sp.nc;
-  const int pair = __builtin_amdgcn_readfirstlane(div_small(local, sp.nc, inv_nc));
-  const int ci = local - pair * sp.nc;
-  const int kvh = a.qblocks == 1 ? pair : pair / a.qblocks;
-  const int qb = a.qblocks == 1 ? 0 : pair % a.qblocks;
+  int at = range_begin(a.sp, cut, wg);
+  const int range_end = range_begin(a.sp, cut, wg + 1);
+  Place place = find_place(a.sp, cut, lanes, l, at);
+  const int rows_at = (at - place.begin);
+  int pair = __builtin_amdgcn_readfirstlane((int)((float)rows_at / (float)place.nb));   // (put right below: the quotient may be off by one)
+  pair -= pair * place.nb > rows_at ? 1 : 0;
+  pair += (pair + 1) * place.nb <= rows_at ? 1 : 0;
 
-  bool bad_b = false, sparse;
-  int s_end, tail_start;
-  const int n_vis = seq_visible(a.sp, sp.len, sp.md, bad_b, sparse, s_end, tail_start);
-  // The chunk size fixes how many units a pair has (sp.nc); the pair's 128-key blocks then go round its units: unit ci
-  // takes the blocks ci, ci + nc, ci + 2 nc, ...  Every unit of a pair gets the same number of blocks to within one
-  // (chunks of consecutive keys leave the last unit of every pair a remainder, which costs a ragged batch a tenth of
-  // its time), and the units of a pair, which run side by side, read one moving window of consecutive rows.
-  const int c0 = ci * 128;
-  const int c1 = n_vis;
-  const int pstep = 128 * sp.nc;
-  const int tail0 = tail_start - s_end;                     // list index p >= s_end maps to key p + tail0
-  // ring store (s_end = sink_lim when sparse): that key sits in row sink_lim + (p + tail0 - sink_lim) % ring_window
-  //                                                               = sink_lim + (p - sink_lim + ring0) % ring_window
+  // ---- the part in work: blocks [x0, x1) of the list of (sequence place.b, pair)
+  int x0, x1, c1, seam, seam_add, wrap_at, new_key;
+  const __bf16 *kbase, *vbase, *knew, *vnew;
   const int ring_window = a.sp.win_blocks << a.sp.blk_shift;
-  const int ring0 = (a.sp.ring && sparse) ? tail0 % ring_window : 0;
-
-  const __bf16* kbase = a.k + (int64_t)b * a.stride_b + (int64_t)kvh * a.stride_h;
-  const __bf16* vbase = a.v + (int64_t)b * a.stride_b + (int64_t)kvh * a.stride_h;
-
-  // FUSED: the appended row is position sp.len - 1, the last key of every list (none when the cache was full).
-  int new_key = -1;
-  const __bf16* knew = nullptr;
-  const __bf16* vnew = nullptr;
-  if constexpr (FUSED) {
-    if (sp.md & 2) {                                         // the sequence takes its row
-      new_key = sp.len - 1;
-      knew = a.k_new + ((int64_t)b * a.hkv + kvh) * D;
-      vnew = a.v_new + ((int64_t)b * a.hkv + kvh) * D;
-      const int last_piece = (n_vis - 1) >> 7;
-      if (ci == last_piece - div_small(last_piece, sp.nc, inv_nc) * sp.nc && qb == 0 && tid < 2 * CPR) {   // this unit owns the list's last block: it stores the row
-        const int c = tid % CPR;
-        const __bf16* src = (tid < CPR ? knew : vnew) + 8 * c;
-        __bf16* dst = const_cast<__bf16*>(tid < CPR ? kbase : vbase) + (int64_t)new_key * a.stride_t + 8 * c;
-        *(u32x4*)dst = *(const u32x4*)src;
-      }
-    } else if (ci == 0 && pair == 0 && tid == 0) {
-      atomicOr(a.status, (uint32_t)FLUX_DEV_KV_OVERFLOW);
+  auto set_part = [&]() __attribute__((always_inline)) {
+    const int kvh = a.qblocks == 1 ? pair : pair / a.qblocks;
+    const int begin = place.begin + pair * place.nb;
+    x0 = at - begin;
+    x1 = min(place.nb, range_end - begin);
+    bool bad = false, sparse;
+    int s_end, tail_start;
+    c1 = seq_visible(a.sp, place.len, place.md, bad, sparse, s_end, tail_start);
+    // list index p >= seam = s_end maps to key p + tail_start - s_end.  Ring store (s_end = sink_lim when sparse): that key sits
+    // in row sink_lim + (key - sink_lim) % ring_window = p + ring0, less ring_window from p = wrap_at on
+    seam = sparse ? s_end : 0x7FFFFFFF;
+    seam_add = tail_start - s_end;
+    wrap_at = 0x7FFFFFFF;
+    if (a.sp.ring && sparse) {
+      seam_add %= ring_window;
+      wrap_at = s_end + ring_window - seam_add;
     }
-  }
-
-  // ---- Q operand: lane (n, g) holds d = 32*kc + 8*g .. +7 of query head kvh*group + 16*qb + n
-  const int qh = 16 * qb + n;
-  bf16x8 qf[KC];
-  {
-    const u32x4 zero = {0, 0, 0, 0};
-    const __bf16* qrow = a.q + ((int64_t)b * a.hq + (int64_t)kvh * a.group + (qh < a.group ? qh : 0)) * D;
-#pragma unroll
-    for (int kc = 0; kc < KC; ++kc) {
-      u32x4 t = *(const u32x4*)(qrow + 32 * kc + 8 * g);
-      qf[kc] = __builtin_bit_cast(bf16x8, qh < a.group ? t : zero);
+    kbase = a.k + (int64_t)place.b * a.stride_b + (int64_t)kvh * a.stride_h;
+    vbase = a.v + (int64_t)place.b * a.stride_b + (int64_t)kvh * a.stride_h;
+    // FUSED: the appended row is position place.len - 1, the last key of every list (none when the cache was full).
+    new_key = -1;
+    if constexpr (FUSED) {
+      knew = a.k_new + ((int64_t)place.b * a.hkv + kvh) * D;
+      vnew = a.v_new + ((int64_t)place.b * a.hkv + kvh) * D;
+      if (place.md & 2) new_key = place.len - 1;            // the sequence takes its row
+      else if (x0 == 0 && pair == 0 && tid == 0) atomicOr(a.status, (uint32_t)FLUX_DEV_KV_OVERFLOW);
     }
-  }
+  };
+  set_part();
 
-  auto key_of = [&](int p) -> int64_t {
-    p = p < c1 ? p : c1 - 1;                                // keep every address inside the list
-    if (!sparse || p < s_end) return (int64_t)p;
-    if (!a.sp.ring) return (int64_t)p + tail0;
-    const int x = p - s_end + ring0;                        // < 2 * ring_window
-    return (int64_t)s_end + (x >= ring_window ? x - ring_window : x);
+  auto key_of = [&](int p) __attribute__((always_inline)) -> int {
+    p = min(p, c1 - 1);                                     // keep every address inside the list
+    return p + (p >= seam ? seam_add : 0) - (p >= wrap_at ? ring_window : 0);
   };
 
-  // A 32-key block whose keys are 32 consecutive cache rows (every block of an FA chunk, and all but the
+  // A 32-key block whose keys are 32 consecutive cache rows (every block of an FA list, and all but the
   // few SA blocks that contain the sink / tail seam, the ring wrap or the end of the list) is addressed as
   // a wave-uniform row pointer plus per-lane offsets fixed for the whole kernel: no per-lane multiplies.
   // The lane's offset is the same for every load of a block (one register for K, one for V); what differs between
@@ -446,13 +494,13 @@ __global__ __launch_bounds__(SMALL ? 512 : 256, SMALL ? 2 : 3) void decode_split
   // (6.2 -> 7.1 TB/s in isolation).
   auto ld = [](const u32x4* p) -> u32x4 { return NT ? __builtin_nontemporal_load(p) : *p; };
   u32x4 kreg[2][KC], vreg[VL];
-  auto load_block = [&](int p0) {                           // p0 is wave-uniform
-    const int64_t r0 = key_of(p0);
+  auto load_block = [&](int p0) __attribute__((always_inline)) {                           // p0 is wave-uniform
+    const int r0 = key_of(p0);
     // (FUSED: the block that holds the appended row takes the per-lane path, where that row comes from k_new / v_new)
-    const bool linear = p0 + 32 <= c1 && key_of(p0 + 31) - r0 == 31 && !(FUSED && new_key >= 0 && r0 + 31 >= new_key);
+    const bool linear = c1 - p0 >= 32 && key_of(p0 + 31) - r0 == 31 && !(FUSED && new_key >= 0 && r0 + 31 >= new_key);
     if (linear) {
-      const __bf16* kb0 = kbase + r0 * a.stride_t;
-      const __bf16* vb0 = vbase + r0 * a.stride_t;
+      const __bf16* kb0 = kbase + (int64_t)r0 * a.stride_t;
+      const __bf16* vb0 = vbase + (int64_t)r0 * a.stride_t;
 #pragma unroll
       for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
@@ -460,250 +508,274 @@ __global__ __launch_bounds__(SMALL ? 512 : 256, SMALL ? 2 : 3) void decode_split
 #pragma unroll
       for (int i = 0; i < VL; ++i) vreg[i] = ld((const u32x4*)(vb0 + i * RPL * a.stride_t + v_lane));
     } else {
+      // all rows first, then all loads: a row worked out between two loads makes the second wait for the first
+      const __bf16 *krow[2], *vrow[VL];
 #pragma unroll
       for (int sb = 0; sb < 2; ++sb) {
-        const int64_t key = key_of(p0 + 16 * sb + n);
-        const __bf16* row = (FUSED && key == new_key) ? knew : kbase + key * a.stride_t;
-#pragma unroll
-        for (int kc = 0; kc < KC; ++kc) kreg[sb][kc] = ld((const u32x4*)(row + 32 * kc + 8 * g));
+        const int key = key_of(p0 + 16 * sb + n);
+        krow[sb] = (FUSED && key == new_key ? knew : kbase + (int64_t)key * a.stride_t) + 8 * g;
       }
 #pragma unroll
       for (int i = 0; i < VL; ++i) {
-        const int e = i * 64 + l;
-        const int64_t key = key_of(p0 + e / CPR);
-        const __bf16* row = (FUSED && key == new_key) ? vnew : vbase + key * a.stride_t;
-        vreg[i] = ld((const u32x4*)(row + (e % CPR) * 8));
+        const int key = key_of(p0 + (i * 64 + l) / CPR);
+        vrow[i] = (FUSED && key == new_key ? vnew : vbase + (int64_t)key * a.stride_t) + (l % CPR) * 8;
       }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+        for (int kc = 0; kc < KC; ++kc) kreg[sb][kc] = ld((const u32x4*)(krow[sb] + 32 * kc));
+#pragma unroll
+      for (int i = 0; i < VL; ++i) vreg[i] = ld((const u32x4*)vrow[i]);
     }
   };
 
   FLUX_LDS __bf16* vs = (FLUX_LDS __bf16*)smem + w * 32 * VROW;
 
-  float m_run = -INFINITY, l_run = 0.f;
-  f32x4 o[DB];
+  // The first block of a part is asked for before anything else of it: the query rows (which the first scores wait
+  // for as well) and the appended row (stored once the part has been streamed) follow behind it.  Asked for in front of
+  // it they hold it up by a memory latency, and by far more in the workgroups that find the memory pipes full of the other
+  // workgroups' blocks: the last ones of an 8 x 4224 key call began to stream 17 us into a launch of 25.
+  int p0, p_end;
+  bf16x8 qf[KC];
+  u32x4 new_row = {0, 0, 0, 0};
+  FLUX_GLOBAL __bf16* new_row_at = nullptr;                 // where this thread's piece of the appended row goes
+  auto begin_part = [&]() __attribute__((always_inline)) {
+    // the part's keys, 32 at a time round the waves: p_end is where they end or the list does
+    p0 = (int)min((int64_t)x0 << a.sp.block_shift, (int64_t)c1) + 32 * w;
+    p_end = (int)min((int64_t)x1 << a.sp.block_shift, (int64_t)c1);
+    if (p0 < p_end) load_block(p0);
+    __builtin_amdgcn_sched_barrier(0);
+    // ---- Q operand: lane (n, g) holds d = 32*kc + 8*g .. +7 of query head kvh*group + 16*qb + n (columns past the group's
+    // last head repeat its first one; what they give is left out at the end)
+    const int kvh = a.qblocks == 1 ? pair : pair / a.qblocks, qb = a.qblocks == 1 ? 0 : pair % a.qblocks;
+    const int qh = 16 * qb + n;
+    const __bf16* qrow = a.q + ((int64_t)place.b * a.hq + (int64_t)kvh * a.group + (qh < a.group ? qh : 0)) * D;
 #pragma unroll
-  for (int i = 0; i < DB; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int kc = 0; kc < KC; ++kc) qf[kc] = *(const bf16x8*)(qrow + 32 * kc + 8 * g);
+    if constexpr (FUSED) {
+      new_row_at = nullptr;
+      if (x0 == 0 && qb == 0 && new_key >= 0 && tid < 2 * CPR) {
+        new_row = *(const u32x4*)((tid < CPR ? knew : vnew) + 8 * (tid % CPR));
+        new_row_at = (FLUX_GLOBAL __bf16*)const_cast<__bf16*>(tid < CPR ? kbase : vbase) + (int64_t)new_key * a.stride_t + 8 * (tid % CPR);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  begin_part();
 
-  // (eight waves: the upper four take every other block of the unit)
-  int p0 = c0 + (SMALL ? (w >> 2) * pstep : 0) + 32 * (w & 3);
-  if (p0 < c1) load_block(p0);
-  while (p0 < c1) {
-    // ---- stage this block's V rows in LDS and take K into MFMA operands
+  for (;;) {
+    float m_run = -INFINITY, l_run = 0.f;
+    f32x4 o[DB];
 #pragma unroll
-    for (int i = 0; i < VL; ++i) {
-      const int e = i * 64 + l;
-      *(FLUX_LDS u32x4*)(vs + (e / CPR) * VROW + (e % CPR) * 8) = vreg[i];
-    }
-    bf16x8 kf[2][KC];
+    for (int i = 0; i < DB; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    while (p0 < p_end) {
+      // ---- stage this block's V rows in LDS and take K into MFMA operands
 #pragma unroll
-    for (int sb = 0; sb < 2; ++sb)
-#pragma unroll
-      for (int kc = 0; kc < KC; ++kc) kf[sb][kc] = __builtin_bit_cast(bf16x8, kreg[sb][kc]);
-    const int pnext = p0 + (SMALL ? 2 * pstep : pstep);
-    // ---- scores: s[sb][i] is key p0 + 16*sb + 4*g + i against query n
-    f32x4 s[2];
-#pragma unroll
-    for (int sb = 0; sb < 2; ++sb) {
-      s[sb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int kc = 0; kc < KC; ++kc)
-        s[sb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[sb][kc], qf[kc], s[sb], 0, 0, 0);
-    }
-    // the next block is asked for once the score MFMAs have taken this block's K registers, which the loads then
-    // reuse (asked for before them, the block in flight needs registers of its own: 30 more per lane)
-    __builtin_amdgcn_sched_barrier(0);
-    if (pnext < c1) load_block(pnext);
-    __builtin_amdgcn_sched_barrier(0);
-    if (p0 + 32 > c1) {
+      for (int i = 0; i < VL; ++i) {
+        const int e = i * 64 + l;
+        *(FLUX_LDS u32x4*)(vs + (e / CPR) * VROW + (e % CPR) * 8) = vreg[i];
+      }
+      bf16x8 kf[2][KC];
 #pragma unroll
       for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (p0 + 16 * sb + 4 * g + i >= c1) s[sb][i] = -INFINITY;
-    }
-    // ---- online softmax (row maximum over the 4 lane groups of this query)
-    float mloc = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
-                       fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 16));
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
-    const float m_new = fmaxf(m_run, mloc);                 // finite: the block holds a valid key
-    const float alpha = fast_exp2((m_run - m_new) * a.scale_log2);
-    const float mneg = -m_new * a.scale_log2;
-    m_run = m_new;
-    uint32_t pk[4];
-    float psum = 0.f;
+        for (int kc = 0; kc < KC; ++kc) kf[sb][kc] = __builtin_bit_cast(bf16x8, kreg[sb][kc]);
+      const int pnext = p_end - p0 > 32 * W ? p0 + 32 * W : p_end;
+      // ---- scores: s[sb][i] is key p0 + 16*sb + 4*g + i against query n
+      f32x4 s[2];
 #pragma unroll
-    for (int sb = 0; sb < 2; ++sb) {
-      const float p0f = fast_exp2(__builtin_fmaf(s[sb][0], a.scale_log2, mneg));
-      const float p1f = fast_exp2(__builtin_fmaf(s[sb][1], a.scale_log2, mneg));
-      const float p2f = fast_exp2(__builtin_fmaf(s[sb][2], a.scale_log2, mneg));
-      const float p3f = fast_exp2(__builtin_fmaf(s[sb][3], a.scale_log2, mneg));
-      pk[2 * sb] = pack_bf16(p0f, p1f);
-      pk[2 * sb + 1] = pack_bf16(p2f, p3f);
-      // the denominator sums the same rounded weights the numerator uses
-      psum += (bf16_lo(pk[2 * sb]) + bf16_hi(pk[2 * sb])) + (bf16_lo(pk[2 * sb + 1]) + bf16_hi(pk[2 * sb + 1]));
-    }
-    l_run = l_run * alpha + psum;
-    const bf16x8 pf = __builtin_bit_cast(bf16x8, u32x4{pk[0], pk[1], pk[2], pk[3]});
-    // ---- O^T += V^T P^T
+      for (int sb = 0; sb < 2; ++sb) {
+        s[sb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      o[db] *= alpha;
-      FLUX_LDS __bf16* src = vs + (4 * g + (n >> 2)) * VROW + 16 * db + 4 * (n & 3);
-      const bf16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((FLUX_LDS bf16x4*)src);
-      const bf16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((FLUX_LDS bf16x4*)(src + 16 * VROW));
-      const bf16x8 vf = __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
-      o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf, o[db], 0, 0, 0);
+        for (int kc = 0; kc < KC; ++kc)
+          s[sb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[sb][kc], qf[kc], s[sb], 0, 0, 0);
+      }
+      // the next block is asked for once the score MFMAs have taken this block's K registers, which the loads then
+      // reuse (asked for before them, the block in flight needs registers of its own: 30 more per lane)
+      __builtin_amdgcn_sched_barrier(0);
+      if (pnext < p_end) load_block(pnext);
+      __builtin_amdgcn_sched_barrier(0);
+      if (c1 - p0 < 32) {
+#pragma unroll
+        for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (p0 + 16 * sb + 4 * g + i >= c1) s[sb][i] = -INFINITY;
+      }
+      // ---- online softmax (row maximum over the 4 lane groups of this query)
+      float mloc = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
+                         fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
+      mloc = fmaxf(mloc, __shfl_xor(mloc, 16));
+      mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
+      const float m_new = fmaxf(m_run, mloc);               // finite: the block holds a valid key
+      const float alpha = fast_exp2((m_run - m_new) * a.scale_log2);
+      const float mneg = -m_new * a.scale_log2;
+      m_run = m_new;
+      uint32_t pk[4];
+      float psum = 0.f;
+#pragma unroll
+      for (int sb = 0; sb < 2; ++sb) {
+        const float p0f = fast_exp2(__builtin_fmaf(s[sb][0], a.scale_log2, mneg));
+        const float p1f = fast_exp2(__builtin_fmaf(s[sb][1], a.scale_log2, mneg));
+        const float p2f = fast_exp2(__builtin_fmaf(s[sb][2], a.scale_log2, mneg));
+        const float p3f = fast_exp2(__builtin_fmaf(s[sb][3], a.scale_log2, mneg));
+        pk[2 * sb] = pack_bf16(p0f, p1f);
+        pk[2 * sb + 1] = pack_bf16(p2f, p3f);
+        // the denominator sums the same rounded weights the numerator uses
+        psum += (bf16_lo(pk[2 * sb]) + bf16_hi(pk[2 * sb])) + (bf16_lo(pk[2 * sb + 1]) + bf16_hi(pk[2 * sb + 1]));
+      }
+      l_run = l_run * alpha + psum;
+      const bf16x8 pf = __builtin_bit_cast(bf16x8, u32x4{pk[0], pk[1], pk[2], pk[3]});
+      // ---- O^T += V^T P^T
+#pragma unroll
+      for (int db = 0; db < DB; ++db) {
+        o[db] *= alpha;
+        FLUX_LDS __bf16* src = vs + (4 * g + (n >> 2)) * VROW + 16 * db + 4 * (n & 3);
+        const bf16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((FLUX_LDS bf16x4*)src);
+        const bf16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((FLUX_LDS bf16x4*)(src + 16 * VROW));
+        const bf16x8 vf = __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
+        o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf, o[db], 0, 0, 0);
+      }
+      p0 = pnext;
     }
-    p0 = pnext;
-  }
+    if (FUSED && new_row_at) *(FLUX_GLOBAL u32x4*)new_row_at = new_row;
 
-  auto store_out = [&](int qi, int d, float r) __attribute__((always_inline)) {
-    const int64_t off = ((int64_t)b * a.hq + (int64_t)kvh * a.group + 16 * qb + qi) * D + d;
-    if (a.out_fp32) ((float*)a.out)[off] = r;
-    else ((__bf16*)a.out)[off] = (__bf16)r;
-  };
-  // ---- merge the waves through LDS: red[w][n][0..D-1] = O, [D] = m, [D+1] = l
-  l_run += __shfl_xor(l_run, 16);
-  l_run += __shfl_xor(l_run, 32);
-  __syncthreads();                                          // every wave is done with its V staging
-  FLUX_LDS float* red = (FLUX_LDS float*)smem;
-  static_assert(W * 16 * RED * 4 <= W * 32 * VROW * 2, "merge buffer must fit the staging buffer");
-  {
-    FLUX_LDS float* mine = red + (w * 16 + n) * RED;
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) mine[16 * db + 4 * g + i] = o[db][i];
-    if (g == 0) {
-      mine[D] = m_run;
-      mine[D + 1] = l_run;
+    // Nothing is in flight any more, which the compiler does not see for a wave without blocks: it would wait for the next
+    // part's keys in front of the next part's query rows.
+    __builtin_amdgcn_s_waitcnt(0x0F70);                     // vmcnt(0)
+    // (the arguments that only the end of a part needs are read again here: kept in scalar registers they push the loop's
+    // values out of them)
+    const FLUX_CONSTANT DecodeArgs* e = (const FLUX_CONSTANT DecodeArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(e));
+    // ---- what the end of this part needs, and on to the next one: its first block is in flight meanwhile
+    const int nq = min(16, e->group - (e->qblocks == 1 ? 0 : 16 * (pair % e->qblocks)));
+    const int64_t out0 = ((int64_t)place.b * e->hq + (int64_t)(e->qblocks == 1 ? pair : pair / e->qblocks) * e->group + (e->qblocks == 1 ? 0 : 16 * (pair % e->qblocks))) * D;
+    const int list0 = place.begin + pair * place.nb;
+    const bool whole = x0 == 0 && x1 == place.nb;           // the pair lies in this range
+    const int first = whole ? wg : range_of(a.sp, cut, list0);
+    const int parts = whole ? 1 : range_of(a.sp, cut, list0 + place.nb - 1) - first + 1;
+    at = list0 + x1;
+    const bool more = at < range_end;
+    if (more) {
+      if (++pair == a.sp.pps) {
+        place = next_place(a.sp, cut, lanes, l, place);
+        pair = 0;
+      }
+      set_part();
+      begin_part();
     }
-  }
-  __syncthreads();
-  const int nq = min(16, a.group - 16 * qb);
-  if (IN_PLACE && sp.nc == 1) {                             // the only unit of its pair: nothing to merge with
-    for (int idx = tid; idx < nq * D; idx += 64 * W) {
-      const int qi = idx / D, d = idx % D;
-      float m = -INFINITY, num = 0.f, den = 0.f;
+
+    // ---- merge the waves through LDS: red[w][n][0..D-1] = O, ml[w][n] = (m, l); only the columns of heads that exist
+    l_run += __shfl_xor(l_run, 16);
+    l_run += __shfl_xor(l_run, 32);
+    __syncthreads();                                        // every wave is done with its V staging
+    FLUX_LDS float* red = (FLUX_LDS float*)smem;
+    FLUX_LDS f32x2* ml = (FLUX_LDS f32x2*)(red + W * 16 * RED);
+    if (n < nq) {
+      FLUX_LDS float* mine = red + (w * 16 + n) * RED + 4 * g;
 #pragma unroll
-      for (int ww = 0; ww < W; ++ww) m = fmaxf(m, red[(ww * 16 + qi) * RED + D]);
+      for (int db = 0; db < DB; ++db) *(FLUX_LDS f32x4*)(mine + 16 * db) = o[db];
+      if (g == 0) ml[w * 16 + n] = f32x2{m_run, l_run};
+    }
+    __syncthreads();
+    auto store_out = [&](int qi, int d, f32x4 r) __attribute__((always_inline)) {
+      const int64_t off = out0 + qi * D + d;
+      if (e->out_fp32) *(f32x4*)((float*)e->out + off) = r;
+      else *(u32x2*)((__bf16*)e->out + off) = u32x2{pack_bf16(r[0], r[1]), pack_bf16(r[2], r[3])};
+    };
+    const int row0 = part_place(first, wg - first) * e->rpu;
+    for (int idx = tid; idx < nq * (D / 4); idx += 64 * W) {
+      const int qi = idx / (D / 4), d = 4 * (idx % (D / 4));
+      f32x2 x[W];
+      float m = -INFINITY;
 #pragma unroll
       for (int ww = 0; ww < W; ++ww) {
-        const float wgt = fast_exp2((red[(ww * 16 + qi) * RED + D] - m) * a.scale_log2);
-        num += wgt * red[(ww * 16 + qi) * RED + d];
-        den += wgt * red[(ww * 16 + qi) * RED + D + 1];
+        x[ww] = ml[ww * 16 + qi];
+        m = fmaxf(m, x[ww][0]);
       }
-      store_out(qi, d, num / den);
-    }
-    finish();
-    return;
-  }
-  for (int idx = tid; idx < nq * RED; idx += 64 * W) {
-    const int qi = idx / RED, e = idx % RED;
-    float mw[W], m = -INFINITY;
-#pragma unroll
-    for (int ww = 0; ww < W; ++ww) {
-      mw[ww] = red[(ww * 16 + qi) * RED + D];
-      m = fmaxf(m, mw[ww]);
-    }
-    float val;
-    if (e == D) {
-      val = m;
-    } else {
-      val = 0.f;
+      f32x4 val = {0.f, 0.f, 0.f, 0.f};
+      float den = 0.f;
 #pragma unroll
       for (int ww = 0; ww < W; ++ww) {
-        const float wgt = fast_exp2((mw[ww] - m) * a.scale_log2);   // exp2(-inf) = 0 for idle waves
-        val += wgt * red[(ww * 16 + qi) * RED + e];                 // e == D+1 merges l the same way
+        const float wgt = fast_exp2((x[ww][0] - m) * e->scale_log2);        // exp2(-inf) = 0 for idle waves
+        val += wgt * *(FLUX_LDS f32x4*)(red + (ww * 16 + qi) * RED + d);
+        den += wgt * x[ww][1];
+      }
+      if (whole) {                                          // nothing to merge with
+        store_out(qi, d, f32x4{val[0] / den, val[1] / den, val[2] / den, val[3] / den});
+      } else if constexpr (IN_PLACE) {
+        store16_dev(e->part_o, ((row0 + qi) * D + d) * 4, val);
+        if (d == 0) __hip_atomic_store((unsigned long long*)(e->part_ml + 2 * (row0 + qi)), __builtin_bit_cast(unsigned long long, f32x2{m, den}), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      } else {
+        *(f32x4*)(e->part_o + (row0 + qi) * D + d) = val;
+        if (d == 0) *(f32x2*)(e->part_ml + 2 * (row0 + qi)) = f32x2{m, den};
       }
     }
-    // the units of one pair are consecutive: inside their block the rows run [query head][chunk], so that the merge
-    // reads one head's chunks as one contiguous run
-    float* dst = a.partials + (((int64_t)(unit - ci) * a.rpu) + (int64_t)qi * sp.nc + ci) * RED + e;
-    if constexpr (IN_PLACE) __hip_atomic_store(dst, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else *dst = val;
-  }
-  if constexpr (IN_PLACE) {
-    // ---- the unit that arrives last merges the pair
-    __shared__ int last_of_pair;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // this wave's rows have reached the point all XCDs see
-    __syncthreads();
-    uint32_t* count = a.arrived + 1 + b * a.sp.pps + pair;
-    if (tid == 0) last_of_pair = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(sp.nc - 1);
-    __syncthreads();
-    if (last_of_pair) {
-      if (tid == 0) *count = 0;                             // ready for the next call on this stream
-      const float* rows = a.partials + (int64_t)(unit - ci) * a.rpu * RED;
-      for (int idx = tid; idx < nq * D; idx += 64 * W) {
-        const int qi = idx / D, d = idx % D;
-        const Merged r = merge_rows<D, true, 1, 8>(rows + (int64_t)qi * sp.nc * RED, sp.nc, a.scale_log2, d, 0);
-        store_out(qi, d, r.num / r.den);
+    const bool counts = FUSED && !more && w == W - 1;
+    if (counts) count_in();                                 // (every wave of the workgroup has read the lengths)
+    if (IN_PLACE && !whole) {
+      // ---- the part that arrives last merges the pair
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wave's rows have reached the point all XCDs see
+      __syncthreads();
+      if (tid == 0) {
+        uint32_t* count = e->arrived + kCounterStride * (1 + kDecodeGather + first);   // (a range holds the beginning of one unfinished pair at most)
+        const bool done = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(parts - 1);
+        if (done) *count = 0;                               // ready for the next call on this stream
+        last_of_pair = done;
       }
+      __syncthreads();
+      if (counts) count_out();
+      if (last_of_pair) merge_pair<D, true>(e->part_o, e->part_ml, e->rpu, first, parts, nq, e->scale_log2, smem, w, l, store_out);
     }
-    finish();
+    if (counts && whole) count_out();
+    if (!more) break;
+    __syncthreads();                                        // the merge buffer becomes V staging again
   }
 }
 
-// Merge the chunks of one (sequence, query head): out = sum_c w_c O_c / sum_c w_c l_c,
-// w_c = exp(m_c - max m), chunks taken in index order.
+// The merge of a pair's parts as a launch of its own, one workgroup per (KV head, query block) and sequence.
 struct CombineArgs {
-  const float* partials;
-  const int* table;       // the split the first kernel took: [batch][2] = first unit, chunks per pair
+  SplitArgs sp;
+  const float* part_o;
+  const float* part_ml;
+  const int* table;       // the cut the first kernel took (see write_cut_table)
   int hq, group, qblocks, rpu, out_fp32;
   float scale_log2;
   void* out;
-  // the fused decode step only (bump = 1): the lengths, which this kernel moves on.  Nothing reads them any more
-  // at that point: the first kernel has ended and this one takes the split from the table.
-  int bump, capacity;
-  int32_t* kv_len_rw;
 };
 
-// G groups of D threads per (sequence, query head), each with every G-th chunk; the partial results meet in LDS.
-// Bound by latencies (the split table, then the rows): all rows of up to 8 G chunks are asked for at once (with maximum,
-// weights and sums as three dependent passes over the rows a layer took 0.9 - 1.3 us longer).  One group is enough where
-// a list has few chunks, and four times the threads cost 0.7 us where there are a thousand heads to merge.
-template <int D, int G>
-__global__ __launch_bounds__(G * D) void decode_combine_kernel(CombineArgs a) {
-  constexpr int RED = D + 2;
-  const int tid = threadIdx.x, d = tid % D, grp = tid / D, head = blockIdx.x, b = blockIdx.y;
-  const int first_unit = a.table[2 * b], nc = a.table[2 * b + 1];
-  const int kvh = head / a.group, hh = head - kvh * a.group;
-  const int64_t unit0 = first_unit + (int64_t)(kvh * a.qblocks + hh / 16) * nc;
-  const float* base = a.partials + (unit0 * a.rpu + (int64_t)(hh % 16) * nc) * RED;
-  Merged r = merge_rows<D, false, G, 8>(base, nc, a.scale_log2, d, grp);
-  if constexpr (G > 1) {
-    __shared__ Merged part[G][D];
-    part[grp][d] = r;
-    __syncthreads();
-    r = {-INFINITY, 0.f, 0.f};
-#pragma unroll
-    for (int i = 0; i < G; ++i) r.m = fmaxf(r.m, part[i][d].m);
-#pragma unroll
-    for (int i = 0; i < G; ++i) {
-      const float w = fast_exp2((part[i][d].m - r.m) * a.scale_log2);       // exp2(-inf) = 0 for a group without chunks
-      r.num += w * part[i][d].num;
-      r.den += w * part[i][d].den;
-    }
+template <int D>
+__global__ __launch_bounds__(256) void decode_combine_kernel(CombineArgs a) {
+  __shared__ __attribute__((aligned(16))) char smem[4 * 64 * sizeof(Merged)];
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, pair = blockIdx.x, b = blockIdx.y;
+  const int kvh = pair / a.qblocks, qb = pair - kvh * a.qblocks;
+  const int nq = min(16, a.group - 16 * qb);
+  const int nb = a.table[2 * b + 1], begin = a.table[2 * b] + pair * nb;
+  const int64_t out0 = ((int64_t)b * a.hq + (int64_t)kvh * a.group + 16 * qb) * D;
+  auto store_out = [&](int qi, int d, f32x4 r) __attribute__((always_inline)) {
+    const int64_t off = out0 + qi * D + d;
+    if (a.out_fp32) *(f32x4*)((float*)a.out + off) = r;
+    else *(u32x2*)((__bf16*)a.out + off) = u32x2{pack_bf16(r[0], r[1]), pack_bf16(r[2], r[3])};
+  };
+  if (nb == 0) {                                            // an empty cache yields zeros
+    for (int it = tid; it < nq * (D / 4); it += 256) store_out(it / (D / 4), 4 * (it % (D / 4)), f32x4{0.f, 0.f, 0.f, 0.f});
+    return;
   }
-  if (grp == 0) {
-    const float x = nc > 0 ? r.num / r.den : 0.f;                           // an empty cache yields zeros
-    const int64_t off = ((int64_t)b * a.hq + head) * D + d;
-    if (a.out_fp32) ((float*)a.out)[off] = x;
-    else ((__bf16*)a.out)[off] = (__bf16)x;
-  }
-  if (a.bump && head == 0 && tid == 0) {
-    int len = a.kv_len_rw[b];
-    len = len < 0 ? 0 : (len > a.capacity ? a.capacity : len);
-    a.kv_len_rw[b] = len < a.capacity ? len + 1 : len;
-  }
+  Cut cut;
+  cut.total = a.table[2 * a.sp.batch - 2] + a.sp.pps * a.table[2 * a.sp.batch - 1];
+  cut.align = a.table[2 * a.sp.batch];
+  const int first = range_of(a.sp, cut, begin), parts = range_of(a.sp, cut, begin + nb - 1) - first + 1;
+  if (parts < 2) return;                                    // done by the first kernel
+  merge_pair<D, false>(a.part_o, a.part_ml, a.rpu, first, parts, nq, a.scale_log2, smem, w, l, store_out);
 }
 
-// c.small_counters may be null: a call of few short lists then takes two launches.
+// c.decode_counters may be null: the call then takes two launches.
 hipError_t launch_decode(const Ctx& c, const flux_attn_cfg& cfg, const void* q, int max_kv_len,
                          const flux_kv_cache& cache, const uint8_t* mode, int ring, const void* k_new,
                          const void* v_new, void* out, hipStream_t s) {
-  const bool fused = k_new != nullptr;                       // append + attend + merge in one launch
+  const bool fused = k_new != nullptr;                       // append + attend + merge in one launch (needs the counters)
   const DecodePlan plan = plan_decode(cfg, cache.batch, max_kv_len);
   const float scale = cfg.softmax_scale != 0.f ? cfg.softmax_scale : 1.0f / sqrtf((float)cfg.head_dim);
   DecodeArgs a;
@@ -725,6 +797,8 @@ hipError_t launch_decode(const Ctx& c, const flux_attn_cfg& cfg, const void* q, 
   a.sp.max_keys = max_kv_len;
   a.sp.pps = plan.pps;
   a.sp.bump = fused ? 1 : 0;
+  a.sp.block_shift = plan.block_shift;
+  a.sp.aligned_shift = plan.aligned_shift;
   a.k_new = (const __bf16*)k_new;
   a.v_new = (const __bf16*)v_new;
   a.hq = cfg.n_q_heads;
@@ -733,50 +807,42 @@ hipError_t launch_decode(const Ctx& c, const flux_attn_cfg& cfg, const void* q, 
   a.qblocks = (a.group + 15) / 16;
   a.rpu = plan.rpu;
   a.scale_log2 = scale * kLog2e;
-  a.table = (int*)c.partials;                                // the split table sits in front of the partial rows
-  a.partials = c.partials + plan.table_floats;
+  a.table = (int*)c.partials;                                // the table sits in front of the rows
+  a.part_o = c.small && !plan.in_partials ? c.small : c.partials + plan.table_floats + 64;   // (64: the word behind the table)
+  a.part_ml = a.part_o + (size_t)2 * plan.wgs * plan.rpu * cfg.head_dim;
   a.status = c.status;
-  const dim3 grid(plan.units);
+  a.arrived = c.decode_counters;
+  a.kv_len_rw = cache.kv_len;
+  a.out = out;
+  a.out_fp32 = cfg.out_dtype;
+  const dim3 grid(plan.wgs);
   // K and V bytes one call may read.  A call of a model whose layers together stream more than the 256 MB last-level
   // cache finds none of its rows there, whatever its own size (an SA layer reads 138 MB of a 4 GB cache): from 64 MB
   // on the rows are fetched with nontemporal loads (SA layer 34.5 -> 33.4 us, FA layers as before); smaller calls are
   // bound by their launches either way.
   const bool nt = 4.0 * cache.batch * cfg.n_kv_heads * cfg.head_dim * (double)max_kv_len > 64.0 * 1024 * 1024;
-  a.arrived = c.small_counters;
-  a.kv_len_rw = cache.kv_len;
-  a.out = out;
-  a.out_fp32 = cfg.out_dtype;
-  const bool small = decode_small(cfg, cache.batch, max_kv_len) && (c.small_counters || !fused);
-  if (small && c.small_counters) {
-    if (cfg.head_dim == 128) {
-      if (fused) hipLaunchKernelGGL((decode_splitk_kernel<128, false, true, true>), grid, dim3(512), 0, s, a);
-      else hipLaunchKernelGGL((decode_splitk_kernel<128, false, false, true>), grid, dim3(512), 0, s, a);
-    } else {
-      if (fused) hipLaunchKernelGGL((decode_splitk_kernel<64, false, true, true>), grid, dim3(512), 0, s, a);
-      else hipLaunchKernelGGL((decode_splitk_kernel<64, false, false, true>), grid, dim3(512), 0, s, a);
-    }
-    return hipGetLastError();
-  }
-  auto launch = [&](auto d, auto f) {
+  auto launch = [&](auto d) {
     constexpr int D = decltype(d)::value;
-    constexpr bool FU = decltype(f)::value;
-    if (small) {
-      if constexpr (!FU) hipLaunchKernelGGL((decode_splitk_kernel<D, false, false, true, true>), grid, dim3(512), 0, s, a);
-    } else if (nt) hipLaunchKernelGGL((decode_splitk_kernel<D, true, FU>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((decode_splitk_kernel<D, false, FU>), grid, dim3(256), 0, s, a);
+    if (fused) {
+      if (nt) hipLaunchKernelGGL((decode_splitk_kernel<D, true, true, true>), grid, dim3(256), 0, s, a);
+      else hipLaunchKernelGGL((decode_splitk_kernel<D, false, true, true>), grid, dim3(256), 0, s, a);
+    } else if (c.decode_counters) {
+      if (nt) hipLaunchKernelGGL((decode_splitk_kernel<D, true, false, true>), grid, dim3(256), 0, s, a);
+      else hipLaunchKernelGGL((decode_splitk_kernel<D, false, false, true>), grid, dim3(256), 0, s, a);
+    } else {
+      if (nt) hipLaunchKernelGGL((decode_splitk_kernel<D, true, false, false>), grid, dim3(256), 0, s, a);
+      else hipLaunchKernelGGL((decode_splitk_kernel<D, false, false, false>), grid, dim3(256), 0, s, a);
+    }
   };
-  if (cfg.head_dim == 128) {
-    if (fused) launch(std::integral_constant<int, 128>(), std::true_type());
-    else launch(std::integral_constant<int, 128>(), std::false_type());
-  } else {
-    if (fused) launch(std::integral_constant<int, 64>(), std::true_type());
-    else launch(std::integral_constant<int, 64>(), std::false_type());
-  }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (cfg.head_dim == 128) launch(std::integral_constant<int, 128>());
+  else launch(std::integral_constant<int, 64>());
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || c.decode_counters) return e;
 
   CombineArgs ca;
-  ca.partials = a.partials;
+  ca.sp = a.sp;
+  ca.part_o = a.part_o;
+  ca.part_ml = a.part_ml;
   ca.table = a.table;
   ca.hq = cfg.n_q_heads;
   ca.group = a.group;
@@ -785,20 +851,9 @@ hipError_t launch_decode(const Ctx& c, const flux_attn_cfg& cfg, const void* q, 
   ca.out_fp32 = cfg.out_dtype;
   ca.scale_log2 = a.scale_log2;
   ca.out = out;
-  ca.bump = a.sp.bump;
-  ca.capacity = cache.capacity;
-  ca.kv_len_rw = cache.kv_len;
-  const dim3 cgrid(cfg.n_q_heads, cache.batch);
-  // chunks of the longest list, as far as the host can tell: the bound, or about twice a pair's share of the units
-  const long long pairs = (long long)cache.batch * plan.pps;
-  const bool few = small || max_kv_len <= 8 * kMinChunk || 2 * kTargetUnits <= 8 * pairs;
-  if (cfg.head_dim == 128) {
-    if (few) hipLaunchKernelGGL((decode_combine_kernel<128, 1>), cgrid, dim3(128), 0, s, ca);
-    else hipLaunchKernelGGL((decode_combine_kernel<128, 4>), cgrid, dim3(512), 0, s, ca);
-  } else {
-    if (few) hipLaunchKernelGGL((decode_combine_kernel<64, 1>), cgrid, dim3(64), 0, s, ca);
-    else hipLaunchKernelGGL((decode_combine_kernel<64, 4>), cgrid, dim3(256), 0, s, ca);
-  }
+  const dim3 cgrid(plan.pps, cache.batch);
+  if (cfg.head_dim == 128) hipLaunchKernelGGL(decode_combine_kernel<128>, cgrid, dim3(256), 0, s, ca);
+  else hipLaunchKernelGGL(decode_combine_kernel<64>, cgrid, dim3(256), 0, s, ca);
   return hipGetLastError();
 }
 

@@ -130,9 +130,9 @@ int flux_create(flux_ctx** out, int device, size_t workspace_bytes) {
   ctx->c.ws_bytes = workspace_bytes;
   ctx->c.status = (uint32_t*)ctx->c.ws;
   ctx->c.counters = (uint32_t*)(ctx->c.ws + 256);
-  ctx->c.small_counters = (uint32_t*)(ctx->c.ws + 512);
+  ctx->c.decode_counters = (uint32_t*)(ctx->c.ws + kDecodeCountersAt);
   ctx->c.router_counters = (uint32_t*)(ctx->c.ws + 1024);
-  static_assert(1024 + 4 * kRouterCounters <= kHeaderBytes && 512 + 4 * (1 + kSmallPairs) <= 1024, "the counters must fit the header");
+  static_assert(1024 + 4 * kRouterCounters <= kDecodeCountersAt, "the counters must fit the header");
   ctx->c.small = (float*)(ctx->c.ws + kHeaderBytes);
   ctx->c.partials = (float*)(ctx->c.ws + kHeaderBytes + kSmallBytes);
   ctx->c.partials_bytes = workspace_bytes - kHeaderBytes - kSmallBytes;

@@ -30,11 +30,13 @@ typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t u32x2;
 
 #define FLUX_LDS __attribute__((address_space(3)))
 #define FLUX_GLOBAL __attribute__((address_space(1)))
+#define FLUX_CONSTANT __attribute__((address_space(4)))
 
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -46,7 +48,7 @@ struct Ctx {
   // carved regions (device pointers)
   uint32_t* status;        // sticky status word
   uint32_t* counters;      // kCounters zero-initialised arrival counters; users reset them to zero
-  uint32_t* small_counters;   // 1 + kSmallPairs of the same kind, for the decode calls merged in place; null: such calls take two launches
+  uint32_t* decode_counters;  // kDecodeCounters of the same kind; null: decode calls take two launches
   uint32_t* router_counters;  // kRouterCounters of the same kind, one per sequence of a router call
   float* small;            // router scratch: pooled vectors and hidden activations
   float* partials;         // split-K partial results
@@ -81,8 +83,16 @@ __device__ __forceinline__ int window_start(int i, int shift, int win_blocks) {
 
 constexpr int kCounters = 64;
 constexpr int kRouterCounters = 512;
-constexpr size_t kSmallBytes = 8u << 20;      // router: batch * (splits * hidden + inner) floats
-constexpr size_t kHeaderBytes = 4096;         // status + counters
+// Arrival counters of the decode calls, each on a line of its own (counts on one line are taken one after the other, some
+// 10 ns each): words whose workgroups have all read the lengths; the words that workgroups count themselves on; one per
+// workgroup, for the pair that begins in its range and goes on behind it.
+constexpr int kCounterStride = 32;            // words
+constexpr int kDecodeGather = 32;
+constexpr int kDecodeWgsShift = 8, kDecodeAlignedShift = 9;
+constexpr int kDecodeCounters = 1 + kDecodeGather + (1 << kDecodeAlignedShift);
+constexpr size_t kSmallBytes = 8u << 20;      // router: batch * (splits * hidden + inner) floats; decode: the rows of parts
+constexpr size_t kDecodeCountersAt = 4096;    // bytes
+constexpr size_t kHeaderBytes = kDecodeCountersAt + (kDecodeCounters * kCounterStride * 4 + 4095) / 4096 * 4096;   // status + counters
 constexpr int kPrefillWideMinRows = 32768;    // prefill launches whose longest prompt has at least this many rows use 256-row workgroups
 
 // ---- launchers (each validates nothing: flux_api.hip has done it) ---------------------------
@@ -92,51 +102,62 @@ hipError_t launch_kv_append(const Ctx& c, const flux_kv_cache& cache, int hkv, i
 hipError_t launch_kv_compact_ring(const flux_kv_cache& src, const flux_kv_cache& dst, int hkv, int d, int n_sink,
                                   int window, hipStream_t s);
 
+// Decode shares the visible keys of a call out over 2^kDecodeWgsShift workgroups, one per CU, in equal ranges; calls of at
+// most 2^kDecodeAlignedShift times 128 keys take one workgroup per 128 keys of a list.  The cut itself is taken on the device;
+// the host only bounds it.  A CU takes in about 27 bytes per ns from memory, whatever its workgroups have asked for, which is
+// its even share of what the memory delivers: a call takes as long as the CU with the most keys.  (Units of whole chunks of a
+// list left the fullest CU 18 % over the mean in a batch of 32 ragged lists and 44 % in 16 lists of 2112 keys, and the third
+// workgroup of a CU, whose lengths are asked for behind the others' keys, began to stream when those were done.)  Two
+// workgroups per CU take no more in, start later and leave twice the rows to merge: us with two / one, 32/8 heads of 128:
+// 8 x 4224 keys 29.7 / 28.1, 1 x 100000 69.8 / 65.0, 8 x 131072 652.5 / 644.9, 32 ragged lists of 28/4 heads 37.4 / 36.8.
 struct DecodePlan {
-  int units;        // workgroups launched: an upper bound on the units of the split the device takes
+  int units;        // what the scratch is sized by: the units of a cut into chunks of kMinChunk keys and more
   int pps;          // (KV head, query block) pairs per sequence
-  int rpu;          // partial rows each unit writes
-  int table_floats; // 4-byte words in front of the partial rows that hold the split table (2 per sequence, rounded to 256 B)
+  int rpu;          // partial rows of a unit
+  int table_floats; // 4-byte words in front of the partial rows that hold the cut as a table (rounded to 256 B)
+  int wgs;          // workgroups launched
+  int aligned_shift;   // log2 of the most where every one takes its keys from one list
+  int block_shift;  // log2 of the keys of a block
+  bool in_partials; // the rows of parts need the partials region (they fit the small one otherwise)
 };
-// The split-K decode cuts the visible keys of a call into about kTargetUnits workgroups of at least kMinChunk keys
-// (the split itself is taken on the device; the host only bounds it).
-constexpr int kTargetUnits = 1024;              // about that many workgroups: 4 per CU (three fit a CU at once)
-constexpr int kMinChunk = 256;                  // 64 keys per wave: keeps the per-chunk merge a small part of the streaming
+constexpr int kTargetUnits = 1024;
+constexpr int kMinChunk = 256;
 inline DecodePlan plan_decode(const flux_attn_cfg& cfg, int batch, int max_kv_len) {
-  // Upper bound on the units the device-side split can produce: kTargetUnits + one per pair from the chunk
-  // size it picks, and no more than the pairs times the chunks of the longest list at the smallest chunk.
   DecodePlan p;
   const int group = cfg.n_q_heads / cfg.n_kv_heads;
   p.pps = cfg.n_kv_heads * ((group + 15) / 16);
   p.rpu = group < 16 ? group : 16;
-  const long long pairs = (long long)batch * p.pps;
-  const long long by_len = pairs * (((long long)(max_kv_len > 0 ? max_kv_len : 1) + kMinChunk - 1) / kMinChunk);
+  const long long pairs = (long long)batch * p.pps, keys = max_kv_len > 0 ? max_kv_len : 1;
+  const long long by_len = pairs * ((keys + kMinChunk - 1) / kMinChunk);
   const long long by_target = kTargetUnits + pairs;
   p.units = (int)(by_len < by_target ? by_len : by_target);
-  if (p.units < 1) p.units = 1;                  // one workgroup always runs: it writes the split table
+  if (p.units < 1) p.units = 1;
   p.table_floats = (2 * batch + 63) / 64 * 64;
+  // a range leaves rows in two places at most (see part_place); never fewer workgroups than share the keys out otherwise
+  static_assert(kDecodeAlignedShift > kDecodeWgsShift, "halved below");
+  const long long by_four = pairs * ((keys + 127) / 128);
+  auto bytes = [&](long long wgs) { return 2 * wgs * p.rpu * (cfg.head_dim + 2) * (long long)sizeof(float); };
+  p.aligned_shift = kDecodeAlignedShift;
+  p.wgs = (int)(by_four < (1 << p.aligned_shift) ? by_four : (1 << p.aligned_shift));
+  p.in_partials = false;
+  if (bytes(p.wgs) > (long long)kSmallBytes) {
+    if (2ll * p.wgs <= p.units) {
+      p.in_partials = true;
+    } else {
+      --p.aligned_shift;
+      p.wgs = 1 << p.aligned_shift;
+    }
+  }
+  // blocks are counted in 32 bits: where the bounds allow more of them, they are larger
+  p.block_shift = 5;
+  while (pairs * ((keys >> p.block_shift) + 4) > 0x7FFFFFFFll && p.block_shift < 30) ++p.block_shift;
   return p;
-}
-// Decode calls of few short lists are bound by latencies (launches, the split, two dependent loads) and not by bytes: one
-// launch that merges in place (decode.hip, SMALL).  Split-K + merge kernel / one launch, us on the device, 32/8 heads of
-// 128: 1 x 200 keys 10.2 / 6.2, 1 x 2001 11.1 / 9.1, 1 x 4200 12.0 / 11.1, 4 x 2000 13.3 / 11.6; beyond the bounds below
-// the merge at the end of a workgroup costs more than the launch: 1 x 8000 13.4 / 15.0, 4 x 4000 19.4 / 23.4, 28/4 heads
-// 4 x 4000 14.0 / 14.9.
-constexpr int kSmallPairs = 60;                 // (more pairs have not been timed in this form)
-constexpr int kSmallUnits = 256;                // a workgroup per CU
-constexpr int kSmallKeys = 4352;                // 17 chunks: what a window of 4096 keys and 128 sinks takes
-constexpr int kSmallRows = 72;                  // rows that the last unit of a pair merges: query heads x chunks
-inline bool decode_small(const flux_attn_cfg& cfg, int batch, int max_kv_len) {
-  const int group = cfg.n_q_heads / cfg.n_kv_heads;
-  if (max_kv_len < 1 || max_kv_len > kSmallKeys || group > 16 || (long long)batch * cfg.n_kv_heads > kSmallPairs) return false;
-  const int chunks = (max_kv_len + kMinChunk - 1) / kMinChunk;
-  return batch * cfg.n_kv_heads * chunks <= kSmallUnits && group * chunks <= kSmallRows;
 }
 inline size_t decode_partials_bytes(const flux_attn_cfg& cfg, const DecodePlan& p) {
   return ((size_t)p.table_floats + (size_t)p.units * p.rpu * (cfg.head_dim + 2)) * sizeof(float);
 }
-// k_new / v_new != nullptr: the fused decode step (append one row per sequence, then attend: two launches instead of
-// three); needs c.counters and a cache that is not a ring.
+// k_new / v_new != nullptr: the fused decode step (append one row per sequence, then attend: one launch instead of
+// two); needs c.decode_counters and a cache that is not a ring.
 hipError_t launch_decode(const Ctx& c, const flux_attn_cfg& cfg, const void* q, int max_kv_len,
                          const flux_kv_cache& cache, const uint8_t* mode, int ring, const void* k_new,
                          const void* v_new, void* out, hipStream_t s);

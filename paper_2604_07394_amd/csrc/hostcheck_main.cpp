@@ -10,7 +10,8 @@
 #include "../../include/flux.h"
 
 extern "C" const void *hostcheck_status, *hostcheck_partials, *hostcheck_counters;   // what the last decode launcher was given
-extern "C" int hostcheck_decode_small(const flux_attn_cfg* cfg, int batch, int max_kv_len);
+extern "C" int hostcheck_decode_wgs(const flux_attn_cfg* cfg, int batch, int max_kv_len);
+extern "C" int hostcheck_decode_rows_fit(const flux_attn_cfg* cfg, int batch, int max_kv_len);
 
 static int failures = 0;
 #define EXPECT(expr, want)                                                                   \
@@ -82,7 +83,7 @@ int main() {
   EXPECT(flux_attn_decode_static(&g16, p, 1 << 20, &bigc, pb, p, nullptr, nullptr), FLUX_EWORKSPACE);
   EXPECT(flux_attn_decode_static(&cfg, p, 32, &kc, pb, p, (uint32_t*)(buf + 2), nullptr), FLUX_EINVAL);
   // the static scratch outlives every caller: its calls leave nothing there that a later one goes by but the status word,
-  // so a short call (which a context merges in one launch, on arrival counters) is given no counters
+  // so a call (which a context merges in one launch, on arrival counters) is given no counters
   uint32_t word = 0;
   EXPECT(flux_attn_decode_static(&cfg, p, 32, &kc, pb, p, &word, nullptr), FLUX_EHIP);
   EXPECT(hostcheck_partials != nullptr, 1);
@@ -91,23 +92,22 @@ int main() {
   EXPECT(flux_attn_decode_static(&cfg, p, 32, &kc, pb, p, nullptr, nullptr), FLUX_EHIP);
   EXPECT(hostcheck_counters == nullptr, 1);
   EXPECT((const char*)hostcheck_partials - (const char*)hostcheck_status, 256);
-  // ---- which decode calls are merged in the launch that streams them: on either side of every bound
-  auto small = [](int hq, int hkv, int d, int batch, int keys) {
+  // ---- workgroups of a decode call, and the room that the rows of their parts have
+  auto wgs = [](int hq, int hkv, int d, int batch, int keys) {
     const flux_attn_cfg c = {hq, hkv, d, 4, 16, 0.f, 0, 0};
-    return hostcheck_decode_small(&c, batch, keys);
+    EXPECT(hostcheck_decode_rows_fit(&c, batch, keys), 1);
+    return hostcheck_decode_wgs(&c, batch, keys);
   };
-  EXPECT(small(4, 1, 128, 1, 0), 0);
-  EXPECT(small(4, 1, 128, 1, 1), 1);
-  EXPECT(small(32, 8, 128, 1, 4352), 1);                    // 17 chunks of 256 keys
-  EXPECT(small(32, 8, 128, 1, 4353), 0);
-  EXPECT(small(8, 8, 64, 4, 2048), 1);                      // 256 units
-  EXPECT(small(8, 8, 64, 4, 2049), 0);
-  EXPECT(small(20, 20, 128, 3, 701), 1);                    // 60 pairs
-  EXPECT(small(21, 21, 128, 3, 701), 0);
-  EXPECT(small(16, 1, 64, 2, 1024), 1);                     // 16 query heads x 4 chunks to merge
-  EXPECT(small(16, 1, 64, 2, 1281), 0);                     // ... x 6
-  EXPECT(small(17, 1, 64, 1, 100), 0);                      // more query heads than rows of a unit
-  EXPECT(small(8, 8, 64, INT_MAX, 100), 0);
+  EXPECT(wgs(4, 1, 128, 1, 0), 1);
+  EXPECT(wgs(4, 1, 128, 1, 129), 2);
+  EXPECT(wgs(32, 8, 128, 1, 8192), 512);
+  EXPECT(wgs(32, 8, 128, 8, 131072), 512);
+  EXPECT(wgs(16, 1, 128, 1, 4096), 32);
+  EXPECT(wgs(16, 1, 128, 504, 100), 504);                   // 16 rows of 128 per part: the most that the small region holds
+  EXPECT(wgs(16, 1, 128, 505, 100), 256);                   // ... and neither region
+  EXPECT(wgs(16, 1, 128, 1025, 100), 512);                  // ... and the partials
+  EXPECT(wgs(40, 2, 64, 100, 1 << 20), 512);                // two query blocks
+  EXPECT(wgs(8, 8, 64, INT_MAX / 16, INT_MAX), 512);
   // ---- append, ring, router
   EXPECT(flux_kv_append(ctx, &kc, 2, 128, p, p, pi, 10, 10, nullptr), FLUX_EHIP);
   EXPECT(flux_kv_append(ctx, &kc, 2, 128, p, p, pi, INT_MAX, INT_MAX, nullptr), FLUX_ECAPACITY);

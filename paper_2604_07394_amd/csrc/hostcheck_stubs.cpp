@@ -9,8 +9,13 @@ hipError_t hipGetDevice(int* device) { *device = 0; return hipSuccess; }
 hipError_t hipGetSymbolAddress(void** p, const void* symbol) { *p = const_cast<void*>(symbol); return hipSuccess; }
 // of the last launch_decode
 const void *hostcheck_status, *hostcheck_partials, *hostcheck_counters;
-// whether a decode call with counters is merged in the launch that streams it
-int hostcheck_decode_small(const flux_attn_cfg* cfg, int batch, int max_kv_len) { return flux::decode_small(*cfg, batch, max_kv_len); }
+// what a decode call launches, and what its parts leave behind against the room that the regions of a context have
+int hostcheck_decode_wgs(const flux_attn_cfg* cfg, int batch, int max_kv_len) { return flux::plan_decode(*cfg, batch, max_kv_len).wgs; }
+int hostcheck_decode_rows_fit(const flux_attn_cfg* cfg, int batch, int max_kv_len) {
+  const flux::DecodePlan p = flux::plan_decode(*cfg, batch, max_kv_len);
+  const size_t rows = (size_t)2 * p.wgs * p.rpu * (cfg->head_dim + 2) * sizeof(float);
+  return rows <= (p.in_partials ? flux::decode_partials_bytes(*cfg, p) - p.table_floats * sizeof(float) : flux::kSmallBytes);
+}
 }
 
 namespace flux {
@@ -22,7 +27,7 @@ hipError_t launch_decode(const Ctx& c, const flux_attn_cfg&, const void*, int, c
                          const void*, void*, hipStream_t) {
   hostcheck_status = c.status;
   hostcheck_partials = c.partials;
-  hostcheck_counters = c.counters ? c.counters : c.small_counters ? c.small_counters : c.router_counters;
+  hostcheck_counters = c.counters ? c.counters : c.decode_counters ? c.decode_counters : c.router_counters;
   return hipErrorNoDevice;
 }
 hipError_t launch_prefill(const Ctx&, const flux_attn_cfg&, const void*, const int32_t*, int, int, const flux_kv_cache&,

@@ -1,0 +1,79 @@
+"""Decode calls where the ranges of workgroups meet the lists in every way: one list per workgroup, lists cut into fours and
+eights, ranges that begin and end inside lists, whole lists inside a range, lists that go on over several ranges, empty caches
+and more sequences than lanes.  Against the oracle at the attention tolerance; the fused step, the call without a context
+(its merge is a launch of its own) and a replayed graph give the same bits."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import flux_oracle as O
+from paper_2604_07394_amd import synth
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+FA, SA = 1, 0
+
+
+@pytest.mark.parametrize("hq,hkv,d,lens", [
+    (8, 4, 64, [(i * 379) % 1500 for i in range(70)]),        # equal ranges over more than 64 sequences, some empty
+    (40, 2, 64, [4000, 0, 1, 3100, 2050]),                    # by eight blocks; two query blocks per KV head
+    (16, 16, 64, [1024] * 4),                                 # by four: as many as there may be
+    (16, 16, 64, [1024] * 4 + [1]),                           # ... and one list more: equal ranges
+    (4, 4, 128, [256, 224, 1]),                               # lists of up to eight blocks: one workgroup each
+    (4, 4, 128, [256, 257, 1]),                               # ... and one of nine
+    (6, 2, 128, [33000]),                                     # 32 columns of heads, parts in several runs of the merge
+    (32, 2, 128, [9000, 8000, 700]),                          # 16 heads per KV head: no waves to share the runs
+    (7, 1, 64, [70000, 3]),                                   # one pair over nearly all ranges
+])
+def test_ranges_and_lists(hq, hkv, d, lens):
+    from paper_2604_07394_amd import binding as F
+    ctx = F.flux_create(0)
+    b, n_sink, window, seed = len(lens), 8, 3000, 800 + hq
+    modes = [FA if i % 3 != 1 else SA for i in range(b)]
+    kb = synth.normal_bf16(seed, synth.stream_id(synth.STREAM_K), (sum(lens) + b, hkv, d))
+    vb = synth.normal_bf16(seed, synth.stream_id(synth.STREAM_V), (sum(lens) + b, hkv, d))
+    qb = synth.normal_bf16(seed, synth.stream_id(synth.STREAM_QDEC), (b, hq, d))
+    cfg = F.attn_cfg(hq, hkv, d, n_sink, window, 0.0, 1)
+    t, cap = sum(lens), max(lens) + 1
+    cu = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int32, device="cuda")
+    md = torch.tensor(modes, dtype=torch.uint8, device="cuda")
+    q, kn, vn = H.bits_to_torch(qb), H.bits_to_torch(kb[t:]), H.bits_to_torch(vb[t:])
+    cache = F.KVCache.empty(b, hkv, cap, d)
+    cache.k.fill_(float("nan"))
+    cache.v.fill_(float("nan"))
+    F.flux_kv_append(ctx, cache, hkv, d, H.bits_to_torch(kb[:t]), H.bits_to_torch(vb[:t]), cu, t, max(lens))
+    out = torch.full((b, hq, d), float("nan"), dtype=torch.float32, device="cuda")
+    F.flux_attn_decode(ctx, cfg, q, max(lens), cache, md, out)            # (an empty cache yields zeros)
+    torch.cuda.synchronize()
+    assert torch.isfinite(out).all()
+    assert all(n > 0 or not out[i].any() for i, n in enumerate(lens))
+    F.flux_attn_decode_append(ctx, cfg, q, kn, vn, cap, cache, md, out)
+    torch.cuda.synchronize()
+    assert cache.kv_len.tolist() == [n + 1 for n in lens]
+    kf, vf, qf = O.bf16_to_f64(kb), O.bf16_to_f64(vb), O.bf16_to_f64(qb)
+    at = 0
+    for i, n in enumerate(lens):
+        if b < 10 or i % 7 == 0:
+            k1, v1 = np.concatenate([kf[at:at + n], kf[t + i:t + i + 1]]), np.concatenate([vf[at:at + n], vf[t + i:t + i + 1]])
+            H.assert_close(out[i].cpu().numpy(), O.attention(qf[i:i + 1], k1, v1, modes[i], n_sink, window)[0], f"sequence {i} of {n + 1} keys")
+        at += n
+    again = torch.empty_like(out)
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    for bound in (cap, cap, cap):
+        again.fill_(float("nan"))
+        F.flux_attn_decode_static(cfg, q, bound, cache, md, again, status)
+        torch.cuda.synchronize()
+        assert torch.equal(again, out) and int(status[0]) == 0
+    g = torch.cuda.CUDAGraph()
+    s = torch.cuda.Stream()
+    with torch.cuda.graph(g, stream=s):
+        cache.kv_len.sub_(1)
+        F.flux_attn_decode_append(ctx, cfg, q, kn, vn, cap, cache, md, again, stream=s)
+    for _ in range(4):
+        again.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(again, out) and cache.kv_len.tolist() == [n + 1 for n in lens]
+    assert F.flux_last_device_status(ctx) == 0
+    F.flux_destroy(ctx)

@@ -45,6 +45,7 @@ struct PrefillArgs {
   int xcd_map;            // 0 plain, 1 pairs-per-XCD, 2 XCDs-per-pair, 3 planned on the device (see the kernel)
   int sink_lim, win_blocks, blk_shift;   // SA geometry (see sa_geom)
   int n_qtiles;
+  int turn;               // block-sparse form: query tiles after which the pairs of a round change XCD
   float scale_log2;
   int out_fp32;
   void* out;
@@ -396,9 +397,10 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
       // shares), at no cost where it does not: the heads of a tile change places from tile to tile, so that a CU
       // (which sees every 32nd workgroup of its XCD) meets all heads of the group; and the eight pairs of a round
       // change XCD every 16 tiles (one round of resident workgroups), so that every XCD works through two rounds of
-      // every pair instead of all rounds of one.  A round streams its K/V rows from behind the L2 anyway.
+      // every pair instead of all rounds of one.  A round streams its K/V rows from behind the L2 anyway.  Shorter prompts of
+      // the block-sparse form have fewer tiles than make that even, so their pairs change sooner (launch_prefill).
       const int r = j / (gw * a.n_qtiles), qtd = (j / gw) % a.n_qtiles, g = (j + qtd) % gw;
-      const int pair = ((x + qtd / (PACK ? 32 : 16)) & 7) + 8 * r;
+      const int pair = ((x + qtd / (BS ? a.turn : PACK ? 32 : 16)) & 7) + 8 * r;
       b = pair / a.hkv;
       h = (pair % a.hkv) * a.group + g;
       qt = a.n_qtiles - 1 - qtd;
@@ -1071,6 +1073,11 @@ hipError_t launch_prefill(const Ctx& c, const flux_attn_cfg& cfg, const void* q,
   const int grp = pack ? a.group : 1;                       // heads whose rows share a tile
   const long long n_qtiles = ((long long)max_q_len * grp + BM - 1) / BM;
   a.n_qtiles = (int)n_qtiles;
+  // The pairs of a block-sparse launch change XCD every 16 tiles, those of shorter prompts 16 times over the prompt: XA on
+  // structured input, us for append, selection and launch with 16 tiles and as here: 4096 tokens 124 / 119.5, 16384 tokens
+  // 478 / 470, 7000 and 13000 tokens 472 / 452, 16/8 heads 12000 tokens 192 / 187; not sooner for long ones, whose workgroups
+  // share what the L2 holds (32768 tokens, everything kept, every 16, 8, 4 and 1 tiles: 7480, 7540, 7610 and 7980).
+  a.turn = n_qtiles < 32 ? 2 : n_qtiles < 256 ? (int)n_qtiles / 16 : 16;
   a.split_units = 0;
   a.part_o = a.part_ml = nullptr;
   a.tile_info = nullptr;

@@ -146,6 +146,20 @@ def test_all_kept_is_fa_and_sink_window_blocks_are_block_granular_sa_bit_for_bit
     assert np.array_equal(nothing[:64], fa.cpu().numpy()[:64])
 
 
+@pytest.mark.parametrize("n", [97, 2000, 4100, 4224, 6200])
+def test_every_tile_is_worked_on_whatever_the_prompt_length_says_about_the_order(F, ctx, n):
+    """The pairs of a launch change XCD after a number of tiles that depends on the prompt (2 below 32 tiles, a sixteenth
+    of them from there on): with everything kept the launch is FA bit for bit, for tile counts on both sides of a step
+    and 16 pairs, the second sequence shorter than the bound."""
+    case = Case(F, ctx, 90, [0, 0], [n, n // 3], 8, 8, 64)
+    everything = np.ones((2, 1, case.n_qb, case.n_kb), bool)
+    got = case.run(everything, [SA, SA], 1)
+    fa = torch.full((n + n // 3, 8, 64), float("nan"), dtype=torch.float32, device="cuda")
+    F.flux_attn_prefill(ctx, F.attn_cfg(8, 8, 64, 0, 1, 0.0, 1), H.bits_to_torch(case.qb), cu([n, n // 3]), n, n, case.cache, u8([FA, FA]), fa)
+    torch.cuda.synchronize()
+    assert np.array_equal(got, fa.cpu().numpy())
+
+
 def test_blocks_nobody_keeps_are_never_read(F, ctx):
     """Key blocks that no query block of a 128-row tile keeps are skipped, not masked: poisoning their K and V
     rows with NaN leaves the output bit-identical."""

@@ -2,7 +2,8 @@
 // sink + window subset of Sec. 4.1 / App. C.3), chosen per sequence by the cached mode byte.
 //
 // Shape of the computation (one workgroup = 128 query rows, 4 waves x 32 rows = 2 column blocks of 16 queries;
-// launches for long prompts use 8 waves per workgroup, 256 rows; which rows these are, see the kernel):
+// launches for long prompts use 8 waves per workgroup, 256 rows, launches of few tiles 4 waves x 16 rows; which rows these
+// are, see the kernel):
 //   for each VISITED 64-key block (FA: all blocks up to the diagonal; SA: the sink blocks and the
 //   blocks that intersect the tile's window, nothing else: hidden blocks are skipped, not masked)
 //     S^T[key][q]  = K[key][:] . Q[q][:]     MFMA 16x16x32 bf16, A = K rows from LDS, B = Q in registers
@@ -307,17 +308,19 @@ __device__ __forceinline__ PrefillUnit prefill_plan(const PrefillArgs& a, int l,
   return u;
 }
 
-// A tile is BM = 32 * NW rows.  PACK: they are the query rows of ALL heads of the group, token by token: row R is head
+// A tile is BM = 16 * QB * NW rows.  PACK: they are the query rows of ALL heads of the group, token by token: row R is head
 // R % group of token R / group.  Short runs of queries then fill their tiles (16 new tokens of a group of 4 are half a
 // tile, not an eighth of four), a tile spans few tokens, so that little of what the diagonal or a window's start cuts is
 // worked out for nothing, and its query rows are contiguous in memory.  Otherwise a tile is 128 tokens of one head:
 // finding the rows costs a workgroup about a microsecond, more than that saves where tiles are full (8 x 2048 tokens
 // packed 3 % slower), and in the block-sparse form the keep matrix differs between heads.
-// NW: waves per workgroup, 4 (two workgroups per CU) or 8 (one)
-template <int D, bool BS, int NW, bool PLAN = false, bool PACK = NW == 8>
+// NW: waves per workgroup, 4 (two workgroups per CU) or 8 (one).  QB: column blocks of 16 rows per wave, 1 in launches of few
+// tiles (where that pays, see launch_prefill)
+template <int D, bool BS, int NW, bool PLAN = false, bool PACK = NW == 8, int QB = 2>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(PrefillArgs a) {
   constexpr bool SPLIT = PLAN && PACK;    // tiles may be split
-  constexpr int BM = 32 * NW;             // query rows per workgroup
+  constexpr int WR = 16 * QB;             // query rows per wave
+  constexpr int BM = WR * NW;             // query rows per workgroup
   constexpr int BN = 64;                  // keys per iteration: two halves of 32, the K dimension of one PV MFMA
   constexpr int KC = D / 32;              // MFMA k-steps over the head dimension (QK^T)
   constexpr int DB = D / 16;              // 16-wide output blocks over the head dimension (PV)
@@ -446,10 +449,10 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
   // query rows of the tile / of this wave, as absolute positions
   const int i_tile_min = pos0 + tok0;
   const int i_tile_max = i_tile_min + __builtin_amdgcn_readfirstlane(tok_of(rows - 1));
-  const int r_w0 = 32 * w;                                   // first row of this wave, within the tile
+  const int r_w0 = WR * w;                                   // first row of this wave, within the tile
   const bool wave_active = r_w0 < rows;
   const int i_w_min = i_tile_min + __builtin_amdgcn_readfirstlane(tok_of(r_w0));
-  const int i_w_max = wave_active ? i_tile_min + __builtin_amdgcn_readfirstlane(tok_of(min(r_w0 + 31, rows - 1))) : i_w_min - 1;
+  const int i_w_max = wave_active ? i_tile_min + __builtin_amdgcn_readfirstlane(tok_of(min(r_w0 + WR - 1, rows - 1))) : i_w_min - 1;
   // where row x lies in q and out
   const int64_t tile_off = ((int64_t)(q_begin + tok0) * a.hq + h) * D;
   auto row_off = [&](int x) {
@@ -458,9 +461,9 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
   };
   // this lane's two query rows (column n of column block qb; rows past the last one repeat it): position, and first key
   // of the row's SA window
-  int i_mine[2], w_lo_mine[2];
+  int i_mine[QB], w_lo_mine[QB];
 #pragma unroll
-  for (int qb = 0; qb < 2; ++qb) {
+  for (int qb = 0; qb < QB; ++qb) {
     i_mine[qb] = i_tile_min + tok_of(min(r_w0 + 16 * qb + n, rows - 1));
     w_lo_mine[qb] = window_start(i_mine[qb], a.blk_shift, a.win_blocks);
   }
@@ -469,9 +472,9 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
   const int w_lo_last = window_start(max(i_w_max, i_w_min), a.blk_shift, a.win_blocks);
 
   // ---- Q operand: lane (n, g) holds d = 32*kc + 8*g .. +7 of its two query rows
-  bf16x8 qf[2][KC];
+  bf16x8 qf[QB][KC];
 #pragma unroll
-  for (int qb = 0; qb < 2; ++qb) {
+  for (int qb = 0; qb < QB; ++qb) {
     const __bf16* qrow = a.q + row_off(min(r_w0 + 16 * qb + n, rows - 1));
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc) qf[qb][kc] = *(const bf16x8*)(qrow + 32 * kc + 8 * g);
@@ -567,15 +570,20 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
 #pragma unroll
   for (int db = 0; db < DB; ++db) v_rd[db] = KTILE + v_row * ROWB + ((db ^ v_xr) * 32) + (n & 3) * 8;
 
-  float m_ref[2] = {-INFINITY, -INFINITY};                   // the score the exponents of a row refer to
-  float mneg[2] = {0.f, 0.f};                                // -m_ref * scale_log2 (0 while a row has no reference yet)
-  float l_run[2] = {0.f, 0.f};                               // this lane's part of the row sums
+  float m_ref[QB];                                           // the score the exponents of a row refer to
+  float mneg[QB];                                            // -m_ref * scale_log2 (0 while a row has no reference yet)
+  float l_run[QB];                                           // this lane's part of the row sums
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) {
+    m_ref[qb] = -INFINITY;
+    mneg[qb] = l_run[qb] = 0.f;
+  }
   bool all_ref = false;                                      // wave-uniform: every row of the wave has a reference
-  f32x4 o[DB][2];
+  f32x4 o[DB][QB];
 #pragma unroll
   for (int i = 0; i < DB; ++i)
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) o[i][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int qb = 0; qb < QB; ++qb) o[i][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // ---- which iterations are PLAIN for this wave: the wave is active, every key of the block is visible to
   // every row of the wave (no element mask, nothing to skip).  In tile indices: the block ends at or before the
@@ -698,8 +706,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
     //   K fragments of half 0 | S^T half 0, the K fragments of half 1 read between its MFMAs |
     //   S^T half 1, the V fragments of half 0 read between its MFMAs | weights |
     //   O^T += half 0, the V fragments of half 1 read between its MFMAs | O^T += half 1
-    f32x4 s[KB][2];              // s[kb][qb][i]: key j0 + 16*kb + 4*g + i against query row (qb, n)
-    bf16x8 pf[2][KS];            // pf[qb][ks]: weights of keys 32*ks + {4g..4g+3, 16+4g..16+4g+3}, as a B operand
+    f32x4 s[KB][QB];             // s[kb][qb][i]: key j0 + 16*kb + 4*g + i against query row (qb, n)
+    bf16x8 pf[QB][KS];           // pf[qb][ks]: weights of keys 32*ks + {4g..4g+3, 16+4g..16+4g+3}, as a B operand
     bf16x8 kf[KB][KC];
     bf16x8 vf[KS][DB];
     auto read_k = [&](int kb, int kc) { kf[kb][kc] = *(FLUX_LDS bf16x8*)(st + k_rd[kc] + 16 * kb * KPITCH); };
@@ -712,11 +720,11 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
     // Softmax weights against the reference m_ref the accumulators already refer to, WITHOUT looking for the
     // block's maximum first: any reference gives the same quotient, and fp32 / bf16 keep their relative
     // precision over the whole exponent range.  A row without a reference yet uses 0.
-    float l_blk[2];
+    float l_blk[QB];
     auto weights = [&]() {
       const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
 #pragma unroll
-      for (int qb = 0; qb < 2; ++qb) {
+      for (int qb = 0; qb < QB; ++qb) {
         l_blk[qb] = 0.f;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
@@ -738,7 +746,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb)
+        for (int qb = 0; qb < QB; ++qb)
           o[db][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[ks][db], pf[qb][ks], o[db][qb], 0, 0, 0);
     };
     // Only when a row has no reference yet, or some weight of the block left the guarded range (or
@@ -749,9 +757,9 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
     auto weights_guarded = [&]() {
       weights();
       // (one ballot per comparison: each is then the comparison's own lane mask, with no vector instruction between)
-      if (!all_ref || (__builtin_amdgcn_ballot_w64(!(l_blk[0] < kWeightGuard)) | __builtin_amdgcn_ballot_w64(!(l_blk[1] < kWeightGuard))) != 0) {
+      if (!all_ref || (__builtin_amdgcn_ballot_w64(!(l_blk[0] < kWeightGuard)) | __builtin_amdgcn_ballot_w64(!(l_blk[QB - 1] < kWeightGuard))) != 0) {
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
+        for (int qb = 0; qb < QB; ++qb) {
           float mloc = s[0][qb][0];
 #pragma unroll
           for (int kb = 0; kb < KB; ++kb)
@@ -773,10 +781,10 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
           }
         }
         weights();
-        all_ref = __builtin_amdgcn_ballot_w64((m_ref[0] == -INFINITY) | (m_ref[1] == -INFINITY)) == 0;
+        all_ref = __builtin_amdgcn_ballot_w64((m_ref[0] == -INFINITY) | (m_ref[QB - 1] == -INFINITY)) == 0;
       }
-      l_run[0] += l_blk[0];
-      l_run[1] += l_blk[1];
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) l_run[qb] += l_blk[qb];
     };
 
     // a block that an edge of the visible set crosses, or that this wave does not see at all, needs the
@@ -813,7 +821,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
       for (int t = 0; t < 2 * KC; ++t) {
         const int kc = t >> 1, kb = t & 1;
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) s[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][kc], qf[qb][kc], s[kb][qb], 0, 0, 0);
+        for (int qb = 0; qb < QB; ++qb) s[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][kc], qf[qb][kc], s[kb][qb], 0, 0, 0);
         read_k(2 + kb, kc);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -821,7 +829,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
       for (int t = 0; t < 2 * KC; ++t) {
         const int kc = t >> 1, kb = 2 + (t & 1);
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) s[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][kc], qf[qb][kc], s[kb][qb], 0, 0, 0);
+        for (int qb = 0; qb < QB; ++qb) s[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][kc], qf[qb][kc], s[kb][qb], 0, 0, 0);
 #pragma unroll
         for (int db = t * DB / (2 * KC); db < (t + 1) * DB / (2 * KC); ++db) read_v(0, db);
         __builtin_amdgcn_sched_barrier(0);
@@ -835,7 +843,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
     // (bound - j0 - 4*g) and compared with constants.
     if (mask_edge) {
 #pragma unroll
-      for (int qb = 0; qb < 2; ++qb) {
+      for (int qb = 0; qb < QB; ++qb) {
         const int hi = i_mine[qb] - j0 - 4 * g, lo = w_lo_mine[qb] - j0 - 4 * g, sl = a.sink_lim - j0 - 4 * g;
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb)
@@ -849,7 +857,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
       scores();
     } else if (mask_causal) {
 #pragma unroll
-      for (int qb = 0; qb < 2; ++qb) {
+      for (int qb = 0; qb < QB; ++qb) {
         int hi = i_mine[qb] - j0 - 4 * g;
         // block-sparse form: a row whose query block does not keep this key block sees none of it
         if constexpr (BS) hi = ((bs_rows >> ((i_mine[qb] >> 6) - rb0)) & 1) ? hi : -1;
@@ -863,7 +871,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) s[kb][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int qb = 0; qb < QB; ++qb) s[kb][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
       scores();
     }
     // The softmax part runs at a raised wave priority: while it is short, the other wave of this SIMD is mostly
@@ -877,7 +885,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
 #pragma unroll
     for (int db = 0; db < DB; ++db) {
 #pragma unroll
-      for (int qb = 0; qb < 2; ++qb) o[db][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[0][db], pf[qb][0], o[db][qb], 0, 0, 0);
+      for (int qb = 0; qb < QB; ++qb) o[db][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[0][db], pf[qb][0], o[db][qb], 0, 0, 0);
       read_v(1, db);
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -908,7 +916,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
   FLUX_GLOBAL void* f_out = SPLIT ? fin.out : (FLUX_GLOBAL void*)a.out;
   const float f_inv = __builtin_amdgcn_rcpf((float)f_grp);
 #pragma unroll
-  for (int qb = 0; qb < 2; ++qb) {
+  for (int qb = 0; qb < QB; ++qb) {
     float l_tot = l_run[qb];
     l_tot += __shfl_xor(l_tot, 16);
     l_tot += __shfl_xor(l_tot, 32);
@@ -1071,7 +1079,18 @@ hipError_t launch_prefill(const Ctx& c, const flux_attn_cfg& cfg, const void* q,
   const long long unpacked = whole / n_pairs;
   const bool pack = split || wide || (plan && (max_kv_len > max_q_len ? packed < unpacked : 4 * packed <= 3 * unpacked));
   const int grp = pack ? a.group : 1;                       // heads whose rows share a tile
-  const long long n_qtiles = ((long long)max_q_len * grp + BM - 1) / BM;
+  // Few tiles take 64 rows each, 16 per wave: twice the workgroups, and half the work of a block in each of them, where a
+  // workgroup (or two) per CU walks its blocks one after the other and the chip waits for the longest.  us with 128 rows /
+  // with 64, 32/8 heads of 128 unless said, append included: 512 tokens 23.3 / 19.9, 1000 33.3 / 28.2, 1500 46.1 / 41.2; 8/2
+  // heads of 64, 1000 tokens 22.6 / 18.2; 16/8 heads, 3000 tokens 75.8 / 67.2; 700 tokens behind 900 42.1 / 35.0.  64-row
+  // tiles read K and V twice as often, so it ends where all of them are not resident at once: above half as many 128-row
+  // tiles as the chip holds if they walk lists of one length (1500 tokens behind 1500 78 / 87, a sparse layer of 128 + 512
+  // keys at 1500 tokens 36.1 / 38.8, 600, 580 and 500 tokens 32.0 / 34.5), later for one whole prompt that no window cuts,
+  // whose lists are half as long in the mean (1700 tokens 49.5 / 47.3, 2000 57.8 / 58.9).
+  const int resident = cfg.head_dim == 64 ? kResident64 : kResident128;
+  const bool triangular = cache.batch == 1 && max_kv_len == max_q_len && a.sink_lim + ((long long)a.win_blocks << a.blk_shift) >= max_q_len;
+  const bool half = !bm && !plan && !wide && whole <= (triangular ? resident / 8 * 7 : resident / 2);
+  const long long n_qtiles = half ? (max_q_len + 63ll) / 64 : ((long long)max_q_len * grp + BM - 1) / BM;
   a.n_qtiles = (int)n_qtiles;
   // The pairs of a block-sparse launch change XCD every 16 tiles, those of shorter prompts 16 times over the prompt: XA on
   // structured input, us for append, selection and launch with 16 tiles and as here: 4096 tokens 124 / 119.5, 16384 tokens
@@ -1116,6 +1135,8 @@ hipError_t launch_prefill(const Ctx& c, const flux_attn_cfg& cfg, const void* q,
     else hipLaunchKernelGGL((prefill_kernel<64, false, 4, true>), grid, dim3(256), 0, s, a);
   } else {
     if (wide) hipLaunchKernelGGL((prefill_kernel<128, false, 8>), grid, dim3(512), 0, s, a);
+    else if (half && d128) hipLaunchKernelGGL((prefill_kernel<128, false, 4, false, false, 1>), grid, dim3(256), 0, s, a);
+    else if (half) hipLaunchKernelGGL((prefill_kernel<64, false, 4, false, false, 1>), grid, dim3(256), 0, s, a);
     else if (d128) hipLaunchKernelGGL((prefill_kernel<128, false, 4>), grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL((prefill_kernel<64, false, 4>), grid, dim3(256), 0, s, a);
   }

@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
 from dataclasses import dataclass
 
 import torch
@@ -43,6 +44,9 @@ class FluxKVCache(C.Structure):
                 ("kv_len", C.c_void_p), ("batch", C.c_int32), ("capacity", C.c_int32)]
 
 
+_pack_cache = struct.Struct("@PPqqqPii").pack                # the bytes of a FluxKVCache
+assert struct.calcsize("@PPqqqPii") == C.sizeof(FluxKVCache)
+
 _lib.flux_create.argtypes = [C.POINTER(C.c_void_p), C.c_int, C.c_size_t]
 _lib.flux_create.restype = C.c_int
 _lib.flux_destroy.argtypes = [C.c_void_p]
@@ -56,35 +60,35 @@ _lib.flux_last_device_status.restype = C.c_int
 _lib.flux_router.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_void_p, C.c_void_p,
                              C.c_void_p, C.c_void_p, C.c_int, C.c_void_p, C.c_void_p, C.c_void_p]
 _lib.flux_router.restype = C.c_int
-_lib.flux_kv_append.argtypes = [C.c_void_p, C.POINTER(FluxKVCache), C.c_int, C.c_int, C.c_void_p, C.c_void_p,
+_lib.flux_kv_append.argtypes = [C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_void_p, C.c_void_p,
                                 C.c_void_p, C.c_int, C.c_int, C.c_void_p]
 _lib.flux_kv_append.restype = C.c_int
 _lib.flux_attn_prefill.argtypes = [C.c_void_p, C.POINTER(FluxAttnCfg), C.c_void_p, C.c_void_p, C.c_int, C.c_int,
-                                   C.POINTER(FluxKVCache), C.c_void_p, C.c_void_p, C.c_void_p]
+                                   C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]
 _lib.flux_attn_prefill.restype = C.c_int
 _lib.flux_attn_prefill_blocksparse.argtypes = [C.c_void_p, C.POINTER(FluxAttnCfg), C.c_void_p, C.c_void_p, C.c_int, C.c_int,
-                                               C.POINTER(FluxKVCache), C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int,
+                                               C.c_void_p, C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int,
                                                C.c_void_p, C.c_void_p]
 _lib.flux_attn_prefill_blocksparse.restype = C.c_int
 _lib.flux_xa_select.argtypes = [C.c_void_p, C.POINTER(FluxAttnCfg), C.c_void_p, C.c_void_p, C.c_int, C.c_int,
-                                C.POINTER(FluxKVCache), C.c_int, C.c_float, C.c_void_p, C.c_int, C.c_int, C.c_void_p]
+                                C.c_void_p, C.c_int, C.c_float, C.c_void_p, C.c_int, C.c_int, C.c_void_p]
 _lib.flux_xa_select.restype = C.c_int
-_lib.flux_attn_decode.argtypes = [C.c_void_p, C.POINTER(FluxAttnCfg), C.c_void_p, C.c_int, C.POINTER(FluxKVCache),
+_lib.flux_attn_decode.argtypes = [C.c_void_p, C.POINTER(FluxAttnCfg), C.c_void_p, C.c_int, C.c_void_p,
                                   C.c_void_p, C.c_void_p, C.c_void_p]
 _lib.flux_attn_decode.restype = C.c_int
 _lib.flux_attn_decode_append.argtypes = [C.c_void_p, C.POINTER(FluxAttnCfg), C.c_void_p, C.c_void_p, C.c_void_p, C.c_int,
-                                         C.POINTER(FluxKVCache), C.c_void_p, C.c_void_p, C.c_void_p]
+                                         C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]
 _lib.flux_attn_decode_append.restype = C.c_int
-_lib.flux_attn_decode_static.argtypes = [C.POINTER(FluxAttnCfg), C.c_void_p, C.c_int, C.POINTER(FluxKVCache), C.c_void_p,
+_lib.flux_attn_decode_static.argtypes = [C.POINTER(FluxAttnCfg), C.c_void_p, C.c_int, C.c_void_p, C.c_void_p,
                                          C.c_void_p, C.c_void_p, C.c_void_p]
 _lib.flux_attn_decode_static.restype = C.c_int
-_lib.flux_kv_append_ring.argtypes = [C.c_void_p, C.POINTER(FluxKVCache), C.c_int, C.c_int, C.c_int, C.c_int, C.c_void_p,
+_lib.flux_kv_append_ring.argtypes = [C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int, C.c_void_p,
                                      C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_void_p]
 _lib.flux_kv_append_ring.restype = C.c_int
-_lib.flux_kv_compact_ring.argtypes = [C.c_void_p, C.POINTER(FluxKVCache), C.POINTER(FluxKVCache), C.c_int, C.c_int,
+_lib.flux_kv_compact_ring.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int, C.c_int,
                                       C.c_int, C.c_int, C.c_void_p]
 _lib.flux_kv_compact_ring.restype = C.c_int
-_lib.flux_attn_decode_ring.argtypes = [C.c_void_p, C.POINTER(FluxAttnCfg), C.c_void_p, C.POINTER(FluxKVCache),
+_lib.flux_attn_decode_ring.argtypes = [C.c_void_p, C.POINTER(FluxAttnCfg), C.c_void_p, C.c_void_p,
                                        C.c_void_p, C.c_void_p]
 _lib.flux_attn_decode_ring.restype = C.c_int
 
@@ -101,9 +105,7 @@ def _check(rc: int) -> None:
 
 
 def _ptr(t) -> int | None:
-    if t is None:
-        return None
-    if isinstance(t, int):
+    if t is None or isinstance(t, int):
         return t
     return t.data_ptr()
 
@@ -171,8 +173,17 @@ class KVCache:
                            self.k.stride(2), self.kv_len.data_ptr(), b, cap)
 
 
-def _cache_struct(cache) -> FluxKVCache:
-    return cache if isinstance(cache, FluxKVCache) else cache.c_struct()
+def _cache_arg(cache):
+    """What a call is given for its cache: a reference to the struct, or its bytes.  A ctypes struct takes three times as
+    long to fill as the bytes to pack (c_struct 2.7 us, this 0.9), which shows where the kernels of a call take less time
+    than the call; nothing is kept between calls."""
+    if type(cache) is not KVCache:
+        return C.byref(cache if isinstance(cache, FluxKVCache) else cache.c_struct())
+    k, v = cache.k, cache.v
+    strides = k.stride()
+    assert strides == v.stride() and strides[3] == 1
+    b, _, cap, _ = k.shape
+    return _pack_cache(k.data_ptr(), v.data_ptr(), strides[0], strides[1], strides[2], cache.kv_len.data_ptr(), b, cap)
 
 
 def flux_router(ctx, x, cu_seqlens, batch, hidden, pool, w1, b1, w2, b2, inner, mode_out, logits_out=None,
@@ -182,63 +193,53 @@ def flux_router(ctx, x, cu_seqlens, batch, hidden, pool, w1, b1, w2, b2, inner, 
 
 
 def flux_kv_append(ctx, cache, n_kv_heads, head_dim, k_new, v_new, cu_new, total_new, max_new, stream=None) -> None:
-    cs = _cache_struct(cache)
-    _check(_lib.flux_kv_append(ctx, C.byref(cs), n_kv_heads, head_dim, _ptr(k_new), _ptr(v_new), _ptr(cu_new),
+    _check(_lib.flux_kv_append(ctx, _cache_arg(cache), n_kv_heads, head_dim, _ptr(k_new), _ptr(v_new), _ptr(cu_new),
                                total_new, max_new, _stream(stream)))
 
 
 def flux_attn_prefill(ctx, cfg, q, cu_q, max_q_len, max_kv_len, cache, mode, out, stream=None) -> None:
-    cs = _cache_struct(cache)
-    _check(_lib.flux_attn_prefill(ctx, C.byref(cfg), _ptr(q), _ptr(cu_q), max_q_len, max_kv_len, C.byref(cs),
+    _check(_lib.flux_attn_prefill(ctx, C.byref(cfg), _ptr(q), _ptr(cu_q), max_q_len, max_kv_len, _cache_arg(cache),
                                   _ptr(mode), _ptr(out), _stream(stream)))
 
 
 def flux_attn_prefill_blocksparse(ctx, cfg, q, cu_q, max_q_len, max_kv_len, cache, mode, block_mask, mask_heads,
                                   n_qblocks, n_kblocks, out, stream=None) -> None:
-    cs = _cache_struct(cache)
-    _check(_lib.flux_attn_prefill_blocksparse(ctx, C.byref(cfg), _ptr(q), _ptr(cu_q), max_q_len, max_kv_len, C.byref(cs),
+    _check(_lib.flux_attn_prefill_blocksparse(ctx, C.byref(cfg), _ptr(q), _ptr(cu_q), max_q_len, max_kv_len, _cache_arg(cache),
                                               _ptr(mode), _ptr(block_mask), mask_heads, n_qblocks, n_kblocks, _ptr(out),
                                               _stream(stream)))
 
 
 def flux_xa_select(ctx, cfg, q, cu_q, max_q_len, max_kv_len, cache, stride, threshold, block_mask, n_qblocks, n_kblocks,
                    stream=None) -> None:
-    cs = _cache_struct(cache)
-    _check(_lib.flux_xa_select(ctx, C.byref(cfg), _ptr(q), _ptr(cu_q), max_q_len, max_kv_len, C.byref(cs), stride,
+    _check(_lib.flux_xa_select(ctx, C.byref(cfg), _ptr(q), _ptr(cu_q), max_q_len, max_kv_len, _cache_arg(cache), stride,
                                threshold, _ptr(block_mask), n_qblocks, n_kblocks, _stream(stream)))
 
 
 def flux_attn_decode(ctx, cfg, q, max_kv_len, cache, mode, out, stream=None) -> None:
-    cs = _cache_struct(cache)
-    _check(_lib.flux_attn_decode(ctx, C.byref(cfg), _ptr(q), max_kv_len, C.byref(cs), _ptr(mode), _ptr(out),
+    _check(_lib.flux_attn_decode(ctx, C.byref(cfg), _ptr(q), max_kv_len, _cache_arg(cache), _ptr(mode), _ptr(out),
                                  _stream(stream)))
 
 
 def flux_attn_decode_append(ctx, cfg, q, k_new, v_new, max_kv_len, cache, mode, out, stream=None) -> None:
-    cs = _cache_struct(cache)
-    _check(_lib.flux_attn_decode_append(ctx, C.byref(cfg), _ptr(q), _ptr(k_new), _ptr(v_new), max_kv_len, C.byref(cs),
+    _check(_lib.flux_attn_decode_append(ctx, C.byref(cfg), _ptr(q), _ptr(k_new), _ptr(v_new), max_kv_len, _cache_arg(cache),
                                         _ptr(mode), _ptr(out), _stream(stream)))
 
 
 def flux_attn_decode_static(cfg, q, max_kv_len, cache, mode, out, status=None, stream=None) -> None:
-    cs = _cache_struct(cache)
-    _check(_lib.flux_attn_decode_static(C.byref(cfg), _ptr(q), max_kv_len, C.byref(cs), _ptr(mode), _ptr(out),
+    _check(_lib.flux_attn_decode_static(C.byref(cfg), _ptr(q), max_kv_len, _cache_arg(cache), _ptr(mode), _ptr(out),
                                         _ptr(status), _stream(stream)))
 
 
 def flux_kv_append_ring(ctx, ring, n_kv_heads, head_dim, n_sink, window, k_new, v_new, cu_new, total_new, max_new,
                         stream=None) -> None:
-    cs = _cache_struct(ring)
-    _check(_lib.flux_kv_append_ring(ctx, C.byref(cs), n_kv_heads, head_dim, n_sink, window, _ptr(k_new), _ptr(v_new),
+    _check(_lib.flux_kv_append_ring(ctx, _cache_arg(ring), n_kv_heads, head_dim, n_sink, window, _ptr(k_new), _ptr(v_new),
                                     _ptr(cu_new), total_new, max_new, _stream(stream)))
 
 
 def flux_kv_compact_ring(ctx, src, dst, n_kv_heads, head_dim, n_sink, window, stream=None) -> None:
-    ss, ds = _cache_struct(src), _cache_struct(dst)
-    _check(_lib.flux_kv_compact_ring(ctx, C.byref(ss), C.byref(ds), n_kv_heads, head_dim, n_sink, window,
+    _check(_lib.flux_kv_compact_ring(ctx, _cache_arg(src), _cache_arg(dst), n_kv_heads, head_dim, n_sink, window,
                                      _stream(stream)))
 
 
 def flux_attn_decode_ring(ctx, cfg, q, ring, out, stream=None) -> None:
-    cs = _cache_struct(ring)
-    _check(_lib.flux_attn_decode_ring(ctx, C.byref(cfg), _ptr(q), C.byref(cs), _ptr(out), _stream(stream)))
+    _check(_lib.flux_attn_decode_ring(ctx, C.byref(cfg), _ptr(q), _cache_arg(ring), _ptr(out), _stream(stream)))

@@ -130,6 +130,7 @@ int flux_create(flux_ctx** out, int device, size_t workspace_bytes) {
   ctx->c.ws_bytes = workspace_bytes;
   ctx->c.status = (uint32_t*)ctx->c.ws;
   ctx->c.counters = (uint32_t*)(ctx->c.ws + 256);
+  ctx->c.append_counters = (uint32_t*)(ctx->c.ws + kAppendCountersAt);
   ctx->c.decode_counters = (uint32_t*)(ctx->c.ws + kDecodeCountersAt);
   ctx->c.router_counters = (uint32_t*)(ctx->c.ws + 1024);
   static_assert(1024 + 4 * kRouterCounters <= kDecodeCountersAt, "the counters must fit the header");

@@ -48,6 +48,7 @@ struct Ctx {
   // carved regions (device pointers)
   uint32_t* status;        // sticky status word
   uint32_t* counters;      // kCounters zero-initialised arrival counters; users reset them to zero
+  uint32_t* append_counters;  // kAppendGather of the same kind, kCounterStride apart
   uint32_t* decode_counters;  // kDecodeCounters of the same kind; null: decode calls take two launches
   uint32_t* router_counters;  // kRouterCounters of the same kind, one per sequence of a router call
   float* small;            // router scratch: pooled vectors and hidden activations
@@ -90,9 +91,12 @@ constexpr int kCounterStride = 32;            // words
 constexpr int kDecodeGather = 32;
 constexpr int kDecodeWgsShift = 8, kDecodeAlignedShift = 9;
 constexpr int kDecodeCounters = 1 + kDecodeGather + (1 << kDecodeAlignedShift);
+constexpr int kAppendGather = 16;             // words that the workgroups of an append count themselves on, each on a line of its own
 constexpr size_t kSmallBytes = 8u << 20;      // router: batch * (splits * hidden + inner) floats; decode: the rows of parts
 constexpr size_t kDecodeCountersAt = 4096;    // bytes
 constexpr size_t kHeaderBytes = kDecodeCountersAt + (kDecodeCounters * kCounterStride * 4 + 4095) / 4096 * 4096;   // status + counters
+constexpr size_t kAppendCountersAt = kDecodeCountersAt + kDecodeCounters * kCounterStride * 4;
+static_assert(kAppendCountersAt + kAppendGather * kCounterStride * 4 <= kHeaderBytes, "the counters of the append lie behind those of decode");
 constexpr int kPrefillWideMinRows = 32768;    // prefill launches whose longest prompt has at least this many rows use 256-row workgroups
 
 // ---- launchers (each validates nothing: flux_api.hip has done it) ---------------------------

@@ -21,22 +21,28 @@ struct AppendArgs {
   int batch, capacity, hkv, cpr_shift;     // 1 << cpr_shift chunks per row
   int total_new;
   int ring, n_sink, window;                // ring != 0: sink + ring rows, lengths are logical
-  uint32_t* counter;
+  uint32_t* counter;                       // workgroups (or words of `gather` whose workgroups) that have arrived
+  uint32_t* gather;                        // kAppendGather words that workgroups count themselves on
   uint32_t* status;
 };
 
 constexpr int kAppendTokens = 4;            // token rows a thread has in flight in a launch of more than kAppendFew workgroups
-constexpr int kAppendFew = 256;
+constexpr int kAppendFew = 4096;
 constexpr int kAppendTable = 1024;          // sequences whose lengths fit the table in LDS
-constexpr int kAppendBlocks = 512;          // workgroups at most
+constexpr uint32_t kAppendOneWord = 64;     // workgroups up to which all count themselves on one word
+static_assert(kAppendOneWord >= kAppendGather && 512 / kAppendTokens > kAppendOneWord, "every word of a launch that counts on several is used");
 
-// What bounds it: the copy where there is much to copy; else latencies and the arrival counter.  Every workgroup counts
-// itself on one word (some 10 ns each, one after the other), so there are few of them, each with four token rows per
-// thread in flight; and the lengths are read once into LDS, where a row's sequence is then looked up (looked up in global
-// memory for every row, that is a chain of 4 to 6 loads).  8 KV heads of 128: 1195 tokens of 4 sequences 10.4 -> 7.2 us,
-// 6466 tokens of 5 32 -> 18.3, 16384 tokens 44.5 -> 32, 32768 tokens 66.7 -> 56 (4.8 TB/s); 256 and 1024 workgroups: 21.7
-// and 22.6 for the 6466 tokens.
-template <int U>   // token rows a thread has in flight; with one, lengths are looked up in global memory
+// What bounds it: the copy where there is much to copy, else latencies.  Workgroups that count themselves on one word do
+// so one after the other, some 10 ns each, which 512 of them waited 5 us for; so each counts itself on one of 16 words, and
+// who completes a word on the last one (up to 64 workgroups the second step takes longer than it saves).  With that a token
+// row per thread and as many workgroups as that takes are fastest up to 4096 of them.  Longer copies keep four rows per
+// thread in flight and read the lengths into LDS once, where a row's sequence is looked up.  us on one word with at most
+// 256 such workgroups, and 512 of four rows / now, 8 KV heads of 128: 256 tokens 4.9 / 4.2, 512 6.4 / 4.4, 1195 tokens of 4
+// sequences 7.6 / 5.8, 2000 9.3 / 6.9, 6466 of 5 17.0 / 14.5, 8192 20.0 / 15.8 (4.3 TB/s), 600 of one token 8.4 / 6.0; 16384
+// 32.5 and 32768 56 (4.8 TB/s) as before.
+// U: token rows a thread has in flight (with one, lengths are looked up in global memory); ONE: the workgroups count
+// themselves on one word
+template <int U, bool ONE>
 __global__ __launch_bounds__(256) void kv_append_kernel(AppendArgs a) {
   __shared__ int is_last;
   __shared__ int s_cu[kAppendTable + 1], s_len[kAppendTable];
@@ -113,7 +119,17 @@ __global__ __launch_bounds__(256) void kv_append_kernel(AppendArgs a) {
   // fence is needed for this read-before-write order.
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (tid == 0) is_last = (atomicAdd(a.counter, 1u) == gridDim.x - 1);
+  if (tid == 0) {
+    const uint32_t n = gridDim.x;
+    bool last = true;
+    if (!ONE) {
+      const uint32_t x = blockIdx.x & (kAppendGather - 1);
+      uint32_t* word = a.gather + x * kCounterStride;
+      last = atomicAdd(word, 1u) == (n - x + kAppendGather - 1) / kAppendGather - 1;
+      if (last) *word = 0;                                   // ready for the next launch on this stream
+    }
+    is_last = last && atomicAdd(a.counter, 1u) == (ONE ? n : kAppendGather) - 1;
+  }
   __syncthreads();
   if (is_last) {
     for (int b = tid; b < a.batch; b += blockDim.x) {
@@ -148,19 +164,22 @@ hipError_t launch_kv_append(const Ctx& c, const flux_kv_cache& cache, int hkv, i
   a.n_sink = n_sink;
   a.window = window;
   a.counter = c.counters + 0;
+  a.gather = c.append_counters;
   a.status = c.status;
   const int cpt = hkv * (d / 8);
   const int tpi = 256 / (cpt < 256 ? cpt : 256);
-  // A launch of few workgroups with one token row per thread is as short as it gets (4 rows per thread and the table: 100
-  // tokens 4.3 against 3.0 us, one token 2.8 / 2.4); from there on the counter shows.  Many sequences take longer to look
-  // up, which more workgroups share: 600 sequences of one token 11.0 / 9.2, 200 of three 8.9 / 8.5, 1500 of one at 4 KV heads
-  // 12.9 / 10.8.
+  // One token row per thread up to 4096 workgroups (us with four and the table / with one: 1195 tokens 6.9 / 5.8, 6466 15.0 /
+  // 14.5, 32 x 200 15.0 / 14.5).  Many sequences take longer to look up in global memory, so there the table serves from 512
+  // on.  Four rows per thread: 1024 workgroups where that is one or two rounds (8192 tokens of 128 to 1024 sequences), 512 for more (32768
+  // tokens 56.0, with 1024 56.7).
   const long long single = ((long long)total_new + tpi - 1) / tpi;
-  if (single <= (cache.batch <= 128 ? kAppendFew : 2 * kAppendFew)) {
-    hipLaunchKernelGGL(kv_append_kernel<1>, dim3((unsigned)(single < 1 ? 1 : single)), dim3(256), 0, s, a);
+  if (single <= (cache.batch <= 128 ? kAppendFew : 512)) {
+    const dim3 grid((unsigned)(single < 1 ? 1 : single));
+    if (grid.x <= kAppendOneWord) hipLaunchKernelGGL((kv_append_kernel<1, true>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((kv_append_kernel<1, false>), grid, dim3(256), 0, s, a);
   } else {
-    const long long blocks = (single + kAppendTokens - 1) / kAppendTokens;
-    hipLaunchKernelGGL(kv_append_kernel<kAppendTokens>, dim3((unsigned)(blocks < kAppendBlocks ? blocks : kAppendBlocks)), dim3(256), 0, s, a);
+    const long long blocks = (single + kAppendTokens - 1) / kAppendTokens, most = blocks < 2048 ? 1024 : 512;
+    hipLaunchKernelGGL((kv_append_kernel<kAppendTokens, false>), dim3((unsigned)(blocks < most ? blocks : most)), dim3(256), 0, s, a);
   }
   return hipGetLastError();
 }

@@ -133,7 +133,7 @@ int flux_create(flux_ctx** out, int device, size_t workspace_bytes) {
   ctx->c.append_counters = (uint32_t*)(ctx->c.ws + kAppendCountersAt);
   ctx->c.decode_counters = (uint32_t*)(ctx->c.ws + kDecodeCountersAt);
   ctx->c.router_counters = (uint32_t*)(ctx->c.ws + 1024);
-  static_assert(1024 + 4 * kRouterCounters <= kDecodeCountersAt, "the counters must fit the header");
+  static_assert(1024 + 4 * kRouterCounters <= kDecodeCountersAt && 1024 + 4 * kRouterLines * kCounterStride <= kDecodeCountersAt, "the counters must fit the header");
   ctx->c.small = (float*)(ctx->c.ws + kHeaderBytes);
   ctx->c.partials = (float*)(ctx->c.ws + kHeaderBytes + kSmallBytes);
   ctx->c.partials_bytes = workspace_bytes - kHeaderBytes - kSmallBytes;

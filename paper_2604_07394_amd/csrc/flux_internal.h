@@ -84,6 +84,7 @@ __device__ __forceinline__ int window_start(int i, int shift, int win_blocks) {
 
 constexpr int kCounters = 64;
 constexpr int kRouterCounters = 512;
+constexpr int kRouterLines = 24;              // router calls of at most so many sequences have each counter on a line of its own
 // Arrival counters of the decode calls, each on a line of its own (counts on one line are taken one after the other, some
 // 10 ns each): words whose workgroups have all read the lengths; the words that workgroups count themselves on; one per
 // workgroup, for the pair that begins in its range and goes on behind it.

@@ -45,7 +45,7 @@ struct SplitArgs {
   int pps;                // (KV head, query block) pairs per sequence = hkv * qblocks
   int bump;               // 1: the call also appends one row per sequence, so every list is one key longer than kv_len says
   int block_shift;        // lists are cut into blocks of 2^block_shift keys
-  int aligned_shift;      // few blocks: one workgroup per 4 or 8 of a list while that takes at most 2^aligned_shift (see Cut)
+  int aligned_shift;      // few blocks: one workgroup per 4, 8 or 16 of a list while that takes at most 2^aligned_shift (see Cut)
 };
 
 struct DecodeArgs {
@@ -115,7 +115,7 @@ static_assert(kResidentUnits == 1 << kDecodeWgsShift, "every CU takes the same")
 // ---- the cut.  Blocks of all pairs, sequence by sequence and pair by pair, numbered from 0.  While they are few (one per
 // wave of two workgroups per CU) every list is rounded up to a multiple of 4 and a workgroup takes 4, so that none
 // crosses from one pair into the next; 8 where every list has no more than that (nothing to merge) or more than 64 (half
-// the rows to merge); otherwise the lists lie end to end as they are, and workgroup u takes
+// the rows to merge); 16 where many of the lists are short; otherwise the lists lie end to end as they are, and workgroup u takes
 // [range_begin(u), range_begin(u + 1)).
 struct Cut {
   int total;        // blocks
@@ -150,11 +150,11 @@ __device__ __forceinline__ int padded(Cut c, int nb) { return ((nb + (1 << c.ali
 __device__ __forceinline__ Cut find_cut(const SplitArgs& s, int lane, Lanes& r) {
   r.bad = false;
   Cut c = {0, 2};
-  for (;;) {                                                // (once with the lists rounded up, and again without if that is too many)
+  for (bool first = true;; first = false) {                 // (with the lists rounded up, and again if that is too many)
     int total = 0;
     for (int b0 = 0; b0 < s.batch; b0 += 64) {
       int len = 0, md = 1, nb = 0;
-      if (b0 == 0 && c.align == 0) {
+      if (b0 == 0 && !first) {
         len = r.len, md = r.md, nb = r.nb;
       } else if (b0 + lane < s.batch) {
         bool bad, sparse;
@@ -163,7 +163,7 @@ __device__ __forceinline__ Cut find_cut(const SplitArgs& s, int lane, Lanes& r) 
         nb = blocks_of(s, seq_visible(s, len, md, bad, sparse, s_end, tail_start));
         r.bad |= bad;
       }
-      if (b0 == 0 && c.align > 0) c.align = s.batch <= 64 && __builtin_amdgcn_ballot_w64(nb > 8 && nb <= 64) == 0 ? 3 : 2;
+      if (b0 == 0 && first) c.align = s.batch <= 64 && __builtin_amdgcn_ballot_w64(nb > 8 && nb <= 64) == 0 ? 3 : 2;
       const int incl = wave_inclusive_sum(s.pps * padded(c, nb));
       if (b0 == 0) {
         r.len = len;
@@ -175,7 +175,13 @@ __device__ __forceinline__ Cut find_cut(const SplitArgs& s, int lane, Lanes& r) 
     }
     c.total = total;
     if (c.align == 0 || total <= 1 << (s.aligned_shift + c.align)) return c;
-    c.align = 0;
+    // A range that holds several whole lists works them off one after the other, and each costs it the latency of its first
+    // rows: where a quarter of the lists are shorter than a range, 16 blocks of one list per workgroup instead, if that is
+    // not too many workgroups (us before / now, two layers of 32/8 heads of 128: 29 lists of 139 to 2305 keys, two thirds of
+    // them sparse, 69.8 / 55.7, 13 lists of 144 to 13696 keys 92.6 / 83; but four layers of 16 lists of 2112 keys 98 / 114, and
+    // 32 blocks per workgroup for 32 lists of 513 to 6295 keys 78 / 90)
+    const bool many_short = s.batch <= 64 && 4 * __builtin_popcountll(__builtin_amdgcn_ballot_w64(r.nb > 0 && r.nb < total >> kDecodeWgsShift)) >= s.batch;
+    c.align = first && many_short ? 4 : 0;
   }
 }
 

@@ -20,6 +20,7 @@ FA, SA = 1, 0
     (40, 2, 64, [4000, 0, 1, 3100, 2050]),                    # by eight blocks; two query blocks per KV head
     (16, 16, 64, [1024] * 4),                                 # by four: as many as there may be
     (16, 16, 64, [1024] * 4 + [1]),                           # ... and one list more: equal ranges
+    (16, 16, 64, [1500, 100, 1490, 70, 40, 1400, 0, 33]),     # by sixteen: half of the lists shorter than a range
     (4, 4, 128, [256, 224, 1]),                               # lists of up to eight blocks: one workgroup each
     (4, 4, 128, [256, 257, 1]),                               # ... and one of nine
     (6, 2, 128, [33000]),                                     # 32 columns of heads, parts in several runs of the merge

@@ -813,8 +813,9 @@ hipError_t launch_decode(const Ctx& c, const flux_attn_cfg& cfg, const void* q, 
   a.qblocks = (a.group + 15) / 16;
   a.rpu = plan.rpu;
   a.scale_log2 = scale * kLog2e;
-  a.table = (int*)c.partials;                                // the table sits in front of the rows
-  a.part_o = c.small && !plan.in_partials ? c.small : c.partials + plan.table_floats + 64;   // (64: the word behind the table)
+  a.table = (int*)c.partials;                                // (calls of two launches only)
+  const bool two_launches = !c.decode_counters;
+  a.part_o = two_launches || plan.in_partials ? c.partials + decode_rows_at(plan, two_launches) : c.small;
   a.part_ml = a.part_o + (size_t)2 * plan.wgs * plan.rpu * cfg.head_dim;
   a.status = c.status;
   a.arrived = c.decode_counters;

@@ -317,7 +317,7 @@ int flux_attn_decode_static(const flux_attn_cfg* cfg, const void* q, int max_kv_
   if (max_kv_len > cache->capacity) return FLUX_ECAPACITY;
   if (!aligned16(q) || !aligned16(out) || ((uintptr_t)status & 3u)) return FLUX_EINVAL;
   const DecodePlan p = plan_decode(*cfg, cache->batch, max_kv_len);
-  if (decode_partials_bytes(*cfg, p) > FLUX_STATIC_SCRATCH_BYTES - kStaticHeader) return FLUX_EWORKSPACE;
+  if (decode_static_bytes(*cfg, p) > FLUX_STATIC_SCRATCH_BYTES - kStaticHeader) return FLUX_EWORKSPACE;
   char* base = nullptr;
   const hipError_t es = static_scratch(&base);
   if (es != hipSuccess) return hip_fail(es);

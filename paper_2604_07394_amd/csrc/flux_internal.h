@@ -119,7 +119,8 @@ struct DecodePlan {
   int units;        // what the scratch is sized by: the units of a cut into chunks of kMinChunk keys and more
   int pps;          // (KV head, query block) pairs per sequence
   int rpu;          // partial rows of a unit
-  int table_floats; // 4-byte words in front of the partial rows that hold the cut as a table (rounded to 256 B)
+  int table_floats; // two 4-byte words per sequence (rounded to 256 B), which the documented size of the scratch counts
+  int table_words;  // calls of two launches: words in front of the rows that hold the cut as a table (rounded to 256 B)
   int wgs;          // workgroups launched
   int aligned_shift;   // log2 of the most where every one takes its keys from one list
   int block_shift;  // log2 of the keys of a block
@@ -138,6 +139,7 @@ inline DecodePlan plan_decode(const flux_attn_cfg& cfg, int batch, int max_kv_le
   p.units = (int)(by_len < by_target ? by_len : by_target);
   if (p.units < 1) p.units = 1;
   p.table_floats = (2 * batch + 63) / 64 * 64;
+  p.table_words = (2 * batch + 1 + 63) / 64 * 64;            // (two per sequence and one behind them, see write_cut_table)
   // a range leaves rows in two places at most (see part_place); never fewer workgroups than share the keys out otherwise
   static_assert(kDecodeAlignedShift > kDecodeWgsShift, "halved below");
   const long long by_four = pairs * ((keys + 127) / 128);
@@ -160,6 +162,15 @@ inline DecodePlan plan_decode(const flux_attn_cfg& cfg, int batch, int max_kv_le
 }
 inline size_t decode_partials_bytes(const flux_attn_cfg& cfg, const DecodePlan& p) {
   return ((size_t)p.table_floats + (size_t)p.units * p.rpu * (cfg.head_dim + 2)) * sizeof(float);
+}
+// Where the rows of parts begin in the partials, in floats: behind the table, which only calls of two launches leave there.
+// (A call of one launch that keeps its rows there takes at most `units` of them, all that decode_partials_bytes counts.)
+inline size_t decode_rows_at(const DecodePlan& p, bool two_launches) { return two_launches ? p.table_words : 0; }
+// Bytes of the static scratch that a call takes: the documented size, and what the table and the rows of parts take.
+inline size_t decode_static_bytes(const flux_attn_cfg& cfg, const DecodePlan& p) {
+  const size_t said = decode_partials_bytes(cfg, p);
+  const size_t used = (decode_rows_at(p, true) + (size_t)2 * p.wgs * p.rpu * (cfg.head_dim + 2)) * sizeof(float);
+  return said > used ? said : used;
 }
 // k_new / v_new != nullptr: the fused decode step (append one row per sequence, then attend: one launch instead of
 // two); needs c.decode_counters and a cache that is not a ring.

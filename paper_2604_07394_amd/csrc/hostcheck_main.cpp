@@ -11,6 +11,7 @@
 
 extern "C" const void *hostcheck_status, *hostcheck_partials, *hostcheck_counters;   // what the last decode launcher was given
 extern "C" int hostcheck_decode_wgs(const flux_attn_cfg* cfg, int batch, int max_kv_len);
+extern "C" int hostcheck_decode_in_partials(const flux_attn_cfg* cfg, int batch, int max_kv_len);
 extern "C" int hostcheck_decode_rows_fit(const flux_attn_cfg* cfg, int batch, int max_kv_len);
 
 static int failures = 0;
@@ -108,6 +109,22 @@ int main() {
   EXPECT(wgs(16, 1, 128, 1025, 100), 512);                  // ... and the partials
   EXPECT(wgs(40, 2, 64, 100, 1 << 20), 512);                // two query blocks
   EXPECT(wgs(8, 8, 64, INT_MAX / 16, INT_MAX), 512);
+  // rows in the partials that take all of what flux_workspace_needed counts (2 x 512 places, 1024 units), and shapes around
+  auto in_partials = [](int hq, int hkv, int batch, int keys) {
+    const flux_attn_cfg c = {hq, hkv, 128, 4, 16, 0.f, 0, 0};
+    EXPECT(hostcheck_decode_rows_fit(&c, batch, keys), 1);
+    return hostcheck_decode_in_partials(&c, batch, keys);
+  };
+  EXPECT(in_partials(16, 1, 8, 32768), 1);
+  EXPECT(in_partials(32, 2, 8, 16384), 1);
+  EXPECT(in_partials(64, 4, 1, 65536), 1);
+  EXPECT(in_partials(16, 1, 1024, 256), 1);
+  EXPECT(in_partials(16, 1, 8, 32513), 1);
+  EXPECT(in_partials(16, 1, 8, 32512), 0);                  // 1016 units
+  EXPECT(in_partials(16, 1, 32, 8192), 1);
+  EXPECT(in_partials(16, 1, 512, 512), 1);
+  for (int batch = 1; batch <= 2048; batch += batch < 40 ? 1 : 31)
+    for (int keys = 1; keys < 200000; keys += 1 + keys / 3) (void)in_partials(32, 2, batch, keys);
   // ---- append, ring, router
   EXPECT(flux_kv_append(ctx, &kc, 2, 128, p, p, pi, 10, 10, nullptr), FLUX_EHIP);
   EXPECT(flux_kv_append(ctx, &kc, 2, 128, p, p, pi, INT_MAX, INT_MAX, nullptr), FLUX_ECAPACITY);

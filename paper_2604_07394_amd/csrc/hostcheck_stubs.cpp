@@ -9,12 +9,19 @@ hipError_t hipGetDevice(int* device) { *device = 0; return hipSuccess; }
 hipError_t hipGetSymbolAddress(void** p, const void* symbol) { *p = const_cast<void*>(symbol); return hipSuccess; }
 // of the last launch_decode
 const void *hostcheck_status, *hostcheck_partials, *hostcheck_counters;
-// what a decode call launches, and what its parts leave behind against the room that the regions of a context have
+// what a decode call launches, and whether the rows that its parts leave behind end within what holds them: the small
+// region or the partials of a context whose workspace is exactly what flux_workspace_needed says, and the static scratch
+// where flux_attn_decode_static accepts the shape
 int hostcheck_decode_wgs(const flux_attn_cfg* cfg, int batch, int max_kv_len) { return flux::plan_decode(*cfg, batch, max_kv_len).wgs; }
+int hostcheck_decode_in_partials(const flux_attn_cfg* cfg, int batch, int max_kv_len) { return flux::plan_decode(*cfg, batch, max_kv_len).in_partials; }
 int hostcheck_decode_rows_fit(const flux_attn_cfg* cfg, int batch, int max_kv_len) {
   const flux::DecodePlan p = flux::plan_decode(*cfg, batch, max_kv_len);
   const size_t rows = (size_t)2 * p.wgs * p.rpu * (cfg->head_dim + 2) * sizeof(float);
-  return rows <= (p.in_partials ? flux::decode_partials_bytes(*cfg, p) - p.table_floats * sizeof(float) : flux::kSmallBytes);
+  const size_t partials = flux_workspace_needed(cfg, batch, max_kv_len) - flux::kHeaderBytes - flux::kSmallBytes;
+  const bool context = p.in_partials ? flux::decode_rows_at(p, false) * sizeof(float) + rows <= partials : rows <= flux::kSmallBytes;
+  const size_t scratch = FLUX_STATIC_SCRATCH_BYTES - 256;
+  const bool fixed = flux::decode_static_bytes(*cfg, p) > scratch || flux::decode_rows_at(p, true) * sizeof(float) + rows <= scratch;
+  return context && fixed;
 }
 }
 

@@ -78,3 +78,45 @@ def test_ranges_and_lists(hq, hkv, d, lens):
         assert torch.equal(again, out) and cache.kv_len.tolist() == [n + 1 for n in lens]
     assert F.flux_last_device_status(ctx) == 0
     F.flux_destroy(ctx)
+
+
+# 16 query heads per KV head of 128: the rows of 512 workgroups do not fit the small region.  Where the host's bounds allow 1024
+# units of 256 keys they go to the partials (which a workspace of the reported size has just the room for), otherwise 256
+# workgroups share the keys out.  The last case has its keys in the sequences at the end, behind empty ones.
+@pytest.mark.parametrize("hq,hkv,lens,bounds", [
+    (16, 1, [16300] * 8, (16301, 32768)),                     # 256 equal ranges / 512 workgroups by eight blocks, in the partials
+    (32, 2, [8100] * 8, (8101, 16384)),
+    (64, 4, [32768], (32769, 65536)),
+    (16, 1, [16300, 700, 0, 33, 9000, 1, 128, 4000], (16301, 32768)),   # equal ranges
+    (16, 1, [100 + i % 29 for i in range(505)], (129, 300)),  # more lists than workgroups whose rows fit
+    (16, 1, [0] * 384 + [512] * 128, (512, 600)),
+])
+def test_rows_of_sixteen_heads(hq, hkv, lens, bounds):
+    from paper_2604_07394_amd import binding as F
+    b, d, cap = len(lens), 128, max(max(bounds), max(lens) + 1)
+    g = torch.Generator(device="cuda").manual_seed(hq + b)
+    k, v = (torch.empty(b, hkv, cap, d, dtype=torch.bfloat16, device="cuda").normal_(generator=g) for _ in range(2))
+    q = torch.empty(b, hq, d, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    cache = F.KVCache(k, v, torch.tensor(lens, dtype=torch.int32, device="cuda"))
+    md = torch.full((b,), FA, dtype=torch.uint8, device="cuda")
+    cfg = F.attn_cfg(hq, hkv, d, 8, 3000, 0.0, 1)
+    rows = sorted({lens.index(n) for n in lens})[:3] + [b - 1]
+    want = {i: O.attention(q[i:i + 1].double().cpu().numpy(), k[i, :, :lens[i]].transpose(0, 1).double().cpu().numpy(),
+                           v[i, :, :lens[i]].transpose(0, 1).double().cpu().numpy(), FA, 8, 3000)[0] for i in rows if lens[i] > 0}
+    for bound in bounds:
+        ctx = F.flux_create(0, F.flux_workspace_needed(cfg, b, bound))
+        outs = []
+        for turn in range(3):
+            out = torch.full((b, hq, d), float("nan"), dtype=torch.float32, device="cuda")
+            if turn < 2:
+                F.flux_attn_decode(ctx, cfg, q, bound, cache, md, out)
+            else:
+                F.flux_attn_decode_static(cfg, q, bound, cache, md, out)
+            torch.cuda.synchronize()
+            outs.append(out)
+        assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+        assert all(n > 0 or not outs[0][i].any() for i, n in enumerate(lens))
+        for i in want:
+            H.assert_close(outs[0][i].cpu().numpy(), want[i], f"sequence {i} under bound {bound}")
+        assert F.flux_last_device_status(ctx) == 0
+        F.flux_destroy(ctx)

@@ -45,7 +45,7 @@ struct SplitArgs {
   int pps;                // (KV head, query block) pairs per sequence = hkv * qblocks
   int bump;               // 1: the call also appends one row per sequence, so every list is one key longer than kv_len says
   int block_shift;        // lists are cut into blocks of 2^block_shift keys
-  int aligned_shift;      // few blocks: one workgroup per 4, 8 or 16 of a list while that takes at most 2^aligned_shift (see Cut)
+  int aligned_shift;      // few blocks: one workgroup per 4, 8 or 16 of a list while that takes at most 2^aligned_shift (see Cut); < 0: not
 };
 
 struct DecodeArgs {
@@ -149,7 +149,7 @@ __device__ __forceinline__ int padded(Cut c, int nb) { return ((nb + (1 << c.ali
 
 __device__ __forceinline__ Cut find_cut(const SplitArgs& s, int lane, Lanes& r) {
   r.bad = false;
-  Cut c = {0, 2};
+  Cut c = {0, 0};
   for (bool first = true;; first = false) {                 // (with the lists rounded up, and again if that is too many)
     int total = 0;
     for (int b0 = 0; b0 < s.batch; b0 += 64) {
@@ -163,7 +163,7 @@ __device__ __forceinline__ Cut find_cut(const SplitArgs& s, int lane, Lanes& r) 
         nb = blocks_of(s, seq_visible(s, len, md, bad, sparse, s_end, tail_start));
         r.bad |= bad;
       }
-      if (b0 == 0 && first) c.align = s.batch <= 64 && __builtin_amdgcn_ballot_w64(nb > 8 && nb <= 64) == 0 ? 3 : 2;
+      if (b0 == 0 && first && s.aligned_shift >= 0) c.align = s.batch <= 64 && __builtin_amdgcn_ballot_w64(nb > 8 && nb <= 64) == 0 ? 3 : 2;
       const int incl = wave_inclusive_sum(s.pps * padded(c, nb));
       if (b0 == 0) {
         r.len = len;

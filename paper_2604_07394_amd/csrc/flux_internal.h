@@ -122,7 +122,7 @@ struct DecodePlan {
   int table_floats; // two 4-byte words per sequence (rounded to 256 B), which the documented size of the scratch counts
   int table_words;  // calls of two launches: words in front of the rows that hold the cut as a table (rounded to 256 B)
   int wgs;          // workgroups launched
-  int aligned_shift;   // log2 of the most where every one takes its keys from one list
+  int aligned_shift;   // log2 of the most where every one takes its keys from one list; < 0: never
   int block_shift;  // log2 of the keys of a block
   bool in_partials; // the rows of parts need the partials region (they fit the small one otherwise)
 };
@@ -155,9 +155,12 @@ inline DecodePlan plan_decode(const flux_attn_cfg& cfg, int batch, int max_kv_le
       p.wgs = 1 << p.aligned_shift;
     }
   }
-  // blocks are counted in 32 bits: where the bounds allow more of them, they are larger
+  // blocks are counted in 32 bits: where the bounds allow more of them, they are larger; and calls of very many lists do not
+  // round them up (by 16 blocks at most)
+  const bool rounded = pairs <= 1 << 20;
+  if (!rounded) p.aligned_shift = -1;
   p.block_shift = 5;
-  while (pairs * ((keys >> p.block_shift) + 4) > 0x7FFFFFFFll && p.block_shift < 30) ++p.block_shift;
+  while (pairs * ((keys >> p.block_shift) + (rounded ? 16 : 1)) > 0x7FFFFFFFll && p.block_shift < 30) ++p.block_shift;
   return p;
 }
 inline size_t decode_partials_bytes(const flux_attn_cfg& cfg, const DecodePlan& p) {

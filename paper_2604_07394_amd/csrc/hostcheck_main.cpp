@@ -12,6 +12,7 @@
 extern "C" const void *hostcheck_status, *hostcheck_partials, *hostcheck_counters;   // what the last decode launcher was given
 extern "C" int hostcheck_decode_wgs(const flux_attn_cfg* cfg, int batch, int max_kv_len);
 extern "C" int hostcheck_decode_in_partials(const flux_attn_cfg* cfg, int batch, int max_kv_len);
+extern "C" int hostcheck_decode_blocks_fit(const flux_attn_cfg* cfg, int batch, int max_kv_len);
 extern "C" int hostcheck_decode_rows_fit(const flux_attn_cfg* cfg, int batch, int max_kv_len);
 
 static int failures = 0;
@@ -97,6 +98,7 @@ int main() {
   auto wgs = [](int hq, int hkv, int d, int batch, int keys) {
     const flux_attn_cfg c = {hq, hkv, d, 4, 16, 0.f, 0, 0};
     EXPECT(hostcheck_decode_rows_fit(&c, batch, keys), 1);
+    EXPECT(hostcheck_decode_blocks_fit(&c, batch, keys), 1);
     return hostcheck_decode_wgs(&c, batch, keys);
   };
   EXPECT(wgs(4, 1, 128, 1, 0), 1);
@@ -109,6 +111,7 @@ int main() {
   EXPECT(wgs(16, 1, 128, 1025, 100), 512);                  // ... and the partials
   EXPECT(wgs(40, 2, 64, 100, 1 << 20), 512);                // two query blocks
   EXPECT(wgs(8, 8, 64, INT_MAX / 16, INT_MAX), 512);
+  EXPECT(wgs(1 << 22, 1 << 22, 64, 64, 32), 512);           // lists of one block: sixteen if rounded up
   // rows in the partials that take all of what flux_workspace_needed counts (2 x 512 places, 1024 units), and shapes around
   auto in_partials = [](int hq, int hkv, int batch, int keys) {
     const flux_attn_cfg c = {hq, hkv, 128, 4, 16, 0.f, 0, 0};

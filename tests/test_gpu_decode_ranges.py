@@ -120,3 +120,48 @@ def test_rows_of_sixteen_heads(hq, hkv, lens, bounds):
             H.assert_close(outs[0][i].cpu().numpy(), want[i], f"sequence {i} under bound {bound}")
         assert F.flux_last_device_status(ctx) == 0
         F.flux_destroy(ctx)
+
+
+@pytest.mark.parametrize("hq,hkv,d,n,batch", [(32, 8, 128, 4224, 8), (4, 1, 128, 32768, 2), (28, 4, 128, 2112, 16), (8, 2, 64, 700, 3), (16, 1, 64, 250, 2)])
+def test_the_error_of_a_list_is_that_of_its_sums(hq, hkv, d, n, batch):
+    """However a list is cut, its weights reach the result to 2^-16 (two bf16 terms, the second rounded from what eight bits
+    leave) and scores and sums are fp32.  The sum over keys of weight errors is against one of the weights themselves, both
+    with V's random signs: 2^-16 of the result at the most where they all lie on one side, and as much again for the scores'
+    exponents (2^-22 of a score of some 5 * log2(e), and the sums).  Weights of one bf16 term lie ten times above the bound."""
+    from paper_2604_07394_amd import binding as F
+    g = torch.Generator(device="cuda").manual_seed(n)
+    k, v = (torch.empty(batch, hkv, n, d, dtype=torch.bfloat16, device="cuda").normal_(generator=g) for _ in range(2))
+    q = torch.empty(batch, hq, d, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    out = torch.full((batch, hq, d), float("nan"), dtype=torch.float32, device="cuda")
+    ctx = F.flux_create(0)
+    F.flux_attn_decode(ctx, F.attn_cfg(hq, hkv, d, 0, 1, 0.0, 1), q, n, F.KVCache(k, v, torch.full((batch,), n, dtype=torch.int32, device="cuda")),
+                       torch.full((batch,), FA, dtype=torch.uint8, device="cuda"), out)
+    torch.cuda.synchronize()
+    for b in (0, batch - 1):
+        s = (q[b].double().cpu().view(hkv, -1, d) @ k[b].double().cpu().transpose(1, 2)) * d ** -0.5
+        want = (torch.softmax(s, -1) @ v[b].double().cpu()).view(hq, d)
+        err = float((out[b].cpu().double() - want).norm() / want.norm())
+        print(f"rel-L2 {err:.2e}")
+        assert err <= 2 * 2.0 ** -16
+    F.flux_destroy(ctx)
+
+
+def test_an_infinite_value_row_stays_infinite():
+    """A row of V that holds an infinity gives that infinity, whatever bits its weight has (one key: a weight of exactly 1;
+    32 equal keys: 1 each; 64 keys of different weights)."""
+    from paper_2604_07394_amd import binding as F
+    ctx = F.flux_create(0)
+    for n in (32, 64):
+        k = torch.zeros(1, 1, n, 64, dtype=torch.bfloat16, device="cuda")
+        if n == 64:
+            k.normal_(generator=torch.Generator(device="cuda").manual_seed(1))
+        v = torch.ones(1, 1, n, 64, dtype=torch.bfloat16, device="cuda")
+        v[0, 0, 5, 3], v[0, 0, 9, 4] = float("inf"), -float("inf")
+        out = torch.zeros(1, 4, 64, dtype=torch.float32, device="cuda")
+        F.flux_attn_decode(ctx, F.attn_cfg(4, 1, 64, 0, 1, 0.0, 1), torch.ones(1, 4, 64, dtype=torch.bfloat16, device="cuda"), n,
+                           F.KVCache(k, v, torch.tensor([n], dtype=torch.int32, device="cuda")), torch.ones(1, dtype=torch.uint8, device="cuda"), out)
+        torch.cuda.synchronize()
+        assert torch.isposinf(out[:, :, 3]).all() and torch.isneginf(out[:, :, 4]).all()
+        out[:, :, 3:5] = 1.0
+        assert torch.allclose(out, torch.ones_like(out), atol=1e-5)
+    F.flux_destroy(ctx)

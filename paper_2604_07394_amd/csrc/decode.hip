@@ -139,49 +139,93 @@ __device__ __forceinline__ int part_place(int first, int i) { return i == 0 ? 2 
 
 __device__ __forceinline__ int blocks_of(const SplitArgs& s, int nv) { return (nv >> s.block_shift) + ((nv & ((1 << s.block_shift) - 1)) != 0 ? 1 : 0); }
 
-// Lane i of the wave looks after sequences i, i + 64, ...; a batch of up to 64 takes one load per lane.
+// ---- the sequences of a call.  Lane i of every wave looks after `run` of them from i * run on: one each in a batch of up to
+// 64, which stays in registers; larger batches of up to kDecodeTable are read once, by all waves together, into a table in LDS.
+// (Read in groups of 64, each behind the one before it, for both passes of the cut and for every list that a range goes on to:
+// us before / now, 1000 lists of 20 to 200 keys at 28/4 heads 119.1 / 107.2, 512 of 50 to 300 at 32/8 130.9 / 127.0.)
+constexpr int kDecodeTable = 2048;
+struct Seq {
+  int len, md, nb;  // rows, mode bits (see load_seq), blocks
+};
+typedef FLUX_LDS u32x2 SeqTable;   // [run][64]: sequence i * run + j is entry j * 64 + i; its rows, and 4 * blocks + mode bits
+
+__device__ __forceinline__ Seq load_counted(const SplitArgs& s, int b, bool& bad) {
+  Seq q;
+  bool sparse;
+  int s_end, tail_start;
+  load_seq(s, b, q.len, q.md, bad);
+  q.nb = blocks_of(s, seq_visible(s, q.len, q.md, bad, sparse, s_end, tail_start));
+  return q;
+}
+__device__ __forceinline__ Seq seq_at(const SplitArgs& s, const SeqTable* table, int run, int i, int j) {
+  if (run * 64 <= kDecodeTable) {
+    const u32x2 e = table[j * 64 + i];
+    return Seq{(int)e[0], (int)(e[1] & 3), (int)(e[1] >> 2)};
+  }
+  bool bad;
+  return load_counted(s, i * run + j, bad);
+}
+
 struct Lanes {
-  int len, md, nb;  // of this lane's sequence among the first 64
-  int incl;         // blocks up to and including it
+  Seq q;            // batches of up to 64: this lane's sequence
+  int run;          // sequences of a lane
+  int incl;         // blocks up to and including this lane's
   bool bad;         // this lane saw a clamp trip
 };
 __device__ __forceinline__ int padded(Cut c, int nb) { return ((nb + (1 << c.align) - 1) >> c.align) << c.align; }
 
-__device__ __forceinline__ Cut find_cut(const SplitArgs& s, int lane, Lanes& r) {
+// (called by all waves of a workgroup, w: this one, of W)
+template <int W>
+__device__ __forceinline__ Cut find_cut(const SplitArgs& s, int lane, int w, SeqTable* table, Lanes& r) {
+  r.run = (s.batch + 63) >> 6;
   r.bad = false;
-  Cut c = {0, 0};
-  for (bool first = true;; first = false) {                 // (with the lists rounded up, and again if that is too many)
-    int total = 0;
-    for (int b0 = 0; b0 < s.batch; b0 += 64) {
-      int len = 0, md = 1, nb = 0;
-      if (b0 == 0 && !first) {
-        len = r.len, md = r.md, nb = r.nb;
-      } else if (b0 + lane < s.batch) {
-        bool bad, sparse;
-        int s_end, tail_start;
-        load_seq(s, b0 + lane, len, md, bad);
-        nb = blocks_of(s, seq_visible(s, len, md, bad, sparse, s_end, tail_start));
+  r.q = Seq{0, 1, 0};
+  if (r.run == 1) {
+    if (lane < s.batch) r.q = load_counted(s, lane, r.bad);
+  } else if (r.run * 64 <= kDecodeTable) {
+    for (int j = w; j < r.run; j += W) {
+      Seq q = {0, 1, 0};
+      bool bad = false;
+      if (lane * r.run + j < s.batch) q = load_counted(s, lane * r.run + j, bad);
+      table[j * 64 + lane] = u32x2{(uint32_t)q.len, (uint32_t)(4 * q.nb + q.md)};
+      r.bad |= bad;
+    }
+    __syncthreads();
+  }
+  // f(blocks) for every sequence of this lane
+  auto each = [&](auto f) __attribute__((always_inline)) {
+    if (r.run == 1) {
+      f(r.q.nb);
+    } else if (r.run * 64 <= kDecodeTable) {
+      for (int j = 0; j < r.run; ++j) f(seq_at(s, table, r.run, lane, j).nb);
+    } else {
+      for (int j = 0; j < r.run && lane * r.run + j < s.batch; ++j) {
+        bool bad = false;
+        f(load_counted(s, lane * r.run + j, bad).nb);
         r.bad |= bad;
       }
-      if (b0 == 0 && first && s.aligned_shift >= 0) c.align = s.batch <= 64 && __builtin_amdgcn_ballot_w64(nb > 8 && nb <= 64) == 0 ? 3 : 2;
-      const int incl = wave_inclusive_sum(s.pps * padded(c, nb));
-      if (b0 == 0) {
-        r.len = len;
-        r.md = md;
-        r.nb = nb;
-        r.incl = incl;
-      }
-      total += __builtin_amdgcn_readlane(incl, 63);
     }
-    c.total = total;
-    if (c.align == 0 || total <= 1 << (s.aligned_shift + c.align)) return c;
+  };
+  Cut c = {0, 0};
+  if (s.aligned_shift >= 0) {
+    bool between = false;
+    each([&](int nb) __attribute__((always_inline)) { between |= nb > 8 && nb <= 64; });
+    c.align = __builtin_amdgcn_ballot_w64(between) == 0 ? 3 : 2;
+  }
+  for (bool first = true;; first = false) {                 // (with the lists rounded up, and again if that is too many)
+    int mine = 0;
+    each([&](int nb) __attribute__((always_inline)) { mine += padded(c, nb); });
+    r.incl = wave_inclusive_sum(s.pps * mine);
+    c.total = __builtin_amdgcn_readlane(r.incl, 63);
+    if (c.align == 0 || c.total <= 1 << (s.aligned_shift + c.align)) return c;
     // A range that holds several whole lists works them off one after the other, and each costs it the latency of its first
     // rows: where a quarter of the lists are shorter than a range, 16 blocks of one list per workgroup instead, if that is
     // not too many workgroups (us before / now, two layers of 32/8 heads of 128: 29 lists of 139 to 2305 keys, two thirds of
     // them sparse, 69.8 / 55.7, 13 lists of 144 to 13696 keys 92.6 / 83; but four layers of 16 lists of 2112 keys 98 / 114, and
     // 32 blocks per workgroup for 32 lists of 513 to 6295 keys 78 / 90)
-    const bool many_short = s.batch <= 64 && 4 * __builtin_popcountll(__builtin_amdgcn_ballot_w64(r.nb > 0 && r.nb < total >> kDecodeWgsShift)) >= s.batch;
-    c.align = first && many_short ? 4 : 0;
+    int brief = 0;                                          // four for a list shorter than a range, less one for every list
+    each([&](int nb) __attribute__((always_inline)) { brief += nb == 0 ? 0 : nb < c.total >> kDecodeWgsShift ? 3 : -1; });
+    c.align = first && __builtin_amdgcn_readlane(wave_inclusive_sum(brief), 63) >= 0 ? 4 : 0;
   }
 }
 
@@ -191,45 +235,26 @@ struct Place {
   int begin;        // first block of its first pair
   int nb;           // blocks of a pair, as numbered
 };
-__device__ __forceinline__ Place find_place(const SplitArgs& s, Cut c, const Lanes& r, int lane, int x) {
+__device__ __forceinline__ Place find_place(const SplitArgs& s, Cut c, const Lanes& r, int lane, const SeqTable* table, int x) {
+  const int i = __builtin_amdgcn_readfirstlane(__builtin_popcountll(__builtin_amdgcn_ballot_w64(r.incl <= x)));   // whose lane
+  if (r.run == 1) {
+    const int nb = padded(c, __builtin_amdgcn_readlane(r.q.nb, i));
+    return Place{i, __builtin_amdgcn_readlane(r.q.len, i), __builtin_amdgcn_readlane(r.q.md, i), __builtin_amdgcn_readlane(r.incl, i) - s.pps * nb, nb};
+  }
   Place p = {0, 0, 1, 0, 1};
-  int base = 0;
-  for (int b0 = 0; b0 < s.batch; b0 += 64) {
-    int len = r.len, md = r.md, nb = padded(c, r.nb), incl = r.incl;
-    if (b0 > 0) {
-      len = 0, md = 1, nb = 0;
-      if (b0 + lane < s.batch) {
-        bool bad, sparse;
-        int s_end, tail_start;
-        load_seq(s, b0 + lane, len, md, bad);
-        nb = padded(c, blocks_of(s, seq_visible(s, len, md, bad, sparse, s_end, tail_start)));
-      }
-      incl = wave_inclusive_sum(s.pps * nb);
-    }
-    const int end = base + __builtin_amdgcn_readlane(incl, 63);
+  int base = i > 0 ? __builtin_amdgcn_readlane(r.incl, i - 1) : 0;
+  for (int j0 = 0; j0 < r.run; j0 += 64) {
+    Seq q = {0, 1, 0};
+    if (j0 + lane < r.run && i * r.run + j0 + lane < s.batch) q = seq_at(s, table, r.run, i, j0 + lane);
+    const int nb = padded(c, q.nb), incl = base + wave_inclusive_sum(s.pps * nb);
+    const int end = __builtin_amdgcn_readlane(incl, 63);
     if (x < end) {                                          // wave-uniform
-      const int i = __builtin_amdgcn_readfirstlane(__builtin_popcountll(__builtin_amdgcn_ballot_w64(base + incl <= x)));
-      p.b = b0 + i;
-      p.len = __builtin_amdgcn_readlane(len, i);
-      p.md = __builtin_amdgcn_readlane(md, i);
-      p.nb = __builtin_amdgcn_readlane(nb, i);
-      p.begin = base + __builtin_amdgcn_readlane(incl, i) - s.pps * p.nb;
+      const int j = __builtin_amdgcn_readfirstlane(__builtin_popcountll(__builtin_amdgcn_ballot_w64(incl <= x)));
+      p.nb = __builtin_amdgcn_readlane(nb, j);
+      p = Place{i * r.run + j0 + j, __builtin_amdgcn_readlane(q.len, j), __builtin_amdgcn_readlane(q.md, j), __builtin_amdgcn_readlane(incl, j) - s.pps * p.nb, p.nb};
       break;
     }
     base = end;
-  }
-  return p;
-}
-// The next sequence behind p that has keys (there is one).
-__device__ __forceinline__ Place next_place(const SplitArgs& s, Cut c, const Lanes& r, int lane, Place p) {
-  const int begin = p.begin + s.pps * p.nb;
-  if (s.batch <= 64) return find_place(s, c, r, lane, begin);
-  for (int b = p.b + 1; b < s.batch; ++b) {
-    bool bad, sparse;
-    int len, md, s_end, tail_start;
-    load_seq(s, b, len, md, bad);
-    const int nb = __builtin_amdgcn_readfirstlane(padded(c, blocks_of(s, seq_visible(s, len, md, bad, sparse, s_end, tail_start))));
-    if (nb > 0) return Place{b, __builtin_amdgcn_readfirstlane(len), __builtin_amdgcn_readfirstlane(md), begin, nb};
   }
   return p;
 }
@@ -382,9 +407,11 @@ __global__ __launch_bounds__(256, 2) void decode_splitk_kernel(DecodeArgs a) {
   const int wg = blockIdx.x;
 
   // ---- the range of this workgroup
+  __shared__ u32x2 s_seq[kDecodeTable];
+  SeqTable* const seqs = (SeqTable*)s_seq;
   Lanes lanes;
-  const Cut cut = find_cut(a.sp, l, lanes);
-  if (wg == 0 && w == 0 && lanes.bad) atomicOr(a.status, (uint32_t)FLUX_DEV_BAD_LENGTH);
+  const Cut cut = find_cut<W>(a.sp, l, w, seqs, lanes);
+  if (wg == 0 && lanes.bad) atomicOr(a.status, (uint32_t)FLUX_DEV_BAD_LENGTH);
   // FUSED: the workgroups count themselves, first on one of kDecodeGather words (a word takes some 10 ns per count), when
   // all their waves hold the lengths; the one that completes the count moves the lengths on.  Called by one wave, in two
   // steps: the answer to the first count is not waited for until there is nothing else to do.
@@ -412,7 +439,7 @@ __global__ __launch_bounds__(256, 2) void decode_splitk_kernel(DecodeArgs a) {
     if constexpr (!IN_PLACE) {
       // leaves the cut behind for the merge kernel, which then needs neither the lengths nor the scan
       if (w == 0) write_cut_table(a.sp, cut, l, a.table);
-    } else if (a.sp.batch > 64 || __builtin_amdgcn_ballot_w64(l < a.sp.batch && lanes.nb == 0) != 0) {
+    } else if (a.sp.batch > 64 || __builtin_amdgcn_ballot_w64(l < a.sp.batch && lanes.q.nb == 0) != 0) {
       // sequences without keys have no blocks: their rows are zero
       for (int b0 = 0; b0 < a.sp.batch; b0 += 64) {
         int len = 1, md;
@@ -441,7 +468,7 @@ __global__ __launch_bounds__(256, 2) void decode_splitk_kernel(DecodeArgs a) {
   }
   int at = range_begin(a.sp, cut, wg);
   const int range_end = range_begin(a.sp, cut, wg + 1);
-  Place place = find_place(a.sp, cut, lanes, l, at);
+  Place place = find_place(a.sp, cut, lanes, l, seqs, at);
   const int rows_at = (at - place.begin);
   int pair = __builtin_amdgcn_readfirstlane((int)((float)rows_at / (float)place.nb));   // (put right below: the quotient may be off by one)
   pair -= pair * place.nb > rows_at ? 1 : 0;
@@ -674,7 +701,7 @@ __global__ __launch_bounds__(256, 2) void decode_splitk_kernel(DecodeArgs a) {
     const bool more = at < range_end;
     if (more) {
       if (++pair == a.sp.pps) {
-        place = next_place(a.sp, cut, lanes, l, place);
+        place = find_place(a.sp, cut, lanes, l, seqs, place.begin + a.sp.pps * place.nb);   // (the next one that has keys)
         pair = 0;
       }
       set_part();

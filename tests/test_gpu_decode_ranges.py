@@ -18,6 +18,10 @@ FA, SA = 1, 0
 @pytest.mark.parametrize("hq,hkv,d,lens", [
     (8, 4, 64, [(i * 379) % 1500 for i in range(70)]),        # equal ranges over more than 64 sequences, some empty
     (40, 2, 64, [4000, 0, 1, 3100, 2050]),                    # by eight blocks; two query blocks per KV head
+    (2, 1, 64, [(i * 131) % 97 if i % 5 else 0 for i in range(2048)]),   # 32 sequences per lane, all that the table in LDS holds
+    (2, 1, 64, [(i * 131) % 97 if i % 5 else 0 for i in range(2049)]),   # ... and more
+    (4, 2, 128, [0] * 30 + [900] + [0] * 200 + [40, 3000] + [0] * 60),   # runs of empty caches between lists
+    (4, 4, 128, [256] * 65),                                  # more than 64 sequences: by eight, one workgroup each
     (16, 16, 64, [1024] * 4),                                 # by four: as many as there may be
     (16, 16, 64, [1024] * 4 + [1]),                           # ... and one list more: equal ranges
     (16, 16, 64, [1500, 100, 1490, 70, 40, 1400, 0, 33]),     # by sixteen: half of the lists shorter than a range
@@ -55,7 +59,7 @@ def test_ranges_and_lists(hq, hkv, d, lens):
     kf, vf, qf = O.bf16_to_f64(kb), O.bf16_to_f64(vb), O.bf16_to_f64(qb)
     at = 0
     for i, n in enumerate(lens):
-        if b < 10 or i % 7 == 0:
+        if b < 10 or i % (7 if b < 300 else 101) == 0 or n > 800:
             k1, v1 = np.concatenate([kf[at:at + n], kf[t + i:t + i + 1]]), np.concatenate([vf[at:at + n], vf[t + i:t + i + 1]])
             H.assert_close(out[i].cpu().numpy(), O.attention(qf[i:i + 1], k1, v1, modes[i], n_sink, window)[0], f"sequence {i} of {n + 1} keys")
         at += n

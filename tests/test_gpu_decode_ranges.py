@@ -169,3 +169,32 @@ def test_an_infinite_value_row_stays_infinite():
         out[:, :, 3:5] = 1.0
         assert torch.allclose(out, torch.ones_like(out), atol=1e-5)
     F.flux_destroy(ctx)
+
+
+@pytest.mark.parametrize("fp32", [0, 1])
+@pytest.mark.parametrize("lens", [[0], [0] * 70, [0] * 300 + [5], [0, 0, 700, 0] * 8, [3000] + [0] * 63, [0] * 64 + [3000]])
+def test_every_empty_cache_yields_zeros(lens, fp32):
+    """The rows of sequences without keys are shared out over the workgroups: all of them are written, by calls with and
+    without a context, where other workgroups have keys to stream and where nobody has."""
+    from paper_2604_07394_amd import binding as F
+    b, hq, hkv, d, cap = len(lens), 6, 2, 64, 3072
+    g = torch.Generator(device="cuda").manual_seed(b)
+    k, v = (torch.empty(b, hkv, cap, d, dtype=torch.bfloat16, device="cuda").normal_(generator=g) for _ in range(2))
+    q = torch.empty(b, hq, d, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    cache = F.KVCache(k, v, torch.tensor(lens, dtype=torch.int32, device="cuda"))
+    md = torch.tensor([FA if i % 2 else SA for i in range(b)], dtype=torch.uint8, device="cuda")
+    ctx, cfg = F.flux_create(0), F.attn_cfg(hq, hkv, d, 8, 3000, 0.0, fp32)
+    outs = []
+    for call in ("context", "static"):
+        out = torch.full((b, hq, d), float("nan"), dtype=torch.float32 if fp32 else torch.bfloat16, device="cuda")
+        if call == "context":
+            F.flux_attn_decode(ctx, cfg, q, cap, cache, md, out)
+        else:
+            F.flux_attn_decode_static(cfg, q, cap, cache, md, out)
+        torch.cuda.synchronize()
+        assert torch.isfinite(out.float()).all()
+        assert all(n > 0 or not out[i].any() for i, n in enumerate(lens)) and all(n == 0 or out[i].any() for i, n in enumerate(lens))
+        outs.append(out)
+    assert torch.equal(*outs)
+    assert F.flux_last_device_status(ctx) == 0
+    F.flux_destroy(ctx)

@@ -115,20 +115,21 @@ static_assert(kResidentUnits == 1 << kDecodeWgsShift, "every CU takes the same")
 // ---- the cut.  Blocks of all pairs, sequence by sequence and pair by pair, numbered from 0.  While they are few (one per
 // wave of two workgroups per CU) every list is rounded up to a multiple of 4 and a workgroup takes 4, so that none
 // crosses from one pair into the next; 8 where every list has no more than that (nothing to merge) or more than 64 (half
-// the rows to merge); 16 where many of the lists are short; otherwise the lists lie end to end as they are, and workgroup u takes
-// [range_begin(u), range_begin(u + 1)).
+// the rows to merge); 16 where many of the lists are short; otherwise the lists lie end to end as they are, and workgroup u of 256
+// or 512 takes [range_begin(u), range_begin(u + 1)).
 struct Cut {
   int total;        // blocks
+  int shift;        // equal shares: log2 of the workgroups
   int align;        // log2 of the blocks that a workgroup takes of a list; 0: an equal share of all lists
 };
-__device__ __forceinline__ int cut_wgs(const SplitArgs& s, Cut c) { return c.align > 0 ? c.total >> c.align : 1 << kDecodeWgsShift; }
+__device__ __forceinline__ int cut_wgs(const SplitArgs& s, Cut c) { return c.align > 0 ? c.total >> c.align : 1 << c.shift; }
 __device__ __forceinline__ int range_begin(const SplitArgs& s, Cut c, int u) {
-  return c.align > 0 ? u << c.align : (int)(((unsigned long long)(unsigned)u * (unsigned)c.total) >> kDecodeWgsShift);
+  return c.align > 0 ? u << c.align : (int)(((unsigned long long)(unsigned)u * (unsigned)c.total) >> c.shift);
 }
 // the workgroup whose range holds block x
 __device__ __forceinline__ int range_of(const SplitArgs& s, Cut c, int x) {
   if (c.align > 0) return x >> c.align;
-  int u = min((int)((float)x * ((float)(1 << kDecodeWgsShift) / (float)c.total)), (1 << kDecodeWgsShift) - 1);
+  int u = min((int)((float)x * ((float)(1 << c.shift) / (float)c.total)), (1 << c.shift) - 1);
   while (range_begin(s, c, u) > x) --u;
   while (range_begin(s, c, u + 1) <= x) ++u;
   return u;
@@ -206,7 +207,7 @@ __device__ __forceinline__ Cut find_cut(const SplitArgs& s, int lane, int w, Seq
       }
     }
   };
-  Cut c = {0, 0};
+  Cut c = {0, kDecodeWgsShift, 0};
   if (s.aligned_shift >= 0) {
     bool between = false;
     each([&](int nb) __attribute__((always_inline)) { between |= nb > 8 && nb <= 64; });
@@ -217,7 +218,7 @@ __device__ __forceinline__ Cut find_cut(const SplitArgs& s, int lane, int w, Seq
     each([&](int nb) __attribute__((always_inline)) { mine += padded(c, nb); });
     r.incl = wave_inclusive_sum(s.pps * mine);
     c.total = __builtin_amdgcn_readlane(r.incl, 63);
-    if (c.align == 0 || c.total <= 1 << (s.aligned_shift + c.align)) return c;
+    if (c.align == 0 || c.total <= 1 << (s.aligned_shift + c.align)) break;
     // A range that holds several whole lists works them off one after the other, and each costs it the latency of its first
     // rows: where a quarter of the lists are shorter than a range, 16 blocks of one list per workgroup instead, if that is
     // not too many workgroups (us before / now, two layers of 32/8 heads of 128: 29 lists of 139 to 2305 keys, two thirds of
@@ -227,6 +228,16 @@ __device__ __forceinline__ Cut find_cut(const SplitArgs& s, int lane, int w, Seq
     each([&](int nb) __attribute__((always_inline)) { brief += nb == 0 ? 0 : nb < c.total >> kDecodeWgsShift ? 3 : -1; });
     c.align = first && __builtin_amdgcn_readlane(wave_inclusive_sum(brief), 63) >= 0 ? 4 : 0;
   }
+  // Where there are as many lists as CUs, most ranges begin, end or cross from one list into the next several times, and a
+  // CU stands still at each seam: two workgroups per CU then, if so many were launched (us with one / two, 32/8 heads of 128: 128
+  // lists of 300 keys 39.9 / 35.9, 128 of 100 to 3000 61.8 / 52.7, 100 of 100 to 8000 147 / 126, 1000 of 20 to 200 at 28/4
+  // heads 107 / 83; but 16 lists of 2112, 128 in all, 29.0 / 30.6)
+  if (c.align == 0 && gridDim.x >= 2 << kDecodeWgsShift) {
+    int lists = 0;
+    each([&](int nb) __attribute__((always_inline)) { lists += nb != 0 ? s.pps : 0; });
+    if (__builtin_amdgcn_readlane(wave_inclusive_sum(lists), 63) >= 1 << kDecodeWgsShift) c.shift = kDecodeWgsShift + 1;
+  }
+  return c;
 }
 
 // The sequence whose lists hold block x (x < total).
@@ -259,7 +270,7 @@ __device__ __forceinline__ Place find_place(const SplitArgs& s, Cut c, const Lan
   return p;
 }
 
-// The cut as a table, for the merge kernel: entry b = (first block, blocks per pair) of sequence b; behind them, align.
+// The cut as a table, for the merge kernel: entry b = (first block, blocks per pair) of sequence b; behind them, shift and align.
 __device__ __forceinline__ void write_cut_table(const SplitArgs& s, Cut c, int lane, int* table) {
   for (int b0 = 0, base = 0; b0 < s.batch; b0 += 64) {
     int nb = 0;
@@ -276,7 +287,7 @@ __device__ __forceinline__ void write_cut_table(const SplitArgs& s, Cut c, int l
     }
     base += __builtin_amdgcn_readlane(incl, 63);
   }
-  if (lane == 0) table[2 * s.batch] = c.align;
+  if (lane == 0) table[2 * s.batch] = 16 * c.shift + c.align;
 }
 
 // ---- rows that pass between workgroups of one launch, which may sit on different XCDs: written and read at device
@@ -816,7 +827,8 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(CombineArgs a) {
   }
   Cut cut;
   cut.total = a.table[2 * a.sp.batch - 2] + a.sp.pps * a.table[2 * a.sp.batch - 1];
-  cut.align = a.table[2 * a.sp.batch];
+  cut.shift = a.table[2 * a.sp.batch] >> 4;
+  cut.align = a.table[2 * a.sp.batch] & 15;
   const int first = range_of(a.sp, cut, begin), parts = range_of(a.sp, cut, begin + nb - 1) - first + 1;
   if (parts < 2) return;                                    // done by the first kernel
   merge_pair<D, false>(a.part_o, a.part_ml, a.rpu, first, parts, nq, a.scale_log2, smem, w, l, store_out);

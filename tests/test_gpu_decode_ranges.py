@@ -21,6 +21,8 @@ FA, SA = 1, 0
     (2, 1, 64, [(i * 131) % 97 if i % 5 else 0 for i in range(2048)]),   # 32 sequences per lane, all that the table in LDS holds
     (2, 1, 64, [(i * 131) % 97 if i % 5 else 0 for i in range(2049)]),   # ... and more
     (4, 2, 128, [0] * 30 + [900] + [0] * 200 + [40, 3000] + [0] * 60),   # runs of empty caches between lists
+    (4, 4, 128, [900, 340, 1200] * 22),                       # 264 lists: 512 equal ranges
+    (4, 4, 128, [900, 340, 1200] * 21),                       # 252: 256 of them
     (4, 4, 128, [256] * 65),                                  # more than 64 sequences: by eight, one workgroup each
     (16, 16, 64, [1024] * 4),                                 # by four: as many as there may be
     (16, 16, 64, [1024] * 4 + [1]),                           # ... and one list more: equal ranges

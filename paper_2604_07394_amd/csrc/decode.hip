@@ -237,6 +237,9 @@ __device__ __forceinline__ Cut find_cut(const SplitArgs& s, int lane, int w, Seq
     each([&](int nb) __attribute__((always_inline)) { lists += nb != 0 ? s.pps : 0; });
     if (__builtin_amdgcn_readlane(wave_inclusive_sum(lists), 63) >= 1 << kDecodeWgsShift) c.shift = kDecodeWgsShift + 1;
   }
+  // (lists that are not rounded up may have fewer blocks than there are workgroups: no range is empty, or it would be counted
+  // among the parts of a list)
+  while (c.align == 0 && c.shift > 0 && c.total >> c.shift == 0) --c.shift;
   return c;
 }
 

@@ -200,3 +200,31 @@ def test_every_empty_cache_yields_zeros(lens, fp32):
     assert torch.equal(*outs)
     assert F.flux_last_device_status(ctx) == 0
     F.flux_destroy(ctx)
+
+
+def test_more_than_a_million_lists_with_few_keys():
+    """Above 2^20 lists nothing is rounded up, so that the live ones may have fewer blocks than there are workgroups: 256 of
+    them would hold empty ranges between the blocks of a list, which nobody counts."""
+    from paper_2604_07394_amd import binding as F
+    b, h, d, cap = 131073, 8, 64, 200
+    live = {0: 130, 1: 1, 77777: 200, b - 1: 65}
+    k, v = (torch.empty(4, h, cap, d, dtype=torch.bfloat16, device="cuda").normal_(generator=torch.Generator(device="cuda").manual_seed(i)) for i in range(2))
+    cache = F.KVCache(k[:1].expand(b, h, cap, d), v[:1].expand(b, h, cap, d), torch.zeros(b, dtype=torch.int32, device="cuda"))
+    q = torch.zeros(b, h, d, dtype=torch.bfloat16, device="cuda").normal_(generator=torch.Generator(device="cuda").manual_seed(2))
+    cfg = F.attn_cfg(h, h, d, 0, 1, 0.0, 1)
+    ctx = F.flux_create(0, F.flux_workspace_needed(cfg, b, cap))
+    md = torch.ones(b, dtype=torch.uint8, device="cuda")
+    out = torch.full((b, h, d), float("nan"), dtype=torch.float32, device="cuda")
+    for lens in (live, {5: 33}, {i: 190 for i in range(0, b, 3000)}):
+        cache.kv_len.zero_()
+        cache.kv_len[torch.tensor(list(lens), device="cuda")] = torch.tensor(list(lens.values()), dtype=torch.int32, device="cuda")
+        for _ in range(2):
+            out.fill_(float("nan"))
+            F.flux_attn_decode(ctx, cfg, q, cap, cache, md, out)
+            torch.cuda.synchronize()
+            assert torch.isfinite(out).all() and int((out.abs().sum((1, 2)) > 0).sum()) == len(lens)
+            for i, n in lens.items():
+                s = (q[i].double().cpu()[:, None] @ k[0, :, :n].double().cpu().transpose(1, 2))[:, 0] * d ** -0.5
+                H.assert_close(out[i].cpu().numpy(), (torch.softmax(s, -1)[:, None] @ v[0, :, :n].double().cpu())[:, 0].numpy(), f"sequence {i}")
+    assert F.flux_last_device_status(ctx) == 0
+    F.flux_destroy(ctx)

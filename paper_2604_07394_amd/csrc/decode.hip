@@ -115,12 +115,14 @@ static_assert(kResidentUnits == 1 << kDecodeWgsShift, "every CU takes the same")
 // ---- the cut.  Blocks of all pairs, sequence by sequence and pair by pair, numbered from 0.  While they are few (one per
 // wave of two workgroups per CU) every list is rounded up to a multiple of 4 and a workgroup takes 4, so that none
 // crosses from one pair into the next; 8 where every list has no more than that (nothing to merge) or more than 64 (half
-// the rows to merge); 16 where many of the lists are short; otherwise the lists lie end to end as they are, and workgroup u of 256
-// or 512 takes [range_begin(u), range_begin(u + 1)).
+// the rows to merge).  Otherwise the lists lie end to end, and workgroup u of 256 or 512 takes [range_begin(u),
+// range_begin(u + 1)): equal shares not of the blocks but of what they take, for which a list is counted as a multiple of
+// the four waves and kSeam blocks more (see find_cut).
 struct Cut {
   int total;        // blocks
   int shift;        // equal shares: log2 of the workgroups
   int align;        // log2 of the blocks that a workgroup takes of a list; 0: an equal share of all lists
+  int round, pad;   // a list of nb blocks is counted as nb rounded up to a multiple of round + 1, and pad more
 };
 __device__ __forceinline__ int cut_wgs(const SplitArgs& s, Cut c) { return c.align > 0 ? c.total >> c.align : 1 << c.shift; }
 __device__ __forceinline__ int range_begin(const SplitArgs& s, Cut c, int u) {
@@ -173,11 +175,23 @@ struct Lanes {
   int incl;         // blocks up to and including this lane's
   bool bad;         // this lane saw a clamp trip
 };
-__device__ __forceinline__ int padded(Cut c, int nb) { return ((nb + (1 << c.align) - 1) >> c.align) << c.align; }
+__device__ __forceinline__ int counted(Cut c, int nb) { return nb > 0 ? ((nb + c.round) & ~c.round) + c.pad : 0; }
 
 // (called by all waves of a workgroup, w: this one, of W)
-template <int W>
+template <int D, int W>
 __device__ __forceinline__ Cut find_cut(const SplitArgs& s, int lane, int w, SeqTable* table, Lanes& r) {
+  // Going on from one list to the next, a workgroup stands still for a memory latency and the merge of its waves, about as long
+  // as four blocks of head dimension 128 take, and for up to three waves without a block.  Ranges of equally many blocks that
+  // held whole lists, such as the eight sparse ones of a sequence among long ones, were the last ones of their call: us
+  // before / now per layer, 32/8 heads of 128: 13 lists of 1223 to 15370 keys, half of them cut at 144, 42.5 / 32.0, 32 ragged ones at
+  // 28/4 heads 40.1 / 36.9, 16 ring lists of 2112 at 28/4 25.0 / 23.7, 13 of 144 to 13696 37.1 / 33.7, 29 of 139 to 2305 26.8
+  // / 26.3, 21 of 296 to 4373 at head dimension 64 23.4 / 18.7.  (3 to 6 blocks, and 5 to 12 at head dimension 64, differ by 2 %.)
+  constexpr int kSeam = 512 / D;
+  // Two workgroups per CU where there are as many lists as CUs, since at most seams the other one goes on (us with one / two,
+  // 32/8 heads of 128: 128 lists of 300 keys 39.9 / 34.5, 128 of 100 to 3000 61.8 / 52.6, 1000 of 20 to 200 at 28/4 heads 107 /
+  // 82; but 16 lists of 2112, 128 in all, 29.4 / 31.0, 8 x 131072 629 / 665).  At head dimension 64 from a quarter of that on:
+  // one workgroup has half the bytes in flight there (21 sequences of 296 to 4373 keys 22.8 / 20.5).
+  constexpr int kLists = D == 64 ? 64 : 256;
   r.run = (s.batch + 63) >> 6;
   r.bad = false;
   r.q = Seq{0, 1, 0};
@@ -193,11 +207,39 @@ __device__ __forceinline__ Cut find_cut(const SplitArgs& s, int lane, int w, Seq
     }
     __syncthreads();
   }
-  // f(blocks) for every sequence of this lane
-  auto each = [&](auto f) __attribute__((always_inline)) {
-    if (r.run == 1) {
-      f(r.q.nb);
-    } else if (r.run * 64 <= kDecodeTable) {
+  // each(f): f(blocks) for every sequence of this lane
+  auto take = [&](auto each) __attribute__((always_inline)) {
+    Cut c = {0, kDecodeWgsShift, 0, 0, 0};
+    if (s.aligned_shift >= 0) {
+      bool between = false;
+      each([&](int nb) __attribute__((always_inline)) { between |= nb > 8 && nb <= 64; });
+      c.align = __builtin_amdgcn_ballot_w64(between) == 0 ? 3 : 2;
+      c.round = (1 << c.align) - 1;
+    }
+    for (;;) {                                              // (rounded up for workgroups of one list, and for ranges if that is too many)
+      int mine = 0;
+      each([&](int nb) __attribute__((always_inline)) { mine += counted(c, nb); });
+      r.incl = wave_inclusive_sum(s.pps * mine);
+      c.total = __builtin_amdgcn_readlane(r.incl, 63);
+      if (c.align == 0 || c.total <= 1 << (s.aligned_shift + c.align)) break;
+      c.align = 0;
+      c.round = W - 1;
+      c.pad = kSeam;
+    }
+    if (c.align > 0) return c;
+    if (gridDim.x >= 2 << kDecodeWgsShift) {
+      int lists = 0;
+      each([&](int nb) __attribute__((always_inline)) { lists += nb != 0 ? s.pps : 0; });
+      if (__builtin_amdgcn_readlane(wave_inclusive_sum(lists), 63) >= kLists) c.shift = kDecodeWgsShift + 1;
+    }
+    // (lists that are not rounded up may have fewer blocks than there are workgroups: no range is empty, or it would be
+    // counted among the parts of a list)
+    while (c.shift > 0 && c.total >> c.shift == 0) --c.shift;
+    return c;
+  };
+  if (__builtin_expect(r.run == 1, 1)) return take([&](auto f) __attribute__((always_inline)) { f(r.q.nb); });
+  return take([&](auto f) __attribute__((always_inline)) {
+    if (r.run * 64 <= kDecodeTable) {
       for (int j = 0; j < r.run; ++j) f(seq_at(s, table, r.run, lane, j).nb);
     } else {
       for (int j = 0; j < r.run && lane * r.run + j < s.batch; ++j) {
@@ -206,66 +248,33 @@ __device__ __forceinline__ Cut find_cut(const SplitArgs& s, int lane, int w, Seq
         r.bad |= bad;
       }
     }
-  };
-  Cut c = {0, kDecodeWgsShift, 0};
-  if (s.aligned_shift >= 0) {
-    bool between = false;
-    each([&](int nb) __attribute__((always_inline)) { between |= nb > 8 && nb <= 64; });
-    c.align = __builtin_amdgcn_ballot_w64(between) == 0 ? 3 : 2;
-  }
-  for (bool first = true;; first = false) {                 // (with the lists rounded up, and again if that is too many)
-    int mine = 0;
-    each([&](int nb) __attribute__((always_inline)) { mine += padded(c, nb); });
-    r.incl = wave_inclusive_sum(s.pps * mine);
-    c.total = __builtin_amdgcn_readlane(r.incl, 63);
-    if (c.align == 0 || c.total <= 1 << (s.aligned_shift + c.align)) break;
-    // A range that holds several whole lists works them off one after the other, and each costs it the latency of its first
-    // rows: where a quarter of the lists are shorter than a range, 16 blocks of one list per workgroup instead, if that is
-    // not too many workgroups (us before / now, two layers of 32/8 heads of 128: 29 lists of 139 to 2305 keys, two thirds of
-    // them sparse, 69.8 / 55.7, 13 lists of 144 to 13696 keys 92.6 / 83; but four layers of 16 lists of 2112 keys 98 / 114, and
-    // 32 blocks per workgroup for 32 lists of 513 to 6295 keys 78 / 90)
-    int brief = 0;                                          // four for a list shorter than a range, less one for every list
-    each([&](int nb) __attribute__((always_inline)) { brief += nb == 0 ? 0 : nb < c.total >> kDecodeWgsShift ? 3 : -1; });
-    c.align = first && __builtin_amdgcn_readlane(wave_inclusive_sum(brief), 63) >= 0 ? 4 : 0;
-  }
-  // Where there are as many lists as CUs, most ranges begin, end or cross from one list into the next several times, and a
-  // CU stands still at each seam: two workgroups per CU then, if so many were launched (us with one / two, 32/8 heads of 128: 128
-  // lists of 300 keys 39.9 / 35.9, 128 of 100 to 3000 61.8 / 52.7, 100 of 100 to 8000 147 / 126, 1000 of 20 to 200 at 28/4
-  // heads 107 / 83; but 16 lists of 2112, 128 in all, 29.0 / 30.6)
-  if (c.align == 0 && gridDim.x >= 2 << kDecodeWgsShift) {
-    int lists = 0;
-    each([&](int nb) __attribute__((always_inline)) { lists += nb != 0 ? s.pps : 0; });
-    if (__builtin_amdgcn_readlane(wave_inclusive_sum(lists), 63) >= 1 << kDecodeWgsShift) c.shift = kDecodeWgsShift + 1;
-  }
-  // (lists that are not rounded up may have fewer blocks than there are workgroups: no range is empty, or it would be counted
-  // among the parts of a list)
-  while (c.align == 0 && c.shift > 0 && c.total >> c.shift == 0) --c.shift;
-  return c;
+  });
 }
 
 // The sequence whose lists hold block x (x < total).
 struct Place {
   int b, len, md;
   int begin;        // first block of its first pair
-  int nb;           // blocks of a pair, as numbered
+  int nb;           // blocks of a pair, as counted
+  int real;         // ... that there are
 };
 __device__ __forceinline__ Place find_place(const SplitArgs& s, Cut c, const Lanes& r, int lane, const SeqTable* table, int x) {
   const int i = __builtin_amdgcn_readfirstlane(__builtin_popcountll(__builtin_amdgcn_ballot_w64(r.incl <= x)));   // whose lane
   if (r.run == 1) {
-    const int nb = padded(c, __builtin_amdgcn_readlane(r.q.nb, i));
-    return Place{i, __builtin_amdgcn_readlane(r.q.len, i), __builtin_amdgcn_readlane(r.q.md, i), __builtin_amdgcn_readlane(r.incl, i) - s.pps * nb, nb};
+    const int real = __builtin_amdgcn_readlane(r.q.nb, i), nb = counted(c, real);
+    return Place{i, __builtin_amdgcn_readlane(r.q.len, i), __builtin_amdgcn_readlane(r.q.md, i), __builtin_amdgcn_readlane(r.incl, i) - s.pps * nb, nb, real};
   }
-  Place p = {0, 0, 1, 0, 1};
+  Place p = {0, 0, 1, 0, 1, 1};
   int base = i > 0 ? __builtin_amdgcn_readlane(r.incl, i - 1) : 0;
   for (int j0 = 0; j0 < r.run; j0 += 64) {
     Seq q = {0, 1, 0};
     if (j0 + lane < r.run && i * r.run + j0 + lane < s.batch) q = seq_at(s, table, r.run, i, j0 + lane);
-    const int nb = padded(c, q.nb), incl = base + wave_inclusive_sum(s.pps * nb);
+    const int nb = counted(c, q.nb), incl = base + wave_inclusive_sum(s.pps * nb);
     const int end = __builtin_amdgcn_readlane(incl, 63);
     if (x < end) {                                          // wave-uniform
       const int j = __builtin_amdgcn_readfirstlane(__builtin_popcountll(__builtin_amdgcn_ballot_w64(incl <= x)));
       p.nb = __builtin_amdgcn_readlane(nb, j);
-      p = Place{i * r.run + j0 + j, __builtin_amdgcn_readlane(q.len, j), __builtin_amdgcn_readlane(q.md, j), __builtin_amdgcn_readlane(incl, j) - s.pps * p.nb, p.nb};
+      p = Place{i * r.run + j0 + j, __builtin_amdgcn_readlane(q.len, j), __builtin_amdgcn_readlane(q.md, j), __builtin_amdgcn_readlane(incl, j) - s.pps * p.nb, p.nb, __builtin_amdgcn_readlane(q.nb, j)};
       break;
     }
     base = end;
@@ -273,7 +282,7 @@ __device__ __forceinline__ Place find_place(const SplitArgs& s, Cut c, const Lan
   return p;
 }
 
-// The cut as a table, for the merge kernel: entry b = (first block, blocks per pair) of sequence b; behind them, shift and align.
+// The cut as a table, for the merge kernel: entry b = (first block, blocks per pair) of sequence b; behind them, the cut.
 __device__ __forceinline__ void write_cut_table(const SplitArgs& s, Cut c, int lane, int* table) {
   for (int b0 = 0, base = 0; b0 < s.batch; b0 += 64) {
     int nb = 0;
@@ -281,16 +290,23 @@ __device__ __forceinline__ void write_cut_table(const SplitArgs& s, Cut c, int l
       bool bad, sparse;
       int len, md, s_end, tail_start;
       load_seq(s, b0 + lane, len, md, bad);
-      nb = padded(c, blocks_of(s, seq_visible(s, len, md, bad, sparse, s_end, tail_start)));
+      nb = blocks_of(s, seq_visible(s, len, md, bad, sparse, s_end, tail_start));
     }
-    const int incl = wave_inclusive_sum(s.pps * nb);
+    const int incl = wave_inclusive_sum(s.pps * counted(c, nb));
     if (b0 + lane < s.batch) {
-      table[2 * (b0 + lane)] = base + incl - s.pps * nb;
+      table[2 * (b0 + lane)] = base + incl - s.pps * counted(c, nb);
       table[2 * (b0 + lane) + 1] = nb;
     }
     base += __builtin_amdgcn_readlane(incl, 63);
   }
-  if (lane == 0) table[2 * s.batch] = 16 * c.shift + c.align;
+  if (lane == 0) {
+    int* const t = table + 2 * s.batch;
+    t[0] = c.total;
+    t[1] = c.shift;
+    t[2] = c.align;
+    t[3] = c.round;
+    t[4] = c.pad;
+  }
 }
 
 // ---- rows that pass between workgroups of one launch, which may sit on different XCDs: written and read at device
@@ -424,7 +440,7 @@ __global__ __launch_bounds__(256, 2) void decode_splitk_kernel(DecodeArgs a) {
   __shared__ u32x2 s_seq[kDecodeTable];
   SeqTable* const seqs = (SeqTable*)s_seq;
   Lanes lanes;
-  const Cut cut = find_cut<W>(a.sp, l, w, seqs, lanes);
+  const Cut cut = find_cut<D, W>(a.sp, l, w, seqs, lanes);
   if (wg == 0 && lanes.bad) atomicOr(a.status, (uint32_t)FLUX_DEV_BAD_LENGTH);
   // FUSED: the workgroups count themselves, first on one of kDecodeGather words (a word takes some 10 ns per count), when
   // all their waves hold the lengths; the one that completes the count moves the lengths on.  Called by one wave, in two
@@ -505,7 +521,7 @@ __global__ __launch_bounds__(256, 2) void decode_splitk_kernel(DecodeArgs a) {
     const int kvh = a.qblocks == 1 ? pair : pair / a.qblocks;
     const int begin = place.begin + pair * place.nb;
     x0 = at - begin;
-    x1 = min(place.nb, range_end - begin);
+    x1 = min(place.real, range_end - begin);
     bool bad = false, sparse;
     int s_end, tail_start;
     c1 = seq_visible(a.sp, place.len, place.md, bad, sparse, s_end, tail_start);
@@ -717,10 +733,11 @@ __global__ __launch_bounds__(256, 2) void decode_splitk_kernel(DecodeArgs a) {
     const int nq = min(16, e->group - (e->qblocks == 1 ? 0 : 16 * (pair % e->qblocks)));
     const int64_t out0 = ((int64_t)place.b * e->hq + (int64_t)(e->qblocks == 1 ? pair : pair / e->qblocks) * e->group + (e->qblocks == 1 ? 0 : 16 * (pair % e->qblocks))) * D;
     const int list0 = place.begin + pair * place.nb;
-    const bool whole = x0 == 0 && x1 == place.nb;           // the pair lies in this range
+    const bool empty = x0 >= x1;                            // (the range begins in what is only counted behind a list)
+    const bool whole = empty || (x0 == 0 && x1 == place.real);   // the pair lies in this range
     const int first = whole ? wg : range_of(a.sp, cut, list0);
-    const int parts = whole ? 1 : range_of(a.sp, cut, list0 + place.nb - 1) - first + 1;
-    at = list0 + x1;
+    const int parts = whole ? 1 : range_of(a.sp, cut, list0 + place.real - 1) - first + 1;
+    at = x1 < place.real ? range_end : list0 + place.nb;
     const bool more = at < range_end;
     if (more) {
       if (++pair == a.sp.pps) {
@@ -750,7 +767,7 @@ __global__ __launch_bounds__(256, 2) void decode_splitk_kernel(DecodeArgs a) {
       else *(u32x2*)((__bf16*)e->out + off) = u32x2{pack_bf16(r[0], r[1]), pack_bf16(r[2], r[3])};
     };
     const int row0 = part_place(first, wg - first) * e->rpu;
-    for (int idx = tid; idx < nq * (D / 4); idx += 64 * W) {
+    for (int idx = tid; !empty && idx < nq * (D / 4); idx += 64 * W) {
       const int qi = idx / (D / 4), d = 4 * (idx % (D / 4));
       f32x2 x[W];
       float m = -INFINITY;
@@ -817,7 +834,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(CombineArgs a) {
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, pair = blockIdx.x, b = blockIdx.y;
   const int kvh = pair / a.qblocks, qb = pair - kvh * a.qblocks;
   const int nq = min(16, a.group - 16 * qb);
-  const int nb = a.table[2 * b + 1], begin = a.table[2 * b] + pair * nb;
+  const int nb = a.table[2 * b + 1];
   const int64_t out0 = ((int64_t)b * a.hq + (int64_t)kvh * a.group + 16 * qb) * D;
   auto store_out = [&](int qi, int d, f32x4 r) __attribute__((always_inline)) {
     const int64_t off = out0 + qi * D + d;
@@ -828,10 +845,9 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(CombineArgs a) {
     for (int it = tid; it < nq * (D / 4); it += 256) store_out(it / (D / 4), 4 * (it % (D / 4)), f32x4{0.f, 0.f, 0.f, 0.f});
     return;
   }
-  Cut cut;
-  cut.total = a.table[2 * a.sp.batch - 2] + a.sp.pps * a.table[2 * a.sp.batch - 1];
-  cut.shift = a.table[2 * a.sp.batch] >> 4;
-  cut.align = a.table[2 * a.sp.batch] & 15;
+  const int* const t = a.table + 2 * a.sp.batch;
+  const Cut cut = {t[0], t[1], t[2], t[3], t[4]};
+  const int begin = a.table[2 * b] + pair * counted(cut, nb);
   const int first = range_of(a.sp, cut, begin), parts = range_of(a.sp, cut, begin + nb - 1) - first + 1;
   if (parts < 2) return;                                    // done by the first kernel
   merge_pair<D, false>(a.part_o, a.part_ml, a.rpu, first, parts, nq, a.scale_log2, smem, w, l, store_out);

@@ -139,7 +139,7 @@ inline DecodePlan plan_decode(const flux_attn_cfg& cfg, int batch, int max_kv_le
   p.units = (int)(by_len < by_target ? by_len : by_target);
   if (p.units < 1) p.units = 1;
   p.table_floats = (2 * batch + 63) / 64 * 64;
-  p.table_words = (2 * batch + 1 + 63) / 64 * 64;            // (two per sequence and one behind them, see write_cut_table)
+  p.table_words = (2 * batch + 5 + 63) / 64 * 64;            // (two per sequence and five behind them, see write_cut_table)
   // a range leaves rows in two places at most (see part_place); never fewer workgroups than share the keys out otherwise
   static_assert(kDecodeAlignedShift > kDecodeWgsShift, "halved below");
   const long long by_four = pairs * ((keys + 127) / 128);
@@ -155,8 +155,8 @@ inline DecodePlan plan_decode(const flux_attn_cfg& cfg, int batch, int max_kv_le
       p.wgs = 1 << p.aligned_shift;
     }
   }
-  // blocks are counted in 32 bits: where the bounds allow more of them, they are larger; and calls of very many lists do not
-  // round them up (by 16 blocks at most)
+  // blocks are counted in 32 bits: where the bounds allow more of them, they are larger; and in calls of very many lists they
+  // are counted as they are (a list may be counted as up to 15 blocks more otherwise)
   const bool rounded = pairs <= 1 << 20;
   if (!rounded) p.aligned_shift = -1;
   p.block_shift = 5;

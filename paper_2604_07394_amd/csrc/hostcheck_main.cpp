@@ -111,7 +111,7 @@ int main() {
   EXPECT(wgs(16, 1, 128, 1025, 100), 512);                  // ... and the partials
   EXPECT(wgs(40, 2, 64, 100, 1 << 20), 512);                // two query blocks
   EXPECT(wgs(8, 8, 64, INT_MAX / 16, INT_MAX), 512);
-  EXPECT(wgs(1 << 22, 1 << 22, 64, 64, 32), 512);           // lists of one block: sixteen if rounded up
+  EXPECT(wgs(1 << 22, 1 << 22, 64, 64, 32), 512);           // lists of one block
   // rows in the partials that take all of what flux_workspace_needed counts (2 x 512 places, 1024 units), and shapes around
   auto in_partials = [](int hq, int hkv, int batch, int keys) {
     const flux_attn_cfg c = {hq, hkv, 128, 4, 16, 0.f, 0, 0};

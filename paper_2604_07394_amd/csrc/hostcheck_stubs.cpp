@@ -14,12 +14,11 @@ const void *hostcheck_status, *hostcheck_partials, *hostcheck_counters;
 // where flux_attn_decode_static accepts the shape
 int hostcheck_decode_wgs(const flux_attn_cfg* cfg, int batch, int max_kv_len) { return flux::plan_decode(*cfg, batch, max_kv_len).wgs; }
 int hostcheck_decode_in_partials(const flux_attn_cfg* cfg, int batch, int max_kv_len) { return flux::plan_decode(*cfg, batch, max_kv_len).in_partials; }
-// whether the blocks of all lists, each rounded up to the most that a workgroup takes of one where that is done, can be
-// counted in 32 bits
+// whether the blocks of all lists can be counted in 32 bits, each as up to 15 more where that is done
 int hostcheck_decode_blocks_fit(const flux_attn_cfg* cfg, int batch, int max_kv_len) {
   const flux::DecodePlan p = flux::plan_decode(*cfg, batch, max_kv_len);
   const long long blocks = ((long long)max_kv_len + (1ll << p.block_shift) - 1) >> p.block_shift;
-  return (__int128)batch * p.pps * (p.aligned_shift < 0 ? blocks : (blocks + 15) / 16 * 16) <= INT32_MAX;
+  return (__int128)batch * p.pps * (blocks + (p.aligned_shift < 0 ? 0 : 15)) <= INT32_MAX;
 }
 int hostcheck_decode_rows_fit(const flux_attn_cfg* cfg, int batch, int max_kv_len) {
   const flux::DecodePlan p = flux::plan_decode(*cfg, batch, max_kv_len);

@@ -21,12 +21,14 @@ FA, SA = 1, 0
     (2, 1, 64, [(i * 131) % 97 if i % 5 else 0 for i in range(2048)]),   # 32 sequences per lane, all that the table in LDS holds
     (2, 1, 64, [(i * 131) % 97 if i % 5 else 0 for i in range(2049)]),   # ... and more
     (4, 2, 128, [0] * 30 + [900] + [0] * 200 + [40, 3000] + [0] * 60),   # runs of empty caches between lists
+    (8, 8, 128, [20000, 40, 17000, 90, 33, 64, 15000, 300]),  # ranges that begin behind the last block of a short list
+    (8, 8, 64, [20000, 40, 17000, 90, 33, 64, 15000, 300]),   # ... and 64 lists of head dimension 64: 512 of them
     (4, 4, 128, [900, 340, 1200] * 22),                       # 264 lists: 512 equal ranges
     (4, 4, 128, [900, 340, 1200] * 21),                       # 252: 256 of them
     (4, 4, 128, [256] * 65),                                  # more than 64 sequences: by eight, one workgroup each
     (16, 16, 64, [1024] * 4),                                 # by four: as many as there may be
     (16, 16, 64, [1024] * 4 + [1]),                           # ... and one list more: equal ranges
-    (16, 16, 64, [1500, 100, 1490, 70, 40, 1400, 0, 33]),     # by sixteen: half of the lists shorter than a range
+    (16, 16, 64, [1500, 100, 1490, 70, 40, 1400, 0, 33]),     # half of the lists shorter than a range
     (4, 4, 128, [256, 224, 1]),                               # lists of up to eight blocks: one workgroup each
     (4, 4, 128, [256, 257, 1]),                               # ... and one of nine
     (6, 2, 128, [33000]),                                     # 32 columns of heads, parts in several runs of the merge

@@ -45,6 +45,7 @@ struct SplitArgs {
   int pps;                // (KV head, query block) pairs per sequence = hkv * qblocks
   int bump;               // 1: the call also appends one row per sequence, so every list is one key longer than kv_len says
   int block_shift;        // lists are cut into blocks of 2^block_shift keys
+  int most_by_four;       // calls of eight waves: workgroups up to which they take four blocks of a list where lists are merged
   int aligned_shift;      // few blocks: one workgroup per 4, 8 or 16 of a list while that takes at most 2^aligned_shift (see Cut); < 0: not
 };
 
@@ -115,7 +116,7 @@ static_assert(kResidentUnits == 1 << kDecodeWgsShift, "every CU takes the same")
 // ---- the cut.  Blocks of all pairs, sequence by sequence and pair by pair, numbered from 0.  While they are few (one per
 // wave of two workgroups per CU) every list is rounded up to a multiple of 4 and a workgroup takes 4, so that none
 // crosses from one pair into the next; 8 where every list has no more than that (nothing to merge) or more than 64 (half
-// the rows to merge).  Otherwise the lists lie end to end, and workgroup u of 256 or 512 takes [range_begin(u),
+// the rows to merge).  (Calls of eight waves: see kDecodeFewWgs.)  Otherwise the lists lie end to end, and workgroup u of 256 or 512 takes [range_begin(u),
 // range_begin(u + 1)): equal shares not of the blocks but of what they take, for which a list is counted as a multiple of
 // the four waves and kSeam blocks more (see find_cut).
 struct Cut {
@@ -174,6 +175,7 @@ struct Lanes {
   int run;          // sequences of a lane
   int incl;         // blocks up to and including this lane's
   bool bad;         // this lane saw a clamp trip
+  bool merged;      // calls of eight waves: some list takes more than one workgroup
 };
 __device__ __forceinline__ int counted(Cut c, int nb) { return nb > 0 ? ((nb + c.round) & ~c.round) + c.pad : 0; }
 
@@ -195,7 +197,7 @@ __device__ __forceinline__ Cut find_cut(const SplitArgs& s, int lane, int w, Seq
   r.run = (s.batch + 63) >> 6;
   r.bad = false;
   r.q = Seq{0, 1, 0};
-  if (r.run == 1) {
+  if (__builtin_expect(r.run == 1, 1)) {
     if (lane < s.batch) r.q = load_counted(s, lane, r.bad);
   } else if (r.run * 64 <= kDecodeTable) {
     for (int j = w; j < r.run; j += W) {
@@ -210,6 +212,23 @@ __device__ __forceinline__ Cut find_cut(const SplitArgs& s, int lane, int w, Seq
   // each(f): f(blocks) for every sequence of this lane
   auto take = [&](auto each) __attribute__((always_inline)) {
     Cut c = {0, kDecodeWgsShift, 0, 0, 0};
+    if constexpr (W == 8) {
+      bool merged = false;                                  // some list takes more than one workgroup
+      int mine = 0, by_four = 0;
+      each([&](int nb) __attribute__((always_inline)) {
+        merged |= nb > 8;
+        mine += (nb + 7) & ~7;
+        by_four += (nb + 3) & ~3;
+      });
+      int incl = wave_inclusive_sum(s.pps * by_four);
+      r.merged = __builtin_amdgcn_ballot_w64(merged) != 0;
+      c.align = r.merged && __builtin_amdgcn_readlane(incl, 63) <= 4 * s.most_by_four ? 2 : 3;
+      if (c.align == 3) incl = wave_inclusive_sum(s.pps * mine);
+      c.round = (1 << c.align) - 1;
+      r.incl = incl;
+      c.total = __builtin_amdgcn_readlane(incl, 63);
+      return c;
+    }
     if (s.aligned_shift >= 0) {
       bool between = false;
       each([&](int nb) __attribute__((always_inline)) { between |= nb > 8 && nb <= 64; });
@@ -260,7 +279,7 @@ struct Place {
 };
 __device__ __forceinline__ Place find_place(const SplitArgs& s, Cut c, const Lanes& r, int lane, const SeqTable* table, int x) {
   const int i = __builtin_amdgcn_readfirstlane(__builtin_popcountll(__builtin_amdgcn_ballot_w64(r.incl <= x)));   // whose lane
-  if (r.run == 1) {
+  if (__builtin_expect(r.run == 1, 1)) {
     const int real = __builtin_amdgcn_readlane(r.q.nb, i), nb = counted(c, real);
     return Place{i, __builtin_amdgcn_readlane(r.q.len, i), __builtin_amdgcn_readlane(r.q.md, i), __builtin_amdgcn_readlane(r.incl, i) - s.pps * nb, nb, real};
   }
@@ -378,7 +397,7 @@ __device__ __forceinline__ Merged merge_runs(const float* part_o, const float* p
 }
 // All heads of one pair by a workgroup of four waves; `store` is given (head, column, four values).  Where the heads take one
 // or two waves and there are several runs, the other waves take every other run and all meet in LDS (Merged[4][64]).
-template <int D, bool DEV, class Store>
+template <int D, bool DEV, int W, class Store>
 __device__ __forceinline__ void merge_pair(const float* part_o, const float* part_ml, int rpu, int first, int parts, int nq, float scale_log2, char* lds, int w, int l, Store store) {
   constexpr int TPR = D / 4, HPW = 64 / TPR;
   auto finish = [&](int head0, const Merged& r) __attribute__((always_inline)) {
@@ -387,7 +406,7 @@ __device__ __forceinline__ void merge_pair(const float* part_o, const float* par
   };
   const int groups = (nq + HPW - 1) / HPW;                  // of heads that a wave takes at a time
   const int split = groups > 2 || parts <= 16 ? 1 : 4 / groups;
-  for (int i = w; i < groups * split; i += 4) {
+  for (int i = w; i < groups * split; i += W) {
     const int head0 = (split == 1 ? i : i % groups) * HPW;
     const Merged r = merge_runs<D, DEV>(part_o, part_ml, rpu, first, parts, nq, scale_log2, head0, split == 1 ? 0 : i / groups, split, l);
     if (split == 1) finish(head0, r);
@@ -416,9 +435,11 @@ __device__ __forceinline__ void merge_pair(const float* part_o, const float* par
 // IN_PLACE: the part that arrives last at its pair merges the pair.  Its rows pass between workgroups that may sit on
 // different XCDs: they are written and read with device-scope accesses, and a part counts itself only after its own
 // stores have been acknowledged.
-template <int D, bool NT, bool FUSED, bool IN_PLACE>
-__global__ __launch_bounds__(256, 2) void decode_splitk_kernel(DecodeArgs a) {
-  constexpr int W = 4;                // waves per workgroup
+//
+// W: waves per workgroup, 4, or 8 in calls of few short lists (see DecodePlan): eight blocks of one list per workgroup, so that
+// a wave has one block and no second wait for memory.
+template <int D, bool NT, bool FUSED, bool IN_PLACE, int W = 4>
+__global__ __launch_bounds__(64 * W, 2) void decode_splitk_kernel(DecodeArgs a) {
   constexpr int KC = D / 32;          // MFMA k-steps over the head dimension
   constexpr int DB = D / 16;          // 16-wide output blocks over the head dimension
   constexpr int VL = D / 16;          // 16-byte V loads per lane per 32-key block
@@ -437,33 +458,43 @@ __global__ __launch_bounds__(256, 2) void decode_splitk_kernel(DecodeArgs a) {
   const int wg = blockIdx.x;
 
   // ---- the range of this workgroup
-  __shared__ u32x2 s_seq[kDecodeTable];
+  __shared__ u32x2 s_seq[W == 8 ? kDecodeFewWgs : kDecodeTable];   // (a call of eight waves has no more sequences than workgroups)
   SeqTable* const seqs = (SeqTable*)s_seq;
   Lanes lanes;
   const Cut cut = find_cut<D, W>(a.sp, l, w, seqs, lanes);
+  if constexpr (W == 8) __builtin_assume(cut.align > 0);
   if (wg == 0 && lanes.bad) atomicOr(a.status, (uint32_t)FLUX_DEV_BAD_LENGTH);
   // FUSED: the workgroups count themselves, first on one of kDecodeGather words (a word takes some 10 ns per count), when
   // all their waves hold the lengths; the one that completes the count moves the lengths on.  Called by one wave, in two
-  // steps: the answer to the first count is not waited for until there is nothing else to do.
+  // steps: the answer to the first count is not waited for until there is nothing else to do.  Few workgroups of eight waves
+  // count themselves on one word, where their answers have the time (see below).
+  const bool one_word = W == 8 && !lanes.merged && (int)gridDim.x <= kDecodeOneWord;   // (and no words to count)
   uint32_t counted = 0;
   auto count_in = [&]() __attribute__((always_inline)) {
-    if (l == 0) counted = __hip_atomic_fetch_add(a.arrived + kCounterStride * (1 + (wg & (kDecodeGather - 1))), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (l == 0) counted = __hip_atomic_fetch_add(a.arrived + (one_word ? 0 : kCounterStride * (1 + (wg & (kDecodeGather - 1)))), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
-  auto count_out = [&]() __attribute__((always_inline)) {
+  bool counts_words = one_word;
+  auto count_word = [&]() __attribute__((always_inline)) {  // whoever completes a word counts it
+    if (one_word) return;
     const int x = wg & (kDecodeGather - 1), expected = ((int)gridDim.x - 1 - x) / kDecodeGather + 1;
-    const int words = min((int)gridDim.x, kDecodeGather);
-    if (__builtin_amdgcn_readfirstlane(counted) + 1 != (uint32_t)expected) return;
-    if (l == 0) {
+    counts_words = __builtin_amdgcn_readfirstlane(counted) + 1 == (uint32_t)expected;
+    if (counts_words && l == 0) {
       a.arrived[kCounterStride * (1 + x)] = 0;              // ready for the next call on this stream
       counted = __hip_atomic_fetch_add(a.arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (__builtin_amdgcn_readfirstlane(counted) + 1 != (uint32_t)words) return;
+  };
+  auto move_lengths = [&]() __attribute__((always_inline)) {
+    if (!counts_words || __builtin_amdgcn_readfirstlane(counted) + 1 != (uint32_t)(one_word ? (int)gridDim.x : min((int)gridDim.x, kDecodeGather))) return;
     for (int i = l; i < a.sp.batch; i += 64) {
       int len = a.kv_len_rw[i];
       len = len < 0 ? 0 : (len > a.sp.capacity ? a.sp.capacity : len);
       a.kv_len_rw[i] = len < a.sp.capacity ? len + 1 : len;
     }
     if (l == 0) a.arrived[0] = 0;
+  };
+  auto count_out = [&]() __attribute__((always_inline)) {
+    count_word();
+    move_lengths();
   };
   if (wg == (int)gridDim.x - 1) {
     if constexpr (!IN_PLACE) {
@@ -616,8 +647,8 @@ __global__ __launch_bounds__(256, 2) void decode_splitk_kernel(DecodeArgs a) {
     // the part's keys, 32 at a time round the waves: p_end is where they end or the list does
     p0 = (int)min((int64_t)x0 << a.sp.block_shift, (int64_t)c1) + 32 * w;
     p_end = (int)min((int64_t)x1 << a.sp.block_shift, (int64_t)c1);
-    if (p0 < p_end) load_block(p0);
-    __builtin_amdgcn_sched_barrier(0);
+    if (W == 4 && p0 < p_end) load_block(p0);               // (eight waves have so little in flight that the order is free:
+    __builtin_amdgcn_sched_barrier(0);                      // 1 x 144 keys 6.7 us so, 6.6 with the queries first)
     // ---- Q operand: lane (n, g) holds d = 32*kc + 8*g .. +7 of query head kvh*group + 16*qb + n (columns past the group's
     // last head repeat its first one; what they give is left out at the end)
     const int kvh = a.qblocks == 1 ? pair : pair / a.qblocks, qb = a.qblocks == 1 ? 0 : pair % a.qblocks;
@@ -625,6 +656,11 @@ __global__ __launch_bounds__(256, 2) void decode_splitk_kernel(DecodeArgs a) {
     const __bf16* qrow = a.q + ((int64_t)place.b * a.hq + (int64_t)kvh * a.group + (qh < a.group ? qh : 0)) * D;
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc) qf[kc] = *(const bf16x8*)(qrow + 32 * kc + 8 * g);
+    if constexpr (W == 8) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (p0 < p_end) load_block(p0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     if constexpr (FUSED) {
       new_row_at = nullptr;
       if (x0 == 0 && qb == 0 && new_key >= 0 && tid < 2 * CPR) {
@@ -635,6 +671,15 @@ __global__ __launch_bounds__(256, 2) void decode_splitk_kernel(DecodeArgs a) {
     __builtin_amdgcn_sched_barrier(0);
   };
   begin_part();
+  // Eight waves: nothing reads the lengths behind here, so workgroups with a whole list count themselves while its keys are on
+  // their way (3 x 144 keys 7.4 us counted at the end, 7.0 so).  The others do it at the end, where they wait for their rows anyway
+  // (1 x 2001 9.8 counted there, 10.1 here).
+  if constexpr (FUSED && W == 8) {
+    if (x0 == 0 && x1 == place.real) {
+      __builtin_amdgcn_s_barrier();                         // every wave holds the lengths
+      if (w == W - 1) count_in();
+    }
+  }
 
   for (;;) {
     float m_run = -INFINITY, l_run = 0.f;
@@ -654,7 +699,7 @@ __global__ __launch_bounds__(256, 2) void decode_splitk_kernel(DecodeArgs a) {
       for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
         for (int kc = 0; kc < KC; ++kc) kf[sb][kc] = __builtin_bit_cast(bf16x8, kreg[sb][kc]);
-      const int pnext = p_end - p0 > 32 * W ? p0 + 32 * W : p_end;
+      const int pnext = W == 4 && p_end - p0 > 32 * W ? p0 + 32 * W : p_end;   // (of eight waves, each has one block at most)
       // ---- scores: s[sb][i] is key p0 + 16*sb + 4*g + i against query n
       f32x4 s[2];
 #pragma unroll
@@ -667,7 +712,7 @@ __global__ __launch_bounds__(256, 2) void decode_splitk_kernel(DecodeArgs a) {
       // the next block is asked for once the score MFMAs have taken this block's K registers, which the loads then
       // reuse (asked for before them, the block in flight needs registers of its own: 30 more per lane)
       __builtin_amdgcn_sched_barrier(0);
-      if (pnext < p_end) load_block(pnext);
+      if (W == 4 && pnext < p_end) load_block(pnext);
       __builtin_amdgcn_sched_barrier(0);
       if (c1 - p0 < 32) {
 #pragma unroll
@@ -728,7 +773,7 @@ __global__ __launch_bounds__(256, 2) void decode_splitk_kernel(DecodeArgs a) {
     // (the arguments that only the end of a part needs are read again here: kept in scalar registers they push the loop's
     // values out of them)
     const FLUX_CONSTANT DecodeArgs* e = (const FLUX_CONSTANT DecodeArgs*)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(e));
+    if constexpr (W == 4) asm volatile("" : "+s"(e));
     // ---- what the end of this part needs, and on to the next one: its first block is in flight meanwhile
     const int nq = min(16, e->group - (e->qblocks == 1 ? 0 : 16 * (pair % e->qblocks)));
     const int64_t out0 = ((int64_t)place.b * e->hq + (int64_t)(e->qblocks == 1 ? pair : pair / e->qblocks) * e->group + (e->qblocks == 1 ? 0 : 16 * (pair % e->qblocks))) * D;
@@ -738,7 +783,7 @@ __global__ __launch_bounds__(256, 2) void decode_splitk_kernel(DecodeArgs a) {
     const int first = whole ? wg : range_of(a.sp, cut, list0);
     const int parts = whole ? 1 : range_of(a.sp, cut, list0 + place.real - 1) - first + 1;
     at = x1 < place.real ? range_end : list0 + place.nb;
-    const bool more = at < range_end;
+    const bool more = W == 4 && at < range_end;
     if (more) {
       if (++pair == a.sp.pps) {
         place = find_place(a.sp, cut, lanes, l, seqs, place.begin + a.sp.pps * place.nb);   // (the next one that has keys)
@@ -795,7 +840,7 @@ __global__ __launch_bounds__(256, 2) void decode_splitk_kernel(DecodeArgs a) {
       }
     }
     const bool counts = FUSED && !more && w == W - 1;
-    if (counts) count_in();                                 // (every wave of the workgroup has read the lengths)
+    if (counts && (W == 4 || !whole)) count_in();                       // (every wave of the workgroup has read the lengths)
     if (IN_PLACE && !whole) {
       // ---- the part that arrives last merges the pair
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wave's rows have reached the point all XCDs see
@@ -808,7 +853,7 @@ __global__ __launch_bounds__(256, 2) void decode_splitk_kernel(DecodeArgs a) {
       }
       __syncthreads();
       if (counts) count_out();
-      if (last_of_pair) merge_pair<D, true>(e->part_o, e->part_ml, e->rpu, first, parts, nq, e->scale_log2, smem, w, l, store_out);
+      if (last_of_pair) merge_pair<D, true, W>(e->part_o, e->part_ml, e->rpu, first, parts, nq, e->scale_log2, smem, w, l, store_out);
     }
     if (counts && whole) count_out();
     if (!more) break;
@@ -850,7 +895,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(CombineArgs a) {
   const int begin = a.table[2 * b] + pair * counted(cut, nb);
   const int first = range_of(a.sp, cut, begin), parts = range_of(a.sp, cut, begin + nb - 1) - first + 1;
   if (parts < 2) return;                                    // done by the first kernel
-  merge_pair<D, false>(a.part_o, a.part_ml, a.rpu, first, parts, nq, a.scale_log2, smem, w, l, store_out);
+  merge_pair<D, false, 4>(a.part_o, a.part_ml, a.rpu, first, parts, nq, a.scale_log2, smem, w, l, store_out);
 }
 
 // c.decode_counters may be null: the call then takes two launches.
@@ -881,6 +926,7 @@ hipError_t launch_decode(const Ctx& c, const flux_attn_cfg& cfg, const void* q, 
   a.sp.bump = fused ? 1 : 0;
   a.sp.block_shift = plan.block_shift;
   a.sp.aligned_shift = plan.aligned_shift;
+  a.sp.most_by_four = plan.most_by_four;
   a.k_new = (const __bf16*)k_new;
   a.v_new = (const __bf16*)v_new;
   a.hq = cfg.n_q_heads;
@@ -906,7 +952,11 @@ hipError_t launch_decode(const Ctx& c, const flux_attn_cfg& cfg, const void* q, 
   const bool nt = 4.0 * cache.batch * cfg.n_kv_heads * cfg.head_dim * (double)max_kv_len > 64.0 * 1024 * 1024;
   auto launch = [&](auto d) {
     constexpr int D = decltype(d)::value;
-    if (fused) {
+    if (plan.waves == 8) {                                   // (64 MB at most)
+      if (fused) hipLaunchKernelGGL((decode_splitk_kernel<D, false, true, true, 8>), grid, dim3(512), 0, s, a);
+      else if (c.decode_counters) hipLaunchKernelGGL((decode_splitk_kernel<D, false, false, true, 8>), grid, dim3(512), 0, s, a);
+      else hipLaunchKernelGGL((decode_splitk_kernel<D, false, false, false, 8>), grid, dim3(512), 0, s, a);
+    } else if (fused) {
       if (nt) hipLaunchKernelGGL((decode_splitk_kernel<D, true, true, true>), grid, dim3(256), 0, s, a);
       else hipLaunchKernelGGL((decode_splitk_kernel<D, false, true, true>), grid, dim3(256), 0, s, a);
     } else if (c.decode_counters) {

@@ -90,6 +90,7 @@ constexpr int kRouterLines = 24;              // router calls of at most so many
 // workgroup, for the pair that begins in its range and goes on behind it.
 constexpr int kCounterStride = 32;            // words
 constexpr int kDecodeGather = 32;
+constexpr int kDecodeOneWord = 128;           // workgroups of eight waves up to which all count themselves on the first word
 constexpr int kDecodeWgsShift = 8, kDecodeAlignedShift = 9;
 constexpr int kDecodeCounters = 1 + kDecodeGather + (1 << kDecodeAlignedShift);
 constexpr int kAppendGather = 16;             // words that the workgroups of an append count themselves on, each on a line of its own
@@ -122,10 +123,21 @@ struct DecodePlan {
   int table_floats; // two 4-byte words per sequence (rounded to 256 B), which the documented size of the scratch counts
   int table_words;  // calls of two launches: words in front of the rows that hold the cut as a table (rounded to 256 B)
   int wgs;          // workgroups launched
+  int waves;        // of a workgroup
+  int most_by_four; // calls of eight waves: workgroups up to which merged lists are taken by 128 keys
   int aligned_shift;   // log2 of the most where every one takes its keys from one list; < 0: never
   int block_shift;  // log2 of the keys of a block
   bool in_partials; // the rows of parts need the partials region (they fit the small one otherwise)
 };
+// Calls that two workgroups per CU can hold at 256 keys each are bound by latencies and take eight waves per workgroup, so that
+// each has one block of 32 keys and no second wait for memory (us with four / eight, 32/8 heads of 128 unless said: 3 lists of
+// 144 keys 8.8 / 7.0, 8 of 100 7.5 / 6.4, 5 of 61 to 210 at head dimension 64 7.4 / 5.9, 16 of 250 at 16/8 heads 9.8 / 8.6, 1 x
+// 8000 13.8 / 12.6; with at most 256 workgroups / 512: 5 of 420 to 6881 at 8/2 heads of 64 20.0 / 18.1 for two layers).  Where
+// lists are merged they take 128 keys each while that leaves at most 1024 rows, as a CU takes in its keys no faster than its
+// even share (256 / 128 keys: 1 x 2001 9.8 / 8.5, 11 lists of 66 to 503 38.3 / 34.7 for four layers, 16 of 49 to 710 at 28/4
+// heads 39.6 / 35.0; with eight rows and more per list there is more to merge than to win: 2 lists of 16 heads 11.1 / 12.4).
+constexpr int kDecodeFewWgs = 512;
+constexpr int kDecodeFewRows = 1024;
 constexpr int kTargetUnits = 1024;
 constexpr int kMinChunk = 256;
 inline DecodePlan plan_decode(const flux_attn_cfg& cfg, int batch, int max_kv_len) {
@@ -146,6 +158,14 @@ inline DecodePlan plan_decode(const flux_attn_cfg& cfg, int batch, int max_kv_le
   auto bytes = [&](long long wgs) { return 2 * wgs * p.rpu * (cfg.head_dim + 2) * (long long)sizeof(float); };
   p.aligned_shift = kDecodeAlignedShift;
   p.wgs = (int)(by_four < (1 << p.aligned_shift) ? by_four : (1 << p.aligned_shift));
+  const long long by_eight = pairs * ((keys + 255) / 256);
+  p.waves = 4;
+  p.most_by_four = kDecodeFewRows / p.rpu < kDecodeFewWgs ? kDecodeFewRows / p.rpu : kDecodeFewWgs;
+  const long long few = by_eight > p.most_by_four ? by_eight : (by_four < p.most_by_four ? by_four : p.most_by_four);
+  if (few <= kDecodeFewWgs && bytes(few) <= (long long)kSmallBytes) {
+    p.waves = 8;
+    p.wgs = (int)few;
+  }
   p.in_partials = false;
   if (bytes(p.wgs) > (long long)kSmallBytes) {
     if (2ll * p.wgs <= p.units) {

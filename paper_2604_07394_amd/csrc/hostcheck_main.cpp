@@ -103,7 +103,15 @@ int main() {
   };
   EXPECT(wgs(4, 1, 128, 1, 0), 1);
   EXPECT(wgs(4, 1, 128, 1, 129), 2);
-  EXPECT(wgs(32, 8, 128, 1, 8192), 512);
+  EXPECT(wgs(32, 8, 128, 1, 2049), 136);                    // eight waves, 128 keys each
+  EXPECT(wgs(32, 8, 128, 1, 4096), 256);                    // ... the most that leave 1024 rows
+  EXPECT(wgs(32, 8, 128, 1, 8192), 256);
+  EXPECT(wgs(32, 8, 128, 1, 8193), 264);                    // ... 256 keys each
+  EXPECT(wgs(32, 8, 128, 1, 16384), 512);
+  EXPECT(wgs(32, 8, 128, 1, 16385), 512);                   // four waves
+  EXPECT(wgs(8, 8, 64, 33, 100), 264);
+  EXPECT(wgs(8, 8, 64, 64, 100), 512);
+  EXPECT(wgs(8, 8, 64, 65, 100), 512);
   EXPECT(wgs(32, 8, 128, 8, 131072), 512);
   EXPECT(wgs(16, 1, 128, 1, 4096), 32);
   EXPECT(wgs(16, 1, 128, 504, 100), 504);                   // 16 rows of 128 per part: the most that the small region holds

@@ -26,11 +26,25 @@ FA, SA = 1, 0
     (4, 4, 128, [900, 340, 1200] * 22),                       # 264 lists: 512 equal ranges
     (4, 4, 128, [900, 340, 1200] * 21),                       # 252: 256 of them
     (4, 4, 128, [256] * 65),                                  # more than 64 sequences: by eight, one workgroup each
-    (16, 16, 64, [1024] * 4),                                 # by four: as many as there may be
-    (16, 16, 64, [1024] * 4 + [1]),                           # ... and one list more: equal ranges
+    (16, 16, 64, [1024] * 4),                                 # by four: as many as there may be (of four waves under the loosest bound)
+    (16, 16, 64, [1024] * 4 + [1]),                           # ... and one list more: by eight, equal ranges under the loosest bound
     (16, 16, 64, [1500, 100, 1490, 70, 40, 1400, 0, 33]),     # half of the lists shorter than a range
-    (4, 4, 128, [256, 224, 1]),                               # lists of up to eight blocks: one workgroup each
-    (4, 4, 128, [256, 257, 1]),                               # ... and one of nine
+    # eight waves: every list of up to eight blocks, one of nine (by four), more merged rows than are taken by four, as many
+    # workgroups and sequences as there may be, and one more; counts on one word (up to 128 workgroups) and on 32
+    (4, 4, 128, [256, 224, 1]),
+    (4, 4, 128, [256, 257, 1]),
+    (32, 2, 128, [4000, 33]),
+    (32, 8, 128, [4095]),
+    (32, 8, 128, [4096]),
+    (32, 8, 128, [16383]),
+    (32, 8, 128, [16384]),
+    (8, 8, 64, [(37 * i) % 255 + 1 for i in range(16)]),
+    (8, 8, 64, [(37 * i) % 255 + 1 for i in range(17)]),
+    (8, 8, 64, [(37 * i) % 255 + 1 for i in range(64)]),
+    (8, 8, 64, [(37 * i) % 255 + 1 for i in range(65)]),
+    (16, 1, 128, [(37 * i) % 40 + 1 for i in range(504)]),    # as many rows as the small region holds
+    (1, 1, 64, [(37 * i) % 255 for i in range(512)]),
+    (1, 1, 64, [(37 * i) % 255 for i in range(513)]),
     (6, 2, 128, [33000]),                                     # 32 columns of heads, parts in several runs of the merge
     (32, 2, 128, [9000, 8000, 700]),                          # 16 heads per KV head: no waves to share the runs
     (7, 1, 64, [70000, 3]),                                   # one pair over nearly all ranges
@@ -45,10 +59,11 @@ def test_ranges_and_lists(hq, hkv, d, lens):
     qb = synth.normal_bf16(seed, synth.stream_id(synth.STREAM_QDEC), (b, hq, d))
     cfg = F.attn_cfg(hq, hkv, d, n_sink, window, 0.0, 1)
     t, cap = sum(lens), max(lens) + 1
+    room = max(2 * cap, 20000) if b * hkv <= 200 else cap + 2000
     cu = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int32, device="cuda")
     md = torch.tensor(modes, dtype=torch.uint8, device="cuda")
     q, kn, vn = H.bits_to_torch(qb), H.bits_to_torch(kb[t:]), H.bits_to_torch(vb[t:])
-    cache = F.KVCache.empty(b, hkv, cap, d)
+    cache = F.KVCache.empty(b, hkv, room, d)
     cache.k.fill_(float("nan"))
     cache.v.fill_(float("nan"))
     F.flux_kv_append(ctx, cache, hkv, d, H.bits_to_torch(kb[:t]), H.bits_to_torch(vb[:t]), cu, t, max(lens))
@@ -69,11 +84,17 @@ def test_ranges_and_lists(hq, hkv, d, lens):
         at += n
     again = torch.empty_like(out)
     status = torch.zeros(1, dtype=torch.int32, device="cuda")
-    for bound in (cap, cap, cap):
+    # the bound moves the cut (grid, waves of a workgroup, blocks that it takes): the call without a context gives the bits of the
+    # call with one at every bound, and two cuts of a list differ by what either may be off (see the test of the error below)
+    for bound in (cap, cap + 255, room):
+        same = torch.full_like(out, float("nan"))
+        F.flux_attn_decode(ctx, cfg, q, bound, cache, md, same)
         again.fill_(float("nan"))
         F.flux_attn_decode_static(cfg, q, bound, cache, md, again, status)
         torch.cuda.synchronize()
-        assert torch.equal(again, out) and int(status[0]) == 0
+        assert torch.equal(again, same) and int(status[0]) == 0
+        assert bound > cap or torch.equal(same, out)
+        assert ((same - out).double().flatten(1).norm(dim=1) <= 4 * 2.0 ** -16 * out.double().flatten(1).norm(dim=1)).all()
     g = torch.cuda.CUDAGraph()
     s = torch.cuda.Stream()
     with torch.cuda.graph(g, stream=s):

@@ -110,9 +110,6 @@ __device__ __forceinline__ int seq_visible(const SplitArgs& s, int len, int md, 
   return nv;
 }
 
-constexpr int kResidentUnits = 256;             // workgroups that share long lists out: one per CU
-static_assert(kResidentUnits == 1 << kDecodeWgsShift, "every CU takes the same");
-
 // ---- the cut.  Blocks of all pairs, sequence by sequence and pair by pair, numbered from 0.  While they are few (one per
 // wave of two workgroups per CU) every list is rounded up to a multiple of 4 and a workgroup takes 4, so that none
 // crosses from one pair into the next; 8 where every list has no more than that (nothing to merge) or more than 64 (half
@@ -125,16 +122,16 @@ struct Cut {
   int align;        // log2 of the blocks that a workgroup takes of a list; 0: an equal share of all lists
   int round, pad;   // a list of nb blocks is counted as nb rounded up to a multiple of round + 1, and pad more
 };
-__device__ __forceinline__ int cut_wgs(const SplitArgs& s, Cut c) { return c.align > 0 ? c.total >> c.align : 1 << c.shift; }
-__device__ __forceinline__ int range_begin(const SplitArgs& s, Cut c, int u) {
+__device__ __forceinline__ int cut_wgs(Cut c) { return c.align > 0 ? c.total >> c.align : 1 << c.shift; }
+__device__ __forceinline__ int range_begin(Cut c, int u) {
   return c.align > 0 ? u << c.align : (int)(((unsigned long long)(unsigned)u * (unsigned)c.total) >> c.shift);
 }
 // the workgroup whose range holds block x
-__device__ __forceinline__ int range_of(const SplitArgs& s, Cut c, int x) {
+__device__ __forceinline__ int range_of(Cut c, int x) {
   if (c.align > 0) return x >> c.align;
   int u = min((int)((float)x * ((float)(1 << c.shift) / (float)c.total)), (1 << c.shift) - 1);
-  while (range_begin(s, c, u) > x) --u;
-  while (range_begin(s, c, u + 1) <= x) ++u;
+  while (range_begin(c, u) > x) --u;
+  while (range_begin(c, u + 1) <= x) ++u;
   return u;
 }
 // Where the rows of part `i` of a pair go whose first part lies in the range of workgroup `first`: a range holds at most one
@@ -524,7 +521,7 @@ __global__ __launch_bounds__(64 * W, 2) void decode_splitk_kernel(DecodeArgs a) 
       }
     }
   };
-  if (wg >= cut_wgs(a.sp, cut) || cut.total == 0) {         // nothing to do: uniform for the whole workgroup
+  if (wg >= cut_wgs(cut) || cut.total == 0) {         // nothing to do: uniform for the whole workgroup
     if constexpr (FUSED) {
       asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
       __syncthreads();                                      // every wave holds the lengths
@@ -536,8 +533,8 @@ __global__ __launch_bounds__(64 * W, 2) void decode_splitk_kernel(DecodeArgs a) 
     zero_rows();
     return;
   }
-  int at = range_begin(a.sp, cut, wg);
-  const int range_end = range_begin(a.sp, cut, wg + 1);
+  int at = range_begin(cut, wg);
+  const int range_end = range_begin(cut, wg + 1);
   Place place = find_place(a.sp, cut, lanes, l, seqs, at);
   const int rows_at = (at - place.begin);
   int pair = __builtin_amdgcn_readfirstlane((int)((float)rows_at / (float)place.nb));   // (put right below: the quotient may be off by one)
@@ -780,8 +777,8 @@ __global__ __launch_bounds__(64 * W, 2) void decode_splitk_kernel(DecodeArgs a) 
     const int list0 = place.begin + pair * place.nb;
     const bool empty = x0 >= x1;                            // (the range begins in what is only counted behind a list)
     const bool whole = empty || (x0 == 0 && x1 == place.real);   // the pair lies in this range
-    const int first = whole ? wg : range_of(a.sp, cut, list0);
-    const int parts = whole ? 1 : range_of(a.sp, cut, list0 + place.real - 1) - first + 1;
+    const int first = whole ? wg : range_of(cut, list0);
+    const int parts = whole ? 1 : range_of(cut, list0 + place.real - 1) - first + 1;
     at = x1 < place.real ? range_end : list0 + place.nb;
     const bool more = W == 4 && at < range_end;
     if (more) {
@@ -893,7 +890,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(CombineArgs a) {
   const int* const t = a.table + 2 * a.sp.batch;
   const Cut cut = {t[0], t[1], t[2], t[3], t[4]};
   const int begin = a.table[2 * b] + pair * counted(cut, nb);
-  const int first = range_of(a.sp, cut, begin), parts = range_of(a.sp, cut, begin + nb - 1) - first + 1;
+  const int first = range_of(cut, begin), parts = range_of(cut, begin + nb - 1) - first + 1;
   if (parts < 2) return;                                    // done by the first kernel
   merge_pair<D, false, 4>(a.part_o, a.part_ml, a.rpu, first, parts, nq, a.scale_log2, smem, w, l, store_out);
 }

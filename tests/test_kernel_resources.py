@@ -47,15 +47,15 @@ def workgroups_per_cu(k):
     return min(waves // (k["max_flat_workgroup_size"] // 64), 163840 // max(1, k["group_segment_fixed_size"]))
 
 
-def test_every_two_launch_decode_kernel_holds_the_round_its_split_is_made_for(kernels):
-    """The split of a decode call aims at one round of the workgroups that the chip holds at once (kResidentUnits, three per
-    CU on 256 CUs), and two-launch calls must not lose that to the choice of an instance."""
-    src = open(os.path.join(ROOT, "paper_2604_07394_amd", "csrc", "decode.hip")).read()
-    resident = int(re.search(r"constexpr int kResidentUnits = (\d+);", src).group(1))
-    names = [n for n, k in kernels.items() if "decode_splitk_kernel" in n and k["max_flat_workgroup_size"] == 256]
-    assert len(names) >= 8
+def test_every_decode_kernel_holds_the_round_its_calls_are_made_for(kernels):
+    """A decode call launches up to 512 workgroups (2^kDecodeAlignedShift of four waves, kDecodeFewWgs of eight) that are meant
+    to run side by side, two per CU on 256 CUs: no instance may need more registers or LDS than that leaves, or spill."""
+    src = open(os.path.join(ROOT, "paper_2604_07394_amd", "csrc", "flux_internal.h")).read()
+    most = {256: 1 << int(re.search(r"kDecodeAlignedShift = (\d+);", src).group(1)), 512: int(re.search(r"kDecodeFewWgs = (\d+);", src).group(1))}
+    names = [n for n in kernels if "decode_splitk_kernel" in n]
+    assert sorted(kernels[n]["max_flat_workgroup_size"] for n in names) == [256] * 12 + [512] * 6
     for n in names:
-        assert 256 * workgroups_per_cu(kernels[n]) >= resident, (n, kernels[n])
+        assert 256 * workgroups_per_cu(kernels[n]) >= most[kernels[n]["max_flat_workgroup_size"]] >= 512, (n, kernels[n])
         assert kernels[n]["vgpr_spill_count"] == 0, n
 
 

@@ -114,13 +114,17 @@ int flux_create(flux_ctx** out, int device, size_t workspace_bytes) {
   }
   if (workspace_bytes == 0) workspace_bytes = kHeaderBytes + kSmallBytes + ((size_t)160 << 20);
   if (workspace_bytes < kHeaderBytes + kSmallBytes + 4096) workspace_bytes = kHeaderBytes + kSmallBytes + 4096;
+  if (workspace_bytes > SIZE_MAX - kCountersBytes) {
+    delete ctx;
+    return FLUX_ENOMEM;
+  }
   hipError_t e = hipSetDevice(device);
-  if (e == hipSuccess) e = hipMalloc((void**)&ctx->c.ws, workspace_bytes);
+  if (e == hipSuccess) e = hipMalloc((void**)&ctx->c.ws, workspace_bytes + kCountersBytes);
   if (e != hipSuccess) {
     delete ctx;
     return e == hipErrorOutOfMemory ? FLUX_ENOMEM : hip_fail(e);
   }
-  e = hipMemset(ctx->c.ws, 0, kHeaderBytes);
+  e = hipMemset(ctx->c.ws, 0, kHeaderBytes + kCountersBytes);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) {
     (void)hipFree(ctx->c.ws);
@@ -133,9 +137,9 @@ int flux_create(flux_ctx** out, int device, size_t workspace_bytes) {
   ctx->c.append_counters = (uint32_t*)(ctx->c.ws + kAppendCountersAt);
   ctx->c.decode_counters = (uint32_t*)(ctx->c.ws + kDecodeCountersAt);
   ctx->c.router_counters = (uint32_t*)(ctx->c.ws + 1024);
-  static_assert(1024 + 4 * kRouterCounters <= kDecodeCountersAt && 1024 + 4 * kRouterLines * kCounterStride <= kDecodeCountersAt, "the counters must fit the header");
-  ctx->c.small = (float*)(ctx->c.ws + kHeaderBytes);
-  ctx->c.partials = (float*)(ctx->c.ws + kHeaderBytes + kSmallBytes);
+  static_assert(1024 + 4 * kRouterCounters <= kHeaderBytes && 1024 + 4 * kRouterLines * kCounterStride <= kHeaderBytes, "the counters must fit the header");
+  ctx->c.small = (float*)(ctx->c.ws + kHeaderBytes + kCountersBytes);
+  ctx->c.partials = (float*)(ctx->c.ws + kHeaderBytes + kCountersBytes + kSmallBytes);
   ctx->c.partials_bytes = workspace_bytes - kHeaderBytes - kSmallBytes;
   // set-up on this device also resolves the static scratch of flux_attn_decode_static, so that a caller who
   // created a context first never takes that step inside a region where it would be unwelcome

@@ -44,7 +44,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 struct Ctx {
   int device;              // < 0: no device (argument checking only)
   char* ws;                // device workspace base (256-byte aligned)
-  size_t ws_bytes;
+  size_t ws_bytes;         // as given: the counters that have lines of their own come on top
   // carved regions (device pointers)
   uint32_t* status;        // sticky status word
   uint32_t* counters;      // kCounters zero-initialised arrival counters; users reset them to zero
@@ -95,10 +95,12 @@ constexpr int kDecodeWgsShift = 8, kDecodeAlignedShift = 9;
 constexpr int kDecodeCounters = 1 + kDecodeGather + (1 << kDecodeAlignedShift);
 constexpr int kAppendGather = 16;             // words that the workgroups of an append count themselves on, each on a line of its own
 constexpr size_t kSmallBytes = 8u << 20;      // router: batch * (splits * hidden + inner) floats; decode: the rows of parts
-constexpr size_t kDecodeCountersAt = 4096;    // bytes
-constexpr size_t kHeaderBytes = kDecodeCountersAt + (kDecodeCounters * kCounterStride * 4 + 4095) / 4096 * 4096;   // status + counters
+constexpr size_t kHeaderBytes = 4096;         // status + counters
+// The counters that have lines of their own lie between the header and the router scratch, and are not taken from the bytes
+// that the caller gives a context: a workspace of a given size holds the partials that it held before there were any.
+constexpr size_t kDecodeCountersAt = kHeaderBytes;   // bytes
 constexpr size_t kAppendCountersAt = kDecodeCountersAt + kDecodeCounters * kCounterStride * 4;
-static_assert(kAppendCountersAt + kAppendGather * kCounterStride * 4 <= kHeaderBytes, "the counters of the append lie behind those of decode");
+constexpr size_t kCountersBytes = (kAppendCountersAt + kAppendGather * kCounterStride * 4 - kHeaderBytes + 4095) / 4096 * 4096;
 constexpr int kPrefillWideMinRows = 32768;    // prefill launches whose longest prompt has at least this many rows use 256-row workgroups
 
 // ---- launchers (each validates nothing: flux_api.hip has done it) ---------------------------

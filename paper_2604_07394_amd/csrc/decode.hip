@@ -731,8 +731,8 @@ __global__ __launch_bounds__(64 * W, 2) void decode_splitk_kernel(DecodeArgs a) 
       // 2^-16 of the weight).  Rounded to one bf16 value the result would depend on how a list is cut: the weight of the key
       // that sets a wave's reference is exactly 1, so every wave more has another of the heaviest keys exact.  The matrix
       // cores are idle for most of the time that a block takes to arrive (no call takes longer for it; relative error at 8 x 4224
-      // keys and fp32 output 1.35e-3 with one bf16 value, 4.0e-6 with two).  (2^-40 of the weight in the second term keep it
-      // from being 0 where the first one is not: an infinite V row stays infinite.)
+      // keys and fp32 output 1.35e-3 with one bf16 value, 4.0e-6 with two).  (The second term is never 0, nor so small
+      // that its bf16 value is: an infinite V row stays infinite where the first term is not 0.)
       uint32_t pk[4], rest[4];
       float psum = 0.f;
 #pragma unroll
@@ -743,7 +743,7 @@ __global__ __launch_bounds__(64 * W, 2) void decode_splitk_kernel(DecodeArgs a) 
           const float pb = fast_exp2(__builtin_fmaf(s[sb][2 * i + 1], a.scale_log2, mneg));
           const uint32_t hi = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, pb), __builtin_bit_cast(uint32_t, pa), 0x07060302u);
           pk[2 * sb + i] = hi;
-          rest[2 * sb + i] = pack_bf16(__builtin_fmaf(pa, 0x1p-40f, pa - bf16_lo(hi)), __builtin_fmaf(pb, 0x1p-40f, pb - bf16_hi(hi)));
+          rest[2 * sb + i] = pack_bf16(fmaxf(pa - bf16_lo(hi), 0x1p-126f), fmaxf(pb - bf16_hi(hi), 0x1p-126f));
           psum += pa + pb;
         }
       l_run = l_run * alpha + psum;

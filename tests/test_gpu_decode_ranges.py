@@ -2,6 +2,8 @@
 eights, ranges that begin and end inside lists, whole lists inside a range, lists that go on over several ranges, empty caches
 and more sequences than lanes.  Against the oracle at the attention tolerance; the fused step, the call without a context
 (its merge is a launch of its own) and a replayed graph give the same bits."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -194,6 +196,30 @@ def test_an_infinite_value_row_stays_infinite():
         out[:, :, 3:5] = 1.0
         assert torch.allclose(out, torch.ones_like(out), atol=1e-5)
     F.flux_destroy(ctx)
+
+
+def test_an_infinite_value_row_stays_infinite_down_to_the_smallest_weight():
+    """... and however small its weight is, as long as that is a normal number: sequence i has one key 64 * (8 + i / 16) / 8 below
+    the others (weights of 2^-92 to 2^-125, with and without bits below the upper eight)."""
+    from paper_2604_07394_amd import binding as F
+    b, n, d = 46, 64, 64
+    below = 8 + torch.arange(b, device="cuda") / 16
+    k = torch.zeros(b, 1, n, d, dtype=torch.bfloat16, device="cuda")
+    k[:, 0, 5] = -below[:, None].to(torch.bfloat16)
+    v = torch.ones(b, 1, n, d, dtype=torch.bfloat16, device="cuda")
+    v[:, 0, 5, 3] = float("inf")
+    out = torch.zeros(b, 4, d, dtype=torch.float32, device="cuda")
+    # scale: 1 / 8, or what makes the weights of whole keys powers of two
+    for scale in (0.0, math.log(2) / 6):
+        ctx = F.flux_create(0)
+        F.flux_attn_decode(ctx, F.attn_cfg(4, 1, d, 0, 1, scale, 1), torch.ones(b, 4, d, dtype=torch.bfloat16, device="cuda"), n,
+                           F.KVCache(k, v, torch.full((b,), n, dtype=torch.int32, device="cuda")), torch.ones(b, dtype=torch.uint8, device="cuda"), out)
+        torch.cuda.synchronize()
+        weight = -64 * below * (scale or 0.125) / math.log(2)
+        assert torch.isposinf(out[weight > -126, :, 3]).all(), weight[~torch.isposinf(out[:, :, 3]).all(1)]
+        out[:, :, 3] = 1.0
+        assert torch.allclose(out, torch.ones_like(out), atol=1e-5)
+        F.flux_destroy(ctx)
 
 
 @pytest.mark.parametrize("fp32", [0, 1])

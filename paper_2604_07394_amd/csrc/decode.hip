@@ -115,7 +115,7 @@ __device__ __forceinline__ int seq_visible(const SplitArgs& s, int len, int md, 
 // crosses from one pair into the next; 8 where every list has no more than that (nothing to merge) or more than 64 (half
 // the rows to merge).  (Calls of eight waves: see kDecodeFewWgs.)  Otherwise the lists lie end to end, and workgroup u of 256 or 512 takes [range_begin(u),
 // range_begin(u + 1)): equal shares not of the blocks but of what they take, for which a list is counted as a multiple of
-// the four waves and kSeam blocks more (see find_cut).
+// the waves and some blocks more (see find_cut).
 struct Cut {
   int total;        // blocks
   int shift;        // equal shares: log2 of the workgroups
@@ -185,6 +185,10 @@ __device__ __forceinline__ Cut find_cut(const SplitArgs& s, int lane, int w, Seq
   // before / now per layer, 32/8 heads of 128: 13 lists of 1223 to 15370 keys, half of them cut at 144, 42.5 / 32.0, 32 ragged ones at
   // 28/4 heads 40.1 / 36.9, 16 ring lists of 2112 at 28/4 25.0 / 23.7, 13 of 144 to 13696 37.1 / 33.7, 29 of 139 to 2305 26.8
   // / 26.3, 21 of 296 to 4373 at head dimension 64 23.4 / 18.7.  (3 to 6 blocks, and 5 to 12 at head dimension 64, differ by 2 %.)
+  // With two workgroups per CU (see kLists) the other one streams meanwhile, and a block takes twice as long: a list of head
+  // dimension 128 is a multiple of two and two blocks more then.  us with four and four / so: 104 lists of 1 to 4 keys among 24 of 2000
+  // 53.0 / 48.7, 128 of 50 to 299 31.2 / 30.4, 1000 of 20 to 199 at 28/4 heads 73.4 / 72.1, 53 of 36 to 1044 at 16/8 36.3 / 35.5.
+  // At head dimension 64 there is nothing in it: 136 of 6 to 200 18.9 / 20.4, 122 of 39 to 1278 45.9 / 44.9.
   constexpr int kSeam = 512 / D;
   // Two workgroups per CU where there are as many lists as CUs, since at most seams the other one goes on (us with one / two,
   // 32/8 heads of 128: 128 lists of 300 keys 39.9 / 34.5, 128 of 100 to 3000 61.8 / 52.6, 1000 of 20 to 200 at 28/4 heads 107 /
@@ -232,22 +236,29 @@ __device__ __forceinline__ Cut find_cut(const SplitArgs& s, int lane, int w, Seq
       c.align = __builtin_amdgcn_ballot_w64(between) == 0 ? 3 : 2;
       c.round = (1 << c.align) - 1;
     }
-    for (;;) {                                              // (rounded up for workgroups of one list, and for ranges if that is too many)
+    // an equal share of all lists: over how many ranges, and what a list counts (calls of very many lists do not round)
+    auto share = [&]() __attribute__((always_inline)) {
+      if (gridDim.x >= 2 << kDecodeWgsShift) {
+        int lists = 0;
+        each([&](int nb) __attribute__((always_inline)) { lists += nb != 0 ? s.pps : 0; });
+        if (__builtin_amdgcn_readlane(wave_inclusive_sum(lists), 63) >= kLists) c.shift = kDecodeWgsShift + 1;
+      }
+      c.align = 0;
+      if (s.aligned_shift < 0) return;
+      const bool beside = D == 128 && c.shift > kDecodeWgsShift;
+      c.round = beside ? 1 : W - 1;
+      c.pad = beside ? kSeam / 2 : kSeam;
+    };
+    if (s.aligned_shift < 0) share();
+    for (;;) {
       int mine = 0;
       each([&](int nb) __attribute__((always_inline)) { mine += counted(c, nb); });
       r.incl = wave_inclusive_sum(s.pps * mine);
       c.total = __builtin_amdgcn_readlane(r.incl, 63);
       if (c.align == 0 || c.total <= 1 << (s.aligned_shift + c.align)) break;
-      c.align = 0;
-      c.round = W - 1;
-      c.pad = kSeam;
+      share();
     }
     if (c.align > 0) return c;
-    if (gridDim.x >= 2 << kDecodeWgsShift) {
-      int lists = 0;
-      each([&](int nb) __attribute__((always_inline)) { lists += nb != 0 ? s.pps : 0; });
-      if (__builtin_amdgcn_readlane(wave_inclusive_sum(lists), 63) >= kLists) c.shift = kDecodeWgsShift + 1;
-    }
     // (lists that are not rounded up may have fewer blocks than there are workgroups: no range is empty, or it would be
     // counted among the parts of a list)
     while (c.shift > 0 && c.total >> c.shift == 0) --c.shift;

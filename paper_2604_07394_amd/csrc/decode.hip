@@ -113,9 +113,9 @@ __device__ __forceinline__ int seq_visible(const SplitArgs& s, int len, int md, 
 // ---- the cut.  Blocks of all pairs, sequence by sequence and pair by pair, numbered from 0.  While they are few (one per
 // wave of two workgroups per CU) every list is rounded up to a multiple of 4 and a workgroup takes 4, so that none
 // crosses from one pair into the next; 8 where every list has no more than that (nothing to merge) or more than 64 (half
-// the rows to merge).  (Calls of eight waves: see kDecodeFewWgs.)  Otherwise the lists lie end to end, and workgroup u of 256 or 512 takes [range_begin(u),
-// range_begin(u + 1)): equal shares not of the blocks but of what they take, for which a list is counted as a multiple of
-// the waves and some blocks more (see find_cut).
+// the rows to merge).  (Calls of eight waves: see kDecodeFewWgs.)  Of 256 to 512 short lists it takes one each.  Otherwise the
+// lists lie end to end, and workgroup u of 256 or 512 takes [range_begin(u), range_begin(u + 1)): equal shares not of the
+// blocks but of what they take, for which a list is counted as a multiple of the waves and some blocks more (see find_cut).
 struct Cut {
   int total;        // blocks
   int shift;        // equal shares: log2 of the workgroups
@@ -236,16 +236,48 @@ __device__ __forceinline__ Cut find_cut(const SplitArgs& s, int lane, int w, Seq
       c.align = __builtin_amdgcn_ballot_w64(between) == 0 ? 3 : 2;
       c.round = (1 << c.align) - 1;
     }
-    // an equal share of all lists: over how many ranges, and what a list counts (calls of very many lists do not round)
+    // too many workgroups for that: one for each list where that pays, or an equal share of all lists: over how many ranges, and
+    // what a list counts (calls of very many lists do not round)
     auto share = [&]() __attribute__((always_inline)) {
-      if (gridDim.x >= 2 << kDecodeWgsShift) {
-        int lists = 0;
-        each([&](int nb) __attribute__((always_inline)) { lists += nb != 0 ? s.pps : 0; });
-        if (__builtin_amdgcn_readlane(wave_inclusive_sum(lists), 63) >= kLists) c.shift = kDecodeWgsShift + 1;
+      int lists = 0, blocks = 0;
+      each([&](int nb) __attribute__((always_inline)) {
+        lists += nb != 0 ? s.pps : 0;
+        blocks += s.pps * nb;
+      });
+      lists = __builtin_amdgcn_readlane(wave_inclusive_sum(lists), 63);
+      const bool two = gridDim.x >= 2 << kDecodeWgsShift && lists >= kLists;   // workgroups per CU
+      // 256 to 512 lists of up to 16 blocks take a workgroup each, none of which has a seam or anything to merge; up to 24 blocks
+      // where there are hardly fewer lists than workgroups (us in equal ranges / so, 32/8 heads of 128 unless said: 64 lists of 200
+      // to 328 keys 24.3 / 19.1, 64 of 50 to 296 21.1 / 16.4, 48 of 300 to 508 25.7 / 23.2, 33 of 300 to 508 21.1 / 19.8, 40 of
+      // 50 to 439 at head dimension 64 13.8 / 11.2; 64 of 500 to 760 39.6 / 35.1, 120 of 50 to 630 at 28/4 heads 28.8 / 24.8).
+      // With fewer or longer lists the CU with two of the longest is the last (70 of 50 to 630 at 28/4 21.4 / 26.4, 48 of 700
+      // to 1010 39.7 / 41.2, 33 of 500 to 760 26.7 / 27.9).
+      if (s.aligned_shift >= 0 && two && lists >= 1 << kDecodeWgsShift && lists <= 1 << s.aligned_shift) {
+        const int most = lists > (7 << s.aligned_shift) / 8 ? 24 : 16;
+        bool longer = false;
+        each([&](int nb) __attribute__((always_inline)) { longer |= nb > most; });
+        if (__builtin_amdgcn_ballot_w64(longer) == 0) {
+          c.align = 5;
+          c.round = 31;
+          return;
+        }
       }
       c.align = 0;
+      c.shift = kDecodeWgsShift + (two ? 1 : 0);
       if (s.aligned_shift < 0) return;
-      const bool beside = D == 128 && c.shift > kDecodeWgsShift;
+      // Lists of one length that take a whole number of ranges each: no range has a seam, so they are cut evenly, and one
+      // workgroup per CU is enough (8 lists of 4224 keys 29.6 / 29.4, 32 of 2048 50.9 / 47.3, 64 of 1000 at 28/4 heads 30.6 / 27.1)
+      if ((lists & (lists - 1)) == 0 && lists <= 1 << c.shift) {
+        blocks = __builtin_amdgcn_readlane(wave_inclusive_sum(blocks), 63);
+        bool other = false;
+        each([&](int nb) __attribute__((always_inline)) { other |= nb != 0 && (unsigned)nb * (unsigned)lists != (unsigned)blocks; });
+        if (__builtin_amdgcn_ballot_w64(other) == 0) {
+          if (lists <= 1 << kDecodeWgsShift) c.shift = kDecodeWgsShift;
+          c.round = c.pad = 0;
+          return;
+        }
+      }
+      const bool beside = D == 128 && two;
       c.round = beside ? 1 : W - 1;
       c.pad = beside ? kSeam / 2 : kSeam;
     };

@@ -28,6 +28,14 @@ FA, SA = 1, 0
     (4, 4, 128, [900, 340, 1200] * 22),                       # 264 lists: 512 equal ranges
     (4, 4, 128, [900, 340, 1200] * 21),                       # 252: 256 of them
     (4, 4, 128, [256] * 65),                                  # more than 64 sequences: by eight, one workgroup each
+    (4, 4, 128, [(37 * i) % 480 + 1 for i in range(66)]),     # 264 lists of up to 16 blocks: one workgroup each
+    (8, 8, 64, [(97 * i) % 740 + 1 for i in range(60)]),      # 480 of up to 24: the same
+    (8, 8, 64, [(97 * i) % 740 + 1 for i in range(40)]),      # 320 of them: equal ranges
+    (8, 8, 128, [700] * 64),                                  # 512 lists of one length, one workgroup each
+    (8, 8, 128, [800] * 64),                                  # ... one range each
+    (8, 8, 128, [800] * 32 + [0]),                            # 256 of them, and an empty sequence: 256 ranges
+    (8, 8, 128, [800] * 32 + [801]),                          # (one length: as many blocks)
+    (4, 2, 64, [5001, 0] * 8),                                # 16 lists of one length, 16 ranges each
     (16, 16, 64, [1024] * 4),                                 # by four: as many as there may be (of four waves under the loosest bound)
     (16, 16, 64, [1024] * 4 + [1]),                           # ... and one list more: by eight, equal ranges under the loosest bound
     (16, 16, 64, [1500, 100, 1490, 70, 40, 1400, 0, 33]),     # half of the lists shorter than a range

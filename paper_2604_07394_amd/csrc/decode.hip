@@ -4,14 +4,15 @@
 // Decode is bound by reading the K and V rows of the cache once from HBM.  The work of one
 // (sequence, KV head) pair is the VISIBLE key list (FA: all positions; SA: the sinks followed by the
 // window tail, so the hidden middle of the cache is never addressed) in blocks of 32 keys.  The lists of all pairs
-// are laid end to end, and every workgroup takes the same number of blocks of that one long list, wherever it begins
+// are laid end to end, and every workgroup takes the same share of that one long list, wherever it begins
 // and ends: a run of blocks of one pair is a PART, and a workgroup whose range crosses from one pair into the next works
-// off its parts one after the other.  One 256-thread workgroup serves all query heads of the GQA
+// off its parts one after the other.  (Calls of few keys, and of some hundred short lists, give a workgroup blocks of one
+// list only.)  One workgroup of 256 threads, or 512 in calls of few keys, serves all query heads of the GQA
 // group at once, so every K/V row is fetched exactly once per step.
 //
 // The range is found ON THE DEVICE from the lengths and mode bytes the call finds there (a prefix sum over the batch), so
-// neither the mix of lengths and modes in the batch nor the host's bounds show in how evenly the chip is loaded (see
-// kDecodeWgs for why it is cut into equal ranges).
+// the mix of lengths and modes in the batch does not show in how evenly the chip is loaded (see DecodePlan for why the
+// ranges are equal).
 //
 // Per wave, 32 keys at a time:
 //   S^T[key][q]  = K[key][:] . Q[q][:]       4 (D=128) MFMA 16x16x32 bf16 per 16 keys; the A operand
@@ -23,7 +24,7 @@
 //                                            V operand needs keys along the lane's registers, so V
 //                                            rows are staged in wave-private LDS and read back with
 //                                            the transposing LDS read
-// The four waves keep private (m, l, O) and are merged through LDS at the end of a part.  A pair that lies in one workgroup's
+// The waves keep private (m, l, O) and are merged through LDS at the end of a part.  A pair that lies in one workgroup's
 // range is done then; otherwise the part's unnormalised rows go to the workspace, and the part that arrives last at its
 // pair (an arrival counter) merges the pair's parts in a fixed order (deterministic, no float atomics).  Without arrival
 // counters (the static scratch) a second small kernel does, with the same sums in the same order.
@@ -61,7 +62,7 @@ struct DecodeArgs {
   float scale_log2;       // softmax scale * log2(e)
   float* part_o;          // unnormalised rows of the parts of unfinished pairs, [place][rpu][D] (see part_place)
   float* part_ml;         // their reference (score units) and weight sum, [place][rpu][2]
-  int* table;             // two launches: [batch][2]: first block and blocks per pair of every sequence, for the merge kernel
+  int* table;             // two launches: [batch][2]: first block and blocks per pair of every sequence, and the cut, for the merge kernel
   uint32_t* status;       // sticky device status word
   // the fused decode step only: the row each sequence appends at position kv_len[b], [B, Hkv, D]
   const __bf16* k_new;
@@ -247,13 +248,15 @@ __device__ __forceinline__ Cut find_cut(const SplitArgs& s, int lane, int w, Seq
       lists = __builtin_amdgcn_readlane(wave_inclusive_sum(lists), 63);
       const bool two = gridDim.x >= 2 << kDecodeWgsShift && lists >= kLists;   // workgroups per CU
       // 256 to 512 lists of up to 16 blocks take a workgroup each, none of which has a seam or anything to merge; up to 24 blocks
-      // where there are hardly fewer lists than workgroups (us in equal ranges / so, 32/8 heads of 128 unless said: 64 lists of 200
-      // to 328 keys 24.3 / 19.1, 64 of 50 to 296 21.1 / 16.4, 48 of 300 to 508 25.7 / 23.2, 33 of 300 to 508 21.1 / 19.8, 40 of
-      // 50 to 439 at head dimension 64 13.8 / 11.2; 64 of 500 to 760 39.6 / 35.1, 120 of 50 to 630 at 28/4 heads 28.8 / 24.8).
+      // where there are hardly fewer lists than workgroups, and 24 (32 at head dimension 64) where every CU has one.  us in equal
+      // ranges / so, 32/8 heads of 128 unless said: 64 lists of 200 to 328 keys 24.3 / 19.1, 64 of 50 to 296 21.1 / 16.4, 48 of
+      // 300 to 508 25.7 / 23.2, 33 of 300 to 508 21.1 / 19.8, 40 of 50 to 439 at head dimension 64 13.8 / 11.2; 64 of 500 to 760
+      // 39.6 / 35.1, 120 of 50 to 630 at 28/4 heads 28.8 / 24.8; 32 of 500 to 760 24.6 / 21.3, 32 of 50 to 760 20.9 / 19.7, 32 of
+      // 50 to 630 at head dimension 64 13.4 / 11.1, 32 of 700 to 1010 there 17.0 / 15.2.
       // With fewer or longer lists the CU with two of the longest is the last (70 of 50 to 630 at 28/4 21.4 / 26.4, 48 of 700
-      // to 1010 39.7 / 41.2, 33 of 500 to 760 26.7 / 27.9).
+      // to 1010 39.7 / 41.2, 33 of 500 to 760 26.7 / 27.9, 32 of 50 to 1010 22.4 / 23.8).
       if (s.aligned_shift >= 0 && two && lists >= 1 << kDecodeWgsShift && lists <= 1 << s.aligned_shift) {
-        const int most = lists > (7 << s.aligned_shift) / 8 ? 24 : 16;
+        const int most = lists == 1 << kDecodeWgsShift ? (D == 64 ? 32 : 24) : lists > (7 << s.aligned_shift) / 8 ? 24 : 16;
         bool longer = false;
         each([&](int nb) __attribute__((always_inline)) { longer |= nb > most; });
         if (__builtin_amdgcn_ballot_w64(longer) == 0) {

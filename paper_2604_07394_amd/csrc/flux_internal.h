@@ -110,14 +110,15 @@ hipError_t launch_kv_append(const Ctx& c, const flux_kv_cache& cache, int hkv, i
 hipError_t launch_kv_compact_ring(const flux_kv_cache& src, const flux_kv_cache& dst, int hkv, int d, int n_sink,
                                   int window, hipStream_t s);
 
-// Decode shares the visible keys of a call out over 2^kDecodeWgsShift workgroups, one per CU, in equal ranges; calls of at
-// most 2^kDecodeAlignedShift times 128 keys take one workgroup per 128 keys of a list.  The cut itself is taken on the device;
-// the host only bounds it.  A CU takes in about 27 bytes per ns from memory, whatever its workgroups have asked for, which is
+// Decode shares the visible keys of a call out over 2^kDecodeWgsShift workgroups, one per CU, in equal ranges (two per CU
+// where there are many lists); calls of at most 2^kDecodeAlignedShift times 128 keys take one workgroup per 128 keys of a
+// list, and few keys eight waves per workgroup.  The cut itself is taken on the device; the host only bounds it.  A CU takes in about 27 bytes per ns from memory, whatever its workgroups have asked for, which is
 // its even share of what the memory delivers: a call takes as long as the CU with the most keys.  (Units of whole chunks of a
 // list left the fullest CU 18 % over the mean in a batch of 32 ragged lists and 44 % in 16 lists of 2112 keys, and the third
 // workgroup of a CU, whose lengths are asked for behind the others' keys, began to stream when those were done.)  Two
-// workgroups per CU take no more in, start later and leave twice the rows to merge: us with two / one, 32/8 heads of 128:
-// 8 x 4224 keys 29.7 / 28.1, 1 x 100000 69.8 / 65.0, 8 x 131072 652.5 / 644.9, 32 ragged lists of 28/4 heads 37.4 / 36.8.
+// workgroups per CU take no more in, start later and leave twice the rows to merge: us with two / one, 32/8 heads of 128,
+// weights of one bf16 term: 8 x 4224 keys 29.7 / 28.1, 1 x 100000 69.8 / 65.0, 8 x 131072 652.5 / 644.9, 32 ragged lists of
+// 28/4 heads 37.4 / 36.8 (one, with two terms: 29.4, 37.9 for the first and the last).
 struct DecodePlan {
   int units;        // what the scratch is sized by: the units of a cut into chunks of kMinChunk keys and more
   int pps;          // (KV head, query block) pairs per sequence

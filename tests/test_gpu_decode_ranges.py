@@ -31,6 +31,8 @@ FA, SA = 1, 0
     (4, 4, 128, [(37 * i) % 480 + 1 for i in range(66)]),     # 264 lists of up to 16 blocks: one workgroup each
     (8, 8, 64, [(97 * i) % 740 + 1 for i in range(60)]),      # 480 of up to 24: the same
     (8, 8, 64, [(97 * i) % 740 + 1 for i in range(40)]),      # 320 of them: equal ranges
+    (8, 8, 64, [(97 * i) % 1000 + 1 for i in range(32)]),     # 256 of up to 32: one each
+    (8, 8, 128, [(97 * i) % 760 + 1 for i in range(32)]),     # 256 of up to 24: one each
     (8, 8, 128, [700] * 64),                                  # 512 lists of one length, one workgroup each
     (8, 8, 128, [800] * 64),                                  # ... one range each
     (8, 8, 128, [800] * 32 + [0]),                            # 256 of them, and an empty sequence: 256 ranges

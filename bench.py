@@ -187,7 +187,7 @@ def main():
             "sa_kernel_tflops": flops_sa / (sa_avg * 1e-3) / 1e12 if sa_ms else None,
         }
         achieved = flops_fa / (fa_avg * 1e-3) / 1e12 if fa_ms else 0.0
-        roofline = {"kernel": "prefill_kernel<128, false, 8, false, true> (FA layers; eight waves per workgroup on the rows of all heads of a GQA group from 32768-token prompts on)", "bound": "mfma", "achieved": achieved,
+        roofline = {"kernel": "prefill_kernel<128, false, 8, false, true, 2> (FA layers; eight waves per workgroup on the rows of all heads of a GQA group from 32768-token prompts on)", "bound": "mfma", "achieved": achieved,
                     "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": achieved / PEAK_BF16_TFLOPS,
                     "traffic": None, "traffic_note": "not the profiled workload",
                     "traffic_unit": "bytes per launch",
@@ -412,8 +412,8 @@ def main():
 
         def decode_step(mask, events=None, fused=True):
             """One decode step of the stack: per layer, append the new K/V row of every sequence and attend.
-            fused: one flux_attn_decode_append call per layer (two launches); else flux_kv_append followed by
-            flux_attn_decode (three launches, the same results bit for bit)."""
+            fused: one flux_attn_decode_append call per layer (one launch); else flux_kv_append followed by
+            flux_attn_decode (two launches, the same results bit for bit)."""
             cur["n"] += 1
             for l in range(LD):
                 if not fused:
@@ -540,7 +540,7 @@ def main():
             "fa_layer_ms": fa_avg, "sa_layer_ms": sa_avg,
             "fa_layer_ms_median": float(np.median(fa_ms)) if fa_ms else None,
             "sa_layer_ms_median": float(np.median(sa_ms)) if sa_ms else None,
-            "roofline": {"kernel": "decode_splitk_kernel<128, true, true> + decode_combine_kernel<128, 4> (FA layers)",
+            "roofline": {"kernel": "decode_splitk_kernel<128, true, true, true, 4> (FA layers)",
                          "bound": "hbm", "achieved": ach, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                          "frac": ach / PEAK_HBM_GBS,
                          "traffic": None, "traffic_note": "not the profiled workload",

@@ -152,13 +152,13 @@ def test_fused_step_long_lists_nontemporal_path(lib):
 
 
 @pytest.mark.parametrize("hq,hkv,d,lens,modes", [
-    (4, 1, 128, [1], [FA]),                                   # one key, one unit: nothing to merge
-    (8, 2, 64, [256, 257, 1], [FA, FA, SA]),                  # on either side of a chunk
-    (32, 8, 128, [4351], [FA]),                               # 17 chunks: the longest list of one launch
-    (32, 8, 128, [4352], [FA]),                               # one more key than that after the append: two launches
-    (16, 1, 64, [1000, 3], [SA, FA]),                         # 16 query heads per KV head, four chunks
+    (4, 1, 128, [1], [FA]),                                   # one key: nothing to merge
+    (8, 2, 64, [256, 257, 1], [FA, FA, SA]),                  # on either side of a workgroup's eight blocks
+    (32, 8, 128, [4351], [FA]),                               # eight waves, four blocks per workgroup
+    (32, 8, 128, [4352], [FA]),                               # one more key than 17 times 256 after the append
+    (16, 1, 64, [1000, 3], [SA, FA]),                         # 16 query heads per KV head
     (20, 20, 128, [700, 0, 90], [FA, FA, SA]),                # 60 pairs; an empty cache
-    (21, 21, 128, [700, 0, 90], [FA, FA, SA]),                # 63 pairs: two launches
+    (21, 21, 128, [700, 0, 90], [FA, FA, SA]),                # 63 pairs
 ])
 def test_few_short_lists(lib, hq, hkv, d, lens, modes):
     """Calls of few short lists are merged in the launch that streams them.  Against the oracle, several calls in a row on the

@@ -12,7 +12,7 @@
 //     hidden vector turns it into the two logits and the decision (in launches of many workgroups a third kernel does).
 // Batch 4, hidden 4096, inner 256, pool 100: 17.4 us per call with the head as a
 // third launch and the loads of a column block waiting for those of the one before, 12.8 without, 11.9 with the counters of
-// the sequences on lines of their own (16 sequences 23.4 and 19.6).
+// the sequences on lines of their own (16 sequences 23.4 and 19.6), 11.5 and 17.1 with two row splits instead of seven.
 #include "flux_internal.h"
 
 namespace flux {
@@ -24,54 +24,76 @@ struct PoolArgs {
   float* psum;            // [batch, splits, hidden]
 };
 
+constexpr int kPoolRows = 8;            // rows per lane that are asked for at once where 16 lanes share a row
+constexpr int kPoolOnce = 16 * kPoolRows;   // rows of a split then
+
 // pooled row number t (0-based among the pooled rows) -> row of the sequence
 __device__ __forceinline__ int pooled_row(int t, int n_rows, int pool, bool all) {
   return (all || t < pool) ? t : n_rows - 2 * pool + t;
 }
 
+// CL: lanes that share a row, 8 columns each.  64 (a wave per row) for whole sequences, which are streamed.  16 for pools: a
+// workgroup reads what it would read otherwise, but as 128 rows of 128 columns, all asked for at once, so that a quarter of
+// the row splits hold them all.  The MLP workgroups each read the sums of all splits of their sequence, next to 64 KB of
+// weights: 16 KB per split at hidden 4096, of which pools of 100 + 100 rows had seven (us per call
+// with seven / two, inner 256: batch 1 11.5 / 11.0, 4 12.4 / 11.5, 8 14.4 / 12.7, 16 19.9 / 17.1, 64 46.9 / 41.9; 512
+// sequences of hidden 256 21.5 / 17.1.  One split of two rounds 12.3 at batch 4, four 12.0).
+template <int CL>
 __global__ __launch_bounds__(256) void router_pool_kernel(PoolArgs a) {
-  __shared__ float red[4][512];
-  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
-  const int col = blockIdx.x * 512 + l * 8;
+  constexpr int RL = 256 / CL;                              // rows that the workgroup reads side by side
+  constexpr int COLS = 8 * CL;
+  constexpr int FLY = CL == 64 ? 4 : kPoolRows;             // rows per lane in flight
+  __shared__ float red[4][COLS];
+  const int tid = threadIdx.x, w = tid >> 6;
+  const int cl = tid % CL;
+  const int col = blockIdx.x * COLS + cl * 8;
   const int split = blockIdx.y, b = blockIdx.z;
   const int r0 = a.cu[b];
   const int n_rows = a.cu[b + 1] - r0;
   const bool all = a.pool <= 0 || n_rows <= 2 * a.pool;
   const int n_pooled = all ? n_rows : 2 * a.pool;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  auto add = [&](const u32x4& v) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      acc[2 * i] += bf16_lo(v[i]);
+      acc[2 * i + 1] += bf16_hi(v[i]);
+    }
+  };
   if (col < a.hidden) {
     const __bf16* xc = a.x + (int64_t)r0 * a.hidden + col;
-    const int step = 4 * a.splits;
-    int t = split * 4 + w;
-    // four rows per round, so that four independent 16-byte loads are in flight per lane; every row is
+    const int step = RL * a.splits;
+    int t = split * RL + tid / CL;
+    // several rows per round, so that independent 16-byte loads are in flight per lane; every row is
     // read once, hence nontemporal
-    for (; t + 3 * step < n_pooled; t += 4 * step) {
-      u32x4 v[4];
+    for (; CL == 64 ? t + (FLY - 1) * step < n_pooled : t < n_pooled; t += FLY * step) {
+      u32x4 v[FLY];
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        v[u] = __builtin_nontemporal_load((const u32x4*)(xc + (int64_t)pooled_row(t + u * step, n_rows, a.pool, all) * a.hidden));
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          acc[2 * i] += bf16_lo(v[u][i]);
-          acc[2 * i + 1] += bf16_hi(v[u][i]);
-        }
-    }
-    for (; t < n_pooled; t += step) {
-      const u32x4 v = *(const u32x4*)(xc + (int64_t)pooled_row(t, n_rows, a.pool, all) * a.hidden);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        acc[2 * i] += bf16_lo(v[i]);
-        acc[2 * i + 1] += bf16_hi(v[i]);
+      for (int u = 0; u < FLY; ++u) {
+        const int tu = CL == 64 ? t + u * step : min(t + u * step, n_pooled - 1);   // (rows past the last one are not added)
+        v[u] = __builtin_nontemporal_load((const u32x4*)(xc + (int64_t)pooled_row(tu, n_rows, a.pool, all) * a.hidden));
       }
+#pragma unroll
+      for (int u = 0; u < FLY; ++u)
+        if (CL == 64 || t + u * step < n_pooled) add(v[u]);
+    }
+    if constexpr (CL == 64)
+      for (; t < n_pooled; t += step) add(*(const u32x4*)(xc + (int64_t)pooled_row(t, n_rows, a.pool, all) * a.hidden));
+  }
+  if constexpr (CL == 16) {                                 // the four rows of a wave meet in its first 16 lanes
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      acc[i] = sum_across_halves(acc[i]);
+      acc[i] += __shfl_xor(acc[i], 16);
     }
   }
+  if (CL == 64 || (tid & 63) < 16) {
 #pragma unroll
-  for (int i = 0; i < 8; ++i) red[w][l * 8 + i] = acc[i];
+    for (int i = 0; i < 8; ++i) red[w][cl * 8 + i] = acc[i];
+  }
   __syncthreads();
-  for (int c = tid; c < 512; c += 256) {
-    const int cc = blockIdx.x * 512 + c;
+  for (int c = tid; c < COLS; c += 256) {
+    const int cc = blockIdx.x * COLS + c;
     if (cc < a.hidden)
       a.psum[((int64_t)b * a.splits + split) * a.hidden + cc] = (red[0][c] + red[1][c]) + (red[2][c] + red[3][c]);
   }
@@ -151,27 +173,31 @@ __global__ __launch_bounds__(256, BLK > 2048 ? 2 : (BLK > 1024 ? 3 : 5)) void ro
       v1[k] = *(const u32x4*)(wrow1 + cc);
     }
     // pooled mean: the row-split partial sums are added in split order (fixed, so the result is reproducible); 4
-    // columns per thread and 1024, eight splits' loads in flight together
+    // columns per thread and 1024, the loads of two or eight splits in flight together
     f32x4 s[NQ];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) s[q] = f32x4{0.f, 0.f, 0.f, 0.f};
     const float* p = a.psum + (int64_t)b * a.splits * a.hidden;
-    for (int sp = 0; sp < a.splits; sp += 8) {
-      f32x4 v[8][NQ];
+    auto add_splits = [&](int sp, auto n) __attribute__((always_inline)) {
+      constexpr int N = decltype(n)::value;
+      f32x4 v[N][NQ];
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
+      for (int i = 0; i < N; ++i)
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
           const int c = c0 + 1024 * q + 4 * tid;
           v[i][q] = *(const f32x4*)(p + (int64_t)min(sp + i, a.splits - 1) * a.hidden + (c < a.hidden ? c : 0));
         }
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
+      for (int i = 0; i < N; ++i)
         if (sp + i < a.splits) {
 #pragma unroll
           for (int q = 0; q < NQ; ++q) s[q] += v[i][q];
         }
-    }
+    };
+    if (a.splits <= 2) add_splits(0, std::integral_constant<int, 2>());
+    else
+      for (int sp = 0; sp < a.splits; sp += 8) add_splits(sp, std::integral_constant<int, 8>());
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
       const int c = c0 + 1024 * q + 4 * tid;
@@ -236,9 +262,9 @@ static_assert(kMlpFew <= kRouterCounters, "a counter per sequence");
 hipError_t launch_router(const Ctx& c, const void* x, const int32_t* cu_seqlens, int batch, int hidden, int pool,
                          const void* w1, const void* b1, const void* w2, const void* b2, int inner,
                          uint8_t* mode_out, float* logits_out, hipStream_t s) {
-  // row splits: ~32 pooled rows per workgroup when the count is known, 64 splits for whole-sequence
+  // row splits: kPoolOnce pooled rows per workgroup when the count is known, 64 splits for whole-sequence
   // pooling, bounded by the scratch region
-  int splits = pool > 0 ? (2 * pool + 31) / 32 : 64;
+  int splits = pool > 0 ? (2 * pool + kPoolOnce - 1) / kPoolOnce : 64;
   const size_t per_split = (size_t)batch * hidden * sizeof(float);
   const size_t hbytes = (size_t)batch * inner * sizeof(float);
   size_t room = kSmallBytes - hbytes;
@@ -248,7 +274,8 @@ hipError_t launch_router(const Ctx& c, const void* x, const int32_t* cu_seqlens,
   float* hbuf = c.small + (size_t)splits * batch * hidden;
 
   PoolArgs pa{(const __bf16*)x, cu_seqlens, hidden, pool, splits, psum};
-  hipLaunchKernelGGL(router_pool_kernel, dim3((hidden + 511) / 512, splits, batch), dim3(256), 0, s, pa);
+  if (pool > 0) hipLaunchKernelGGL(router_pool_kernel<16>, dim3((hidden + 127) / 128, splits, batch), dim3(256), 0, s, pa);
+  else hipLaunchKernelGGL(router_pool_kernel<64>, dim3((hidden + 511) / 512, splits, batch), dim3(256), 0, s, pa);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
 

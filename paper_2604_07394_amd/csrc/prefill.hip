@@ -498,15 +498,19 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
   int it0 = 0, n_iter = n_blocks, n_parts = 1;             // (n_iter: one past its last)
   if (SPLIT && chunk < n_blocks) {
     n_parts = (n_blocks + chunk - 1) / chunk;
-    if (ci >= n_parts) return;                               // uniform
     it0 = (int)((int64_t)ci * n_blocks / n_parts);
     n_iter = (int)((int64_t)(ci + 1) * n_blocks / n_parts);
-  } else if (SPLIT && ci > 0) {
-    return;
   }
-  if (SPLIT && tid == 0) {
+  if (SPLIT && tid == 0 && ci < n_parts) {
     fin = {rows, rem0, grp, a.hq, n_parts > 1 ? slot0 + ci * slot_step : -1, a.out_fp32, tile_off, (FLUX_GLOBAL void*)a.out, (FLUX_GLOBAL float*)a.part_o, (FLUX_GLOBAL float*)a.part_ml};
     if (a.split_units > 0 && ci == 0) a.tile_info[((int64_t)b * a.hkv + kvh) * a.n_qtiles + qt] = i32x4{slot0, slot_step, n_parts, 0};
+  }
+  if constexpr (SPLIT) {
+    // (said to be uniform behind the branch of one thread: the loop over the blocks is compiled for lanes that leave it at
+    // different times otherwise)
+    it0 = __builtin_amdgcn_readfirstlane(it0);
+    n_iter = __builtin_amdgcn_readfirstlane(n_iter);
+    if (__builtin_amdgcn_readfirstlane(ci) >= __builtin_amdgcn_readfirstlane(n_parts)) return;
   }
 
   const char* kbase = (const char*)(a.k + (int64_t)b * a.stride_b + (int64_t)kvh * a.stride_h);
@@ -521,13 +525,13 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
   // swizzle of row (w + NW*t)*RPI + l/CPR is (4w + l/16) & (CPR-1) for both head sizes, a per-lane constant.
   const int v_lrow = l / CPR;
   const int k_chunk = (l % CPR) ^ ((4 * w + (l >> 4)) & (CPR - 1));
-  auto k_slot = [&](int t, int rmax) { return min((w + NW * t) * RPI + v_lrow, rmax) * pitch_g + k_chunk * 16; };
+  auto k_slot = [&](int t, int rmax) __attribute__((always_inline)) { return min((w + NW * t) * RPI + v_lrow, rmax) * pitch_g + k_chunk * 16; };
   // the 32-byte units of a V row are XOR-swizzled by the row (D = 128: row & 7; D = 64, two rows per 64
   // banks: (row >> 1) & 3), which makes the transposing reads below conflict-free; the row of transfer
   // w + NW*t, lane l is (w + NW*t) * RPI + l / CPR, so the swizzle is a per-lane constant
   const int v_swz = D == 128 ? ((4 * (w & 1) + v_lrow) << 1) : (((v_lrow >> 1) & 3) << 1);
   const int v_chunk = (l % CPR) ^ v_swz;
-  auto v_slot = [&](int t, int rmax) { return min((w + NW * t) * RPI + v_lrow, rmax) * pitch_g + v_chunk * 16; };
+  auto v_slot = [&](int t, int rmax) __attribute__((always_inline)) { return min((w + NW * t) * RPI + v_lrow, rmax) * pitch_g + v_chunk * 16; };
   int k_off[KPW], v_off[VPW];                                // byte offsets inside a tile that is fully cached
 #pragma unroll
   for (int t = 0; t < KPW; ++t) k_off[t] = k_slot(t, BN);
@@ -538,11 +542,11 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
   const uint32_t lds_w = lds0 + 1024 * w;                    // this wave's 1 KB slot inside every NW KB of a stage
 
   // tile index (in units of BN keys) of iteration `it`: the blocks [0, n_a) first, then [win0, win0 + n_b)
-  auto tile_of = [&](int it) { return it < n_a ? it : win0 + (it - n_a); };
+  auto tile_of = [&](int it) __attribute__((always_inline)) { return it < n_a ? it : win0 + (it - n_a); };
 
   // All transfers of one tile with rows clamped to the cached length: the first tile, and a last tile that
   // is only partly inside the cache.
-  auto issue_tile_clamped = [&](int tile, int stage) {
+  auto issue_tile_clamped = [&](int tile, int stage) __attribute__((always_inline)) {
     const int j0 = tile * BN;
     const int rmax = len - 1 - j0;                           // rows past the cached length are clamped
     const char* kt = kbase + (int64_t)j0 * pitch_g;
@@ -629,10 +633,10 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
   if constexpr (BS) {
     if (sa) bm_seq = a.bmask + ((int64_t)b * a.bm_heads + (a.bm_heads > 1 ? h : 0)) * a.bm_qblocks * (int64_t)a.bm_kblocks;
   }
-  auto next_kept_block = [&](int& rows) -> int {
+  auto next_kept_block = [&](int& rows) __attribute__((always_inline)) -> int {
     for (;;) {
       const unsigned long long any = scan_bits[0] | scan_bits[1] | scan_bits[2];
-      if (any != 0) {
+      if (__builtin_expect(any != 0, 1)) {
         const int bit = __builtin_ctzll(any);
         rows = (int)((scan_bits[0] >> bit) & 1) | (int)(((scan_bits[1] >> bit) & 1) << 1) | (int)(((scan_bits[2] >> bit) & 1) << 2);
         const unsigned long long clr = ~(1ull << bit);
@@ -648,12 +652,14 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
       for (int r = 0; r < 3; ++r) {
         const int rb = rb0 + r;                              // absolute query block
         bool keep = r < n_rb && kbk <= rb;                   // never a later block (causal), nothing for absent rows
-        if (keep && kbk < rb && bm_seq != nullptr) {         // the diagonal block is kept whatever the flag says
+        if (r < n_rb && bm_seq != nullptr) {
+          // (no branch that differs between lanes, see weights_guarded: every lane reads a flag of the matrix)
           const int rq = rb - (pos0 >> 6);
+          const bool flag = bm_seq[(int64_t)min(rq, a.bm_qblocks - 1) * a.bm_kblocks + min(kbk, a.bm_kblocks - 1)] != 0;
           // a matrix too small for the lengths found on the device hides what it does not cover, and says so
-          const bool inside = rq < a.bm_qblocks && kbk < a.bm_kblocks;
-          if (!inside && w == 0 && h == 0) atomicOr(a.status, (uint32_t)FLUX_DEV_BAD_LENGTH);
-          keep = inside && bm_seq[(int64_t)rq * a.bm_kblocks + kbk] != 0;
+          const bool inside = rq < a.bm_qblocks && kbk < a.bm_kblocks, asked = keep && kbk < rb;   // the diagonal block is kept whatever the flag says
+          if (__builtin_expect(__builtin_amdgcn_ballot_w64(asked && !inside) != 0 && w == 0 && h == 0, 0)) atomicOr(a.status, (uint32_t)FLUX_DEV_BAD_LENGTH);
+          keep = keep && (!asked || (inside && flag));
         }
         scan_bits[r] = __builtin_amdgcn_ballot_w64(keep);
       }
@@ -663,14 +669,14 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
 
   // One iteration.  STG (the LDS stage of this tile) is a compile-time constant: the loop is unrolled by two so
   // that every LDS address is a loop-invariant register plus an immediate.
-  auto iteration = [&](int it, auto stg_c) {
+  auto iteration = [&](int it, auto stg_c) __attribute__((always_inline)) {
     constexpr int STG = decltype(stg_c)::value;
     __builtin_amdgcn_s_waitcnt(0x0F70);                      // vmcnt(0): this wave's transfers have landed
     __syncthreads();                                         // ... and everyone's; the other stage is free
     if constexpr (BS) {
       nxt_kb = next_kept_block(nxt_rows);
-      if (nxt_kb >= 0) {                                     // the next kept block, in flight during the math below
-        if ((nxt_kb + 1) * BN <= len) {
+      if (__builtin_expect(nxt_kb >= 0, 1)) {                // the next kept block, in flight during the math below
+        if (__builtin_expect((nxt_kb + 1) * BN <= len, 1)) {
           const int64_t off = (int64_t)nxt_kb * step_b;
           if constexpr (KPW == 4) dma_tile4<(STG ^ 1) * STAGE, KTILE>(kbase + off, vbase + off, k_off, v_off, lds_w);
           else dma_tile2<(STG ^ 1) * STAGE, KTILE, 1024 * NW>(kbase + off, vbase + off, k_off, v_off, lds_w);
@@ -678,7 +684,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
           issue_tile_clamped(nxt_kb, STG ^ 1);
         }
       }
-    } else if (it + 1 < lim_whole) {                         // the next tile, in flight during the math below
+    } else if (__builtin_expect(it + 1 < lim_whole, 1)) {    // the next tile, in flight during the math below
       if constexpr (KPW == 4) dma_tile4<(STG ^ 1) * STAGE, KTILE>(kt_n, vt_n, k_off, v_off, lds_w);
       else dma_tile2<(STG ^ 1) * STAGE, KTILE, 1024 * NW>(kt_n, vt_n, k_off, v_off, lds_w);
       const int64_t adv = it + 2 == n_a ? jump_b : step_b;   // on to the tile after it (the window part starts at win0)
@@ -697,7 +703,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
       plain = wave_active && k_lo && k_hi && bs_j0 + BN - 1 <= i_w_min;
       cur_kb = nxt_kb;                                       // the state moves on; this iteration keeps bs_j0 / bs_rows
       cur_rows = nxt_rows;
-      if (!plain && (!wave_active || bs_j0 > i_w_max || !(k_lo || k_hi))) return;   // nothing for this wave here
+      if (__builtin_expect(!plain && (!wave_active || bs_j0 > i_w_max || !(k_lo || k_hi)), 0)) return;   // nothing for this wave here
     }
 
     FLUX_LDS char* st = (FLUX_LDS char*)smem + STG * STAGE;
@@ -710,8 +716,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
     bf16x8 pf[QB][KS];           // pf[qb][ks]: weights of keys 32*ks + {4g..4g+3, 16+4g..16+4g+3}, as a B operand
     bf16x8 kf[KB][KC];
     bf16x8 vf[KS][DB];
-    auto read_k = [&](int kb, int kc) { kf[kb][kc] = *(FLUX_LDS bf16x8*)(st + k_rd[kc] + 16 * kb * KPITCH); };
-    auto read_v = [&](int ks, int db) {
+    auto read_k = [&](int kb, int kc) __attribute__((always_inline)) { kf[kb][kc] = *(FLUX_LDS bf16x8*)(st + k_rd[kc] + 16 * kb * KPITCH); };
+    auto read_v = [&](int ks, int db) __attribute__((always_inline)) {
       FLUX_LDS char* vp = st + v_rd[db] + 32 * ks * ROWB;
       const bf16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((FLUX_LDS bf16x4*)vp);
       const bf16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((FLUX_LDS bf16x4*)(vp + 16 * ROWB));
@@ -721,7 +727,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
     // block's maximum first: any reference gives the same quotient, and fp32 / bf16 keep their relative
     // precision over the whole exponent range.  A row without a reference yet uses 0.
     float l_blk[QB];
-    auto weights = [&]() {
+    auto weights = [&]() __attribute__((always_inline)) {
       const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb) {
@@ -742,7 +748,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
         }
       }
     };
-    auto accumulate = [&](int ks) {        // o[db][qb][i] is d = 16*db + 4*g + i of query row (qb, n)
+    auto accumulate = [&](int ks) __attribute__((always_inline)) {        // o[db][qb][i] is d = 16*db + 4*g + i of query row (qb, n)
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -754,10 +760,10 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
     // redo the weights.  In the steady state the maximum, its cross-lane steps and the rescale are not executed.  Rows
     // that need no move keep their reference, so that a row's result does not depend on the rows that share its wave
     // (launch shapes group rows differently, and give the same bits).
-    auto weights_guarded = [&]() {
+    auto weights_guarded = [&]() __attribute__((always_inline)) {
       weights();
       // (one ballot per comparison: each is then the comparison's own lane mask, with no vector instruction between)
-      if (!all_ref || (__builtin_amdgcn_ballot_w64(!(l_blk[0] < kWeightGuard)) | __builtin_amdgcn_ballot_w64(!(l_blk[QB - 1] < kWeightGuard))) != 0) {
+      if (__builtin_expect(!all_ref || (__builtin_amdgcn_ballot_w64(!(l_blk[0] < kWeightGuard)) | __builtin_amdgcn_ballot_w64(!(l_blk[QB - 1] < kWeightGuard))) != 0, 0)) {
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
           float mloc = s[0][qb][0];
@@ -771,14 +777,15 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
           // the row moves whatever the others do)
           const bool move = m_ref[qb] == -INFINITY || __builtin_fmaf(mloc, a.scale_log2, mneg[qb]) >= 31.f;
           const float m_new = fmaxf(m_ref[qb], mloc);
-          if (move && m_new > m_ref[qb]) {                                       // false while both are -inf
-            const float al = fast_exp2((m_ref[qb] - m_new) * a.scale_log2);      // 0 for a row's first reference
-            l_run[qb] *= al;
+          // (selects and no branch: a branch that differs between lanes makes the compiler structurise the whole loop, which
+          // leaves taken branches behind in every block)
+          const bool moves = move && m_new > m_ref[qb];                          // false while both are -inf
+          const float al = moves ? fast_exp2((m_ref[qb] - m_new) * a.scale_log2) : 1.f;   // 0 for a row's first reference
+          l_run[qb] *= al;
 #pragma unroll
-            for (int db = 0; db < DB; ++db) o[db][qb] *= al;
-            m_ref[qb] = m_new;
-            mneg[qb] = -m_new * a.scale_log2;
-          }
+          for (int db = 0; db < DB; ++db) o[db][qb] *= al;
+          m_ref[qb] = moves ? m_new : m_ref[qb];
+          mneg[qb] = moves ? -m_new * a.scale_log2 : mneg[qb];
         }
         weights();
         all_ref = __builtin_amdgcn_ballot_w64((m_ref[0] == -INFINITY) | (m_ref[QB - 1] == -INFINITY)) == 0;
@@ -794,7 +801,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
     if constexpr (BS) {
       j0 = bs_j0;
       mask_causal = !plain;
-    } else if (!plain) {
+    } else if (__builtin_expect(!plain, 0)) {
       j0 = tile_of(it) * BN;
       bool skip = !wave_active || j0 > i_w_max;
       mask_causal = j0 + BN - 1 > i_w_min;                   // the diagonal crosses the block
@@ -807,6 +814,11 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
       }
       if (skip) return;
     }
+    // Wave priorities: the second product above the scores, and those above the softmax and the transfers.  Of the two waves of
+    // a SIMD one then gets through its MFMAs while the other does its vector work, instead of both taking turns at either (us with
+    // the softmax raised, nothing raised, and so, 32/8 heads of 128: 8192 tokens 458 / 465 / 438, 4000 126 / 133 / 118, 4 x 512
+    // behind 16000 491 / 469 / 435, 32768 tokens 6899 / 6760 / 6655; other orders of the four parts lie between).
+    __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -816,7 +828,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
     // fragments of keys 0..31 read between them: a read between two MFMAs costs the wave a few cycles, in a run of
     // reads sixteen, and every fragment is asked for at least sixteen MFMAs before its use.  The accumulators start
     // from what the caller put into s.
-    auto scores = [&]() {
+    auto scores = [&]() __attribute__((always_inline)) {
 #pragma unroll
       for (int t = 0; t < 2 * KC; ++t) {
         const int kc = t >> 1, kb = t & 1;
@@ -841,7 +853,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
     // compiler keeps masked and unmasked scores in different registers and copies all 32 of them in every plain
     // block.)  Key j = j0 + 4*g + c with the constant c = 16*kb + i, so each bound is moved into the lane once
     // (bound - j0 - 4*g) and compared with constants.
-    if (mask_edge) {
+    if (__builtin_expect(mask_edge, 0)) {
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb) {
         const int hi = i_mine[qb] - j0 - 4 * g, lo = w_lo_mine[qb] - j0 - 4 * g, sl = a.sink_lim - j0 - 4 * g;
@@ -855,7 +867,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
           }
       }
       scores();
-    } else if (mask_causal) {
+    } else if (__builtin_expect(mask_causal, 0)) {
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb) {
         int hi = i_mine[qb] - j0 - 4 * g;
@@ -874,12 +886,9 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
         for (int qb = 0; qb < QB; ++qb) s[kb][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
       scores();
     }
-    // The softmax part runs at a raised wave priority: while it is short, the other wave of this SIMD is mostly
-    // inside a run of MFMAs, which queue on the matrix pipe anyway, so letting the vector work through first
-    // shortens this wave's way back to its own MFMAs (measured: +2.7 % on the FA launch).
-    __builtin_amdgcn_s_setprio(1);
-    weights_guarded();
     __builtin_amdgcn_s_setprio(0);
+    weights_guarded();
+    __builtin_amdgcn_s_setprio(2);
     __builtin_amdgcn_sched_barrier(0);
     // O^T += keys 0..31 with the V fragments of keys 32..63 read between the MFMAs
 #pragma unroll
@@ -890,20 +899,21 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
       __builtin_amdgcn_sched_barrier(0);
     }
     accumulate(1);
+    __builtin_amdgcn_s_setprio(0);
   };
 
   if constexpr (!BS) {
     if (n_iter > it0) issue_tile_clamped(tile_of(it0), 0);
     for (int it = it0; it < n_iter; it += 2) {
       iteration(it, std::integral_constant<int, 0>());
-      if (it + 1 < n_iter) iteration(it + 1, std::integral_constant<int, 1>());
+      if (__builtin_expect(it + 1 < n_iter, 1)) iteration(it + 1, std::integral_constant<int, 1>());
     }
   } else {
     cur_kb = next_kept_block(cur_rows);
     if (cur_kb >= 0) issue_tile_clamped(cur_kb, 0);
     while (cur_kb >= 0) {
       iteration(0, std::integral_constant<int, 0>());
-      if (cur_kb < 0) break;
+      if (__builtin_expect(cur_kb < 0, 0)) break;
       iteration(0, std::integral_constant<int, 1>());
     }
   }

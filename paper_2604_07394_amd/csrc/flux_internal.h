@@ -101,7 +101,6 @@ constexpr size_t kHeaderBytes = 4096;         // status + counters
 constexpr size_t kDecodeCountersAt = kHeaderBytes;   // bytes
 constexpr size_t kAppendCountersAt = kDecodeCountersAt + kDecodeCounters * kCounterStride * 4;
 constexpr size_t kCountersBytes = (kAppendCountersAt + kAppendGather * kCounterStride * 4 - kHeaderBytes + 4095) / 4096 * 4096;
-constexpr int kPrefillWideMinRows = 32768;    // prefill launches whose longest prompt has at least this many rows use 256-row workgroups
 
 // ---- launchers (each validates nothing: flux_api.hip has done it) ---------------------------
 hipError_t launch_kv_append(const Ctx& c, const flux_kv_cache& cache, int hkv, int d, const void* k_new,

@@ -2,8 +2,7 @@
 // sink + window subset of Sec. 4.1 / App. C.3), chosen per sequence by the cached mode byte.
 //
 // Shape of the computation (one workgroup = 128 query rows, 4 waves x 32 rows = 2 column blocks of 16 queries;
-// launches for long prompts use 8 waves per workgroup, 256 rows, launches of few tiles 4 waves x 16 rows; which rows these
-// are, see the kernel):
+// launches of few tiles 4 waves x 16 rows; which rows these are, see the kernel):
 //   for each VISITED 64-key block (FA: all blocks up to the diagonal; SA: the sink blocks and the
 //   blocks that intersect the tile's window, nothing else: hidden blocks are skipped, not masked)
 //     S^T[key][q]  = K[key][:] . Q[q][:]     MFMA 16x16x32 bf16, A = K rows from LDS, B = Q in registers
@@ -82,13 +81,13 @@ __device__ __forceinline__ void dma_tile4(const char* kt, const char* vt, const 
                    [o5] "i"(OFF + KT + 4096), [o6] "i"(OFF + KT + 8192), [o7] "i"(OFF + KT + 12288)
                : "memory", "m0", "scc");
 }
-template <int OFF, int KT, int STEP = 4096>   // STEP: bytes between the two transfers of a wave (1 KB per wave of the workgroup)
+template <int OFF, int KT>
 __device__ __forceinline__ void dma_tile2(const char* kt, const char* vt, const int (&ko)[2], const int (&vo)[2],
                                           uint32_t lds_base) {
   asm volatile(FLUX_DMA_ONE("k0", "kt", "o0") FLUX_DMA_ONE("k1", "kt", "o1") FLUX_DMA_ONE("v0", "vt", "o4")
                FLUX_DMA_ONE("v1", "vt", "o5")
                : : [k0] "v"(ko[0]), [k1] "v"(ko[1]), [v0] "v"(vo[0]), [v1] "v"(vo[1]), [kt] "s"(kt), [vt] "s"(vt),
-                   [lds] "s"(lds_base), [o0] "i"(OFF), [o1] "i"(OFF + STEP), [o4] "i"(OFF + KT), [o5] "i"(OFF + KT + STEP)
+                   [lds] "s"(lds_base), [o0] "i"(OFF), [o1] "i"(OFF + 4096), [o4] "i"(OFF + KT), [o5] "i"(OFF + KT + 4096)
                : "memory", "m0", "scc");
 }
 
@@ -314,10 +313,13 @@ __device__ __forceinline__ PrefillUnit prefill_plan(const PrefillArgs& a, int l,
 // worked out for nothing, and its query rows are contiguous in memory.  Otherwise a tile is 128 tokens of one head:
 // finding the rows costs a workgroup about a microsecond, more than that saves where tiles are full (8 x 2048 tokens
 // packed 3 % slower), and in the block-sparse form the keep matrix differs between heads.
-// NW: waves per workgroup, 4 (two workgroups per CU) or 8 (one).  QB: column blocks of 16 rows per wave, 1 in launches of few
-// tiles (where that pays, see launch_prefill)
-template <int D, bool BS, int NW, bool PLAN = false, bool PACK = NW == 8, int QB = 2>
-__global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(PrefillArgs a) {
+// QB: column blocks of 16 rows per wave, 1 in launches of few tiles (where that pays, see launch_prefill)
+// (Eight waves and 256 rows per workgroup, one per CU, which transfer every tile once for twice the rows, were 1 to 3 % faster from
+// 32768 tokens on until the loop lost its taken branches; us with eight / with four since: 32768 tokens 7013 / 6767, 28/4 heads
+// 6063 / 5894, 65536 tokens 27328 / 27320, sparse layers 1752 / 1750 and 3637 / 3632, 16384 tokens behind 16384 5073 / 5017.)
+template <int D, bool BS, bool PLAN = false, bool PACK = false, int QB = 2>
+__global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
+  constexpr int NW = 4;                   // waves, two workgroups per CU
   constexpr bool SPLIT = PLAN && PACK;    // tiles may be split
   constexpr int WR = 16 * QB;             // query rows per wave
   constexpr int BM = WR * NW;             // query rows per workgroup
@@ -366,7 +368,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
   int q_begin, n_q, len, ci = 0, chunk = 0x7FFFFFFF, slot0 = 0, slot_step = 0;
   bool sa;
   if constexpr (PLAN) {
-    const PrefillUnit u = prefill_plan<PACK>(a, l, BM, NW == 8 ? 256 : (D == 64 ? kResident64 : kResident128));
+    const PrefillUnit u = prefill_plan<PACK>(a, l, BM, D == 64 ? kResident64 : kResident128);
     if (u.b < 0) return;                                     // uniform for the workgroup
     b = u.b;
     h = u.kvh * a.group;
@@ -387,11 +389,11 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
   } else {
     const int i = blockIdx.x;
     const int n_pairs = a.batch * a.hkv;
-    const int gw = a.group / grp;                            // workgroups per (pair, query tile)
+    const int gw = a.group;                                  // workgroups per (pair, query tile)
     if (a.xcd_map == 1) {                                    // n_pairs a multiple of 8: eight pairs at a time, one per XCD
       const int x = i & 7;
       int j = i >> 3;
-      if (!BS && NW == 4) j = pair_long_with_short(j, gridDim.x >> 3);
+      if (!BS) j = pair_long_with_short(j, gridDim.x >> 3);
       // An XCD takes its pairs one after the other (all tiles of a pair, heaviest first, the heads of a tile next to
       // each other).  Interleaving the pairs tile by tile looks more even, but in a ragged batch the tiles past a
       // short sequence's end are empty workgroups, and at fixed places of a short period they keep falling to the
@@ -403,7 +405,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
       // every pair instead of all rounds of one.  A round streams its K/V rows from behind the L2 anyway.  Shorter prompts of
       // the block-sparse form have fewer tiles than make that even, so their pairs change sooner (launch_prefill).
       const int r = j / (gw * a.n_qtiles), qtd = (j / gw) % a.n_qtiles, g = (j + qtd) % gw;
-      const int pair = ((x + qtd / (BS ? a.turn : PACK ? 32 : 16)) & 7) + 8 * r;
+      const int pair = ((x + qtd / (BS ? a.turn : 16)) & 7) + 8 * r;
       b = pair / a.hkv;
       h = (pair % a.hkv) * a.group + g;
       qt = a.n_qtiles - 1 - qtd;
@@ -416,10 +418,9 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
       qt = a.n_qtiles - 1 - qtd;
       if (qt < 0) return;                                    // padding of the last round (uniform)
     } else {                                                 // any other shape: plain order, heavy tiles first
-      const int heads = a.hq / grp;
       qt = a.n_qtiles - 1 - i % a.n_qtiles;
-      h = grp * ((i / a.n_qtiles) % heads);
-      b = i / (a.n_qtiles * heads);
+      h = (i / a.n_qtiles) % a.hq;
+      b = i / (a.n_qtiles * a.hq);
     }
     q_begin = a.cu_q[b];
     const int n_q_given = a.cu_q[b + 1] - q_begin;
@@ -679,14 +680,14 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void prefill_kernel(Prefi
         if (__builtin_expect((nxt_kb + 1) * BN <= len, 1)) {
           const int64_t off = (int64_t)nxt_kb * step_b;
           if constexpr (KPW == 4) dma_tile4<(STG ^ 1) * STAGE, KTILE>(kbase + off, vbase + off, k_off, v_off, lds_w);
-          else dma_tile2<(STG ^ 1) * STAGE, KTILE, 1024 * NW>(kbase + off, vbase + off, k_off, v_off, lds_w);
+          else dma_tile2<(STG ^ 1) * STAGE, KTILE>(kbase + off, vbase + off, k_off, v_off, lds_w);
         } else {
           issue_tile_clamped(nxt_kb, STG ^ 1);
         }
       }
     } else if (__builtin_expect(it + 1 < lim_whole, 1)) {    // the next tile, in flight during the math below
       if constexpr (KPW == 4) dma_tile4<(STG ^ 1) * STAGE, KTILE>(kt_n, vt_n, k_off, v_off, lds_w);
-      else dma_tile2<(STG ^ 1) * STAGE, KTILE, 1024 * NW>(kt_n, vt_n, k_off, v_off, lds_w);
+      else dma_tile2<(STG ^ 1) * STAGE, KTILE>(kt_n, vt_n, k_off, v_off, lds_w);
       const int64_t adv = it + 2 == n_a ? jump_b : step_b;   // on to the tile after it (the window part starts at win0)
       kt_n += adv;
       vt_n += adv;
@@ -1039,20 +1040,7 @@ hipError_t launch_prefill(const Ctx& c, const flux_attn_cfg& cfg, const void* q,
   a.sink_lim = geom.sink_lim;
   a.win_blocks = geom.win_blocks;
   a.blk_shift = geom.shift;
-  // Long prompts at head dimension 128 run with eight waves and 256 rows per workgroup (one workgroup per CU) that share
-  // every K/V tile, so that each wave issues half the tile transfers per block.  Measured with 256 rows of one head
-  // against the four-wave shape: FA launches gain 1-3 % from 16384 tokens up; SA launches lose 4 % at 16384 tokens (more
-  // of a 256-row tile's blocks are cut by the window's start and by the diagonal), under 1 % at 32768 and nothing at
-  // 65536; short prompts lose 4-25 % (fewer, longer workgroups).  The rows of two heads of a
-  // group in a tile gain 1 % on SA launches, those of all heads (64 tokens x 4 heads) no more than the runs differ beyond
-  // that.  Hence the bound on the longest prompt of the launch, which is all the host knows.  The results are those of the
-  // unsplit four-wave shape bit for bit.  The block-sparse form keeps four waves (its scan handles three query blocks per
-  // tile).
-  // A chunk of half that length of a prompt that long (chunked prefill: every workgroup walks many blocks) gains too:
-  // FA +1-2 %, SA +0-1.5 % for 16384-row chunks behind 16384 to 114688 cached positions.
-  const bool wide = !bm && cfg.head_dim == 128 &&
-                    (max_q_len >= kPrefillWideMinRows || (max_q_len >= kPrefillWideMinRows / 2 && max_kv_len >= kPrefillWideMinRows));
-  const int BM = wide ? 256 : 128;
+  constexpr int BM = 128;
   a.scale_log2 = scale * kLog2e;
   a.out_fp32 = cfg.out_dtype;
   a.out = out;
@@ -1080,15 +1068,14 @@ hipError_t launch_prefill(const Ctx& c, const flux_attn_cfg& cfg, const void* q,
   const long long tiles = n_pairs * packed, blocks = ((long long)max_kv_len + 63) / 64;
   const long long unit_bytes = (long long)BM * (cfg.head_dim + 2) * 4, info_bytes = ((tiles + 1) * 16 + 255) / 256 * 256;
   const long long fit = ((long long)c.partials_bytes - info_bytes) / unit_bytes - tiles - 8 * cache.batch;   // units beyond one per tile
-  const bool split = !bm && !wide && cache.batch <= 64 && max_kv_len > max_q_len && blocks > kMinSplitBlocks &&
+  const bool split = !bm && cache.batch <= 64 && max_kv_len > max_q_len && blocks > kMinSplitBlocks &&
                      ((tiles <= 768 && split_pays((int)tiles, (int)blocks, cfg.head_dim == 64 ? kResident64 : kResident128)) ||
                       (cache.batch > 1 && ((tiles <= kSplitFewTiles && blocks >= 40) || (tiles <= kSplitMaxTiles && blocks >= 128)))) &&
                      fit >= 64 && (tiles + 8) * blocks < 0x7FFFFFFFll;
   const long long whole = n_pairs * a.group * ((max_q_len + 127ll) / 128);    // tiles of one head each
-  const bool plan = split || (!bm && cache.batch > 1 && cache.batch <= 64 && (wide || whole >= kPlanTiles));
+  const bool plan = split || (!bm && cache.batch > 1 && cache.batch <= 64 && whole >= kPlanTiles);
   const long long unpacked = whole / n_pairs;
-  const bool pack = split || wide || (plan && (max_kv_len > max_q_len ? packed < unpacked : 4 * packed <= 3 * unpacked));
-  const int grp = pack ? a.group : 1;                       // heads whose rows share a tile
+  const bool pack = split || (plan && (max_kv_len > max_q_len ? packed < unpacked : 4 * packed <= 3 * unpacked));
   // Few tiles take 64 rows each, 16 per wave: twice the workgroups, and half the work of a block in each of them, where a
   // workgroup (or two) per CU walks its blocks one after the other and the chip waits for the longest.  us with 128 rows /
   // with 64, 32/8 heads of 128 unless said, append included: 512 tokens 23.3 / 19.9, 1000 33.3 / 28.2, 1500 46.1 / 41.2; 8/2
@@ -1099,8 +1086,8 @@ hipError_t launch_prefill(const Ctx& c, const flux_attn_cfg& cfg, const void* q,
   // whose lists are half as long in the mean (1700 tokens 49.5 / 47.3, 2000 57.8 / 58.9).
   const int resident = cfg.head_dim == 64 ? kResident64 : kResident128;
   const bool triangular = cache.batch == 1 && max_kv_len == max_q_len && a.sink_lim + ((long long)a.win_blocks << a.blk_shift) >= max_q_len;
-  const bool half = !bm && !plan && !wide && whole <= (triangular ? resident / 8 * 7 : resident / 2);
-  const long long n_qtiles = half ? (max_q_len + 63ll) / 64 : ((long long)max_q_len * grp + BM - 1) / BM;
+  const bool half = !bm && !plan && whole <= (triangular ? resident / 8 * 7 : resident / 2);
+  const long long n_qtiles = half ? (max_q_len + 63ll) / 64 : ((long long)max_q_len * (pack ? a.group : 1) + BM - 1) / BM;
   a.n_qtiles = (int)n_qtiles;
   // The pairs of a block-sparse launch change XCD every 16 tiles, those of shorter prompts 16 times over the prompt: XA on
   // structured input, us for append, selection and launch with 16 tiles and as here: 4096 tokens 124 / 119.5, 16384 tokens
@@ -1122,33 +1109,31 @@ hipError_t launch_prefill(const Ctx& c, const flux_attn_cfg& cfg, const void* q,
     }
   } else if (n_pairs % 8 == 0) {
     a.xcd_map = 1;
-    n_wg = n_qtiles * (cfg.n_q_heads / grp) * cache.batch;
+    n_wg = n_qtiles * cfg.n_q_heads * cache.batch;
   } else if (8 % n_pairs == 0) {
     a.xcd_map = 2;
     const long long share = 8 / n_pairs;
-    n_wg = 8 * (a.group / grp) * ((n_qtiles + share - 1) / share);
+    n_wg = 8 * a.group * ((n_qtiles + share - 1) / share);
   } else {
     a.xcd_map = 0;
-    n_wg = n_qtiles * (cfg.n_q_heads / grp) * cache.batch;
+    n_wg = n_qtiles * cfg.n_q_heads * cache.batch;
   }
   if (n_wg > 0x7FFFFFFFll) return hipErrorInvalidValue;
   const dim3 grid((unsigned)n_wg);
   const bool d128 = cfg.head_dim == 128;
   if (bm) {
-    if (d128) hipLaunchKernelGGL((prefill_kernel<128, true, 4>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((prefill_kernel<64, true, 4>), grid, dim3(256), 0, s, a);
+    if (d128) hipLaunchKernelGGL((prefill_kernel<128, true>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((prefill_kernel<64, true>), grid, dim3(256), 0, s, a);
   } else if (plan) {
-    if (wide) hipLaunchKernelGGL((prefill_kernel<128, false, 8, true>), grid, dim3(512), 0, s, a);
-    else if (pack && d128) hipLaunchKernelGGL((prefill_kernel<128, false, 4, true, true>), grid, dim3(256), 0, s, a);
-    else if (pack) hipLaunchKernelGGL((prefill_kernel<64, false, 4, true, true>), grid, dim3(256), 0, s, a);
-    else if (d128) hipLaunchKernelGGL((prefill_kernel<128, false, 4, true>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((prefill_kernel<64, false, 4, true>), grid, dim3(256), 0, s, a);
+    if (pack && d128) hipLaunchKernelGGL((prefill_kernel<128, false, true, true>), grid, dim3(256), 0, s, a);
+    else if (pack) hipLaunchKernelGGL((prefill_kernel<64, false, true, true>), grid, dim3(256), 0, s, a);
+    else if (d128) hipLaunchKernelGGL((prefill_kernel<128, false, true>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((prefill_kernel<64, false, true>), grid, dim3(256), 0, s, a);
   } else {
-    if (wide) hipLaunchKernelGGL((prefill_kernel<128, false, 8>), grid, dim3(512), 0, s, a);
-    else if (half && d128) hipLaunchKernelGGL((prefill_kernel<128, false, 4, false, false, 1>), grid, dim3(256), 0, s, a);
-    else if (half) hipLaunchKernelGGL((prefill_kernel<64, false, 4, false, false, 1>), grid, dim3(256), 0, s, a);
-    else if (d128) hipLaunchKernelGGL((prefill_kernel<128, false, 4>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((prefill_kernel<64, false, 4>), grid, dim3(256), 0, s, a);
+    if (half && d128) hipLaunchKernelGGL((prefill_kernel<128, false, false, false, 1>), grid, dim3(256), 0, s, a);
+    else if (half) hipLaunchKernelGGL((prefill_kernel<64, false, false, false, 1>), grid, dim3(256), 0, s, a);
+    else if (d128) hipLaunchKernelGGL((prefill_kernel<128, false>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((prefill_kernel<64, false>), grid, dim3(256), 0, s, a);
   }
   if (a.split_units > 0) {
     const hipError_t e = hipGetLastError();

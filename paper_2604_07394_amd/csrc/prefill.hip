@@ -472,6 +472,30 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
   const int w_lo_first = window_start(i_w_min, a.blk_shift, a.win_blocks);
   const int w_lo_last = window_start(max(i_w_max, i_w_min), a.blk_shift, a.win_blocks);
 
+  // ---- block-sparse form: the visited key blocks come from the keep matrix.  The tile's 128 rows lie in up
+  // to three 64-position query blocks (two when the first query sits on a block boundary); a key block is
+  // visited when any of them keeps it.  The matrix is scanned 64 key blocks at a time: lane l of every wave reads
+  // the flag of key block win + l for each of the tile's query blocks, a ballot turns them into one 64-bit word
+  // per query block, and the blocks are taken from the lowest set bit up.  Every wave runs the same scan (all of
+  // it in scalar registers), so no exchange is needed.  A query block always keeps its own (diagonal) block, and
+  // never a later one; an FA sequence (mode byte 1) keeps everything.
+  const int rb0 = i_tile_min >> 6;                           // absolute index of the tile's first query block
+  const int n_rb = (i_tile_max >> 6) - rb0 + 1;              // 1 .. 3
+  int scan_win = -64;                                        // first key block of the 64 being scanned
+  unsigned long long scan_bits[3] = {0, 0, 0};               // what is left of them, per query block of the tile
+  int cur_kb = -1, cur_rows = 0;                             // the block of this iteration, and which query blocks keep it
+  // The flags of a window are asked for one window ahead, those of the first one in front of the query rows (they come back in
+  // the order they were asked for in; 8 % of the blocks kept, 16384 tokens 222 -> 220 us, 32768 686 -> 674, 65536 2405 -> 2369).  Every lane reads a flag of the matrix, whatever it needs: no branch differs between
+  // lanes, see weights_guarded.
+  const int rq0 = rb0 - (pos0 >> 6);                         // row of the matrix
+  uint8_t flags[3] = {0, 0, 0};
+  auto fetch_flags = [&](int win) __attribute__((always_inline)) {
+    const uint8_t* seq = a.bmask + ((int64_t)b * a.bm_heads + (a.bm_heads > 1 ? h : 0)) * a.bm_qblocks * (int64_t)a.bm_kblocks;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) flags[r] = seq[(int64_t)min(rq0 + r, a.bm_qblocks - 1) * a.bm_kblocks + min(win + l, a.bm_kblocks - 1)];
+  };
+  if constexpr (BS) fetch_flags(0);
+
   // ---- Q operand: lane (n, g) holds d = 32*kc + 8*g .. +7 of its two query rows
   bf16x8 qf[QB][KC];
 #pragma unroll
@@ -618,22 +642,6 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
   const char* kt_n = kbase + (int64_t)(n_iter > it0 + 1 ? tile_of(it0 + 1) : 0) * step_b;   // the tile the next transfer brings in
   const char* vt_n = vbase + (int64_t)(n_iter > it0 + 1 ? tile_of(it0 + 1) : 0) * step_b;
 
-  // ---- block-sparse form: the visited key blocks come from the keep matrix.  The tile's 128 rows lie in up
-  // to three 64-position query blocks (two when the first query sits on a block boundary); a key block is
-  // visited when any of them keeps it.  The matrix is scanned 64 key blocks at a time: lane l of every wave reads
-  // the flag of key block win + l for each of the tile's query blocks, a ballot turns them into one 64-bit word
-  // per query block, and the blocks are taken from the lowest set bit up.  Every wave runs the same scan (all of
-  // it in scalar registers), so no exchange is needed.  A query block always keeps its own (diagonal) block, and
-  // never a later one; an FA sequence (mode byte 1) keeps everything.
-  const int rb0 = i_tile_min >> 6;                           // absolute index of the tile's first query block
-  const int n_rb = (i_tile_max >> 6) - rb0 + 1;              // 1 .. 3
-  int scan_win = -64;                                        // first key block of the 64 being scanned
-  unsigned long long scan_bits[3] = {0, 0, 0};               // what is left of them, per query block of the tile
-  int cur_kb = -1, cur_rows = 0;                             // the block of this iteration, and which query blocks keep it
-  const uint8_t* bm_seq = nullptr;
-  if constexpr (BS) {
-    if (sa) bm_seq = a.bmask + ((int64_t)b * a.bm_heads + (a.bm_heads > 1 ? h : 0)) * a.bm_qblocks * (int64_t)a.bm_kblocks;
-  }
   auto next_kept_block = [&](int& rows) __attribute__((always_inline)) -> int {
     for (;;) {
       const unsigned long long any = scan_bits[0] | scan_bits[1] | scan_bits[2];
@@ -652,18 +660,14 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
 #pragma unroll
       for (int r = 0; r < 3; ++r) {
         const int rb = rb0 + r;                              // absolute query block
-        bool keep = r < n_rb && kbk <= rb;                   // never a later block (causal), nothing for absent rows
-        if (r < n_rb && bm_seq != nullptr) {
-          // (no branch that differs between lanes, see weights_guarded: every lane reads a flag of the matrix)
-          const int rq = rb - (pos0 >> 6);
-          const bool flag = bm_seq[(int64_t)min(rq, a.bm_qblocks - 1) * a.bm_kblocks + min(kbk, a.bm_kblocks - 1)] != 0;
-          // a matrix too small for the lengths found on the device hides what it does not cover, and says so
-          const bool inside = rq < a.bm_qblocks && kbk < a.bm_kblocks, asked = keep && kbk < rb;   // the diagonal block is kept whatever the flag says
-          if (__builtin_expect(__builtin_amdgcn_ballot_w64(asked && !inside) != 0 && w == 0 && h == 0, 0)) atomicOr(a.status, (uint32_t)FLUX_DEV_BAD_LENGTH);
-          keep = keep && (!asked || (inside && flag));
-        }
-        scan_bits[r] = __builtin_amdgcn_ballot_w64(keep);
+        const bool own = r < n_rb && kbk <= rb, asked = own && kbk < rb && sa;   // never a later block (causal), nothing for absent rows;
+        // the diagonal block is kept whatever the flag says.  A matrix too small for the lengths found on the device hides what
+        // it does not cover, and says so
+        const bool inside = rq0 + r < a.bm_qblocks && kbk < a.bm_kblocks;
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(asked && !inside) != 0 && w == 0 && h == 0, 0)) atomicOr(a.status, (uint32_t)FLUX_DEV_BAD_LENGTH);
+        scan_bits[r] = __builtin_amdgcn_ballot_w64(own && (!asked || (inside && flags[r] != 0)));
       }
+      if (scan_win + 64 <= last_blk) fetch_flags(scan_win + 64);
     }
   };
   int nxt_kb = -1, nxt_rows = 0;

@@ -320,7 +320,7 @@ __global__ __launch_bounds__(256, 2) void xa_select_kernel(XaArgs a) {
 // exponentials where the others take the difference of logarithms: there a mass next to the cut may fall on either side.)
 // What bounds it: the rate at which the L2s deliver operand rows to the CUs.  The walk above fetches every key row once
 // per 32 square rows, this form every operand row once per 128 of the other operand: 16384 positions x 32 heads 1.2 GB
-// instead of 2.1 GB (walk 340 us; here 144 us, 700 TFLOP/s at its core, a quarter of it for the 75 MB of means, plus 46 us
+// instead of 2.1 GB (walk 340 us; here 144 us, 700 TFLOP/s at its core, a quarter of it for the 75 MB of means, plus 31 us
 // for the row kernel, which is bound by its vector instructions).
 constexpr int kXaTile = 128;                 // square rows / columns of a tile
 constexpr int kXaPiece = kXaTile * 16;       // floats of a piece: 128 square rows x 16 square columns
@@ -551,10 +551,21 @@ __global__ __launch_bounds__(256, 2) void xa_scores_kernel(XaScoreArgs a) {
 }
 
 // Values of other lanes by data-parallel-primitive moves (CTRL: quad_perm 0x00-0xff, row_ror:n 0x120+n,
-// row_mirror 0x140, row_half_mirror 0x141).
+// row_newbcast:n 0x150+n).
 template <int CTRL>
 __device__ __forceinline__ float dpp(float x) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
+// ... and `none` where there is no such lane (row_shr:n 0x110+n).
+template <int CTRL>
+__device__ __forceinline__ float dpp_or(float x, float none) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, none), __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, false));
+}
+// x f + y, rounded after the product as well
+__device__ __forceinline__ float scaled_sum(float x, float f, float y) {
+#pragma clang fp contract(off)
+  const float p = x * f;
+  return p + y;
 }
 // Lane l ends up with the sum over the wave, added in the order of xor exchanges over 32, 16, 8, 4, 2, 1 (once the lanes
 // whose numbers agree mod 2k hold the same value, the lane k further round the row holds that of lane l ^ k).
@@ -570,8 +581,10 @@ __device__ __forceinline__ float wave_sum_xor(float x) {
   return x;
 }
 
-// One wave per query block; NR: masses a lane holds (one per 64 key blocks).  The row part is the reduction phase of the
-// walk on the same 4 x 16 lanes: lane l reads square row l / 16 of the block, column l % 16 of every piece.  The logarithm
+// One wave per query block; NR: masses a lane holds (one per 64 key blocks).  The row part does what the reduction phase of
+// the walk does, with the same roundings, on four pieces at a time: lane l holds the 4 squares of a key block of square row l / 16.
+// Bound by its vector instructions; with a lane per square and one piece after the other they were more than twice as many (select
+// at 32/8 heads of 128, 16384 positions 151 -> 139 us, 32768 641 -> 591; 8/2 heads of 64, 16384 positions 45.6 -> 41.0).  The logarithm
 // of the summed exponentials of a key block's 4 squares is kept in LDS ([4 rows][tab] per wave).
 template <int NR, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void xa_keep_kernel(XaScoreArgs a) {
@@ -596,45 +609,51 @@ __global__ __launch_bounds__(64 * WAVES) void xa_keep_kernel(XaScoreArgs a) {
   const int n_ct = qb / 4 + 1;                             // pieces up to the diagonal
   const int rt = qb / 32, rows = min(4, (n + kXaStride - 1) / kXaStride - 4 * qb);
   const int64_t tiles0 = xa_tiles_below(a.rt0);
+  // four pieces at a time: lane (rr, rb) has the 4 squares of key block rb % 4 of piece c0 + rb / 4, in row rr
   const float* src = a.e + ((int64_t)bh * (xa_tiles_below(a.rt1) - tiles0) + (xa_tiles_below(rt) - tiles0)) * kXaTileFloats +
-                     (4 * (qb % 32) + rr) * 16 + rb;
-  // m_use is m_row, or 0 while the row has no finite value (the exponentials of -inf are 0 then as well).
-  float m_row = -INFINITY, m_use = 0.f, l_row = 0.f;
-  float e_next[4];
-#pragma unroll
-  for (int u = 0; u < 4; ++u) e_next[u] = src[(int64_t)min(u, n_ct - 1) * kXaPiece];
+                     (4 * (qb % 32) + rr) * 16 + 4 * (rb & 3);
+  auto ask = [&](int c0) { return *(const f32x4*)(src + (int64_t)min(c0 + (rb >> 2), n_ct - 1) * kXaPiece); };
+  // m_row is a row's reference behind the last piece, m the one behind this lane's; what refers to it uses 0 while the row has no
+  // finite value (the exponentials of -inf are 0 then as well).
+  float m_row = -INFINITY, l_row = 0.f;
+  f32x4 e_next = ask(0);
   for (int c0 = 0; c0 < n_ct; c0 += 4) {
-    float e4[4];
+    const f32x4 e = e_next;
+    const bool there = rr < rows && c0 + (rb >> 2) < n_ct; // (rows past the prompt are not written)
+    if (c0 + 4 < n_ct) e_next = ask(c0 + 4);
+    float x[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) e4[u] = rr < rows && c0 + u < n_ct ? e_next[u] : -INFINITY;   // (rows past the prompt are not written)
-    if (c0 + 4 < n_ct) {
+    for (int t = 0; t < 4; ++t) x[t] = there ? e[t] : -INFINITY;
+    float m = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
+    m = fmaxf(m, dpp<0xb1>(m));                            // of the piece ...
+    m = fmaxf(m, dpp<0x4e>(m));
+    m = fmaxf(m, dpp_or<0x114>(m, -INFINITY));             // ... and of those in front of it (row_shr:4, row_shr:8)
+    m = fmaxf(m, dpp_or<0x118>(m, -INFINITY));
+    m = fmaxf(m, m_row);
+    const float m_use = m == -INFINITY ? 0.f : m;
+    float p[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) e_next[u] = src[(int64_t)min(c0 + 4 + u, n_ct - 1) * kXaPiece];
+    for (int t = 0; t < 4; ++t) p[t] = __expf(x[t] - m_use);
+    const float pe = (p[0] + p[1]) + (p[2] + p[3]);
+    table[rr * tab + 4 * c0 + rb] = pe > 0.f ? m_use + __logf(pe) : -INFINITY;
+    float sum = pe + dpp<0xb1>(pe);                        // of the piece
+    sum += dpp<0x4e>(sum);
+    // the pieces one after the other; where a row's reference moves, what it has so far moves along (elsewhere the factor is 1)
+    if (__builtin_amdgcn_ballot_w64(m > m_row) != 0) {
+      const float shifted = dpp<0x114>(m);                  // (by all lanes: a lane that is switched off has nothing to give)
+      const float before = rb < 4 ? m_row : shifted;
+      const float f = before == -INFINITY ? 0.f : __expf(before - m);
+      l_row = scaled_sum(l_row, dpp<0x150>(f), dpp<0x150>(sum));
+      l_row = scaled_sum(l_row, dpp<0x154>(f), dpp<0x154>(sum));
+      l_row = scaled_sum(l_row, dpp<0x158>(f), dpp<0x158>(sum));
+      l_row = scaled_sum(l_row, dpp<0x15c>(f), dpp<0x15c>(sum));
+      m_row = dpp<0x15c>(m);
+    } else {
+      l_row += dpp<0x150>(sum);
+      l_row += dpp<0x154>(sum);
+      l_row += dpp<0x158>(sum);
+      l_row += dpp<0x15c>(sum);
     }
-    float pe_mine = 0.f, m_mine = 0.f;                     // of the piece c0 + rb % 4: its key block rb / 4
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      float mt = e4[u];
-      mt = fmaxf(mt, dpp<0xb1>(mt));
-      mt = fmaxf(mt, dpp<0x4e>(mt));
-      mt = fmaxf(mt, dpp<0x141>(mt));
-      mt = fmaxf(mt, dpp<0x140>(mt));
-      if (__builtin_amdgcn_ballot_w64(mt > m_row) != 0) {  // a row's reference moves (in the others the factor is 1)
-        const float m_new = fmaxf(m_row, mt);
-        l_row *= m_row == -INFINITY ? 0.f : __expf(m_row - m_new);
-        m_row = m_new;
-        m_use = m_new == -INFINITY ? 0.f : m_new;
-      }
-      float pe = __expf(e4[u] - m_use);
-      pe += dpp<0xb1>(pe);
-      pe += dpp<0x4e>(pe);
-      pe_mine = (rb & 3) == u ? pe : pe_mine;
-      m_mine = (rb & 3) == u ? m_use : m_mine;
-      pe += dpp<0x141>(pe);
-      pe += dpp<0x140>(pe);
-      l_row += pe;
-    }
-    table[rr * tab + 4 * (c0 + (rb & 3)) + (rb >> 2)] = pe_mine > 0.f ? m_mine + __logf(pe_mine) : -INFINITY;
   }
   const float lse = m_row + __logf(l_row);
   float lse_r[4];
@@ -652,7 +671,7 @@ __global__ __launch_bounds__(64 * WAVES) void xa_keep_kernel(XaScoreArgs a) {
     if (j <= qb) {
       float acc = 0.f;
       for (int r = 0; r < rows; ++r) acc += __expf(table[r * tab + j] - lse_r[r]);
-      mass[i] = acc / (float)rows;
+      mass[i] = rows == 4 ? acc * 0.25f : acc / (float)rows;  // (the same)
       tot += mass[i];
       top = fmaxf(top, mass[i]);
     }
@@ -663,7 +682,11 @@ __global__ __launch_bounds__(64 * WAVES) void xa_keep_kernel(XaScoreArgs a) {
   // ---- the cut: largest t (as a bit pattern; positive floats order like their bits) with sum(mass >= t) >= need
   const float need = a.threshold * tot;
   // (found as soon as at most one mass lies between the bounds: the blocks kept are the same for any t above the mass before)
-  uint32_t lo = 0, hi = __builtin_bit_cast(uint32_t, top) + 1;
+  // (What lies below a mass of half of (tot - need) / (qb + 1) is at most half of what may be left out: far from where roundings
+  // could matter while that is a thousandth of the total, so the search begins there and not at 0.)
+  const float spare = tot - need;
+  uint32_t lo = spare > 1e-3f * tot ? __builtin_bit_cast(uint32_t, 0.5f * spare / (float)(qb + 1)) : 0, hi = __builtin_bit_cast(uint32_t, top) + 1;
+  lo = lo < hi ? lo : hi - 1;
   int above_lo = 64 * NR, above_hi = 0;                    // masses at or above the bounds
   while (hi - lo > 1 && above_lo - above_hi > 1) {
     const uint32_t mid = lo + (hi - lo) / 2;

@@ -32,11 +32,44 @@ constexpr int kAppendTable = 1024;          // sequences whose lengths fit the t
 constexpr uint32_t kAppendOneWord = 64;     // workgroups up to which all count themselves on one word
 static_assert(kAppendOneWord >= kAppendGather && 512 / kAppendTokens > kAppendOneWord, "every word of a launch that counts on several is used");
 
+// The thread that calls counts its workgroup; true for the last one of the launch.
+template <bool ONE>
+__device__ __forceinline__ bool count_arrival(const AppendArgs& a) {
+  const uint32_t n = gridDim.x;
+  if (!ONE) {
+    const uint32_t x = blockIdx.x & (kAppendGather - 1);
+    uint32_t* word = a.gather + x * kCounterStride;
+    if (atomicAdd(word, 1u) != (n - x + kAppendGather - 1) / kAppendGather - 1) return false;
+    *word = 0;                                               // ready for the next launch on this stream
+  }
+  return atomicAdd(a.counter, 1u) == (ONE ? n : kAppendGather) - 1;
+}
+
+__device__ __forceinline__ int length_after(const AppendArgs& a, int len, int n) {
+  len += n > 0 ? n : 0;
+  return !a.ring && len > a.capacity ? a.capacity : len;
+}
+
+// Where token row t goes, of a sequence of length len0 whose n new rows begin with `first`; -1: nowhere.
+__device__ __forceinline__ int64_t row_place(const AppendArgs& a, int b, int len0, int first, int n, int t) {
+  const int pos = len0 + (t - first);
+  int row = pos;
+  bool keep = pos >= 0 && pos < a.capacity;
+  if (a.ring) {
+    // only rows that are still resident after the whole call are written: the sinks and the last
+    // `window` positions (an earlier row of this call may share a ring row with a later one)
+    keep = pos >= 0 && (pos < a.n_sink || pos >= len0 + n - a.window);
+    row = pos < a.n_sink ? pos : a.n_sink + (pos - a.n_sink) % a.window;
+  }
+  return keep ? (int64_t)b * a.stride_b + (int64_t)row * a.stride_t : -1;
+}
+
 // What bounds it: the copy where there is much to copy, else latencies.  Workgroups that count themselves on one word do
 // so one after the other, some 10 ns each, which 512 of them waited 5 us for; so each counts itself on one of 16 words, and
 // who completes a word on the last one (up to 64 workgroups the second step takes longer than it saves).  With that a token
 // row per thread and as many workgroups as that takes are fastest up to 4096 of them.  Longer copies keep four rows per
-// thread in flight and read the lengths into LDS once, where a row's sequence is looked up.  us on one word with at most
+// thread in flight and read the lengths into LDS once, where a row's sequence is looked up.  (Batches up to 64 make their short
+// copies in kv_append_short_kernel below.)  us on one word with at most
 // 256 such workgroups, and 512 of four rows / now, 8 KV heads of 128: 256 tokens 4.9 / 4.2, 512 6.4 / 4.4, 1195 tokens of 4
 // sequences 7.6 / 5.8, 2000 9.3 / 6.9, 6466 of 5 17.0 / 14.5, 8192 20.0 / 15.8 (4.3 TB/s), 600 of one token 8.4 / 6.0; 16384
 // 32.5 and 32768 56 (4.8 TB/s) as before.
@@ -77,18 +110,8 @@ __global__ __launch_bounds__(256) void kv_append_kernel(AppendArgs a) {
           if (cu(mid) <= t) lo = mid; else hi = mid;
         }
         const int len0 = table ? s_len[lo] : a.kv_len[lo];
-        const int pos = len0 + (t - cu(lo));
-        int row = pos;
-        bool keep = pos >= 0 && pos < a.capacity;
-        if (a.ring) {
-          // only rows that are still resident after the whole call are written: the sinks and the last
-          // `window` positions (an earlier row of this call may share a ring row with a later one)
-          const int len1 = len0 + (cu(lo + 1) - cu(lo));
-          keep = pos >= 0 && (pos < a.n_sink || pos >= len1 - a.window);
-          row = pos < a.n_sink ? pos : a.n_sink + (pos - a.n_sink) % a.window;
-        }
-        if (keep) dst0[u] = (int64_t)lo * a.stride_b + (int64_t)row * a.stride_t;
-        else if (!a.ring) overflow = true;
+        dst0[u] = row_place(a, lo, len0, cu(lo), a.ring ? cu(lo + 1) - cu(lo) : 0, t);
+        overflow |= dst0[u] < 0 && !a.ring;
       }
       for (int c = c0; c < cpt; c += lanes) {
         const int h = c >> a.cpr_shift, cc = c - (h << a.cpr_shift);
@@ -119,27 +142,71 @@ __global__ __launch_bounds__(256) void kv_append_kernel(AppendArgs a) {
   // fence is needed for this read-before-write order.
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (tid == 0) {
-    const uint32_t n = gridDim.x;
-    bool last = true;
-    if (!ONE) {
-      const uint32_t x = blockIdx.x & (kAppendGather - 1);
-      uint32_t* word = a.gather + x * kCounterStride;
-      last = atomicAdd(word, 1u) == (n - x + kAppendGather - 1) / kAppendGather - 1;
-      if (last) *word = 0;                                   // ready for the next launch on this stream
-    }
-    is_last = last && atomicAdd(a.counter, 1u) == (ONE ? n : kAppendGather) - 1;
-  }
+  if (tid == 0) is_last = count_arrival<ONE>(a);
   __syncthreads();
   if (is_last) {
     for (int b = tid; b < a.batch; b += blockDim.x) {
-      const int n = a.cu_new[b + 1] - a.cu_new[b];
-      int len = a.kv_len[b] + (n > 0 ? n : 0);
-      if (!a.ring && len > a.capacity) len = a.capacity;
-      a.kv_len[b] = len;
+      a.kv_len[b] = length_after(a, a.kv_len[b], a.cu_new[b + 1] - a.cu_new[b]);
     }
     if (tid == 0) *a.counter = 0;   // ready for the next launch on this stream
   }
+}
+
+// The short copies of up to 64 sequences: one token row per thread, a single pass.  What bounds it: memory latencies one behind
+// the other.  The general kernel waits for the lengths, the new rows, the acknowledgement of the stores, the arrival count and
+// the lengths once more.  Here every wave asks for the lengths, a sequence per lane, and right behind them for the
+// new rows, whose place in the input does not depend on them; a row's sequence is looked up in the registers, the stores are
+// not waited for, and the last workgroup holds the lengths already.  us with the general kernel / now: 16 tokens
+// 3.8 / 3.4, 256 4.25 / 3.8, 1000 4.95 / 4.5, 2000 6.0 / 5.4, 6466 tokens of 5 sequences 13.0 / 11.2, 8192 13.5 / 12.1 (8 KV
+// heads of 128), one token of 16 rings (4 heads) 4.3 / 3.65.  In the general kernel's body the same changes cost its long
+// copies 3 %, so these have a kernel of their own.
+template <bool ONE>
+__global__ __launch_bounds__(256) void kv_append_short_kernel(AppendArgs a) {
+  const int cpt = a.hkv << a.cpr_shift;
+  const int lanes = cpt < 256 ? cpt : 256;
+  const int tpi = 256 / lanes;
+  const int tid = threadIdx.x;
+  const int trow = tid / lanes, c0 = tid - trow * lanes;
+  const int t = (int)blockIdx.x * tpi + trow;
+  const bool valid = trow < tpi && t < a.total_new;
+  const int own = min(tid & 63, a.batch - 1);                // the sequence whose lengths this lane holds
+  const int my_cu = a.cu_new[own], my_end = a.cu_new[own + 1], my_len = a.kv_len[own];
+  __builtin_amdgcn_sched_barrier(0);
+  u32x4 k = {0, 0, 0, 0}, v = {0, 0, 0, 0};
+  if (valid) {
+    k = a.k_new[(int64_t)t * cpt + c0];
+    v = a.v_new[(int64_t)t * cpt + c0];
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  const int my_n = my_end - my_cu;
+  int b = 0;                                                 // largest b with cu_new[b] <= t (all lanes take part)
+  for (int step = a.batch > 1 ? 1 << (31 - __builtin_clz(a.batch - 1)) : 0; step > 0; step >>= 1) {
+    const int first = __shfl(my_cu, b + step);
+    if (b + step < a.batch && first <= t) b += step;
+  }
+  const int len0 = __shfl(my_len, b), first = __shfl(my_cu, b), n = __shfl(my_n, b);
+  if (valid) {
+    const int64_t dst = row_place(a, b, len0, first, n, t);
+    if (dst < 0 && !a.ring) atomicOr(a.status, (uint32_t)FLUX_DEV_KV_OVERFLOW);
+    for (int c = c0; c < cpt && dst >= 0; c += lanes) {
+      const int h = c >> a.cpr_shift;
+      const int64_t off = dst + (int64_t)h * a.stride_h + (c - (h << a.cpr_shift));
+      if (c != c0) {
+        k = a.k_new[(int64_t)t * cpt + c];
+        v = a.v_new[(int64_t)t * cpt + c];
+      }
+      a.kc[off] = k;
+      a.vc[off] = v;
+    }
+  }
+  // as above: a wave has its lengths before its thread passes the barrier, and only then is the workgroup counted
+  asm volatile("" : : "v"(my_len), "v"(my_n) : "memory");
+  __syncthreads();
+  if (tid >= 64) return;
+  const int last = tid == 0 && count_arrival<ONE>(a) ? 1 : 0;
+  if (__builtin_amdgcn_readfirstlane(last) == 0) return;
+  if (tid < a.batch) a.kv_len[tid] = length_after(a, my_len, my_n);
+  if (tid == 0) *a.counter = 0;
 }
 
 hipError_t launch_kv_append(const Ctx& c, const flux_kv_cache& cache, int hkv, int d, const void* k_new,
@@ -175,7 +242,10 @@ hipError_t launch_kv_append(const Ctx& c, const flux_kv_cache& cache, int hkv, i
   const long long single = ((long long)total_new + tpi - 1) / tpi;
   if (single <= (cache.batch <= 128 ? kAppendFew : 512)) {
     const dim3 grid((unsigned)(single < 1 ? 1 : single));
-    if (grid.x <= kAppendOneWord) hipLaunchKernelGGL((kv_append_kernel<1, true>), grid, dim3(256), 0, s, a);
+    if (cache.batch <= 64) {
+      if (grid.x <= kAppendOneWord) hipLaunchKernelGGL(kv_append_short_kernel<true>, grid, dim3(256), 0, s, a);
+      else hipLaunchKernelGGL(kv_append_short_kernel<false>, grid, dim3(256), 0, s, a);
+    } else if (grid.x <= kAppendOneWord) hipLaunchKernelGGL((kv_append_kernel<1, true>), grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL((kv_append_kernel<1, false>), grid, dim3(256), 0, s, a);
   } else {
     const long long blocks = (single + kAppendTokens - 1) / kAppendTokens, most = blocks < 2048 ? 1024 : 512;

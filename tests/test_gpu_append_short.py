@@ -1,0 +1,60 @@
+"""flux_kv_append / flux_kv_append_ring where the launch changes its kernel or a workgroup is not full: batches on both sides of
+64, the whole cache bit for bit (it is a copy) against rows placed one after the other, through several calls."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def F():
+    from paper_2604_07394_amd import binding
+    return binding
+
+
+@pytest.fixture(scope="module")
+def ctx(F):
+    c = F.flux_create(0, 0)
+    yield c
+    F.flux_destroy(c)
+
+
+@pytest.mark.parametrize("ring", [False, True])
+@pytest.mark.parametrize("hkv,d", [(8, 128), (3, 64), (40, 128)])
+@pytest.mark.parametrize("batch", [1, 2, 63, 64, 65])
+def test_append_places_every_row(F, ctx, batch, hkv, d, ring):
+    rng = np.random.default_rng(batch * 100 + hkv)
+    n_sink, window = 5, 32
+    cap = n_sink + window if ring else 61 if batch > 1 else 301
+    lens = rng.integers(0, 12, batch).astype(np.int32)
+    k, v = (torch.zeros(batch, hkv, cap, d, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    cache = F.KVCache(k, v, torch.from_numpy(lens).cuda())
+    want_k, want_v = np.zeros((2, batch, cap, hkv, d), np.int16)
+    overflow = False
+    for call in range(3):
+        new = rng.integers(0, 24, batch)
+        new[batch // 2] = 0 if batch > 1 and call == 0 else 40 if batch > 1 else 90 + call
+        total = int(new.sum())
+        rows = rng.integers(-30000, 30000, (2, total, hkv, d)).astype(np.int16)
+        kn, vn = (torch.from_numpy(r).cuda().view(torch.bfloat16) for r in rows)
+        cu = torch.from_numpy(np.concatenate([[0], np.cumsum(new)]).astype(np.int32)).cuda()
+        if ring:
+            F.flux_kv_append_ring(ctx, cache, hkv, d, n_sink, window, kn, vn, cu, total, int(new.max()))
+        else:
+            F.flux_kv_append(ctx, cache, hkv, d, kn, vn, cu, total, int(new.max()))
+        t = 0
+        for b in range(batch):
+            for pos in range(lens[b], lens[b] + new[b]):
+                row = pos if not ring or pos < n_sink else n_sink + (pos - n_sink) % window
+                overflow |= row >= cap
+                if row < cap:
+                    want_k[b, row], want_v[b, row] = rows[0, t], rows[1, t]
+                t += 1
+            lens[b] += new[b]
+            if not ring:
+                lens[b] = min(lens[b], cap)
+        assert np.array_equal(cache.kv_len.cpu().numpy(), lens), call
+        for got, want in ((k, want_k), (v, want_v)):
+            assert np.array_equal(got.view(torch.int16).cpu().numpy().transpose(0, 2, 1, 3), want), call
+    assert bool(F.flux_last_device_status(ctx) & F.FLUX_DEV_KV_OVERFLOW) == overflow

@@ -935,6 +935,21 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
     float l_tot = l_run[qb];
     l_tot += __shfl_xor(l_tot, 16);
     l_tot += __shfl_xor(l_tot, 32);
+    const float inv = 1.0f / l_tot;
+    // bf16 rows: of two output blocks side by side, the lanes of odd g hand their part of the first to the lane of g - 1 and
+    // get its part of the second, so that a lane stores eight columns in a row, and a store covers 64 bytes of each of its 16 rows
+    // instead of 32: the address unit takes as long per row for either.  (All lanes take part, whatever they store.)  A workgroup
+    // stored its tile in 1.4 us, of the 6 to 7 us between the last block of one workgroup and the first of the next (us with stores
+    // of 8 bytes / now, 32/8 heads of 128: 129 to 3001 tokens in 5 sequences 123.2 / 121.3, 4 x 8192 1565 / 1554, 7000 and 13000
+    // tokens block-sparse 222.6 / 217.1, 16384 226.4 / 222.6).
+    u32x4 pk[DB / 2];
+#pragma unroll
+    for (int db = 0; db < DB; db += 2) {
+      const f32x4 lo = o[db][qb] * inv, hi = o[db + 1][qb] * inv;
+      const auto x0 = __builtin_amdgcn_permlane16_swap(pack_bf16(lo[0], lo[1]), pack_bf16(hi[0], hi[1]), false, false);
+      const auto x1 = __builtin_amdgcn_permlane16_swap(pack_bf16(lo[2], lo[3]), pack_bf16(hi[2], hi[3]), false, false);
+      pk[db / 2] = u32x4{x0[0], x1[0], x0[1], x1[1]};
+    }
     const int x = r_w0 + 16 * qb + n;
     if (x >= f_rows) continue;
     if (SPLIT && f_slot >= 0) {
@@ -948,19 +963,15 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
 #pragma unroll
       for (int db = 0; db < DB; ++db) *(FLUX_GLOBAL f32x4*)(dst + 16 * db) = o[db][qb];
     } else {
-      const float inv = 1.0f / l_tot;
       const int t = !PACK ? x : (int)(((float)(f_rem0 + x) + 0.5f) * f_inv);
       const int64_t off = f_off + (t * f_hq + (PACK ? f_rem0 + x - t * f_grp : 0)) * D;
+      if (f_fp32) {
 #pragma unroll
-      for (int db = 0; db < DB; ++db) {
-        const int d = 16 * db + 4 * g;
-        const float x0 = o[db][qb][0] * inv, x1 = o[db][qb][1] * inv;
-        const float x2 = o[db][qb][2] * inv, x3 = o[db][qb][3] * inv;
-        if (f_fp32) {
-          *(FLUX_GLOBAL f32x4*)((FLUX_GLOBAL float*)f_out + off + d) = f32x4{x0, x1, x2, x3};
-        } else {
-          *(FLUX_GLOBAL u32x2*)((FLUX_GLOBAL __bf16*)f_out + off + d) = u32x2{pack_bf16(x0, x1), pack_bf16(x2, x3)};
-        }
+        for (int db = 0; db < DB; ++db) *(FLUX_GLOBAL f32x4*)((FLUX_GLOBAL float*)f_out + off + 16 * db + 4 * g) = o[db][qb] * inv;
+      } else {
+        FLUX_GLOBAL __bf16* dst = (FLUX_GLOBAL __bf16*)f_out + off + 16 * (g & 1) + 8 * (g >> 1);
+#pragma unroll
+        for (int db = 0; db < DB; db += 2) *(FLUX_GLOBAL u32x4*)(dst + 16 * db) = pk[db / 2];
       }
     }
   }

@@ -32,6 +32,20 @@ namespace flux {
 
 typedef __attribute__((__vector_size__(4 * sizeof(int32_t)))) int32_t i32x4;
 
+// Quotients by a divisor that the host knows: n / d = (mulhi(n, mul) + n) >> shift for n < 2^31 (mul = floor(2^32 (2^shift - d) / d)
+// + 1 with 2^shift >= d).
+struct Divisor {
+  uint32_t mul, shift;
+};
+
+inline Divisor divisor(uint32_t d) {
+  uint32_t shift = 0;
+  while (shift < 31 && (1ull << shift) < d) ++shift;
+  return {(uint32_t)(((((uint64_t)1 << shift) - d) << 32) / d + 1), shift};
+}
+
+__device__ __forceinline__ int quotient(int n, const Divisor& d) { return (int)(((uint32_t)(((uint64_t)(uint32_t)n * d.mul) >> 32) + (uint32_t)n) >> d.shift); }
+
 struct PrefillArgs {
   const __bf16* q;        // [T, Hq, D]
   const int32_t* cu_q;    // [B + 1]
@@ -44,7 +58,8 @@ struct PrefillArgs {
   int hq, hkv, group, batch;
   int xcd_map;            // 0 plain, 1 pairs-per-XCD, 2 XCDs-per-pair, 3 planned on the device (see the kernel)
   int sink_lim, win_blocks, blk_shift;   // SA geometry (see sa_geom)
-  int n_qtiles;
+  int n_qtiles, n_wg;
+  Divisor by_group, by_hkv, by_qtiles;
   int turn;               // block-sparse form: query tiles after which the pairs of a round change XCD
   float scale_log2;
   int out_fp32;
@@ -139,7 +154,7 @@ struct PrefillUnit {
 
 // resident: workgroups of the launch that the chip holds at once
 template <bool PACK>
-__device__ __forceinline__ PrefillUnit prefill_plan(const PrefillArgs& a, int l, int bm, int resident) {
+__device__ __forceinline__ PrefillUnit prefill_plan(const PrefillArgs& a, int wg, int l, int bm, int resident) {
   PrefillUnit u;
   // this lane's sequence: lengths under the clamps, tiles, key blocks of its longest tile (an upper bound for SA)
   int q_begin = 0, n_q = 0, len = 0, tiles = 0, nb = 0;
@@ -159,7 +174,7 @@ __device__ __forceinline__ PrefillUnit prefill_plan(const PrefillArgs& a, int l,
       nb = min(nb, ((min(a.sink_lim, len) + 63) >> 6) + (int)((win + bm) >> 6) + 2);
     }
   }
-  if (blockIdx.x == 0 && threadIdx.x < 64 && bad) atomicOr(a.status, (uint32_t)FLUX_DEV_BAD_LENGTH);
+  if (wg == 0 && threadIdx.x < 64 && bad) atomicOr(a.status, (uint32_t)FLUX_DEV_BAD_LENGTH);
   u.chunk = 0x7FFFFFFF;
   int nc = tiles > 0 ? 1 : 0;
   float share = 0.f;
@@ -197,7 +212,7 @@ __device__ __forceinline__ PrefillUnit prefill_plan(const PrefillArgs& a, int l,
     nc = tiles > 0 ? (nb + u.chunk - 1) / u.chunk : 0;
   }
   const bool parts = __builtin_amdgcn_ballot_w64(nc > 1) != 0;
-  if (PACK && a.split_units > 0 && blockIdx.x == 0 && threadIdx.x == 0) a.tile_info[a.batch * a.hkv * a.n_qtiles] = i32x4{parts, 0, 0, 0};
+  if (PACK && a.split_units > 0 && wg == 0 && threadIdx.x == 0) a.tile_info[a.batch * a.hkv * a.n_qtiles] = i32x4{parts, 0, 0, 0};
   u.b = -1;
   const int t0 = __builtin_amdgcn_readlane(tiles, 0);
   const bool alike = __builtin_amdgcn_ballot_w64(l < a.batch && (tiles != t0 || nb != __builtin_amdgcn_readlane(nb, 0))) == 0;
@@ -207,8 +222,8 @@ __device__ __forceinline__ PrefillUnit prefill_plan(const PrefillArgs& a, int l,
     // residue, or of 8 / hkv residues.  q: the unit's place among those of its head
     const int total = t0 * a.batch;
     int q, nj = total;                                       // nj: units of this XCD
-    const int x = blockIdx.x & 7;
-    int j = blockIdx.x >> 3;
+    const int x = wg & 7;
+    int j = wg >> 3;
     if ((a.hkv & 7) == 0) {
       nj = total * (a.hkv >> 3);
       if (j >= nj) return u;
@@ -225,9 +240,9 @@ __device__ __forceinline__ PrefillUnit prefill_plan(const PrefillArgs& a, int l,
       q = (j << sh) + (x >> (3 - sh));
       if (q >= total) return u;                              // padding of the last round
     } else {
-      if ((int)blockIdx.x >= total * a.hkv) return u;
-      u.kvh = blockIdx.x / total;
-      q = blockIdx.x - u.kvh * total;
+      if (wg >= total * a.hkv) return u;
+      u.kvh = wg / total;
+      q = wg - u.kvh * total;
     }
     // Few rounds: the sequences take turns, heaviest tiles first (28/4 heads, 4 x 1000 tokens 41 us, one sequence after
     // the other 49).  Many rounds, or a sequence that fills a round by itself: one after the other, for the L2 (4 x 8192
@@ -256,7 +271,7 @@ __device__ __forceinline__ PrefillUnit prefill_plan(const PrefillArgs& a, int l,
   int units_s = units, idx_s = l;
   int incl = wave_inclusive_sum(units);
   const int total_units = __builtin_amdgcn_readlane(incl, 63);
-  int id = blockIdx.x;
+  int id = wg;
   if (id >= total_units) return u;                           // (most workgroups, where the host's bounds are far above the lengths)
   // longest first, if they are not all alike: rank by (key blocks, index), then the units in that order
   if (a.batch > 1) {
@@ -295,8 +310,8 @@ __device__ __forceinline__ PrefillUnit prefill_plan(const PrefillArgs& a, int l,
     u.b = -1;
     return u;
   }
-  u.kvh = grp % a.hkv;
-  u.ci = grp / a.hkv;
+  u.ci = quotient(grp, a.by_hkv);
+  u.kvh = grp - u.ci * a.hkv;
   u.tile = n_t - 1 - tt;                                     // heaviest first
   u.slot0 = before + u.kvh * n_t + u.tile;
   u.slot_step = a.hkv * n_t;
@@ -359,22 +374,29 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
   const int l = tid & 63;
   const int g = l >> 4, n = l & 15;
   const int grp = PACK ? a.group : 1;                        // heads whose rows share a tile
+  // (the arguments that a workgroup's start needs, asked for together: tied to its number.  Where tiles may be split the scalar
+  // registers are short as it is, and it gains nothing)
+  int i = blockIdx.x;
+  if constexpr (!SPLIT) asm("" : "+s"(i) : "s"(a.q), "s"(a.cu_q), "s"(a.k), "s"(a.v), "s"(a.stride_b), "s"(a.stride_h), "s"(a.stride_t), "s"(a.kv_len), "s"(a.mode),
+      "s"(a.capacity), "s"(a.hq), "s"(a.hkv), "s"(a.group), "s"(a.batch), "s"(a.xcd_map), "s"(a.sink_lim), "s"(a.win_blocks),
+      "s"(a.blk_shift), "s"(a.n_qtiles), "s"(a.n_wg), "s"(a.by_group), "s"(a.by_hkv), "s"(a.by_qtiles));
   // ---- which (sequence, KV head, tile) this workgroup owns.  Workgroups go to the 8 XCDs round-robin
   // by linear id, and each XCD has its own L2.  The workgroups that an XCD holds at one time are therefore
   // given neighbouring query tiles of one (sequence, KV head) pair, heaviest tiles first,
   // so that they walk the same K/V rows at the same time and the rows come from
   // HBM once per XCD and round instead of once per workgroup.
-  int qt, h, b;                                              // h: first query head of the tile
+  int qt, kvh, h, b;                                         // h: first query head of the tile
   int q_begin, n_q, len, ci = 0, chunk = 0x7FFFFFFF, slot0 = 0, slot_step = 0;
   bool sa;
   if constexpr (PLAN) {
-    const PrefillUnit u = prefill_plan<PACK>(a, l, BM, D == 64 ? kResident64 : kResident128);
+    const PrefillUnit u = prefill_plan<PACK>(a, i, l, BM, D == 64 ? kResident64 : kResident128);
     if (u.b < 0) return;                                     // uniform for the workgroup
     b = u.b;
+    kvh = u.kvh;
     h = u.kvh * a.group;
     qt = u.tile;
     if constexpr (!PACK) {                                   // tiles of one head: the heads of a group next to each other
-      qt = u.tile / a.group;
+      qt = quotient(u.tile, a.by_group);
       h += u.tile - qt * a.group;
     }
     q_begin = u.q_begin;
@@ -387,13 +409,12 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
     slot_step = u.slot_step;
     if (len < 1) return;
   } else {
-    const int i = blockIdx.x;
     const int n_pairs = a.batch * a.hkv;
     const int gw = a.group;                                  // workgroups per (pair, query tile)
     if (a.xcd_map == 1) {                                    // n_pairs a multiple of 8: eight pairs at a time, one per XCD
       const int x = i & 7;
       int j = i >> 3;
-      if (!BS) j = pair_long_with_short(j, gridDim.x >> 3);
+      if (!BS) j = pair_long_with_short(j, a.n_wg >> 3);
       // An XCD takes its pairs one after the other (all tiles of a pair, heaviest first, the heads of a tile next to
       // each other).  Interleaving the pairs tile by tile looks more even, but in a ragged batch the tiles past a
       // short sequence's end are empty workgroups, and at fixed places of a short period they keep falling to the
@@ -404,27 +425,36 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
       // change XCD every 16 tiles (one round of resident workgroups), so that every XCD works through two rounds of
       // every pair instead of all rounds of one.  A round streams its K/V rows from behind the L2 anyway.  Shorter prompts of
       // the block-sparse form have fewer tiles than make that even, so their pairs change sooner (launch_prefill).
-      const int r = j / (gw * a.n_qtiles), qtd = (j / gw) % a.n_qtiles, g = (j + qtd) % gw;
+      const int jg = quotient(j, a.by_group), r = quotient(jg, a.by_qtiles), qtd = jg - r * a.n_qtiles;
+      const int g = j + qtd - quotient(j + qtd, a.by_group) * gw;
       const int pair = ((x + qtd / (BS ? a.turn : 16)) & 7) + 8 * r;
-      b = pair / a.hkv;
-      h = (pair % a.hkv) * a.group + g;
+      b = quotient(pair, a.by_hkv);
+      kvh = pair - b * a.hkv;
+      h = kvh * gw + g;
       qt = a.n_qtiles - 1 - qtd;
     } else if (a.xcd_map == 2) {                             // n_pairs divides 8: 8 / n_pairs XCDs share a pair
-      const int x = i & 7, j = i >> 3, share = 8 / n_pairs;
-      const int pair = x % n_pairs, sl = x / n_pairs;
-      const int g = j % gw, qtd = (j / gw) * share + sl;
-      b = pair / a.hkv;
-      h = (pair % a.hkv) * a.group + g;
+      const int x = i & 7, j = i >> 3, sh = n_pairs >> 1;    // n_pairs = 2^sh: 1, 2 or 4
+      const int pair = x & (n_pairs - 1), jg = quotient(j, a.by_group);
+      const int qtd = (jg << (3 - sh)) + (x >> sh);
+      b = quotient(pair, a.by_hkv);
+      kvh = pair - b * a.hkv;
+      h = kvh * gw + j - jg * gw;
       qt = a.n_qtiles - 1 - qtd;
       if (qt < 0) return;                                    // padding of the last round (uniform)
     } else {                                                 // any other shape: plain order, heavy tiles first
-      qt = a.n_qtiles - 1 - i % a.n_qtiles;
-      h = (i / a.n_qtiles) % a.hq;
-      b = i / (a.n_qtiles * a.hq);
+      const int row = quotient(i, a.by_qtiles);
+      qt = a.n_qtiles - 1 - (i - row * a.n_qtiles);
+      const int head = quotient(row, a.by_group);            // KV head, counted over the sequences
+      b = quotient(head, a.by_hkv);
+      kvh = head - b * a.hkv;
+      h = row - b * a.hq;
     }
+    // (the lengths and the mode byte, all asked for before any of them is looked at)
+    int q_end = a.cu_q[b + 1], mode = a.mode[b];
     q_begin = a.cu_q[b];
-    const int n_q_given = a.cu_q[b + 1] - q_begin;
     len = a.kv_len[b];
+    asm("" : "+s"(q_begin) : "s"(q_end), "s"(len), "v"(mode));
+    const int n_q_given = q_end - q_begin;
     // lengths the host could not see: negative, past the capacity, or more queries than cached positions;
     // they are clamped below, and reported once per sequence
     if (qt == a.n_qtiles - 1 && h == 0 && tid == 0 && (n_q_given < 0 || len < 0 || len > a.capacity || n_q_given > len))
@@ -434,9 +464,8 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
     // the queries are the last n_q cached positions, so there cannot be more of them than positions: the
     // surplus rows of an inconsistent call are not computed (every key tile then starts inside the cache)
     n_q = n_q_given < len ? n_q_given : len;
-    sa = a.mode[b] == 0;
+    sa = __builtin_amdgcn_readfirstlane(mode) == 0;
   }
-  const int kvh = h / a.group;
   const int64_t n_rows = (int64_t)n_q * grp;                 // rows of the pair (of the head, in the block-sparse form)
   if ((int64_t)qt * BM >= n_rows) return;                    // uniform for the workgroup
   const int pos0 = len - n_q;                                // position of the first query
@@ -460,18 +489,6 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
     const int t = tok_of(x);
     return tile_off + (t * a.hq + (PACK ? rem0 + x - t * grp : 0)) * D;
   };
-  // this lane's two query rows (column n of column block qb; rows past the last one repeat it): position, and first key
-  // of the row's SA window
-  int i_mine[QB], w_lo_mine[QB];
-#pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    i_mine[qb] = i_tile_min + tok_of(min(r_w0 + 16 * qb + n, rows - 1));
-    w_lo_mine[qb] = window_start(i_mine[qb], a.blk_shift, a.win_blocks);
-  }
-  // first key of the SA window of the wave's first row and of its last row
-  const int w_lo_first = window_start(i_w_min, a.blk_shift, a.win_blocks);
-  const int w_lo_last = window_start(max(i_w_max, i_w_min), a.blk_shift, a.win_blocks);
-
   // ---- block-sparse form: the visited key blocks come from the keep matrix.  The tile's 128 rows lie in up
   // to three 64-position query blocks (two when the first query sits on a block boundary); a key block is
   // visited when any of them keeps it.  The matrix is scanned 64 key blocks at a time: lane l of every wave reads
@@ -495,15 +512,6 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
     for (int r = 0; r < 3; ++r) flags[r] = seq[(int64_t)min(rq0 + r, a.bm_qblocks - 1) * a.bm_kblocks + min(win + l, a.bm_kblocks - 1)];
   };
   if constexpr (BS) fetch_flags(0);
-
-  // ---- Q operand: lane (n, g) holds d = 32*kc + 8*g .. +7 of its two query rows
-  bf16x8 qf[QB][KC];
-#pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    const __bf16* qrow = a.q + row_off(min(r_w0 + 16 * qb + n, rows - 1));
-#pragma unroll
-    for (int kc = 0; kc < KC; ++kc) qf[qb][kc] = *(const bf16x8*)(qrow + 32 * kc + 8 * g);
-  }
 
   // ---- visited key blocks: [0, n_a) and [win0, win0 + n_b)
   const int last_blk = i_tile_max / BN;
@@ -584,6 +592,37 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
     for (int t = 0; t < VPW; ++t)
       lds_copy16(vt, v_slot(t, rmax), lk + KTILE + 1024 * NW * t);
   };
+
+  // The first tile is asked for as soon as it is known which one that is, in front of the query rows and of all that the loop needs to
+  // know besides (block-sparse form: it is not known yet).  The memory latencies of a workgroup's start show in its time: only
+  // the other workgroup of the CU works meanwhile.  They come one after the other: the arguments (once for all, see above), the
+  // lengths and the mode (together, see above), this.  Workgroups took 3.3 us from their start to the first tile (us before / now, 32/8
+  // heads of 128: 129 to 3001 tokens in 5 sequences 122.6 / 120.9, 1000 tokens 21.2 / 20.8, 32 x 100 24.6 / 23.7, 32768 tokens
+  // sparse 1684 / 1678, 7000 and 13000 tokens block-sparse 217.0 / 212.5).
+  if constexpr (!BS) {
+    if (n_iter > it0) issue_tile_clamped(tile_of(it0), 0);
+  }
+
+  // ---- Q operand: lane (n, g) holds d = 32*kc + 8*g .. +7 of its two query rows
+  bf16x8 qf[QB][KC];
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) {
+    const __bf16* qrow = a.q + row_off(min(r_w0 + 16 * qb + n, rows - 1));
+#pragma unroll
+    for (int kc = 0; kc < KC; ++kc) qf[qb][kc] = *(const bf16x8*)(qrow + 32 * kc + 8 * g);
+  }
+
+  // this lane's two query rows (column n of column block qb; rows past the last one repeat it): position, and first key
+  // of the row's SA window
+  int i_mine[QB], w_lo_mine[QB];
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) {
+    i_mine[qb] = i_tile_min + tok_of(min(r_w0 + 16 * qb + n, rows - 1));
+    w_lo_mine[qb] = window_start(i_mine[qb], a.blk_shift, a.win_blocks);
+  }
+  // first key of the SA window of the wave's first row and of its last row
+  const int w_lo_first = window_start(i_w_min, a.blk_shift, a.win_blocks);
+  const int w_lo_last = window_start(max(i_w_max, i_w_min), a.blk_shift, a.win_blocks);
 
   // ---- per-lane LDS read offsets (bytes, relative to stage 0; the stage is added as an immediate)
   // K fragment (kb, kc): row 16*kb + n, logical chunk 4*kc + g (d = 32*kc + 8*g ..), swizzled by the row
@@ -908,7 +947,6 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
   };
 
   if constexpr (!BS) {
-    if (n_iter > it0) issue_tile_clamped(tile_of(it0), 0);
     for (int it = it0; it < n_iter; it += 2) {
       iteration(it, std::integral_constant<int, 0>());
       if (__builtin_expect(it + 1 < n_iter, 1)) iteration(it + 1, std::integral_constant<int, 1>());
@@ -1104,6 +1142,9 @@ hipError_t launch_prefill(const Ctx& c, const flux_attn_cfg& cfg, const void* q,
   const bool half = !bm && !plan && whole <= (triangular ? resident / 8 * 7 : resident / 2);
   const long long n_qtiles = half ? (max_q_len + 63ll) / 64 : ((long long)max_q_len * (pack ? a.group : 1) + BM - 1) / BM;
   a.n_qtiles = (int)n_qtiles;
+  a.by_group = divisor(a.group);
+  a.by_hkv = divisor(a.hkv);
+  a.by_qtiles = divisor(a.n_qtiles);
   // The pairs of a block-sparse launch change XCD every 16 tiles, those of shorter prompts 16 times over the prompt: XA on
   // structured input, us for append, selection and launch with 16 tiles and as here: 4096 tokens 124 / 119.5, 16384 tokens
   // 478 / 470, 7000 and 13000 tokens 472 / 452, 16/8 heads 12000 tokens 192 / 187; not sooner for long ones, whose workgroups
@@ -1134,6 +1175,7 @@ hipError_t launch_prefill(const Ctx& c, const flux_attn_cfg& cfg, const void* q,
     n_wg = n_qtiles * cfg.n_q_heads * cache.batch;
   }
   if (n_wg > 0x7FFFFFFFll) return hipErrorInvalidValue;
+  a.n_wg = (int)n_wg;
   const dim3 grid((unsigned)n_wg);
   const bool d128 = cfg.head_dim == 128;
   if (bm) {

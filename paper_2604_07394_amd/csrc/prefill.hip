@@ -71,9 +71,10 @@ struct PrefillArgs {
   int bm_heads, bm_qblocks, bm_kblocks;
   // planned launches only: a tile's key blocks may be shared out over several workgroups
   int split_units;        // 0: never; else the units a launch may have beyond one per tile
-  float* part_o;          // unnormalised outputs of a unit, [unit][BM][D]
+  int part_units;         // units whose partial results the workspace holds
+  float* part_o;          // unnormalised outputs of a unit, [unit][BM][D] (sequences whose tiles are split have the first units)
   float* part_ml;         // reference (score units) and weight sum of its rows, [unit][BM][2]
-  i32x4* tile_info;       // [batch][n_kv_heads][n_qtiles]: first unit, unit stride, units of the tile; behind them, whether any tile was split
+  i32x4* tile_info;       // [batch][n_kv_heads][n_qtiles]: first unit, unit stride, units of the tile; behind them, per sequence, the most of them that a tile of it has
 };
 
 constexpr float kWeightGuard = 1073741824.0f;   // 2^30: a block whose weights sum past this moves the softmax reference
@@ -124,7 +125,7 @@ constexpr int kPlanTiles = 512;                 // batches of at least so many t
 constexpr int kSplitUnits = 1024;               // units a launch that splits may have beyond one per tile
 constexpr int kSplitFewTiles = 448;             // merges of at most so many tiles give a row to every thread; batches of at most so
                                                 // many by the host's bounds may split from 40 key blocks on
-constexpr int kSplitMaxTiles = 2048;            // ... and of at most so many from 128 on
+constexpr int kSplitMaxTiles = 16384;           // ... and of at most so many where the lists may be long for so many tiles (see launch_prefill)
 
 // Whether it pays to share out the keys of so many tiles, the longest of which walks so many key blocks: what the idle
 // part of the chip can take of the walk has to be worth the plan, the partial results and the second launch.  us whole /
@@ -204,7 +205,7 @@ __device__ __forceinline__ PrefillUnit prefill_plan(const PrefillArgs& a, int wg
     }
     float cost = units <= resident ? (float)longest : fmaxf((float)longest, share + 0.5f * (float)longest);
     cost += 0.02f * (float)parts;
-    if (units + 8 * a.batch > (int)gridDim.x) cost = 1e30f;                    // (never the last: it splits nothing)
+    if (units + 8 * a.batch > a.n_wg || parts + 8 * a.batch > a.part_units) cost = 1e30f;   // (never the last: it splits nothing)
     int best = (__builtin_bit_cast(int, cost) & ~63) | l;                     // (positive floats order like their bits)
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) best = min(best, __shfl_xor(best, off));
@@ -212,7 +213,7 @@ __device__ __forceinline__ PrefillUnit prefill_plan(const PrefillArgs& a, int wg
     nc = tiles > 0 ? (nb + u.chunk - 1) / u.chunk : 0;
   }
   const bool parts = __builtin_amdgcn_ballot_w64(nc > 1) != 0;
-  if (PACK && a.split_units > 0 && wg == 0 && threadIdx.x == 0) a.tile_info[a.batch * a.hkv * a.n_qtiles] = i32x4{parts, 0, 0, 0};
+  if (PACK && a.split_units > 0 && wg == 0 && threadIdx.x < a.batch) a.tile_info[a.batch * a.hkv * a.n_qtiles + threadIdx.x] = i32x4{nc, 0, 0, 0};
   u.b = -1;
   const int t0 = __builtin_amdgcn_readlane(tiles, 0);
   const bool alike = __builtin_amdgcn_ballot_w64(l < a.batch && (tiles != t0 || nb != __builtin_amdgcn_readlane(nb, 0))) == 0;
@@ -1016,57 +1017,63 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
 }
 
 // The tiles whose key blocks were shared out over several units: out = sum_c w_c O_c / sum_c w_c l_c with
-// w_c = exp(m_c - max m), parts in order.  D / 4 threads per row, a tile's rows over the gridDim.x workgroups of a tile.
+// w_c = exp(m_c - max m), parts in order.  D / 4 threads per row, a tile's rows over the gridDim.x workgroups of a tile, the
+// tiles of a sequence over gridDim.y (as many as there are by the host's bounds, or fewer that take several each: a sequence
+// that is not split costs its workgroups one load).
 template <int D, int BM>
 __global__ __launch_bounds__(256) void prefill_merge_kernel(PrefillArgs a) {
   constexpr int RPP = 1024 / D;           // rows per pass
-  if (a.tile_info[a.batch * a.hkv * a.n_qtiles][0] == 0) return;   // nothing was split
-  const int b = blockIdx.z, kvh = blockIdx.y / a.n_qtiles, qt = blockIdx.y % a.n_qtiles;
+  const int b = blockIdx.z;
+  if (a.tile_info[a.batch * a.hkv * a.n_qtiles + b][0] < 2) return;          // none of its tiles was split
   const int q_begin = a.cu_q[b];
   int n_q = a.cu_q[b + 1] - q_begin, len = a.kv_len[b];
   len = len < 0 ? 0 : (len > a.capacity ? a.capacity : len);
   n_q = min(n_q, len);
-  const int64_t row0 = (int64_t)qt * BM, n_rows = (int64_t)n_q * a.group;
-  if (row0 >= n_rows) return;
-  const i32x4 info = a.tile_info[((int64_t)b * a.hkv + kvh) * a.n_qtiles + qt];
-  const int parts = info[2];
-  if (parts < 2) return;
+  const int64_t n_rows = (int64_t)n_q * a.group;
   const int d = 4 * (threadIdx.x % (D / 4));
   const int per = BM / gridDim.x;
-  for (int x = blockIdx.x * per + threadIdx.x / (D / 4); x < (int)(blockIdx.x + 1) * per; x += RPP) {
-    const int64_t row = row0 + x;
-    if (row >= n_rows) return;
-    const int64_t r0 = (int64_t)info[0] * BM + x, step = (int64_t)info[1] * BM;
-    // four parts at a time, so that their loads are in flight together (the last part again where there are fewer)
-    float m = -INFINITY, den = 0.f;
-    f32x4 num = {0.f, 0.f, 0.f, 0.f};
-    for (int c0 = 0; c0 < parts; c0 += 4) {
-      float mc[4], lc[4];
-      f32x4 oc[4];
+  const int n_t = (int)min((n_rows + BM - 1) / BM, (int64_t)a.n_qtiles);       // of a KV head
+  for (int tile = blockIdx.y; tile < a.hkv * n_t; tile += gridDim.y) {
+    const int kvh = tile / n_t, qt = tile - kvh * n_t;
+    const int64_t row0 = (int64_t)qt * BM;
+    const i32x4 info = a.tile_info[((int64_t)b * a.hkv + kvh) * a.n_qtiles + qt];
+    const int parts = info[2];
+    if (parts < 2) continue;
+    for (int x = blockIdx.x * per + threadIdx.x / (D / 4); x < (int)(blockIdx.x + 1) * per; x += RPP) {
+      const int64_t row = row0 + x;
+      if (row >= n_rows) break;
+      const int64_t r0 = (int64_t)info[0] * BM + x, step = (int64_t)info[1] * BM;
+      // four parts at a time, so that their loads are in flight together (the last part again where there are fewer)
+      float m = -INFINITY, den = 0.f;
+      f32x4 num = {0.f, 0.f, 0.f, 0.f};
+      for (int c0 = 0; c0 < parts; c0 += 4) {
+        float mc[4], lc[4];
+        f32x4 oc[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int64_t r = r0 + min(c0 + u, parts - 1) * step;
-        mc[u] = c0 + u < parts ? a.part_ml[2 * r] : -INFINITY;
-        lc[u] = a.part_ml[2 * r + 1];
-        oc[u] = *(const f32x4*)(a.part_o + r * D + d);
-      }
-      const float m_new = fmaxf(fmaxf(fmaxf(mc[0], mc[1]), fmaxf(mc[2], mc[3])), m);
-      if (m_new == -INFINITY) continue;                      // none of these parts sees a key of the row
-      const float al = fast_exp2((m - m_new) * a.scale_log2);
-      den *= al;
-      num *= al;
-      m = m_new;
+        for (int u = 0; u < 4; ++u) {
+          const int64_t r = r0 + min(c0 + u, parts - 1) * step;
+          mc[u] = c0 + u < parts ? a.part_ml[2 * r] : -INFINITY;
+          lc[u] = a.part_ml[2 * r + 1];
+          oc[u] = *(const f32x4*)(a.part_o + r * D + d);
+        }
+        const float m_new = fmaxf(fmaxf(fmaxf(mc[0], mc[1]), fmaxf(mc[2], mc[3])), m);
+        if (m_new == -INFINITY) continue;                      // none of these parts sees a key of the row
+        const float al = fast_exp2((m - m_new) * a.scale_log2);
+        den *= al;
+        num *= al;
+        m = m_new;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const float w = fast_exp2((mc[u] - m) * a.scale_log2);
-        den += w * lc[u];
-        num += w * oc[u];
+        for (int u = 0; u < 4; ++u) {
+          const float w = fast_exp2((mc[u] - m) * a.scale_log2);
+          den += w * lc[u];
+          num += w * oc[u];
+        }
       }
+      const float inv = 1.0f / den;
+      const int64_t off = ((int64_t)(q_begin + row / a.group) * a.hq + (int64_t)kvh * a.group + row % a.group) * D + d;
+      if (a.out_fp32) *(f32x4*)((float*)a.out + off) = num * inv;
+      else *(u32x2*)((__bf16*)a.out + off) = u32x2{pack_bf16(num[0] * inv, num[1] * inv), pack_bf16(num[2] * inv, num[3] * inv)};
     }
-    const float inv = 1.0f / den;
-    const int64_t off = ((int64_t)(q_begin + row / a.group) * a.hq + (int64_t)kvh * a.group + row % a.group) * D + d;
-    if (a.out_fp32) *(f32x4*)((float*)a.out + off) = num * inv;
-    else *(u32x2*)((__bf16*)a.out + off) = u32x2{pack_bf16(num[0] * inv, num[1] * inv), pack_bf16(num[2] * inv, num[3] * inv)};
   }
 }
 
@@ -1116,15 +1123,21 @@ hipError_t launch_prefill(const Ctx& c, const flux_attn_cfg& cfg, const void* q,
   // not (a layer with a short sparse window, say) pays for the plan and the second launch all the same, 0.5 to 3 us.  So
   // the host lets only those that its bounds say may gain: few tiles for the length of the lists, or a batch (whose bounds
   // count tiles that short sequences do not have) with contexts long enough that one uneven sequence costs more than that:
-  // 512, 40 and 30 tokens behind 5000 to 5800 123 -> 66, 4 x 256 equal ones behind 2300 50 -> 53.
+  // 512, 40 and 30 tokens behind 5000 to 5800 123 -> 66, 4 x 256 equal ones behind 2300 50 -> 53.  The more tiles the bounds count,
+  // the longer the lists have to be: 900, 3000, 200, 100 and 60 tokens behind 500, 700, 30000, 4000 and 60000 (28/4 heads, 3300 tiles,
+  // 939 blocks) 951 -> 270, 238 to 2004 tokens behind 583 to 35383 (2520, 558) 585 -> 305, 504, 61 and 1573 tokens behind 1044,
+  // 5599 and 761 (16/8 heads, 600, 89) 102 -> 54; of those that gain nothing 6 x 700 behind 5000 (28/4 heads, 936, 90) 265 -> 270,
+  // 28 to 2368 tokens behind 767 to 28243 in six sequences (3552, 257) 365 -> 372.  Only sequences whose tiles are split take part in
+  // the partial results, and they have the first units of the launch, so that the workspace need not hold one per tile.
   const long long packed = ((long long)max_q_len * a.group + BM - 1) / BM;    // tiles of a pair whose rows come from all heads
   const long long tiles = n_pairs * packed, blocks = ((long long)max_kv_len + 63) / 64;
-  const long long unit_bytes = (long long)BM * (cfg.head_dim + 2) * 4, info_bytes = ((tiles + 1) * 16 + 255) / 256 * 256;
-  const long long fit = ((long long)c.partials_bytes - info_bytes) / unit_bytes - tiles - 8 * cache.batch;   // units beyond one per tile
+  const long long unit_bytes = (long long)BM * (cfg.head_dim + 2) * 4, info_bytes = ((tiles + cache.batch) * 16 + 255) / 256 * 256;
+  const long long fit = ((long long)c.partials_bytes - info_bytes) / unit_bytes;   // units whose partial results the workspace holds
+  const long long grown = 64 + tiles / 24, least = tiles <= kSplitFewTiles ? 40 : (tiles <= 2048 && grown > 128 ? 128 : grown);
   const bool split = !bm && cache.batch <= 64 && max_kv_len > max_q_len && blocks > kMinSplitBlocks &&
                      ((tiles <= 768 && split_pays((int)tiles, (int)blocks, cfg.head_dim == 64 ? kResident64 : kResident128)) ||
-                      (cache.batch > 1 && ((tiles <= kSplitFewTiles && blocks >= 40) || (tiles <= kSplitMaxTiles && blocks >= 128)))) &&
-                     fit >= 64 && (tiles + 8) * blocks < 0x7FFFFFFFll;
+                      (cache.batch > 1 && tiles <= kSplitMaxTiles && blocks >= least)) &&
+                     fit >= 64 + 8 * cache.batch && (tiles + 8) * blocks < 0x7FFFFFFFll;
   const long long whole = n_pairs * a.group * ((max_q_len + 127ll) / 128);    // tiles of one head each
   const bool plan = split || (!bm && cache.batch > 1 && cache.batch <= 64 && whole >= kPlanTiles);
   const long long unpacked = whole / n_pairs;
@@ -1150,18 +1163,19 @@ hipError_t launch_prefill(const Ctx& c, const flux_attn_cfg& cfg, const void* q,
   // 478 / 470, 7000 and 13000 tokens 472 / 452, 16/8 heads 12000 tokens 192 / 187; not sooner for long ones, whose workgroups
   // share what the L2 holds (32768 tokens, everything kept, every 16, 8, 4 and 1 tiles: 7480, 7540, 7610 and 7980).
   a.turn = n_qtiles < 32 ? 2 : n_qtiles < 256 ? (int)n_qtiles / 16 : 16;
-  a.split_units = 0;
+  a.split_units = a.part_units = 0;
   a.part_o = a.part_ml = nullptr;
   a.tile_info = nullptr;
   long long n_wg;
   if (plan) {
     a.xcd_map = 3;
-    if (split) a.split_units = (int)(fit < kSplitUnits ? fit : kSplitUnits);
+    if (split) a.split_units = kSplitUnits;
     n_wg = (pack ? tiles : whole) + 8 * cache.batch + a.split_units;         // (the units of a sequence are padded to whole rounds of the XCDs)
     if (split) {
       a.tile_info = (i32x4*)c.partials;
+      a.part_units = (int)(fit < n_wg ? fit : n_wg);
       a.part_o = (float*)((char*)c.partials + info_bytes);
-      a.part_ml = a.part_o + n_wg * BM * cfg.head_dim;
+      a.part_ml = a.part_o + (long long)a.part_units * BM * cfg.head_dim;
     }
   } else if (n_pairs % 8 == 0) {
     a.xcd_map = 1;
@@ -1196,7 +1210,9 @@ hipError_t launch_prefill(const Ctx& c, const flux_attn_cfg& cfg, const void* q,
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // (few tiles have many parts each: a row per thread; otherwise two, since most workgroups find nothing to do)
-    const dim3 mgrid(128 * cfg.head_dim / 1024 / (tiles <= kSplitFewTiles ? 1 : 2), (unsigned)(cfg.n_kv_heads * a.n_qtiles), cache.batch);
+    const unsigned per_tile = 128 * cfg.head_dim / 1024 / (tiles <= kSplitFewTiles ? 1 : 2);
+    const long long per_seq = (long long)cfg.n_kv_heads * a.n_qtiles, most = 8192 / (per_tile * cache.batch);
+    const dim3 mgrid(per_tile, (unsigned)(per_seq < most ? per_seq : most), cache.batch);
     if (cfg.head_dim == 128) hipLaunchKernelGGL((prefill_merge_kernel<128, 128>), mgrid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL((prefill_merge_kernel<64, 128>), mgrid, dim3(256), 0, s, a);
   }

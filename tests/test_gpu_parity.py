@@ -85,7 +85,7 @@ class Layer:
 
     def prefill(self, qb, n_q, modes, max_q_len=None, want_ref=True):
         """max_q_len: the host's bound on the longest prompt of the call (default: the longest); a larger bound is
-        valid and chooses the launch shape (from 32768 rows on: 256-row workgroups at head dimension 128)."""
+        valid and chooses the launch shape (by the number of tiles it stands for)."""
         F = self.F
         t = int(sum(n_q))
         out = torch.full((t, self.hq, self.d), float("nan"), dtype=torch.float32, device="cuda")

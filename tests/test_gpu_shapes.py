@@ -54,8 +54,8 @@ def test_odd_shapes(F, ctx, case):
         got, ref = lay.prefill(qb, part, modes)
         H.assert_close(got, ref, what + " prefill")
         if d == 128:
-            # the launch shape of long prompts (256 query rows and eight waves per workgroup), chosen by the host's
-            # bound on the prompt length, which may be larger than needed: the same results bit for bit
+            # the launch shape of long prompts, chosen by the host's bound on the prompt length, which may be larger than
+            # needed: the same results bit for bit
             wide, _ = lay.prefill(qb, part, modes, max_q_len=32768, want_ref=False)
             assert np.array_equal(wide, got), what + " prefill, launch shape of long prompts"
     for step in range(2):

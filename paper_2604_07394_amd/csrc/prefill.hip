@@ -1024,19 +1024,31 @@ template <int D, int BM>
 __global__ __launch_bounds__(256) void prefill_merge_kernel(PrefillArgs a) {
   constexpr int RPP = 1024 / D;           // rows per pass
   const int b = blockIdx.z;
-  if (a.tile_info[a.batch * a.hkv * a.n_qtiles + b][0] < 2) return;          // none of its tiles was split
+  // What says whether there is anything to do is asked for together: the sequence's flag and lengths and, where a workgroup has one tile
+  // by the host's bounds, that tile's entry (whatever it holds if the sequence has no such tile), and the other arguments.  A merge
+  // is latencies one behind the other (us of the whole call with these in a row / together, 32/8 heads of 128: 16 tokens behind 30000
+  // 37.3 / 36.3, 128 behind 16256 52.7 / 51.9, 100 behind 5000 34.7 / 33.7; 8/2 heads of 64, 34 and 112 behind 38574 and 608 30.9 / 29.8).
+  const bool single = (int)gridDim.y == a.hkv * a.n_qtiles;
+  const i32x4* infos = a.tile_info + (int64_t)b * a.hkv * a.n_qtiles;
+  int most = a.tile_info[a.batch * a.hkv * a.n_qtiles + b][0], q_end = a.cu_q[b + 1], len = a.kv_len[b];
   const int q_begin = a.cu_q[b];
-  int n_q = a.cu_q[b + 1] - q_begin, len = a.kv_len[b];
+  i32x4 info = infos[blockIdx.y];                            // (gridDim.y is not larger than the number of entries)
+  asm("" : "+s"(most) : "s"(q_end), "s"(len), "s"(q_begin), "s"(info), "s"(a.capacity), "s"(a.group), "s"(a.hq), "s"(a.by_qtiles), "s"(a.part_o), "s"(a.part_ml),
+      "s"(a.out), "s"(a.out_fp32), "s"(a.scale_log2));
+  if (most < 2) return;                                      // none of its tiles was split
+  int n_q = q_end - q_begin;
   len = len < 0 ? 0 : (len > a.capacity ? a.capacity : len);
   n_q = min(n_q, len);
   const int64_t n_rows = (int64_t)n_q * a.group;
   const int d = 4 * (threadIdx.x % (D / 4));
   const int per = BM / gridDim.x;
-  const int n_t = (int)min((n_rows + BM - 1) / BM, (int64_t)a.n_qtiles);       // of a KV head
+  // tiles of a KV head: all that the bounds count, or those that there are, which then take turns
+  const int n_t = single ? a.n_qtiles : (int)min((n_rows + BM - 1) / BM, (int64_t)a.n_qtiles);
   for (int tile = blockIdx.y; tile < a.hkv * n_t; tile += gridDim.y) {
-    const int kvh = tile / n_t, qt = tile - kvh * n_t;
+    const int kvh = single ? quotient(tile, a.by_qtiles) : tile / n_t, qt = tile - kvh * n_t;
     const int64_t row0 = (int64_t)qt * BM;
-    const i32x4 info = a.tile_info[((int64_t)b * a.hkv + kvh) * a.n_qtiles + qt];
+    if (row0 >= n_rows) continue;
+    if (!single) info = infos[(int64_t)kvh * a.n_qtiles + qt];
     const int parts = info[2];
     if (parts < 2) continue;
     for (int x = blockIdx.x * per + threadIdx.x / (D / 4); x < (int)(blockIdx.x + 1) * per; x += RPP) {

@@ -68,8 +68,8 @@ __device__ __forceinline__ int64_t row_place(const AppendArgs& a, int b, int len
 // so one after the other, some 10 ns each, which 512 of them waited 5 us for; so each counts itself on one of 16 words, and
 // who completes a word on the last one (up to 64 workgroups the second step takes longer than it saves).  With that a token
 // row per thread and as many workgroups as that takes are fastest up to 4096 of them.  Longer copies keep four rows per
-// thread in flight and read the lengths into LDS once, where a row's sequence is looked up.  (Batches up to 64 make their short
-// copies in kv_append_short_kernel below.)  us on one word with at most
+// thread in flight and read the lengths into LDS once, where a row's sequence is looked up.  (Batches up to 64 are
+// copied by kv_append_few_kernel below.)  us on one word with at most
 // 256 such workgroups, and 512 of four rows / now, 8 KV heads of 128: 256 tokens 4.9 / 4.2, 512 6.4 / 4.4, 1195 tokens of 4
 // sequences 7.6 / 5.8, 2000 9.3 / 6.9, 6466 of 5 17.0 / 14.5, 8192 20.0 / 15.8 (4.3 TB/s), 600 of one token 8.4 / 6.0; 16384
 // 32.5 and 32768 56 (4.8 TB/s) as before.
@@ -152,23 +152,26 @@ __global__ __launch_bounds__(256) void kv_append_kernel(AppendArgs a) {
   }
 }
 
-// The short copies of up to 64 sequences: one token row per thread, a single pass.  What bounds it: memory latencies one behind
-// the other.  The general kernel waits for the lengths, the new rows, the acknowledgement of the stores, the arrival count and
-// the lengths once more.  Here every wave asks for the lengths, a sequence per lane, and right behind them for the
-// new rows, whose place in the input does not depend on them; a row's sequence is looked up in the registers, the stores are
-// not waited for, and the last workgroup holds the lengths already.  us with the general kernel / now: 16 tokens
-// 3.8 / 3.4, 256 4.25 / 3.8, 1000 4.95 / 4.5, 2000 6.0 / 5.4, 6466 tokens of 5 sequences 13.0 / 11.2, 8192 13.5 / 12.1 (8 KV
-// heads of 128), one token of 16 rings (4 heads) 4.3 / 3.65.  In the general kernel's body the same changes cost its long
-// copies 3 %, so these have a kernel of their own.
+// Up to 64 sequences: one token row per thread, a single pass, however many workgroups that takes.  What bounds it: short copies
+// memory latencies one behind the other, long ones the memory (5.9 TB/s at 32768 tokens, read and written).  The general kernel waits
+// for the lengths, the new rows, the acknowledgement of the stores, the arrival count and the lengths once more.  Here every wave
+// asks for the lengths, a sequence per lane, and right behind them for the new rows, whose place in the input does not depend on
+// them; a row's sequence is looked up in the registers, the stores are not waited for, and the last workgroup holds the
+// lengths already.  Nothing is shared by the workgroup, so new ones start while others drain, which workgroups that stay for several rows
+// do not make up for by having four in flight.  us with the general kernel / now: 16 tokens
+// 3.8 / 3.4, 256 4.25 / 3.8, 1000 4.95 / 4.5, 2000 6.0 / 5.4, 6466 tokens of 5 sequences 13.0 / 11.2, 8192 13.5 / 12.1, 16384
+// 25.4 / 23.1, 32768 47.6 / 44.3, 65536 107 / 97, 32 x 2048 109 / 95 (8 KV heads of 128), one token of 16 rings (4 heads) 4.3 /
+// 3.65.  In the general kernel's body the same changes cost its long copies 3 %, so these have a kernel of their own.
 template <bool ONE>
-__global__ __launch_bounds__(256) void kv_append_short_kernel(AppendArgs a) {
+__global__ __launch_bounds__(256) void kv_append_few_kernel(AppendArgs a) {
   const int cpt = a.hkv << a.cpr_shift;
   const int lanes = cpt < 256 ? cpt : 256;
   const int tpi = 256 / lanes;
   const int tid = threadIdx.x;
   const int trow = tid / lanes, c0 = tid - trow * lanes;
-  const int t = (int)blockIdx.x * tpi + trow;
-  const bool valid = trow < tpi && t < a.total_new;
+  const uint32_t at = blockIdx.x * (uint32_t)tpi + trow;      // (below 2^31 + 256)
+  const int t = (int)at;
+  const bool valid = trow < tpi && at < (uint32_t)a.total_new;
   const int own = min(tid & 63, a.batch - 1);                // the sequence whose lengths this lane holds
   const int my_cu = a.cu_new[own], my_end = a.cu_new[own + 1], my_len = a.kv_len[own];
   __builtin_amdgcn_sched_barrier(0);
@@ -235,16 +238,17 @@ hipError_t launch_kv_append(const Ctx& c, const flux_kv_cache& cache, int hkv, i
   a.status = c.status;
   const int cpt = hkv * (d / 8);
   const int tpi = 256 / (cpt < 256 ? cpt : 256);
-  // One token row per thread up to 4096 workgroups (us with four and the table / with one: 1195 tokens 6.9 / 5.8, 6466 15.0 /
+  // Up to 64 sequences take one pass of as many workgroups as there are rows (see kv_append_few_kernel).  More of them:
+  // one token row per thread up to 4096 workgroups (us with four and the table / with one: 1195 tokens 6.9 / 5.8, 6466 15.0 /
   // 14.5, 32 x 200 15.0 / 14.5).  Many sequences take longer to look up in global memory, so there the table serves from 512
   // on.  Four rows per thread: 1024 workgroups where that is one or two rounds (8192 tokens of 128 to 1024 sequences), 512 for more (32768
   // tokens 56.0, with 1024 56.7).
   const long long single = ((long long)total_new + tpi - 1) / tpi;
-  if (single <= (cache.batch <= 128 ? kAppendFew : 512)) {
+  if (cache.batch <= 64 || single <= (cache.batch <= 128 ? kAppendFew : 512)) {
     const dim3 grid((unsigned)(single < 1 ? 1 : single));
     if (cache.batch <= 64) {
-      if (grid.x <= kAppendOneWord) hipLaunchKernelGGL(kv_append_short_kernel<true>, grid, dim3(256), 0, s, a);
-      else hipLaunchKernelGGL(kv_append_short_kernel<false>, grid, dim3(256), 0, s, a);
+      if (grid.x <= kAppendOneWord) hipLaunchKernelGGL(kv_append_few_kernel<true>, grid, dim3(256), 0, s, a);
+      else hipLaunchKernelGGL(kv_append_few_kernel<false>, grid, dim3(256), 0, s, a);
     } else if (grid.x <= kAppendOneWord) hipLaunchKernelGGL((kv_append_kernel<1, true>), grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL((kv_append_kernel<1, false>), grid, dim3(256), 0, s, a);
   } else {

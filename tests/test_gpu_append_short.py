@@ -20,6 +20,28 @@ def ctx(F):
     F.flux_destroy(c)
 
 
+def test_long_copies_of_few_sequences(F, ctx):
+    """More workgroups than are resident at once, which count themselves on several words; a row past the capacity is left out."""
+    hkv, d, lens, new, cap = 8, 64, [3, 0, 70], [40000, 1, 9000], 40001
+    g = torch.Generator(device="cuda").manual_seed(3)
+    total = sum(new)
+    kn, vn = (torch.randint(-30000, 30000, (total, hkv, d), generator=g, device="cuda", dtype=torch.int16) for _ in range(2))
+    k, v = (torch.zeros(3, hkv, cap, d, dtype=torch.int16, device="cuda") for _ in range(2))
+    cache = F.KVCache(k.view(torch.bfloat16), v.view(torch.bfloat16), torch.tensor(lens, dtype=torch.int32, device="cuda"))
+    cu = torch.tensor([0, 40000, 40001, total], dtype=torch.int32, device="cuda")
+    F.flux_last_device_status(ctx)
+    F.flux_kv_append(ctx, cache, hkv, d, kn.view(torch.bfloat16), vn.view(torch.bfloat16), cu, total, max(new))
+    for got, rows in ((k, kn), (v, vn)):
+        want, t = torch.zeros_like(got), 0
+        for b in range(3):
+            n = min(new[b], cap - lens[b])
+            want[b, :, lens[b]:lens[b] + n] = rows[t:t + n].transpose(0, 1)
+            t += new[b]
+        assert torch.equal(got, want)
+    assert cache.kv_len.tolist() == [min(cap, a + b) for a, b in zip(lens, new)]
+    assert F.flux_last_device_status(ctx) & F.FLUX_DEV_KV_OVERFLOW
+
+
 @pytest.mark.parametrize("ring", [False, True])
 @pytest.mark.parametrize("hkv,d", [(8, 128), (3, 64), (40, 128)])
 @pytest.mark.parametrize("batch", [1, 2, 63, 64, 65])

@@ -209,7 +209,7 @@ int flux_kv_append(flux_ctx* ctx, const flux_kv_cache* cache, int n_kv_heads, in
   if (ctx->c.device < 0) return hip_fail(hipErrorNoDevice);
   if (total_new == 0) return FLUX_OK;
   const hipError_t e =
-      launch_kv_append(ctx->c, *cache, n_kv_heads, head_dim, k_new, v_new, cu_new, total_new, 0, 0, 0, (hipStream_t)stream);
+      launch_kv_append(ctx->c, *cache, n_kv_heads, head_dim, k_new, v_new, cu_new, total_new, max_new, 0, 0, 0, (hipStream_t)stream);
   return e == hipSuccess ? FLUX_OK : hip_fail(e);
 }
 
@@ -355,7 +355,7 @@ int flux_kv_append_ring(flux_ctx* ctx, const flux_kv_cache* ring, int n_kv_heads
   if ((long long)n_sink + window > ring->capacity) return FLUX_ECAPACITY;
   if (ctx->c.device < 0) return hip_fail(hipErrorNoDevice);
   if (total_new == 0) return FLUX_OK;
-  const hipError_t e = launch_kv_append(ctx->c, *ring, n_kv_heads, head_dim, k_new, v_new, cu_new, total_new, 1,
+  const hipError_t e = launch_kv_append(ctx->c, *ring, n_kv_heads, head_dim, k_new, v_new, cu_new, total_new, max_new, 1,
                                         n_sink, window, (hipStream_t)stream);
   return e == hipSuccess ? FLUX_OK : hip_fail(e);
 }

@@ -102,9 +102,60 @@ constexpr size_t kDecodeCountersAt = kHeaderBytes;   // bytes
 constexpr size_t kAppendCountersAt = kDecodeCountersAt + kDecodeCounters * kCounterStride * 4;
 constexpr size_t kCountersBytes = (kAppendCountersAt + kAppendGather * kCounterStride * 4 - kHeaderBytes + 4095) / 4096 * 4096;
 
+// What launches an append (see the kernels in kv_append.hip).
+enum AppendForm {
+  kAppendEarly,    // up to kAppendLanes sequences: a token row per thread, asked for before its place is known
+  kAppendLate,     // the same, asked for when its place is known, and if it has one
+  kAppendSingle,   // a token row per thread, lengths looked up in memory
+  kAppendWide,     // kAppendTokens rows per thread in flight, lengths looked up in LDS, workgroups that stay
+};
+struct AppendPlan {
+  AppendForm form;
+  unsigned wgs;
+  bool one_word;   // all workgroups count themselves on one word
+};
+constexpr int kAppendLanes = 64;
+constexpr int kAppendTokens = 4;
+constexpr int kAppendFew = 4096;
+constexpr int kAppendResident = 2048;       // workgroups that the chip holds at once
+constexpr unsigned kAppendOneWord = 64;     // workgroups up to which all count themselves on one word
+static_assert(kAppendResident >= (int)kAppendOneWord, "kAppendLate counts on several words");
+static_assert(kAppendOneWord >= kAppendGather && 512 / kAppendTokens > kAppendOneWord, "every word of a launch that counts on several is used");
+// Up to 64 sequences take one pass of as many workgroups as there are rows (see kv_append_few_kernel).  More of them:
+// one token row per thread up to 4096 workgroups (us with four and the table / with one: 1195 tokens 6.9 / 5.8, 6466 15.0 /
+// 14.5, 32 x 200 15.0 / 14.5).  Many sequences take longer to look up in global memory, so there the table serves from 512
+// on.  Four rows per thread: 1024 workgroups where that is one or two rounds (8192 tokens of 128 to 1024 sequences), 512 for more (32768
+// tokens 56.0, with 1024 56.7).
+// A ring append of more workgroups than the chip holds at once does not ask for the rows that it drops (128 + 4096 keys of 8 heads of 128
+// stay of 131072 rows: 105 to 109 us with every row read, 52 to 54 as here); a smaller one waits for latencies, and all its rows are on
+// their way together (us as kAppendEarly / kAppendLate, 64 + 2048 rows of 8 heads of 128 stay: 3000 rows 5.8 / 6.2, 4096 6.35 / 6.65,
+// 5000 6.8 / 7.0, 6000 7.55 / 7.3, 8192 9.15 / 8.55; 64 + 64 stay: 2000 rows 4.6 / 4.7, 4096 5.5 / 5.4, 8192 7.7 / 7.4).
+// Workgroups that only find that their rows are dropped cost less than looking up the sequence of a row, which one or two sequences
+// have little need of, and which shows where they are many (us as kAppendWide / kAppendLate: 8192 rows 8.8 / 8.3, 14000 9.3 / 10.7,
+// 32768 17.6 / 19.0, 2 x 60000 58.6 / 57.9 to 61.3, 3 x 40000 65 / 60 to 63, 8 x 8000 52 / 42 to 45, 64 x 5000 326 / 255 to 262).
+inline AppendPlan plan_append(int batch, int hkv, int d, int total_new, int max_new, int ring, int window) {
+  const int cpt = hkv * (d / 8), tpi = 256 / (cpt < 256 ? cpt : 256);
+  const long long single = ((long long)total_new + tpi - 1) / tpi;
+  AppendPlan p;
+  const bool late = ring && max_new > window && single > kAppendResident;
+  if (batch <= kAppendLanes && !(late && batch <= 2 && single > kAppendFew)) {
+    p.form = late ? kAppendLate : kAppendEarly;
+    p.wgs = (unsigned)single;
+  } else if (single <= (batch <= 128 ? kAppendFew : 512)) {
+    p.form = kAppendSingle;
+    p.wgs = (unsigned)single;
+  } else {
+    const long long blocks = (single + kAppendTokens - 1) / kAppendTokens, most = blocks < 2048 ? 1024 : 512;
+    p.form = kAppendWide;
+    p.wgs = (unsigned)(blocks < most ? blocks : most);
+  }
+  p.one_word = p.form != kAppendWide && p.wgs <= kAppendOneWord;
+  return p;
+}
+
 // ---- launchers (each validates nothing: flux_api.hip has done it) ---------------------------
 hipError_t launch_kv_append(const Ctx& c, const flux_kv_cache& cache, int hkv, int d, const void* k_new,
-                            const void* v_new, const int32_t* cu_new, int total_new, int ring, int n_sink,
+                            const void* v_new, const int32_t* cu_new, int total_new, int max_new, int ring, int n_sink,
                             int window, hipStream_t s);
 hipError_t launch_kv_compact_ring(const flux_kv_cache& src, const flux_kv_cache& dst, int hkv, int d, int n_sink,
                                   int window, hipStream_t s);

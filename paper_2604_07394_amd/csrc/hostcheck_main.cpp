@@ -14,6 +14,7 @@ extern "C" int hostcheck_decode_wgs(const flux_attn_cfg* cfg, int batch, int max
 extern "C" int hostcheck_decode_in_partials(const flux_attn_cfg* cfg, int batch, int max_kv_len);
 extern "C" int hostcheck_decode_blocks_fit(const flux_attn_cfg* cfg, int batch, int max_kv_len);
 extern "C" int hostcheck_decode_rows_fit(const flux_attn_cfg* cfg, int batch, int max_kv_len);
+extern "C" int hostcheck_append(int batch, int hkv, int d, int total_new, int max_new, int ring, int window, unsigned* wgs);
 
 static int failures = 0;
 #define EXPECT(expr, want)                                                                   \
@@ -137,6 +138,22 @@ int main() {
   for (int batch = 1; batch <= 2048; batch += batch < 40 ? 1 : 31)
     for (int keys = 1; keys < 200000; keys += 1 + keys / 3) (void)in_partials(32, 2, batch, keys);
   // ---- append, ring, router
+  // a ring append of more workgroups than the chip holds at once asks for no row before it knows whether it is dropped (forms 0: early, 1:
+  // late, 2: single, 3: wide)
+  unsigned n = 0;
+  EXPECT(hostcheck_append(16, 4, 128, 16, 1, 1, 2048, &n), 0);
+  EXPECT(hostcheck_append(1, 8, 128, 2048, 2048, 1, 2048, &n), 0);
+  EXPECT(hostcheck_append(1, 8, 128, 4096, 4096, 1, 2048, &n), 0);
+  EXPECT(hostcheck_append(1, 8, 128, 4097, 4097, 1, 2048, &n), 1);
+  EXPECT(hostcheck_append(3, 8, 128, 6000, 2000, 1, 2048, &n), 0);
+  EXPECT(hostcheck_append(1, 8, 128, 8192, 8192, 1, 2048, &n), 1);
+  EXPECT(hostcheck_append(1, 8, 128, 32768, 32768, 1, 4096, &n), 3);
+  EXPECT(hostcheck_append(2, 8, 128, 65536, 65535, 1, 4096, &n), 3);
+  EXPECT(hostcheck_append(3, 8, 128, 65536, 65530, 1, 4096, &n), 1);
+  EXPECT(hostcheck_append(64, 8, 128, 1 << 20, 1 << 14, 1, 4096, &n), 1);
+  EXPECT(hostcheck_append(65, 8, 128, 1 << 20, 1 << 14, 1, 4096, &n), 3);
+  EXPECT(hostcheck_append(1, 8, 128, 65536, 65536, 0, 0, &n), 0);
+  EXPECT(n, 32768);
   EXPECT(flux_kv_append(ctx, &kc, 2, 128, p, p, pi, 10, 10, nullptr), FLUX_EHIP);
   EXPECT(flux_kv_append(ctx, &kc, 2, 128, p, p, pi, INT_MAX, INT_MAX, nullptr), FLUX_ECAPACITY);
   EXPECT(flux_kv_append(ctx, &kc, 2, 128, p, p, pi, 5, 6, nullptr), FLUX_EINVAL);

@@ -20,6 +20,12 @@ int hostcheck_decode_blocks_fit(const flux_attn_cfg* cfg, int batch, int max_kv_
   const long long blocks = ((long long)max_kv_len + (1ll << p.block_shift) - 1) >> p.block_shift;
   return (__int128)batch * p.pps * (blocks + (p.aligned_shift < 0 ? 0 : 15)) <= INT32_MAX;
 }
+// how an append is launched
+int hostcheck_append(int batch, int hkv, int d, int total_new, int max_new, int ring, int window, unsigned* wgs) {
+  const flux::AppendPlan p = flux::plan_append(batch, hkv, d, total_new, max_new, ring, window);
+  *wgs = p.wgs;
+  return p.form;
+}
 int hostcheck_decode_rows_fit(const flux_attn_cfg* cfg, int batch, int max_kv_len) {
   const flux::DecodePlan p = flux::plan_decode(*cfg, batch, max_kv_len);
   const size_t rows = (size_t)2 * p.wgs * p.rpu * (cfg->head_dim + 2) * sizeof(float);
@@ -34,7 +40,7 @@ int hostcheck_decode_rows_fit(const flux_attn_cfg* cfg, int batch, int max_kv_le
 namespace flux {
 
 hipError_t launch_kv_append(const Ctx&, const flux_kv_cache&, int, int, const void*, const void*, const int32_t*, int, int, int,
-                            int, hipStream_t) { return hipErrorNoDevice; }
+                            int, int, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_kv_compact_ring(const flux_kv_cache&, const flux_kv_cache&, int, int, int, int, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_decode(const Ctx& c, const flux_attn_cfg&, const void*, int, const flux_kv_cache&, const uint8_t*, int, const void*,
                          const void*, void*, hipStream_t) {

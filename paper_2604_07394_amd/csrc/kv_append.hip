@@ -26,11 +26,7 @@ struct AppendArgs {
   uint32_t* status;
 };
 
-constexpr int kAppendTokens = 4;            // token rows a thread has in flight in a launch of more than kAppendFew workgroups
-constexpr int kAppendFew = 4096;
 constexpr int kAppendTable = 1024;          // sequences whose lengths fit the table in LDS
-constexpr uint32_t kAppendOneWord = 64;     // workgroups up to which all count themselves on one word
-static_assert(kAppendOneWord >= kAppendGather && 512 / kAppendTokens > kAppendOneWord, "every word of a launch that counts on several is used");
 
 // The thread that calls counts its workgroup; true for the last one of the launch.
 template <bool ONE>
@@ -162,7 +158,9 @@ __global__ __launch_bounds__(256) void kv_append_kernel(AppendArgs a) {
 // 3.8 / 3.4, 256 4.25 / 3.8, 1000 4.95 / 4.5, 2000 6.0 / 5.4, 6466 tokens of 5 sequences 13.0 / 11.2, 8192 13.5 / 12.1, 16384
 // 25.4 / 23.1, 32768 47.6 / 44.3, 65536 107 / 97, 32 x 2048 109 / 95 (8 KV heads of 128), one token of 16 rings (4 heads) 4.3 /
 // 3.65.  In the general kernel's body the same changes cost its long copies 3 %, so these have a kernel of their own.
-template <bool ONE>
+// LATE: the new rows are asked for when their place is known, and only those that have one (ring appends that drop rows, see
+// plan_append).
+template <bool ONE, bool LATE>
 __global__ __launch_bounds__(256) void kv_append_few_kernel(AppendArgs a) {
   const int cpt = a.hkv << a.cpr_shift;
   const int lanes = cpt < 256 ? cpt : 256;
@@ -176,7 +174,7 @@ __global__ __launch_bounds__(256) void kv_append_few_kernel(AppendArgs a) {
   const int my_cu = a.cu_new[own], my_end = a.cu_new[own + 1], my_len = a.kv_len[own];
   __builtin_amdgcn_sched_barrier(0);
   u32x4 k = {0, 0, 0, 0}, v = {0, 0, 0, 0};
-  if (valid) {
+  if (!LATE && valid) {
     k = a.k_new[(int64_t)t * cpt + c0];
     v = a.v_new[(int64_t)t * cpt + c0];
   }
@@ -194,7 +192,7 @@ __global__ __launch_bounds__(256) void kv_append_few_kernel(AppendArgs a) {
     for (int c = c0; c < cpt && dst >= 0; c += lanes) {
       const int h = c >> a.cpr_shift;
       const int64_t off = dst + (int64_t)h * a.stride_h + (c - (h << a.cpr_shift));
-      if (c != c0) {
+      if (LATE || c != c0) {
         k = a.k_new[(int64_t)t * cpt + c];
         v = a.v_new[(int64_t)t * cpt + c];
       }
@@ -213,7 +211,7 @@ __global__ __launch_bounds__(256) void kv_append_few_kernel(AppendArgs a) {
 }
 
 hipError_t launch_kv_append(const Ctx& c, const flux_kv_cache& cache, int hkv, int d, const void* k_new,
-                            const void* v_new, const int32_t* cu_new, int total_new, int ring, int n_sink,
+                            const void* v_new, const int32_t* cu_new, int total_new, int max_new, int ring, int n_sink,
                             int window, hipStream_t s) {
   AppendArgs a;
   a.k_new = (const u32x4*)k_new;
@@ -236,25 +234,14 @@ hipError_t launch_kv_append(const Ctx& c, const flux_kv_cache& cache, int hkv, i
   a.counter = c.counters + 0;
   a.gather = c.append_counters;
   a.status = c.status;
-  const int cpt = hkv * (d / 8);
-  const int tpi = 256 / (cpt < 256 ? cpt : 256);
-  // Up to 64 sequences take one pass of as many workgroups as there are rows (see kv_append_few_kernel).  More of them:
-  // one token row per thread up to 4096 workgroups (us with four and the table / with one: 1195 tokens 6.9 / 5.8, 6466 15.0 /
-  // 14.5, 32 x 200 15.0 / 14.5).  Many sequences take longer to look up in global memory, so there the table serves from 512
-  // on.  Four rows per thread: 1024 workgroups where that is one or two rounds (8192 tokens of 128 to 1024 sequences), 512 for more (32768
-  // tokens 56.0, with 1024 56.7).
-  const long long single = ((long long)total_new + tpi - 1) / tpi;
-  if (cache.batch <= 64 || single <= (cache.batch <= 128 ? kAppendFew : 512)) {
-    const dim3 grid((unsigned)(single < 1 ? 1 : single));
-    if (cache.batch <= 64) {
-      if (grid.x <= kAppendOneWord) hipLaunchKernelGGL(kv_append_few_kernel<true>, grid, dim3(256), 0, s, a);
-      else hipLaunchKernelGGL(kv_append_few_kernel<false>, grid, dim3(256), 0, s, a);
-    } else if (grid.x <= kAppendOneWord) hipLaunchKernelGGL((kv_append_kernel<1, true>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((kv_append_kernel<1, false>), grid, dim3(256), 0, s, a);
-  } else {
-    const long long blocks = (single + kAppendTokens - 1) / kAppendTokens, most = blocks < 2048 ? 1024 : 512;
-    hipLaunchKernelGGL((kv_append_kernel<kAppendTokens, false>), dim3((unsigned)(blocks < most ? blocks : most)), dim3(256), 0, s, a);
-  }
+  const AppendPlan p = plan_append(cache.batch, hkv, d, total_new, max_new, ring, window);
+  const dim3 grid(p.wgs), block(256);
+  if (p.form == kAppendWide) hipLaunchKernelGGL((kv_append_kernel<kAppendTokens, false>), grid, block, 0, s, a);
+  else if (p.form == kAppendSingle && p.one_word) hipLaunchKernelGGL((kv_append_kernel<1, true>), grid, block, 0, s, a);
+  else if (p.form == kAppendSingle) hipLaunchKernelGGL((kv_append_kernel<1, false>), grid, block, 0, s, a);
+  else if (p.form == kAppendEarly && p.one_word) hipLaunchKernelGGL((kv_append_few_kernel<true, false>), grid, block, 0, s, a);
+  else if (p.form == kAppendEarly) hipLaunchKernelGGL((kv_append_few_kernel<false, false>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((kv_append_few_kernel<false, true>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 

@@ -80,3 +80,26 @@ def test_append_places_every_row(F, ctx, batch, hkv, d, ring):
         for got, want in ((k, want_k), (v, want_v)):
             assert np.array_equal(got.view(torch.int16).cpu().numpy().transpose(0, 2, 1, 3), want), call
     assert bool(F.flux_last_device_status(ctx) & F.FLUX_DEV_KV_OVERFLOW) == overflow
+
+
+@pytest.mark.parametrize("lens,new,hkv", [([3], [20000], 8), ([700], [8190], 8), ([0, 5000], [9000, 3], 5), ([1, 4], [30000, 800], 8), ([9, 0, 40, 2], [3000, 65, 64, 4097], 17), ([3, 0, 70], [20000, 30, 64], 16)])
+def test_long_ring_appends_keep_the_sinks_and_the_window(F, ctx, lens, new, hkv):
+    """Many workgroups, most of whose rows are dropped: what stays is the sinks and the last 64 rows of every sequence."""
+    d, n_sink, window, batch = 64, 7, 64, len(lens)
+    g = torch.Generator(device="cuda").manual_seed(sum(new))
+    kn, vn = (torch.randint(-30000, 30000, (sum(new), hkv, d), generator=g, device="cuda", dtype=torch.int16) for _ in range(2))
+    k, v = (torch.zeros(batch, hkv, n_sink + window + 2, d, dtype=torch.int16, device="cuda") for _ in range(2))
+    cache = F.KVCache(k.view(torch.bfloat16), v.view(torch.bfloat16), torch.tensor(lens, dtype=torch.int32, device="cuda"))
+    cu = torch.tensor(np.concatenate([[0], np.cumsum(new)]), dtype=torch.int32, device="cuda")
+    F.flux_kv_append_ring(ctx, cache, hkv, d, n_sink, window, kn.view(torch.bfloat16), vn.view(torch.bfloat16), cu, sum(new), max(new))
+    for got, rows in ((k, kn), (v, vn)):
+        want, t = torch.zeros_like(got), 0
+        for b in range(batch):
+            for r in list(range(min(n_sink, new[b]))) + list(range(max(0, new[b] - window), new[b])):
+                pos = lens[b] + r
+                if pos < n_sink or pos >= lens[b] + new[b] - window:
+                    want[b, :, pos if pos < n_sink else n_sink + (pos - n_sink) % window] = rows[t + r]
+            t += new[b]
+        assert torch.equal(got, want)
+    assert cache.kv_len.tolist() == [a + n for a, n in zip(lens, new)]
+    assert F.flux_last_device_status(ctx) == 0

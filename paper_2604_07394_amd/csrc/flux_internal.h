@@ -118,10 +118,11 @@ constexpr int kAppendLanes = 64;
 constexpr int kAppendTokens = 4;
 constexpr int kAppendFew = 4096;
 constexpr int kAppendResident = 2048;       // workgroups that the chip holds at once
+constexpr int kAppendMost = 1 << 22;        // workgroups of a launch with a row per thread (from 2^24 on it would be refused: 2^32 threads)
 constexpr unsigned kAppendOneWord = 64;     // workgroups up to which all count themselves on one word
 static_assert(kAppendResident >= (int)kAppendOneWord, "kAppendLate counts on several words");
 static_assert(kAppendOneWord >= kAppendGather && 512 / kAppendTokens > kAppendOneWord, "every word of a launch that counts on several is used");
-// Up to 64 sequences take one pass of as many workgroups as there are rows (see kv_append_few_kernel).  More of them:
+// Up to 64 sequences take one pass of as many workgroups as there are rows (see kv_append_few_kernel), up to kAppendMost.  More of them:
 // one token row per thread up to 4096 workgroups (us with four and the table / with one: 1195 tokens 6.9 / 5.8, 6466 15.0 /
 // 14.5, 32 x 200 15.0 / 14.5).  Many sequences take longer to look up in global memory, so there the table serves from 512
 // on.  Four rows per thread: 1024 workgroups where that is one or two rounds (8192 tokens of 128 to 1024 sequences), 512 for more (32768
@@ -138,7 +139,7 @@ inline AppendPlan plan_append(int batch, int hkv, int d, int total_new, int max_
   const long long single = ((long long)total_new + tpi - 1) / tpi;
   AppendPlan p;
   const bool late = ring && max_new > window && single > kAppendResident;
-  if (batch <= kAppendLanes && !(late && batch <= 2 && single > kAppendFew)) {
+  if (batch <= kAppendLanes && single <= kAppendMost && !(late && batch <= 2 && single > kAppendFew)) {
     p.form = late ? kAppendLate : kAppendEarly;
     p.wgs = (unsigned)single;
   } else if (single <= (batch <= 128 ? kAppendFew : 512)) {

@@ -7,6 +7,8 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <initializer_list>
+
 #include "../../include/flux.h"
 
 extern "C" const void *hostcheck_status, *hostcheck_partials, *hostcheck_counters;   // what the last decode launcher was given
@@ -154,6 +156,16 @@ int main() {
   EXPECT(hostcheck_append(65, 8, 128, 1 << 20, 1 << 14, 1, 4096, &n), 3);
   EXPECT(hostcheck_append(1, 8, 128, 65536, 65536, 0, 0, &n), 0);
   EXPECT(n, 32768);
+  // a launch has fewer than 2^32 threads, however many rows there are
+  for (int batch : {1, 3, 64, 65, 4096})
+    for (int hkv : {1, 8, 17, 128})
+      for (int total : {1, 1 << 20, 1 << 22, (1 << 24) - 1, 1 << 24, 1 << 25, INT_MAX})
+        for (int max_new : {total, 1}) {
+          (void)hostcheck_append(batch, hkv, 128, total, max_new, 0, 0, &n);
+          EXPECT(n >= 1 && n < (1u << 24), 1);
+          (void)hostcheck_append(batch, hkv, 64, total, max_new, 1, 64, &n);
+          EXPECT(n >= 1 && n < (1u << 24), 1);
+        }
   EXPECT(flux_kv_append(ctx, &kc, 2, 128, p, p, pi, 10, 10, nullptr), FLUX_EHIP);
   EXPECT(flux_kv_append(ctx, &kc, 2, 128, p, p, pi, INT_MAX, INT_MAX, nullptr), FLUX_ECAPACITY);
   EXPECT(flux_kv_append(ctx, &kc, 2, 128, p, p, pi, 5, 6, nullptr), FLUX_EINVAL);

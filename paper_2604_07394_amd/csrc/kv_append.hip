@@ -148,8 +148,8 @@ __global__ __launch_bounds__(256) void kv_append_kernel(AppendArgs a) {
   }
 }
 
-// Up to 64 sequences: one token row per thread, a single pass, however many workgroups that takes.  What bounds it: short copies
-// memory latencies one behind the other, long ones the memory (5.9 TB/s at 32768 tokens, read and written).  The general kernel waits
+// Up to 64 sequences: one token row per thread, a single pass, as many workgroups as that takes (kAppendMost at most).  What
+// bounds it: short copies memory latencies one behind the other, long ones the memory (5.9 TB/s at 32768 tokens, read and written).  The general kernel waits
 // for the lengths, the new rows, the acknowledgement of the stores, the arrival count and the lengths once more.  Here every wave
 // asks for the lengths, a sequence per lane, and right behind them for the new rows, whose place in the input does not depend on
 // them; a row's sequence is looked up in the registers, the stores are not waited for, and the last workgroup holds the
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(256) void kv_append_few_kernel(AppendArgs a) {
   const int tpi = 256 / lanes;
   const int tid = threadIdx.x;
   const int trow = tid / lanes, c0 = tid - trow * lanes;
-  const uint32_t at = blockIdx.x * (uint32_t)tpi + trow;      // (below 2^31 + 256)
+  const uint32_t at = blockIdx.x * (uint32_t)tpi + trow;      // (below 2^31 + 256, and the launch below 2^30 threads)
   const int t = (int)at;
   const bool valid = trow < tpi && at < (uint32_t)a.total_new;
   const int own = min(tid & 63, a.batch - 1);                // the sequence whose lengths this lane holds

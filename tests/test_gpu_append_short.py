@@ -103,3 +103,24 @@ def test_long_ring_appends_keep_the_sinks_and_the_window(F, ctx, lens, new, hkv)
         assert torch.equal(got, want)
     assert cache.kv_len.tolist() == [a + n for a, n in zip(lens, new)]
     assert F.flux_last_device_status(ctx) == 0
+
+
+def test_more_rows_than_a_launch_has_threads_for(F, ctx):
+    """2^24 rows of more than 128 pieces of 16 bytes, of which a ring keeps 71: a thread per piece would be 2^32 threads."""
+    hkv, d, n, n_sink, window = 17, 64, 1 << 24, 7, 64
+    if torch.cuda.mem_get_info()[0] < 64 << 30:
+        pytest.skip("the rows take 36.5 GB")
+    rows = torch.empty(n, hkv, d, dtype=torch.bfloat16, device="cuda")
+    for part in (rows[:n_sink], rows[-window:]):
+        part.copy_(torch.randint(-99, 99, part.shape, device="cuda"))
+    cu = torch.tensor([0, n, n, n], dtype=torch.int32, device="cuda")
+    for batch in (1, 3):
+        cache = F.KVCache(*(torch.zeros(batch, hkv, n_sink + window, d, dtype=torch.bfloat16, device="cuda") for _ in range(2)),
+                          torch.zeros(batch, dtype=torch.int32, device="cuda"))
+        F.flux_kv_append_ring(ctx, cache, hkv, d, n_sink, window, rows, rows, cu[:batch + 1], n, n)
+        assert cache.kv_len.tolist() == [n, 0, 0][:batch]
+        want = torch.cat([rows[:n_sink], rows[-window:].roll((n - window - n_sink) % window, 0)]).transpose(0, 1)
+        for got in (cache.k, cache.v):
+            assert torch.equal(got[0], want) and not got[1:].any()
+    del rows
+    torch.cuda.empty_cache()

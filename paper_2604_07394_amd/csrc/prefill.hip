@@ -375,10 +375,12 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
   const int l = tid & 63;
   const int g = l >> 4, n = l & 15;
   const int grp = PACK ? a.group : 1;                        // heads whose rows share a tile
-  // (the arguments that a workgroup's start needs, asked for together: tied to its number.  Where tiles may be split the scalar
-  // registers are short as it is, and it gains nothing)
+  // (the arguments that a workgroup's start needs, asked for together: tied to its number.  Not where tiles may be split, where the
+  // scalar registers are short as it is and it gains nothing, nor in batches of head dimension 64 (us with / without, 32/8 heads: 1325 and
+  // 2914 tokens behind 2685 and 1017 106.4 / 104.6, 4 x 4000 268.5 / 264.3, 3000, 700 and 5000 151.3 / 150.2, 8 x 700 25.7 / 25.9;
+  // at head dimension 128 8192 and 63 x 100 tokens 597 / 603, 2782, 35, 64 and 802 71.1 / 71.8))
   int i = blockIdx.x;
-  if constexpr (!SPLIT) asm("" : "+s"(i) : "s"(a.q), "s"(a.cu_q), "s"(a.k), "s"(a.v), "s"(a.stride_b), "s"(a.stride_h), "s"(a.stride_t), "s"(a.kv_len), "s"(a.mode),
+  if constexpr (!PLAN || (!PACK && D == 128)) asm("" : "+s"(i) : "s"(a.q), "s"(a.cu_q), "s"(a.k), "s"(a.v), "s"(a.stride_b), "s"(a.stride_h), "s"(a.stride_t), "s"(a.kv_len), "s"(a.mode),
       "s"(a.capacity), "s"(a.hq), "s"(a.hkv), "s"(a.group), "s"(a.batch), "s"(a.xcd_map), "s"(a.sink_lim), "s"(a.win_blocks),
       "s"(a.blk_shift), "s"(a.n_qtiles), "s"(a.n_wg), "s"(a.by_group), "s"(a.by_hkv), "s"(a.by_qtiles));
   // ---- which (sequence, KV head, tile) this workgroup owns.  Workgroups go to the 8 XCDs round-robin

@@ -75,6 +75,7 @@ struct PrefillArgs {
   float* part_o;          // unnormalised outputs of a unit, [unit][BM][D] (sequences whose tiles are split have the first units)
   float* part_ml;         // reference (score units) and weight sum of its rows, [unit][BM][2]
   i32x4* tile_info;       // [batch][n_kv_heads][n_qtiles]: first unit, unit stride, units of the tile; behind them, per sequence, the most of them that a tile of it has
+  int merge_rows, merge_wgs;   // merge launch: rows of a tile per workgroup, workgroups that the tiles of a sequence are shared by
 };
 
 constexpr float kWeightGuard = 1073741824.0f;   // 2^30: a block whose weights sum past this moves the softmax reference
@@ -1019,8 +1020,8 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
 }
 
 // The tiles whose key blocks were shared out over several units: out = sum_c w_c O_c / sum_c w_c l_c with
-// w_c = exp(m_c - max m), parts in order.  D / 4 threads per row, a tile's rows over the gridDim.x workgroups of a tile, the
-// tiles of a sequence over gridDim.y (as many as there are by the host's bounds, or fewer that take several each: a sequence
+// w_c = exp(m_c - max m), parts in order.  D / 4 threads per row, a tile's rows over the gridDim.x workgroups of a tile (merge_rows
+// each), the tiles of a sequence over gridDim.y = merge_wgs (as many as there are by the host's bounds, or fewer that take several each: a sequence
 // that is not split costs its workgroups one load).
 template <int D, int BM>
 __global__ __launch_bounds__(256) void prefill_merge_kernel(PrefillArgs a) {
@@ -1029,31 +1030,42 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(PrefillArgs a) {
   // What says whether there is anything to do is asked for together: the sequence's flag and lengths and, where a workgroup has one tile
   // by the host's bounds, that tile's entry (whatever it holds if the sequence has no such tile), and the other arguments.  A merge
   // is latencies one behind the other (us of the whole call with these in a row / together, 32/8 heads of 128: 16 tokens behind 30000
-  // 37.3 / 36.3, 128 behind 16256 52.7 / 51.9, 100 behind 5000 34.7 / 33.7; 8/2 heads of 64, 34 and 112 behind 38574 and 608 30.9 / 29.8).
-  const bool single = (int)gridDim.y == a.hkv * a.n_qtiles;
+  // 36.6 / 35.4, 128 behind 16256 48.6 / 47.9, 100 behind 5000 34.4 / 33.5; 8/2 heads of 64, 34 and 112 behind 38574 and 608 30.9 / 29.8;
+  // with many workgroups, most of which have nothing to do or all the same, half a us goes the other way: 512, 40 and 30 tokens behind 5000 to
+  // 5800 65.3 / 65.7, 4 x 256 behind 2300 51.8 / 52.3).  The entry comes by a vector load, which a workgroup that leaves does not
+  // wait for (by a scalar load 512, 40 and 30 tokens 66.4), and what the grid is comes with the arguments.
+  const bool single = a.merge_wgs == a.hkv * a.n_qtiles;
   const i32x4* infos = a.tile_info + (int64_t)b * a.hkv * a.n_qtiles;
   int most = a.tile_info[a.batch * a.hkv * a.n_qtiles + b][0], q_end = a.cu_q[b + 1], len = a.kv_len[b];
   const int q_begin = a.cu_q[b];
-  i32x4 info = infos[blockIdx.y];                            // (gridDim.y is not larger than the number of entries)
-  asm("" : "+s"(most) : "s"(q_end), "s"(len), "s"(q_begin), "s"(info), "s"(a.capacity), "s"(a.group), "s"(a.hq), "s"(a.by_qtiles), "s"(a.part_o), "s"(a.part_ml),
-      "s"(a.out), "s"(a.out_fp32), "s"(a.scale_log2));
+  int at = blockIdx.y;                                       // (the workgroups are not more than the entries)
+  asm volatile("" : "+v"(at));
+  const i32x4 mine = infos[at];
+  asm volatile("" : "+s"(most) : "s"(q_end), "s"(len), "s"(q_begin), "s"(a.capacity), "s"(a.group), "s"(a.hq), "s"(a.by_qtiles), "s"(a.part_o), "s"(a.part_ml),
+      "s"(a.out), "s"(a.out_fp32), "s"(a.scale_log2), "s"(a.merge_rows));
   if (most < 2) return;                                      // none of its tiles was split
   int n_q = q_end - q_begin;
   len = len < 0 ? 0 : (len > a.capacity ? a.capacity : len);
   n_q = min(n_q, len);
   const int64_t n_rows = (int64_t)n_q * a.group;
   const int d = 4 * (threadIdx.x % (D / 4));
-  const int per = BM / gridDim.x;
+  const int per = a.merge_rows;
   // tiles of a KV head: all that the bounds count, or those that there are, which then take turns
   const int n_t = single ? a.n_qtiles : (int)min((n_rows + BM - 1) / BM, (int64_t)a.n_qtiles);
-  for (int tile = blockIdx.y; tile < a.hkv * n_t; tile += gridDim.y) {
+  for (int tile = blockIdx.y; tile < a.hkv * n_t; tile += a.merge_wgs) {
     const int kvh = single ? quotient(tile, a.by_qtiles) : tile / n_t, qt = tile - kvh * n_t;
     const int64_t row0 = (int64_t)qt * BM;
     if (row0 >= n_rows) continue;
-    if (!single) info = infos[(int64_t)kvh * a.n_qtiles + qt];
+    i32x4 info;
+    if (single) {
+#pragma unroll
+      for (int i = 0; i < 3; ++i) info[i] = __builtin_amdgcn_readfirstlane(mine[i]);
+    } else {
+      info = infos[(int64_t)kvh * a.n_qtiles + qt];
+    }
     const int parts = info[2];
     if (parts < 2) continue;
-    for (int x = blockIdx.x * per + threadIdx.x / (D / 4); x < (int)(blockIdx.x + 1) * per; x += RPP) {
+    for (int x = (int)blockIdx.x * per + threadIdx.x / (D / 4); x < ((int)blockIdx.x + 1) * per; x += RPP) {
       const int64_t row = row0 + x;
       if (row >= n_rows) break;
       const int64_t r0 = (int64_t)info[0] * BM + x, step = (int64_t)info[1] * BM;
@@ -1226,7 +1238,9 @@ hipError_t launch_prefill(const Ctx& c, const flux_attn_cfg& cfg, const void* q,
     // (few tiles have many parts each: a row per thread; otherwise two, since most workgroups find nothing to do)
     const unsigned per_tile = 128 * cfg.head_dim / 1024 / (tiles <= kSplitFewTiles ? 1 : 2);
     const long long per_seq = (long long)cfg.n_kv_heads * a.n_qtiles, most = 8192 / (per_tile * cache.batch);
-    const dim3 mgrid(per_tile, (unsigned)(per_seq < most ? per_seq : most), cache.batch);
+    a.merge_rows = BM / (int)per_tile;
+    a.merge_wgs = (int)(per_seq < most ? per_seq : most);
+    const dim3 mgrid(per_tile, (unsigned)a.merge_wgs, cache.batch);
     if (cfg.head_dim == 128) hipLaunchKernelGGL((prefill_merge_kernel<128, 128>), mgrid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL((prefill_merge_kernel<64, 128>), mgrid, dim3(256), 0, s, a);
   }

@@ -50,18 +50,22 @@ def parse():
 
 
 def source_digest(names):
-    """sha256 over the kernel sources a counter measurement belongs to (first 16 hex digits)."""
+    """sha256 over the kernel sources a counter measurement belongs to and the flags they are compiled with (first 16 hex
+    digits)."""
     import hashlib
+
+    from paper_2604_07394_amd import build
     h = hashlib.sha256()
     for n in names:
         with open(os.path.join(CSRC, n), "rb") as f:
             h.update(f.read())
+        h.update("\n".join(build.COMMON + build.SOURCE_FLAGS.get(n, [])).encode())
     return h.hexdigest()[:16]
 
 
 def measured_traffic(key, sources):
     """HBM bytes per launch recorded under profiles/ from rocprofv3 counter runs.  A record carries the digest
-    of the kernel sources it was measured on; it is reported only while those sources are unchanged, so a
+    of the kernel sources it was measured on and their compiler flags; it is reported only while those are unchanged, so a
     later kernel change cannot leave a stale figure in the line.  Returns (bytes or None, note)."""
     try:
         for line in open(os.path.join(ROOT, "profiles", "hbm_traffic.txt")):

@@ -64,3 +64,17 @@ def test_router_launches_of_many_workgroups_run_an_instance_that_shares_the_cus(
     workgroups and for narrow layers holds five."""
     k = [v for n, v in kernels.items() if "router_mlp_kernelILi1024E" in n]
     assert len(k) == 1 and workgroups_per_cu(k[0]) >= 5 and k[0]["vgpr_spill_count"] == 0, k
+
+
+def test_counter_records_belong_to_the_compiler_flags_too(monkeypatch):
+    """bench.py reports recorded counters while the digest of their kernel holds: flags change a kernel as its source does."""
+    import bench
+    from paper_2604_07394_amd import build
+    names = ["prefill.hip", "flux_internal.h"]
+    before = bench.source_digest(names)
+    assert before == bench.source_digest(names)
+    monkeypatch.setattr(build, "SOURCE_FLAGS", {})
+    assert bench.source_digest(names) != before
+    monkeypatch.undo()
+    monkeypatch.setattr(build, "COMMON", build.COMMON + ["-O2"])
+    assert bench.source_digest(names) != before

@@ -36,7 +36,7 @@ def kernels(tmp_path_factory):
             for part in re.split(r"\n  - \.", notes)[1:]:
                 get = lambda key: re.search(r"\.?" + key + r":\s*(\S+)", part)
                 if get("name") and get("vgpr_count"):
-                    found[get("symbol").group(1)] = {k: int(get(k).group(1)) for k in ("vgpr_count", "max_flat_workgroup_size", "group_segment_fixed_size", "vgpr_spill_count")}
+                    found[get("symbol").group(1)] = {k: int(get(k).group(1)) for k in ("vgpr_count", "max_flat_workgroup_size", "group_segment_fixed_size", "vgpr_spill_count", "sgpr_spill_count")}
         at = blob.find(MAGIC, at + 1)
     return found
 
@@ -57,6 +57,20 @@ def test_every_decode_kernel_holds_the_round_its_calls_are_made_for(kernels):
     for n in names:
         assert 256 * workgroups_per_cu(kernels[n]) >= most[kernels[n]["max_flat_workgroup_size"]] >= 512, (n, kernels[n])
         assert kernels[n]["vgpr_spill_count"] == 0, n
+
+
+def test_every_prefill_kernel_holds_the_workgroups_its_launches_count_on(kernels):
+    """The rules of a prefill launch (which tiles, whether keys are shared out) count on kResident128 workgroups side by side at
+    head dimension 128 and kResident64 at 64.  prefill.hip is compiled with regions left unstructurised, which is what keeps the
+    registers of its loops down: no instance may spill."""
+    src = open(os.path.join(ROOT, "paper_2604_07394_amd", "csrc", "prefill.hip")).read()
+    names = [n for n in kernels if "prefill_kernel" in n]
+    assert len(names) == 10
+    for n in names:
+        d = 128 if "ILi128E" in n else 64
+        resident = int(re.search(r"kResident%d = (\d+)" % d, src).group(1))
+        assert 256 * workgroups_per_cu(kernels[n]) >= resident >= 512, (n, kernels[n])
+        assert kernels[n]["vgpr_spill_count"] == 0 and kernels[n]["sgpr_spill_count"] == 0, (n, kernels[n])
 
 
 def test_router_launches_of_many_workgroups_run_an_instance_that_shares_the_cus(kernels):

@@ -149,8 +149,8 @@ __global__ __launch_bounds__(256) void kv_append_kernel(AppendArgs a) {
 }
 
 // Up to 64 sequences: one token row per thread, a single pass, as many workgroups as that takes (kAppendMost at most).  What
-// bounds it: short copies memory latencies one behind the other, long ones the memory (5.9 TB/s at 32768 tokens, read and written).  The general kernel waits
-// for the lengths, the new rows, the acknowledgement of the stores, the arrival count and the lengths once more.  Here every wave
+// bounds it: short copies memory latencies one behind the other, long ones the memory (6.1 TB/s at 32768 tokens, read and
+// written).  The general kernel waits for the lengths, the new rows, the acknowledgement of the stores, the arrival count and the lengths once more.  Here every wave
 // asks for the lengths, a sequence per lane, and right behind them for the new rows, whose place in the input does not depend on
 // them; a row's sequence is looked up in the registers, the stores are not waited for, and the last workgroup holds the
 // lengths already.  Nothing is shared by the workgroup, so new ones start while others drain, which workgroups that stay for several rows

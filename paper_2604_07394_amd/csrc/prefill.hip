@@ -32,8 +32,8 @@ namespace flux {
 
 typedef __attribute__((__vector_size__(4 * sizeof(int32_t)))) int32_t i32x4;
 
-// Quotients by a divisor that the host knows: n / d = (mulhi(n, mul) + n) >> shift for n < 2^31 (mul = floor(2^32 (2^shift - d) / d)
-// + 1 with 2^shift >= d).
+// Quotients by a divisor that the host knows, by the round-up method of Granlund and Montgomery (Division by invariant integers using
+// multiplication, 1994): n / d = (mulhi(n, mul) + n) >> shift for n < 2^31 (mul = floor(2^32 (2^shift - d) / d) + 1 with 2^shift >= d).
 struct Divisor {
   uint32_t mul, shift;
 };
@@ -506,8 +506,8 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
   unsigned long long scan_bits[3] = {0, 0, 0};               // what is left of them, per query block of the tile
   int cur_kb = -1, cur_rows = 0;                             // the block of this iteration, and which query blocks keep it
   // The flags of a window are asked for one window ahead, those of the first one in front of the query rows (they come back in
-  // the order they were asked for in; 8 % of the blocks kept, 16384 tokens 222 -> 220 us, 32768 686 -> 674, 65536 2405 -> 2369).  Every lane reads a flag of the matrix, whatever it needs: no branch differs between
-  // lanes, see weights_guarded.
+  // the order they were asked for in; 8 % of the blocks kept, 16384 tokens 222 -> 220 us, 32768 686 -> 674, 65536 2405 -> 2369).
+  // Every lane reads a flag of the matrix, whatever it needs: no branch differs between lanes, see weights_guarded.
   const int rq0 = rb0 - (pos0 >> 6);                         // row of the matrix
   uint8_t flags[3] = {0, 0, 0};
   auto fetch_flags = [&](int win) __attribute__((always_inline)) {
@@ -1152,8 +1152,8 @@ hipError_t launch_prefill(const Ctx& c, const flux_attn_cfg& cfg, const void* q,
   // 512, 40 and 30 tokens behind 5000 to 5800 123 -> 66, 4 x 256 equal ones behind 2300 50 -> 53.  The more tiles the bounds count,
   // the longer the lists have to be: 900, 3000, 200, 100 and 60 tokens behind 500, 700, 30000, 4000 and 60000 (28/4 heads, 3300 tiles,
   // 939 blocks) 951 -> 270, 238 to 2004 tokens behind 583 to 35383 (2520, 558) 585 -> 305, 504, 61 and 1573 tokens behind 1044,
-  // 5599 and 761 (16/8 heads, 600, 89) 102 -> 54; of those that gain nothing 6 x 700 behind 5000 (28/4 heads, 936, 90) 265 -> 270,
-  // 28 to 2368 tokens behind 767 to 28243 in six sequences (3552, 257) 365 -> 372.  Only sequences whose tiles are split take part in
+  // 5599 and 761 (16/8 heads, 600, 89) 102 -> 54; of those that gain nothing 6 x 700 behind 5000 (28/4 heads, 936, 90) 262.1 -> 262.7,
+  // 28 to 2368 tokens behind 767 to 28243 in six sequences (3552, 257) 366.5 -> 369.7.  Only sequences whose tiles are split take part in
   // the partial results, and they have the first units of the launch, so that the workspace need not hold one per tile.
   const long long packed = ((long long)max_q_len * a.group + BM - 1) / BM;    // tiles of a pair whose rows come from all heads
   const long long tiles = n_pairs * packed, blocks = ((long long)max_kv_len + 63) / 64;

@@ -37,7 +37,9 @@ __device__ __forceinline__ int pooled_row(int t, int n_rows, int pool, bool all)
 // the row splits hold them all.  The MLP workgroups each read the sums of all splits of their sequence, next to 64 KB of
 // weights: 16 KB per split at hidden 4096, of which pools of 100 + 100 rows had seven (us per call
 // with seven / two, inner 256: batch 1 11.5 / 11.0, 4 12.4 / 11.5, 8 14.4 / 12.7, 16 19.9 / 17.1, 64 46.9 / 41.9; 512
-// sequences of hidden 256 21.5 / 17.1.  One split of two rounds 12.3 at batch 4, four 12.0).
+// sequences of hidden 256 21.5 / 17.1, hidden 1024, inner 64, batch 4 8.2 either way; with rows and weights not in any cache batch 1
+// 14.0 / 12.4, 4 14.6 / 12.8, 16 22.6 / 18.4, 64 57 / 45.5, hidden 1024, inner 64, batch 4 10.5 / 9.5.  One split of two rounds 12.3
+// at batch 4, four 12.0).
 template <int CL>
 __global__ __launch_bounds__(256) void router_pool_kernel(PoolArgs a) {
   constexpr int RL = 256 / CL;                              // rows that the workgroup reads side by side

@@ -320,8 +320,9 @@ __global__ __launch_bounds__(256, 2) void xa_select_kernel(XaArgs a) {
 // exponentials where the others take the difference of logarithms: there a mass next to the cut may fall on either side.)
 // What bounds it: the rate at which the L2s deliver operand rows to the CUs.  The walk above fetches every key row once
 // per 32 square rows, this form every operand row once per 128 of the other operand: 16384 positions x 32 heads 1.2 GB
-// instead of 2.1 GB (walk 340 us; here 144 us, 700 TFLOP/s at its core, a quarter of it for the 75 MB of means, plus 31 us
-// for the row kernel, which is bound by its vector instructions).
+// instead of 2.1 GB (us for the selection, both kernels, back to back in a replayed graph: walk 340, here 139; traced, one
+// at a time, this kernel takes 138 to 145, 700 TFLOP/s at its core, a quarter of it for the 75 MB of means, and the row kernel,
+// which is bound by its vector instructions, 28 to 30).
 constexpr int kXaTile = 128;                 // square rows / columns of a tile
 constexpr int kXaPiece = kXaTile * 16;       // floats of a piece: 128 square rows x 16 square columns
 
